@@ -13,12 +13,12 @@
 // are always normal fp16 numbers or zero.  The contraction runs on v_mfma_f32_32x32x16_f16 with
 // fp32 accumulation; the tensor scales multiply once in the epilogue.
 //
-// Operand storage: row-major ([rows, K/2] codes, [rows, K/B] scale bytes), or, for blocks of 16 in the 256 x 256
-// kernel, the slab layout of kernels.h, in which the 256 rows x 64 code bytes (and 256 x 8 scale bytes) that a
-// workgroup fetches per K tile are one contiguous piece.  Only addresses differ: per-lane offsets, two base
-// pointers and their step per K tile.
+// Operand storage: row-major ([rows, K/2] codes, [rows, K/B] scale bytes), or, for blocks of 16, the slab layout of
+// kernels.h, in which the 256 rows x 64 code bytes (and 256 x 8 scale bytes) of a K tile are one contiguous piece.  Only
+// addresses differ: per-lane offsets, two base pointers and their step per K tile.
 #include "kernels.h"
 #include "nvfp4_math.h"
+#include "store_lines.h"
 
 namespace nvfp4 {
 
@@ -84,10 +84,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     constexpr int A_BYTES = BM * KTB, B_BYTES = BN * KTB, SA_BYTES = BM * SROW, SB_BYTES = BN * SROW;
     constexpr int STAGE = A_BYTES + B_BYTES + SA_BYTES + SB_BYTES;
     constexpr int CA = BM * 4 / NT, CB = BN * 4 / NT;  // 16-byte chunks per thread per tile
-    static_assert(BM * 4 % NT == 0 && BN * 4 % NT == 0 && BM + BN <= NT * 2, "tile/thread mismatch");
+    static_assert(BM * 4 % NT == 0 && BN * 4 % NT == 0 && BM * 4 >= NT && BN * 4 >= NT, "tile/thread mismatch");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 31, h = lane >> 5;
     const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
@@ -106,39 +107,33 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
 
-    // ---- global -> registers -> LDS staging of one K tile.
+    // ---- global -> LDS staging of one K tile.
     // Rows past the matrix edge are clamped to the last row (their products land in outputs
     // that are never stored), so the code loads carry no predicate.  A K tail (K not a
-    // multiple of 128) is handled through the scales alone: chunks past K are read from a
-    // clamped address and meet zero scales.
-    // Without a K tail the codes go from global memory straight into LDS (global_load_lds, 16
+    // multiple of 128) is handled through the scales alone: a chunk past K is replaced by the
+    // tile's first one and meets zero scales.
+    // The codes go from global memory straight into LDS (global_load_lds, 16
     // bytes per lane): a wave instruction fills 1 KB = 16 consecutive tile rows, lane i landing at
     // byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
-    // the lane fetches.  No staging registers, no LDS store instructions for the codes.
-    constexpr bool DMA = !KTAIL;
+    // the lane fetches.  No staging registers, no LDS store instructions for the codes.  (A K tail
+    // used to be staged through registers by a 128 x 128 kernel of its own: 4096 x 4128 x 4896 took
+    // 539 us, with the direct loads 190.)
     constexpr int NSR = (BM + BN + NT - 1) / NT;  // scale rows per thread
-    uint4 ga[DMA ? 1 : CA], gb[DMA ? 1 : CB];
     uint64_t gs[NSR];
     uint32_t offA[CA], offB[CB];  // byte offset of this thread's chunks inside a K tile column
-    int ldsA[CA], ldsB[CB];
+    const int ch = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
     for (int u = 0; u < CA; ++u) {
-        const int qd = tid + NT * u;
-        const int row = DMA ? (wave * CA + u) * 16 + (lane >> 2) : qd >> 2;
-        const int ch = DMA ? (lane & 3) ^ ((lane >> 4) & 3) : qd & 3;
+        const int row = (wave * CA + u) * 16 + (lane >> 2);
         const int64_t lr = m0 + row < P.M ? row : P.M - 1 - m0;  // row inside the tile, clamped
-        offA[u] = P.a_slab ? (uint32_t)(slab_row(row) * 64 + ch * 16)  // (a slab holds all 256 rows: nothing to clamp)
-                           : (uint32_t)(lr * Kb + ch * 16);       // (relative to the tile's first row: 32 bits suffice)
-        ldsA[u] = DMA ? __builtin_amdgcn_readfirstlane((wave * CA + u) * 1024) : swz(row, ch);
+        offA[u] = P.a_slab ? (uint32_t)(slab_row((int)(m0 & 255) + row) * 64 + ch * 16)  // (a slab holds all 256 rows: nothing to clamp)
+                           : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
     }
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
-        const int qd = tid + NT * u;
-        const int row = DMA ? (wave * CB + u) * 16 + (lane >> 2) : qd >> 2;
-        const int ch = DMA ? (lane & 3) ^ ((lane >> 4) & 3) : qd & 3;
+        const int row = (wave * CB + u) * 16 + (lane >> 2);
         const int64_t lr = n0 + row < P.N ? row : P.N - 1 - n0;
-        offB[u] = P.b_slab ? (uint32_t)(slab_row(row) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
-        ldsB[u] = DMA ? __builtin_amdgcn_readfirstlane(A_BYTES + (wave * CB + u) * 1024) : A_BYTES + swz(row, ch);
+        offB[u] = P.b_slab ? (uint32_t)(slab_row((int)(n0 & 255) + row) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
     }
     typedef __attribute__((address_space(3))) void *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
@@ -168,60 +163,48 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         srow_on[u] = srow < BM + BN;
         srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + gr * Ks;
         srow_step[u] = SPT;
-        if (DMA && (isA ? P.a_slab : P.b_slab) && srow_on[u]) {
-            const int64_t tile = isA ? ty : tx;
+        if (!KTAIL && (isA ? P.a_slab : P.b_slab) && srow_on[u]) {
+            const int64_t base = isA ? m0 : n0;
             const int lrow = isA ? srow : srow - BM;
-            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + tile * nkt * SLAB_SCALE_BYTES + slab_row(lrow) * 8;
+            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + (base >> 8) * nkt * SLAB_SCALE_BYTES + slab_row((int)(base & 255) + lrow) * 8;
             srow_step[u] = (int)SLAB_SCALE_BYTES;
         }
     }
     // codes of K tile kt: base + kt * step (+ the lane offsets above)
-    const uint8_t *baseA = P.a_slab ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
-    const uint8_t *baseB = P.b_slab ? P.B_codes + (int64_t)tx * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
+    const uint8_t *baseA = P.a_slab ? P.A_codes + (m0 >> 8) * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
+    const uint8_t *baseB = P.b_slab ? P.B_codes + (n0 >> 8) * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
     const int64_t stepA = P.a_slab ? SLAB_CODE_BYTES : KTB, stepB = P.b_slab ? SLAB_CODE_BYTES : KTB;
-    const int64_t last_chunk = Kb - 16;
-    // tile kt: codes -> LDS stage `stage` (direct) or staging registers; scale bytes -> registers
+    const int rem = KTAIL ? (int)(P.K - (int64_t)(nkt - 1) * KT) : KT;  // elements of the last K tile
+    // tile kt: codes -> LDS stage `stage` (direct); scale bytes -> registers
     auto fetch = [&](int kt, int stage) {
-        const int64_t kb = (int64_t)kt * KTB;
-        const uint8_t *pa = baseA + kt * stepA, *pb = baseB + kt * stepB;
-        if (!KTAIL) {
-            const uint8_t *ua = uniform_ptr(pa), *ub = uniform_ptr(pb);
-            const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE);
+        const uint8_t *ua = uniform_ptr(baseA + kt * stepA), *ub = uniform_ptr(baseB + kt * stepB);
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE);
+        const bool tail = KTAIL && kt == nkt - 1;
+        const uint32_t back = tail && ch * 32 >= rem ? (uint32_t)ch * 16 : 0u;  // (a chunk past K: the tile's first one)
 #pragma unroll
-            for (int u = 0; u < CA; ++u) dma16(dst + ldsA[u], offA[u], ua);
+        for (int u = 0; u < CA; ++u) dma16(dst + (wave * CA + u) * 1024, KTAIL ? offA[u] - back : offA[u], ua);
 #pragma unroll
-            for (int u = 0; u < CB; ++u) dma16(dst + ldsB[u], offB[u], ub);
+        for (int u = 0; u < CB; ++u) dma16(dst + A_BYTES + (wave * CB + u) * 1024, KTAIL ? offB[u] - back : offB[u], ub);
 #pragma unroll
-            for (int u = 0; u < NSR; ++u) {
-                if (!srow_on[u]) continue;
-                const uint8_t *sp = srow_ptr[u] + (int64_t)kt * srow_step[u];
+        for (int u = 0; u < NSR; ++u) {
+            if (!srow_on[u]) continue;
+            const uint8_t *sp = srow_ptr[u] + (int64_t)kt * srow_step[u];
+            if (tail) {
+                uint64_t sv = 0;  // zero scales past K
+#pragma unroll
+                for (int t = 0; t < SPT; ++t)
+                    if (t * B < rem) sv |= (uint64_t)sp[t] << (8 * t);
+                gs[u] = sv;
+            } else if (KTAIL) {
+                // (the scale rows of a ragged K start at any byte)
+                uint64_t sv = 0;
+                __builtin_memcpy(&sv, sp, SPT);
+                gs[u] = sv;
+            } else {
                 if (SPT == 8) gs[u] = *reinterpret_cast<const uint64_t *>(sp);
                 else if (SPT == 4) gs[u] = *reinterpret_cast<const uint32_t *>(sp);
                 else if (SPT == 2) gs[u] = *reinterpret_cast<const uint16_t *>(sp);
                 else gs[u] = *sp;
-            }
-        } else {
-            // K tail present: clamp chunk addresses, assemble scale bytes one by one, zero past K
-#pragma unroll
-            for (int u = 0; u < CA; ++u) {
-                const int64_t c = kb + ((tid + NT * u) & 3) * 16;
-                ga[u] = *reinterpret_cast<const uint4 *>(pa + offA[u] - (c > last_chunk ? c - last_chunk : 0));
-            }
-#pragma unroll
-            for (int u = 0; u < CB; ++u) {
-                const int64_t c = kb + ((tid + NT * u) & 3) * 16;
-                gb[u] = *reinterpret_cast<const uint4 *>(pb + offB[u] - (c > last_chunk ? c - last_chunk : 0));
-            }
-            const int64_t left = Ks - (int64_t)kt * SPT;
-#pragma unroll
-            for (int u = 0; u < NSR; ++u) {
-                if (!srow_on[u]) continue;
-                const uint8_t *sp = srow_ptr[u] + (int64_t)kt * SPT;
-                uint64_t sv = 0;
-#pragma unroll
-                for (int t = 0; t < SPT; ++t)
-                    if (t < left) sv |= (uint64_t)sp[t] << (8 * t);
-                gs[u] = sv;
             }
         }
     };
@@ -231,14 +214,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     // 32 consecutive rows of one chunk.  For blocks wider than 16 the value is repeated.
     auto stash = [&](int stage) {
         uint8_t *base = lds + stage * STAGE;
-        if (DMA) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's direct-to-LDS loads have landed
-        } else {
-#pragma unroll
-            for (int u = 0; u < CA; ++u) *reinterpret_cast<uint4 *>(base + ldsA[u]) = ga[u];
-#pragma unroll
-            for (int u = 0; u < CB; ++u) *reinterpret_cast<uint4 *>(base + ldsB[u]) = gb[u];
-        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's direct-to-LDS loads have landed
         uint32_t *sS = reinterpret_cast<uint32_t *>(base + A_BYTES + B_BYTES);
 #pragma unroll
         for (int u = 0; u < NSR; ++u) {
@@ -389,129 +365,19 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
 #undef NVFP4_STEP
 #undef NVFP4_INTERLEAVE
 
-    // epilogue.  The MFMA's first operand is the B (N-side) fragment, so accumulator register v of
-    // lane (r, h) of tile (a, b) is output row 32 a + r, column 32 b + 8 (v / 4) + 4 h + v % 4: four
-    // consecutive columns of one row = one packed convert pair and one 8-byte (bf16) or 16-byte
-    // (fp32) store.  Full tiles with a suitably aligned output take that path; edge tiles store
-    // element by element.  bf16 output of the 8-wave shape goes through LDS first (below): measured
-    // 2.5-5 % faster per GEMM than 16-byte pieces that the L2 has to merge into lines, while
-    // nontemporal 8-byte stores that bypass the merging were 30 % slower.
-    const float gg = P.gA[0] * P.gB[0];
-    constexpr int ESZ = OUT_DT == NVFP4_F32 ? 4 : 2;
-    const int64_t row0 = m0 + wm * 32 * TA + r, col0 = n0 + wn * 32 * TB + 4 * h;
-    const bool fast = m0 + BM <= P.M && n0 + BN <= P.N && (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(P.out) & 15) == 0;
-    constexpr bool LINES = TA == 4 && TB == 2 && !KTAIL;  // 128 x 64 per wave: 128-byte (bf16) or 256-byte (fp32) rows
-    if (LINES && OUT_DT == NVFP4_F32 && fast) {
-        // fp32: 32 rows x 256 bytes at a time through the wave's 8 KB, four complete rows per store
-        __syncthreads();
-        uint8_t *const out = reinterpret_cast<uint8_t *>(P.out);
-        uint8_t *const mine = lds + wave * 8192;
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int chunk = 8 * b + 2 * q + h;  // columns 4 chunk .. 4 chunk + 3 of the wave's 64
-                    *reinterpret_cast<float4 *>(mine + r * 256 + ((chunk ^ (r & 15)) << 4)) =
-                        make_float4(acc[a][b][4 * q] * gg, acc[a][b][4 * q + 1] * gg, acc[a][b][4 * q + 2] * gg, acc[a][b][4 * q + 3] * gg);
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int rowl = 4 * i + (lane >> 4), chunk = lane & 15;
-                const uint4 v = *reinterpret_cast<const uint4 *>(mine + rowl * 256 + ((chunk ^ (rowl & 15)) << 4));
-                const int64_t grow = m0 + wm * 128 + 32 * a + rowl, gcol = n0 + wn * 64 + 4 * chunk;
-                *reinterpret_cast<uint4 *>(out + (grow * P.ldc + gcol) * 4) = v;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    } else if (LINES && OUT_DT == NVFP4_BF16 && fast && (P.ldc & 7) == 0) {
-        // Full-line output: the wave transposes its accumulators through a private 8 KB piece of
-        // LDS (64 rows x 128 bytes at a time, 16-byte chunks XOR-swizzled by row) so that a store
-        // instruction writes 8 complete 128-byte rows instead of 32 pieces of 16 bytes.
-        __syncthreads();  // every wave has read the last K tile: the stages may be overwritten
-        uint8_t *const out = reinterpret_cast<uint8_t *>(P.out);
-        uint8_t *const mine = lds + wave * 8192;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-#pragma unroll
-            for (int a2 = 0; a2 < 2; ++a2) {
-                const int a = 2 * half + a2, rowl = 32 * a2 + r;
-#pragma unroll
-                for (int b = 0; b < TB; ++b)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float2v_t lo = {acc[a][b][4 * q] * gg, acc[a][b][4 * q + 1] * gg};
-                        const float2v_t hi = {acc[a][b][4 * q + 2] * gg, acc[a][b][4 * q + 3] * gg};
-                        const bf16x2_t blo = __builtin_convertvector(lo, bf16x2_t), bhi = __builtin_convertvector(hi, bf16x2_t);
-                        uint2 w;
-                        w.x = *reinterpret_cast<const uint32_t *>(&blo);
-                        w.y = *reinterpret_cast<const uint32_t *>(&bhi);
-                        const int chunk = 4 * b + q;  // columns 8 chunk .. 8 chunk + 7 of the wave's 64
-                        *reinterpret_cast<uint2 *>(mine + rowl * 128 + ((chunk ^ (rowl & 7)) << 4) + 8 * h) = w;
-                    }
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int rowl = 8 * i + (lane >> 3), chunk = lane & 7;
-                const uint4 v = *reinterpret_cast<const uint4 *>(mine + rowl * 128 + ((chunk ^ (rowl & 7)) << 4));
-                const int64_t grow = m0 + wm * 128 + 64 * half + rowl, gcol = n0 + wn * 64 + 8 * chunk;
-                *reinterpret_cast<uint4 *>(out + (grow * P.ldc + gcol) * 2) = v;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    } else if (fast) {
-        uint8_t *const out = reinterpret_cast<uint8_t *>(P.out);
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-            uint8_t *prow = out + ((row0 + 32 * a) * P.ldc + col0) * ESZ;
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float y0 = acc[a][b][4 * q] * gg, y1 = acc[a][b][4 * q + 1] * gg;
-                    const float y2 = acc[a][b][4 * q + 2] * gg, y3 = acc[a][b][4 * q + 3] * gg;
-                    uint8_t *dst = prow + (32 * b + 8 * q) * ESZ;
-                    if (OUT_DT == NVFP4_F32) {
-                        *reinterpret_cast<float4 *>(dst) = make_float4(y0, y1, y2, y3);
-                    } else {
-                        const float2v_t lo = {y0, y1}, hi = {y2, y3};
-                        const bf16x2_t blo = __builtin_convertvector(lo, bf16x2_t), bhi = __builtin_convertvector(hi, bf16x2_t);
-                        uint2 w;
-                        w.x = *reinterpret_cast<const uint32_t *>(&blo);
-                        w.y = *reinterpret_cast<const uint32_t *>(&bhi);
-                        *reinterpret_cast<uint2 *>(dst) = w;
-                    }
-                }
-        }
-    } else {
-#pragma unroll
-        for (int a = 0; a < TA; ++a)
-#pragma unroll
-            for (int b = 0; b < TB; ++b) {
-                const int64_t row = row0 + 32 * a;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int64_t col = col0 + 32 * b + 8 * (v >> 2) + (v & 3);
-                    if (row < P.M && col < P.N) {
-                        const float y = acc[a][b][v] * gg;
-                        if (OUT_DT == NVFP4_F32)
-                            reinterpret_cast<float *>(P.out)[row * P.ldc + col] = y;
-                        else
-                            reinterpret_cast<uint16_t *>(P.out)[row * P.ldc + col] = f32_to_bf16_rne(y);
-                    }
-                }
-            }
-    }
+    // epilogue.  The MFMA's first operand is the B (N-side) fragment, so a lane holds four consecutive columns of one row.
+    __syncthreads();  // every wave has read the last K tile: the stages may be overwritten
+    constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 32 * TA, n0 + wn * 32 * TB, lds + wave * PIECE, lane);
 }
 
 template <int B, int WM, int WN, int TA, int TB, bool KTAIL>
 static void launch_f16(const GemmArgs &P, int out_dt, hipStream_t st)
 {
     constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
-    constexpr int LDS_BYTES = 2 * ((BM + BN) * KTB + (BM + BN) * SROW);
+    // two stages, or the epilogue's pieces (one per wave, 32 rows of fp32)
+    constexpr int STAGES = 2 * ((BM + BN) * KTB + (BM + BN) * SROW), PIECES = WM * WN * 32 * 32 * TB * 4;
+    constexpr int LDS_BYTES = STAGES > PIECES ? STAGES : PIECES;
     const unsigned ntiles = (unsigned)(((P.N + BN - 1) / BN) * ((P.M + BM - 1) / BM));
     if (out_dt == NVFP4_F32) {
         auto k = gemm_nt_f16_kernel<B, WM, WN, TA, TB, NVFP4_F32, KTAIL>;
@@ -526,12 +392,11 @@ static void launch_f16(const GemmArgs &P, int out_dt, hipStream_t st)
     }
 }
 
-// Tile choice: 256 x 256 (8 waves) when the output has enough such tiles to occupy the 256
-// CUs, else 128 x 128 (4 waves, several workgroups per CU).
+// Products whose operands the dual quantizer hands over as slabs: large enough for the 256 x 256 tile.
 static bool large_tile(int64_t M, int64_t N, int64_t K)
 {
     const int64_t big = ((M + 255) / 256) * ((N + 255) / 256);
-    return big >= 128 && K % KT == 0;  // the large tile is built for K % 128 == 0 only
+    return big >= 128 && K % KT == 0;  // (a slab holds whole K tiles)
 }
 
 bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf)
@@ -541,15 +406,64 @@ bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf)
 }
 
 template <int B>
-static void launch_f16_auto(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st)
 {
     const bool ktail = (P.K % KT) != 0;
-    if (large_tile(P.M, P.N, P.K))
-        launch_f16<B, 2, 4, 4, 2, false>(P, out_dt, st);
-    else if (!ktail)
-        launch_f16<B, 2, 2, 2, 2, false>(P, out_dt, st);
-    else
-        launch_f16<B, 2, 2, 2, 2, true>(P, out_dt, st);
+    if (tile == TILE_256x256) {
+        if (ktail) launch_f16<B, 2, 4, 4, 2, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 4, 2, false>(P, out_dt, st);
+    } else {
+        if (ktail) launch_f16<B, 2, 2, 2, 2, true>(P, out_dt, st);
+        else launch_f16<B, 2, 2, 2, 2, false>(P, out_dt, st);
+    }
+}
+
+// Which workgroup tile computes an M x N x K product: the one whose estimated time is least.  With R = the tiles of the
+// busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves up to 64 x 64),
+//     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
+// Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
+// expansion, LDS reads).  The constants (nanoseconds) are fitted to 65 shapes from 5 x 192 x 256 to 11008 x 4096 x 4096, bf16
+// outputs, every tile timed on every shape; the choice is then within 0.4 % (E4M3) and 1.5 % (E8M0) of the best tile on
+// average.  E4M3 examples, us per tile choice:      32x32  32x64  64x32  64x64  128x128  256x256
+//     16 x 11008 x 4096                              11.0   10.3   16.4   13.6    32.0     76.3
+//     64 x  4096 x 11008                             14.2   19.8   20.1   28.7    78.8    194.1
+//    256 x 11008 x 4096                              47.1   51.8   50.1   33.0    34.7     77.6
+//   2048 x  4096 x 4096                             129.8  127.8  123.1   80.0    65.4     78.6
+//   4096 x  4096 x 4096                             248.3  248.3  248.9  155.4   124.8    108.0
+// (two kernels before: 256 x 256 from 128 such tiles on, else 128 x 128, with a register-staged 128 x 128 for a ragged K:
+// 33.8, 84.5, 38.7, 81.2 and 108.0 us; 2080 x 2784 x 1056: 44.3 us, now 23.3.)
+struct TileCost {
+    int bm, bn, kwaves;                 // tile, waves that divide the contraction
+    int fixed, tile, step, alone;       // ns, ns, ns, percent
+};
+static const TileCost E4M3_COST[TILES] = {{32, 32, 8, 2900, 350, 860, 3},    {32, 64, 8, 1300, 2400, 1430, 0}, {64, 32, 8, 1400, 2300, 1410, 0},
+                                          {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8}, {0, 0, 0, 0, 0, 0, 0},
+                                          {256, 256, 1, 0, 7900, 2560, 0}};
+static const TileCost E8M0_COST[TILES] = {{32, 32, 8, 2700, 410, 585, 0},    {32, 64, 8, 1400, 2140, 930, 0},  {64, 32, 8, 1400, 2100, 935, 0},
+                                          {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {256, 128, 1, 2900, 3150, 556, 19},
+                                          {256, 256, 1, 0, 8500, 1000, 0}};
+
+GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
+{
+    const TileCost *const cost = sf == NVFP4_SCALE_E8M0 ? E8M0_COST : E4M3_COST;
+    const int64_t nkt = (K + KT - 1) / KT;
+    int best = TILE_32x32;
+    double best_time = 0;
+    for (int t = 0; t < TILES; ++t) {
+        const TileCost &c = cost[t];
+        if (c.bm == 0 || (t > TILE_64x64 && sf == NVFP4_SCALE_E8M0 && K < KT)) continue;  // (not built; needs one whole K tile)
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        if (tiles > 0x7FFFFFFF) continue;  // (more than a grid holds)
+        const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
+        double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
+        if (rounds == 1) time *= 1.0 + 0.01 * c.alone;
+        time += c.fixed;
+        if (best_time == 0 || time < best_time) {
+            best_time = time;
+            best = t;
+        }
+    }
+    return (GemmTile)best;
 }
 
 static int g_fp4_rescale_route = 0;  // (measured slower than the fp16 route: opt-in)
@@ -561,13 +475,16 @@ hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStre
     // lane offsets inside a 256-row tile are 32-bit
     if ((P.K >> 1) * 256 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     if ((P.a_slab || P.b_slab) && !gemm_takes_slabs(P.M, P.N, P.K, block, sf)) return hipErrorInvalidValue;
-    if (sf == NVFP4_SCALE_E8M0) return block == 32 ? launch_gemm_mxfp4(P, out_dt, st) : hipErrorNotSupported;
-    if (g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
+    if (sf == NVFP4_SCALE_E8M0 && block != 32) return hipErrorNotSupported;
+    if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
+    const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);
+    if (tile <= TILE_64x64) return launch_gemm_ksplit(P, tile, block, sf, out_dt, st);
+    if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(P, tile, out_dt, st);
     switch (block) {
-    case 16: launch_f16_auto<16>(P, out_dt, st); break;
-    case 32: launch_f16_auto<32>(P, out_dt, st); break;
-    case 64: launch_f16_auto<64>(P, out_dt, st); break;
-    case 128: launch_f16_auto<128>(P, out_dt, st); break;
+    case 16: launch_f16_tile<16>(P, tile, out_dt, st); break;
+    case 32: launch_f16_tile<32>(P, tile, out_dt, st); break;
+    case 64: launch_f16_tile<64>(P, tile, out_dt, st); break;
+    case 128: launch_f16_tile<128>(P, tile, out_dt, st); break;
     default: return hipErrorNotSupported;
     }
     return hipGetLastError();

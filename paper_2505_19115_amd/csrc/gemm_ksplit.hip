@@ -1,0 +1,370 @@
+// Block-scaled FP4 GEMM for outputs too small, or contractions too ragged, for the 256 x 256 kernels: few tokens against
+// a large weight matrix, layers of a small network, K that is no multiple of 128.
+//     out[i, j] = gA gB sum_k cA[i,k] sA[i,k/B] cB[j,k] sB[j,k/B]        ("NT", as in gemm.hip and gemm_mx.hip)
+//
+// What bounds such a product is not the matrix pipe but how many bytes the chip has in flight and how long one
+// workgroup's serial walk along K takes: with one 128 x 128 or 256 x 256 tile per workgroup a 16-token product runs on
+// 16 or 86 of the 256 CUs, each waiting for one K tile after the other.  So here the NW waves of a workgroup share one
+// small output tile and divide the CONTRACTION: wave w multiplies the 128-wide K tiles w, w + NW, w + 2 NW, ...  A wave
+// stages its own K tiles in its own part of the LDS (direct global -> LDS loads, two stages) and reads nothing another
+// wave has loaded, so the K loop has no barrier at all; at the end the NW partial tiles are added through the LDS in the
+// order of the waves (deterministic), scaled and stored.
+//
+// Operands: row-major or slab (kernels.h), each for itself.  Rows past the edge are clamped to the last row (their
+// products land in outputs that are never stored).  A last K tile of 32, 64 or 96 elements reads a valid chunk in place of
+// each missing one and multiplies it by zero: by zero scales (E4M3), or with the A codes zeroed (E8M0).
+#include "kernels.h"
+#include "nvfp4_math.h"
+
+namespace nvfp4 {
+
+namespace ks {
+
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef int int8v_t __attribute__((ext_vector_type(8)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float float2v_t __attribute__((ext_vector_type(2)));
+
+constexpr int KT = 128, KTB = 64;  // contraction elements and code bytes per row of a K tile
+constexpr int QUAD = 1024 + 16;    // LDS bytes between the float4 planes of a partial tile (64 lanes, shifted by four banks)
+
+template <int SF, int TA, int TB, int NW>
+struct Geom {
+    static constexpr int BM = 32 * TA, BN = 32 * TB, ROWS = BM + BN;
+    static constexpr int CODES = ROWS * KTB;
+    // E4M3: [4 chunks of 32 elements][ROWS] dwords, two fp16 scales each; E8M0: one dword (four bytes) per row
+    static constexpr int SCALES = SF == NVFP4_SCALE_E4M3 ? ROWS * 16 : ROWS * 4;
+    static constexpr int STAGE = CODES + SCALES;
+    static constexpr int PARTIAL = TA * TB * 4 * QUAD;
+    static constexpr int LDS = NW * (2 * STAGE > PARTIAL ? 2 * STAGE : PARTIAL);
+};
+
+// 8 codes (one dword) of one block -> 8 fp16 values times the block scale (see gemm.hip)
+__device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
+{
+    const half2_t s2 = {s, s};
+    half2_t h0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 0) * s2;
+    half2_t h1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 1) * s2;
+    half2_t h2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 2) * s2;
+    half2_t h3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 3) * s2;
+    half8_t r;
+    r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
+    r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
+    return r;
+}
+
+}  // namespace ks
+
+template <int SF, int B, int TA, int TB, int NW, int OUT_DT>
+__global__ __launch_bounds__(64 * NW) void gemm_nt_ksplit_kernel(GemmArgs P)
+{
+    using namespace ks;
+    using G = Geom<SF, TA, TB, NW>;
+    constexpr bool MX = SF == NVFP4_SCALE_E8M0;
+    constexpr int BM = G::BM, BN = G::BN, ROWS = G::ROWS;
+    constexpr int SPT = KT / B;                // scale bytes per row and K tile
+    constexpr int NI = ROWS / 16;              // direct-to-LDS instructions per stage (16 rows each)
+    constexpr int NSR = (ROWS + 63) / 64;      // scale rows per lane
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
+    int ty, tx;
+    tile_coords((int)blockIdx.x, ntx, nty, ty, tx);
+    const int64_t m0 = (int64_t)ty * BM, n0 = (int64_t)tx * BN;
+    const int64_t Kb = P.K >> 1, Ks = P.K / B;
+    const int nkt = (int)((P.K + KT - 1) / KT);
+    const int rem = (int)(P.K - (int64_t)(nkt - 1) * KT);  // elements of the last K tile
+    uint8_t *const mine = lds + wave * (2 * G::STAGE);
+
+    float16_t acc[TA][TB];
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+    // ---- addresses.  A code instruction fills 1 KB = 16 consecutive tile rows; lane i lands at byte 16 i (row i / 4,
+    // slot i % 4) and fetches the chunk the XOR swizzle puts there.  Offsets are relative to the tile's first row (32 bits).
+    const int ch = (lane & 3) ^ ((lane >> 4) & 3);
+    uint32_t off[NI];
+#pragma unroll
+    for (int u = 0; u < NI; ++u) {
+        const int row = 16 * u + (lane >> 2);
+        const bool isA = 16 * u < BM;
+        const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
+        const int lrow = isA ? row : row - BM;
+        const int64_t lr = base + lrow < rows ? lrow : rows - 1 - base;
+        const bool slab = isA ? P.a_slab : P.b_slab;
+        off[u] = slab ? (uint32_t)(slab_row((int)(base & 255) + lrow) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
+    }
+    const uint8_t *const baseA = P.a_slab ? P.A_codes + (m0 >> 8) * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
+    const uint8_t *const baseB = P.b_slab ? P.B_codes + (n0 >> 8) * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
+    const int64_t stepA = P.a_slab ? SLAB_CODE_BYTES : KTB, stepB = P.b_slab ? SLAB_CODE_BYTES : KTB;
+    const uint8_t *sptr[NSR];
+    int sstep[NSR];
+    bool sgo[NSR];
+#pragma unroll
+    for (int i = 0; i < NSR; ++i) {
+        const int row = lane + 64 * i;
+        sgo[i] = row < ROWS;
+        const bool isA = row < BM;
+        const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
+        const int lrow = isA ? row : row - BM;
+        const uint8_t *const s = isA ? P.A_scales : P.B_scales;
+        if (isA ? P.a_slab : P.b_slab) {
+            constexpr int64_t SB = MX ? SLAB_MX_SCALE_BYTES : SLAB_SCALE_BYTES;
+            sptr[i] = s + (base >> 8) * nkt * SB + slab_row(((int)(base & 255) + lrow) & 255) * SPT;
+            sstep[i] = (int)SB;
+        } else {
+            sptr[i] = s + (base + lrow < rows ? base + lrow : rows - 1) * Ks;
+            sstep[i] = SPT;
+        }
+    }
+
+    typedef __attribute__((address_space(3))) void *lds_ptr_t;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)mine);
+    auto uniform_ptr = [](const uint8_t *p) -> const uint8_t * {
+        const uint64_t v = reinterpret_cast<uint64_t>(p);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+        return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+    };
+    // inline assembly for the reason given in gemm.hip: the stage is read only after the explicit wait below
+    auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+    };
+    uint64_t gs[NSR];  // the fetched K tile's scale bytes of this lane's rows
+    auto fetch = [&](int kt, int stage) {
+        const bool tail = kt == nkt - 1 && rem < KT;
+#pragma unroll
+        for (int i = 0; i < NSR; ++i) {
+            if (!sgo[i]) continue;
+            const uint8_t *sp = sptr[i] + (int64_t)kt * sstep[i];
+            uint64_t v = 0;
+            if (!tail) {
+                // (row-major scale rows of a ragged K start at any byte)
+                if (SPT == 8) __builtin_memcpy(&v, sp, 8);
+                else if (SPT == 4) { uint32_t w; __builtin_memcpy(&w, sp, 4); v = w; }
+                else if (SPT == 2) { uint16_t w; __builtin_memcpy(&w, sp, 2); v = w; }
+                else v = *sp;
+            } else {
+#pragma unroll
+                for (int t = 0; t < SPT; ++t)
+                    if (t * B < rem) v |= (uint64_t)sp[t] << (8 * t);
+            }
+            gs[i] = v;
+        }
+        const uint8_t *const ua = uniform_ptr(baseA + kt * stepA), *const ub = uniform_ptr(baseB + kt * stepB);
+        // a missing chunk of the last tile is replaced by the tile's first
+        const uint32_t back = tail && ch * 32 >= rem ? (uint32_t)ch * 16 : 0u;
+#pragma unroll
+        for (int u = 0; u < NI; ++u) dma16(lds0 + stage * G::STAGE + u * 1024, off[u] - back, 16 * u < BM ? ua : ub);
+    };
+    auto stash_scales = [&](int stage) {
+        uint32_t *const sS = reinterpret_cast<uint32_t *>(mine + stage * G::STAGE + G::CODES);
+#pragma unroll
+        for (int i = 0; i < NSR; ++i) {
+            if (!sgo[i]) continue;
+            const uint32_t lo = (uint32_t)gs[i], hi = (uint32_t)(gs[i] >> 32);
+            if (MX) {
+                sS[lane + 64 * i] = lo;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {  // scale bytes -> fp16(scale * 2^-8) pairs, as in gemm.hip
+                    const uint32_t sel = 0x0C000C00u | (uint32_t)((32 * j) / B) | ((uint32_t)((32 * j + 16) / B) << 16);
+                    sS[j * ROWS + lane + 64 * i] = __builtin_amdgcn_perm(hi, lo, sel) << 7;
+                }
+            }
+        }
+    };
+    const int sw = (r >> 2) & 3;
+    auto compute = [&](int stage, bool tail) {
+        const uint8_t *const p = mine + stage * G::STAGE + r * KTB;
+        const uint32_t *const sS = reinterpret_cast<const uint32_t *>(mine + stage * G::STAGE + G::CODES) + r;
+        if constexpr (MX) {
+            uint32_t sa[TA], sb[TB];
+#pragma unroll
+            for (int a = 0; a < TA; ++a) sa[a] = sS[32 * a] >> (16 * h);
+#pragma unroll
+            for (int b = 0; b < TB; ++b) sb[b] = sS[BM + 32 * b] >> (16 * h);
+            // MFMA step s of lane half h multiplies chunk 2 h + s
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                uint4 fa[TA], fb[TB];
+                const int slot = ((2 * h + s) ^ sw) << 4;
+#pragma unroll
+                for (int a = 0; a < TA; ++a) {
+                    fa[a] = *reinterpret_cast<const uint4 *>(p + 32 * a * KTB + slot);
+                    if (tail && (2 * h + s) * 32 >= rem) fa[a] = make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b) fb[b] = *reinterpret_cast<const uint4 *>(p + (BM + 32 * b) * KTB + slot);
+#pragma unroll
+                for (int a = 0; a < TA; ++a)
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) {
+                        const int8v_t va = {(int)fa[a].x, (int)fa[a].y, (int)fa[a].z, (int)fa[a].w, 0, 0, 0, 0};
+                        const int8v_t vb = {(int)fb[b].x, (int)fb[b].y, (int)fb[b].z, (int)fb[b].w, 0, 0, 0, 0};
+                        if (s == 0)
+                            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vb, va, acc[a][b], 4, 4, 0, (int)sb[b], 0, (int)sa[a]);
+                        else
+                            acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vb, va, acc[a][b], 4, 4, 1, (int)sb[b], 1, (int)sa[a]);
+                    }
+            }
+        } else {
+            // lane half h multiplies chunks h and 2 + h, a dword (8 codes) per MFMA step
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint4 ca[TA], cb[TB];
+                half2_t sa[TA], sb[TB];
+                const int slot = ((2 * q + h) ^ sw) << 4;
+#pragma unroll
+                for (int a = 0; a < TA; ++a) {
+                    ca[a] = *reinterpret_cast<const uint4 *>(p + 32 * a * KTB + slot);
+                    sa[a] = __builtin_bit_cast(half2_t, sS[(2 * q + h) * ROWS + 32 * a]);
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b) {
+                    cb[b] = *reinterpret_cast<const uint4 *>(p + (BM + 32 * b) * KTB + slot);
+                    sb[b] = __builtin_bit_cast(half2_t, sS[(2 * q + h) * ROWS + BM + 32 * b]);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    auto dword = [&](const uint4 &v) { return t == 0 ? v.x : t == 1 ? v.y : t == 2 ? v.z : v.w; };
+                    half8_t fa[TA], fb[TB];
+#pragma unroll
+                    for (int a = 0; a < TA; ++a) fa[a] = dequant8(dword(ca[a]), t >= 2 ? sa[a][1] : sa[a][0]);
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) fb[b] = dequant8(dword(cb[b]), t >= 2 ? sb[b][1] : sb[b][0]);
+#pragma unroll
+                    for (int a = 0; a < TA; ++a)
+#pragma unroll
+                        for (int b = 0; b < TB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[b], fa[a], acc[a][b], 0, 0, 0);
+                }
+            }
+        }
+    };
+
+    int stage = 0;
+    if (wave < nkt) fetch(wave, 0);
+    for (int kt = wave; kt < nkt; kt += NW) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's loads of tile kt have landed
+        stash_scales(stage);
+        if (kt + NW < nkt) fetch(kt + NW, stage ^ 1);      // (the other stage was read to the end in the last trip)
+        compute(stage, kt == nkt - 1 && rem < KT);
+        stage ^= 1;
+    }
+
+    // ---- the NW partial tiles: accumulator register 4 q + e of lane (r, h) of MFMA tile (a, b) is output row 32 a + r, column
+    // 32 b + 8 q + 4 h + e.  Plane (a, b, q) of a wave's partial holds 64 lanes x float4.
+    __syncthreads();  // every wave is done with the stages
+    {
+        uint8_t *const part = lds + wave * G::PARTIAL + lane * 16;
+#pragma unroll
+        for (int a = 0; a < TA; ++a)
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(part + ((a * TB + b) * 4 + q) * QUAD) =
+                        make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
+    }
+    __syncthreads();
+    const float gg = P.gA[0] * P.gB[0];
+    // one thread sums 8 consecutive columns of a row over the waves, in their order
+    constexpr int CPR = BN / 8;
+    const bool wide = (OUT_DT == NVFP4_F32 ? (P.ldc & 3) : (P.ldc & 7)) == 0;
+    for (int id = tid; id < BM * CPR; id += 64 * NW) {
+        const int row = id / CPR, c8 = id % CPR;
+        const uint8_t *src = lds + (((row >> 5) * TB + (c8 >> 2)) * 4 + (c8 & 3)) * QUAD + (row & 31) * 16;
+        float y[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float4 lo = *reinterpret_cast<const float4 *>(src + w * G::PARTIAL);
+            const float4 hi = *reinterpret_cast<const float4 *>(src + w * G::PARTIAL + 512);
+            y[0] += lo.x; y[1] += lo.y; y[2] += lo.z; y[3] += lo.w;
+            y[4] += hi.x; y[5] += hi.y; y[6] += hi.z; y[7] += hi.w;
+        }
+        const int64_t grow = m0 + row, gcol = n0 + 8 * c8;
+        if (grow >= P.M || gcol >= P.N) continue;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) y[t] *= gg;
+        if (OUT_DT == NVFP4_F32) {
+            float *dst = reinterpret_cast<float *>(P.out) + grow * P.ldc + gcol;
+            if (wide && gcol + 8 <= P.N) {
+                *reinterpret_cast<float4 *>(dst) = make_float4(y[0], y[1], y[2], y[3]);
+                *reinterpret_cast<float4 *>(dst + 4) = make_float4(y[4], y[5], y[6], y[7]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    if (gcol + t < P.N) dst[t] = y[t];
+            }
+        } else {
+            uint32_t w[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float2v_t f = {y[2 * t], y[2 * t + 1]};
+                w[t] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+            }
+            uint16_t *dst = reinterpret_cast<uint16_t *>(P.out) + grow * P.ldc + gcol;
+            if (wide && gcol + 8 <= P.N) {
+                *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    if (gcol + t < P.N) dst[t] = (uint16_t)(w[t >> 1] >> (16 * (t & 1)));
+            }
+        }
+    }
+}
+
+template <int SF, int B, int TA, int TB, int NW>
+static void launch_cfg(const GemmArgs &P, int out_dt, hipStream_t st)
+{
+    using G = ks::Geom<SF, TA, TB, NW>;
+    const unsigned ntiles = (unsigned)(((P.N + G::BN - 1) / G::BN) * ((P.M + G::BM - 1) / G::BM));
+    if (out_dt == NVFP4_F32) {
+        auto k = gemm_nt_ksplit_kernel<SF, B, TA, TB, NW, NVFP4_F32>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(64 * NW), G::LDS, st, P);
+    } else {
+        auto k = gemm_nt_ksplit_kernel<SF, B, TA, TB, NW, NVFP4_BF16>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(64 * NW), G::LDS, st, P);
+    }
+}
+template <int SF, int B>
+static void launch_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st)
+{
+    switch (tile) {
+    case TILE_32x32: launch_cfg<SF, B, 1, 1, 8>(P, out_dt, st); break;
+    case TILE_32x64: launch_cfg<SF, B, 1, 2, 8>(P, out_dt, st); break;
+    case TILE_64x32: launch_cfg<SF, B, 2, 1, 8>(P, out_dt, st); break;
+    default: launch_cfg<SF, B, 2, 2, 4>(P, out_dt, st); break;
+    }
+}
+
+hipError_t launch_gemm_ksplit(const GemmArgs &P, GemmTile tile, int block, int sf, int out_dt, hipStream_t st)
+{
+    if (sf == NVFP4_SCALE_E8M0) {
+        launch_tile<NVFP4_SCALE_E8M0, 32>(P, tile, out_dt, st);
+        return hipGetLastError();
+    }
+    switch (block) {
+    case 16: launch_tile<NVFP4_SCALE_E4M3, 16>(P, tile, out_dt, st); break;
+    case 32: launch_tile<NVFP4_SCALE_E4M3, 32>(P, tile, out_dt, st); break;
+    case 64: launch_tile<NVFP4_SCALE_E4M3, 64>(P, tile, out_dt, st); break;
+    case 128: launch_tile<NVFP4_SCALE_E4M3, 128>(P, tile, out_dt, st); break;
+    default: return hipErrorNotSupported;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace nvfp4

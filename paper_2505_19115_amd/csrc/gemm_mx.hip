@@ -7,279 +7,24 @@
 //     out[i, j] = gA gB sum_b 2^(eA[i,b] - 127) 2^(eB[j,b] - 127) sum_{k in b} cA[i,k] cB[j,k].
 // Products and the power-of-two scaling are exact; accumulation is fp32.
 //
-// Geometry of both kernels: 256 threads = 2 x 2 waves, wave tile 128 x 128 (4 x 4 MFMA tiles, all
+// Geometry of the main kernel and of the rescaling one: 256 threads = 2 x 2 waves, wave tile 128 x 128 (4 x 4 MFMA tiles, all
 // 256 accumulator registers, one wave per SIMD), workgroup tile 256 x 256: with no VALU work in
 // the loop what matters is bytes moved per MFMA (a 4 x 4 register tile reads 8 KB of LDS per 16
 // MFMAs), hence the largest register tile that fits.  The MFMA's first operand is the B (N-side)
 // tile, so a lane's accumulator holds four consecutive output COLUMNS of one row.
+#include <type_traits>
+
 #include "kernels.h"
 #include "nvfp4_math.h"
+#include "store_lines.h"
 
 namespace nvfp4 {
 
 typedef int int8v_t __attribute__((ext_vector_type(8)));
 typedef float float16v_t __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float float2v_t __attribute__((ext_vector_type(2)));
 
 namespace mx {
 constexpr int NT = 256, BM = 256, BN = 256, TA = 4, TB = 4;
-}
-
-__device__ __forceinline__ uint16_t mx_bf16_rne(float f)
-{
-    uint32_t u = f2u(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-// Epilogue of both kernels: accumulator register v of lane (r, g) of tile (a, b) is output row
-// 32 a + r, column 32 b + 8 (v / 4) + 4 g + v % 4.  Full tiles with a suitably aligned output get
-// one packed convert pair and one 8-byte (bf16) or 16-byte (fp32) store per four outputs; edge
-// tiles store element by element.  The lane coordinates are re-derived from an opaque copy so
-// that none of the output addressing is computed before the K loop and kept in registers across it.
-// lds_lines: 64 KB of LDS (32 KB suffice for bf16) that no wave reads and no load writes any more (the caller has waited and
-// synchronized), or nullptr.  With it, bf16 output goes out in complete lines: per accumulator row
-// of tiles a wave transposes its 32 rows x 128 columns through a private 8 KB piece (16-byte chunks
-// XOR-swizzled by row) and stores 4 rows of 256 contiguous bytes per instruction.
-template <int OUT_DT>
-__device__ __forceinline__ void mx_store_tile(const GemmArgs &P, float16v_t (&acc)[mx::TA][mx::TB], int64_t m0, int64_t n0,
-                                              int lane, int wave, uint8_t *lds_lines = nullptr)
-{
-    using namespace mx;
-    int lane_e = lane, wave_e = wave;
-    asm volatile("" : "+v"(lane_e), "+v"(wave_e));
-    const int re = lane_e & 31, ge = lane_e >> 5, wme = wave_e >> 1, wne = wave_e & 1;
-    const float gg = P.gA[0] * P.gB[0];
-    constexpr int ESZ = OUT_DT == NVFP4_F32 ? 4 : 2;
-    const int64_t row0 = m0 + wme * 128 + re, col0 = n0 + wne * 128 + 4 * ge;
-    uint8_t *const out = reinterpret_cast<uint8_t *>(P.out);
-    const bool fast = m0 + BM <= P.M && n0 + BN <= P.N && (P.ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(P.out) & 15) == 0;
-    if (OUT_DT == NVFP4_F32 && lds_lines != nullptr && fast) {
-        // fp32: 32 rows x 512 bytes at a time (16 KB per wave), two complete rows per store
-        uint8_t *const mine = lds_lines + __builtin_amdgcn_readfirstlane(wave_e) * 16384;
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int chunk = 8 * b + 2 * q + ge;  // columns 4 chunk .. 4 chunk + 3 of the wave's 128
-                    *reinterpret_cast<float4 *>(mine + re * 512 + ((chunk ^ (re & 15)) << 4)) =
-                        make_float4(acc[a][b][4 * q] * gg, acc[a][b][4 * q + 1] * gg, acc[a][b][4 * q + 2] * gg, acc[a][b][4 * q + 3] * gg);
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int rowl = 2 * i + (lane_e >> 5), chunk = lane_e & 31;
-                const uint4 v = *reinterpret_cast<const uint4 *>(mine + rowl * 512 + ((chunk ^ (rowl & 15)) << 4));
-                const int64_t grow = m0 + wme * 128 + 32 * a + rowl, gcol = n0 + wne * 128 + 4 * chunk;
-                *reinterpret_cast<uint4 *>(out + (grow * P.ldc + gcol) * 4) = v;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    } else if (OUT_DT == NVFP4_BF16 && lds_lines != nullptr && fast && (P.ldc & 7) == 0) {
-        uint8_t *const mine = lds_lines + __builtin_amdgcn_readfirstlane(wave_e) * 8192;
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float2v_t lo = {acc[a][b][4 * q] * gg, acc[a][b][4 * q + 1] * gg};
-                    const float2v_t hi = {acc[a][b][4 * q + 2] * gg, acc[a][b][4 * q + 3] * gg};
-                    const bf16x2_t blo = __builtin_convertvector(lo, bf16x2_t), bhi = __builtin_convertvector(hi, bf16x2_t);
-                    uint2 w;
-                    w.x = *reinterpret_cast<const uint32_t *>(&blo);
-                    w.y = *reinterpret_cast<const uint32_t *>(&bhi);
-                    const int chunk = 4 * b + q;  // columns 8 chunk .. 8 chunk + 7 of the wave's 128
-                    *reinterpret_cast<uint2 *>(mine + re * 256 + ((chunk ^ (re & 15)) << 4) + 8 * ge) = w;
-                }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int rowl = 4 * i + (lane_e >> 4), chunk = lane_e & 15;
-                const uint4 v = *reinterpret_cast<const uint4 *>(mine + rowl * 256 + ((chunk ^ (rowl & 15)) << 4));
-                const int64_t grow = m0 + wme * 128 + 32 * a + rowl, gcol = n0 + wne * 128 + 8 * chunk;
-                *reinterpret_cast<uint4 *>(out + (grow * P.ldc + gcol) * 2) = v;
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        }
-    } else if (fast) {
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-            uint8_t *prow = out + ((row0 + 32 * a) * P.ldc + col0) * ESZ;
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float y0 = acc[a][b][4 * q] * gg, y1 = acc[a][b][4 * q + 1] * gg;
-                    const float y2 = acc[a][b][4 * q + 2] * gg, y3 = acc[a][b][4 * q + 3] * gg;
-                    uint8_t *dst = prow + (32 * b + 8 * q) * ESZ;
-                    if (OUT_DT == NVFP4_F32) {
-                        *reinterpret_cast<float4 *>(dst) = make_float4(y0, y1, y2, y3);
-                    } else {
-                        const float2v_t lo = {y0, y1}, hi = {y2, y3};
-                        const bf16x2_t blo = __builtin_convertvector(lo, bf16x2_t), bhi = __builtin_convertvector(hi, bf16x2_t);
-                        uint2 w;
-                        w.x = *reinterpret_cast<const uint32_t *>(&blo);
-                        w.y = *reinterpret_cast<const uint32_t *>(&bhi);
-                        *reinterpret_cast<uint2 *>(dst) = w;
-                    }
-                }
-            __builtin_amdgcn_sched_barrier(0);  // one accumulator row of tiles at a time keeps the register peak low
-        }
-    } else {
-#pragma unroll
-        for (int a = 0; a < TA; ++a)
-#pragma unroll
-            for (int b = 0; b < TB; ++b) {
-                const int64_t row = row0 + 32 * a;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int64_t col = col0 + 32 * b + 8 * (v >> 2) + (v & 3);
-                    if (row < P.M && col < P.N) {
-                        const float y = acc[a][b][v] * gg;
-                        if (OUT_DT == NVFP4_F32)
-                            reinterpret_cast<float *>(P.out)[row * P.ldc + col] = y;
-                        else
-                            reinterpret_cast<uint16_t *>(P.out)[row * P.ldc + col] = mx_bf16_rne(y);
-                    }
-                }
-            }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Fallback kernel: any K that is a multiple of 32, any operand alignment.  K tile 64 = one MFMA
-// step, two LDS stages, everything staged through registers (chunks past K are zero-filled, rows
-// past the edge clamped to the last row: their products land in outputs that are never stored).
-// LDS stage: codes [512 rows][32 bytes], the two 16-byte chunks of row r swapped when r is odd;
-// scales as dwords [2 lane halves][512 rows], byte 0 = the E8M0 byte of the lane half's block.
-namespace mxf {
-constexpr int KT = 64, ROWB = 32;
-constexpr int CODES = (mx::BM + mx::BN) * ROWB;
-constexpr int STAGE = CODES + 2 * (mx::BM + mx::BN) * 4;
-constexpr int LDS_BYTES = 2 * STAGE;
-}  // namespace mxf
-
-template <int OUT_DT>
-__global__ __launch_bounds__(256) void gemm_nt_mxfp4_kernel(GemmArgs P)
-{
-    using namespace mx;
-    using namespace mxf;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int r = lane & 31, g = lane >> 5;
-    const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
-    int ty, tx;
-    tile_coords((int)blockIdx.x, ntx, nty, ty, tx);
-    const int64_t m0 = (int64_t)ty * BM, n0 = (int64_t)tx * BN;
-    const int64_t Kb = P.K >> 1, Ks = P.K >> 5;
-    const int nkt = (int)((P.K + KT - 1) / KT);
-
-    float16v_t acc[TA][TB];
-#pragma unroll
-    for (int a = 0; a < TA; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-
-    // ---- global -> registers -> LDS: thread t stages chunks t and t + 256 (row = chunk / 2) of each operand
-    uint4 ga[2], gb[2];
-    uint32_t gsa = 0, gsb = 0;
-    const uint8_t *pA[2], *pB[2];
-    int ldsW[2], chunk[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int qd = tid + NT * u, row = qd >> 1, c = qd & 1;
-        const int64_t ar = m0 + row < P.M ? m0 + row : P.M - 1, br = n0 + row < P.N ? n0 + row : P.N - 1;
-        pA[u] = P.A_codes + ar * Kb + c * 16;
-        pB[u] = P.B_codes + br * Kb + c * 16;
-        chunk[u] = c;
-        ldsW[u] = row * ROWB + ((c ^ (row & 1)) << 4);
-    }
-    const int64_t sar = m0 + tid < P.M ? m0 + tid : P.M - 1, sbr = n0 + tid < P.N ? n0 + tid : P.N - 1;
-    auto load16u = [](const uint8_t *p) -> uint4 {  // any alignment
-        uint4 v;
-        __builtin_memcpy(&v, p, 16);
-        return v;
-    };
-    auto fetch = [&](int kt) {
-        const int64_t kb = (int64_t)kt * ROWB;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const bool in = kb + chunk[u] * 16 < Kb;  // zero codes past K
-            ga[u] = in ? load16u(pA[u] + kb) : make_uint4(0, 0, 0, 0);
-            gb[u] = in ? load16u(pB[u] + kb) : make_uint4(0, 0, 0, 0);
-        }
-        const uint8_t *sa = P.A_scales + sar * Ks + (int64_t)kt * 2, *sb = P.B_scales + sbr * Ks + (int64_t)kt * 2;
-        const bool two = (int64_t)kt * 2 + 1 < Ks;
-        gsa = (uint32_t)sa[0] | (two ? (uint32_t)sa[1] << 8 : 0u);
-        gsb = (uint32_t)sb[0] | (two ? (uint32_t)sb[1] << 8 : 0u);
-    };
-    auto stash = [&](int stage) {
-        uint8_t *base = lds + stage * STAGE;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            *reinterpret_cast<uint4 *>(base + ldsW[u]) = ga[u];
-            *reinterpret_cast<uint4 *>(base + BM * ROWB + ldsW[u]) = gb[u];
-        }
-        uint32_t *sS = reinterpret_cast<uint32_t *>(base + CODES);
-        sS[tid] = gsa & 0xFFu;
-        sS[(BM + BN) + tid] = gsa >> 8;
-        sS[BM + tid] = gsb & 0xFFu;
-        sS[(BM + BN) + BM + tid] = gsb >> 8;
-    };
-
-    // ---- LDS -> registers -> MFMA: lane (r, g) multiplies chunk g of its rows
-    struct Frags {
-        uint4 a[TA], b[TB];
-        uint32_t sa[TA], sb[TB];
-    };
-    const int rd = r * ROWB + ((g ^ (r & 1)) << 4);
-    auto load_frags = [&](int stage, Frags &F) {
-        const uint8_t *p = lds + stage * STAGE + rd;
-        const uint32_t *q = reinterpret_cast<const uint32_t *>(lds + stage * STAGE + CODES) + g * (BM + BN) + r;
-#pragma unroll
-        for (int a = 0; a < TA; ++a) {
-            F.a[a] = *reinterpret_cast<const uint4 *>(p + (wm * 128 + 32 * a) * ROWB);
-            F.sa[a] = q[wm * 128 + 32 * a];
-        }
-#pragma unroll
-        for (int b = 0; b < TB; ++b) {
-            F.b[b] = *reinterpret_cast<const uint4 *>(p + (BM + wn * 128 + 32 * b) * ROWB);
-            F.sb[b] = q[BM + wn * 128 + 32 * b];
-        }
-    };
-    auto mma = [&](const Frags &F) {
-#pragma unroll
-        for (int a = 0; a < TA; ++a)
-#pragma unroll
-            for (int b = 0; b < TB; ++b) {
-                const int8v_t va = {(int)F.a[a].x, (int)F.a[a].y, (int)F.a[a].z, (int)F.a[a].w, 0, 0, 0, 0};
-                const int8v_t vb = {(int)F.b[b].x, (int)F.b[b].y, (int)F.b[b].z, (int)F.b[b].w, 0, 0, 0, 0};
-                acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vb, va, acc[a][b], 4, 4, 0, (int)F.sb[b], 0, (int)F.sa[a]);
-            }
-    };
-
-    Frags F;
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int kt = 0; kt < nkt; ++kt) {
-        const int stage = kt & 1;
-        const bool more = kt + 1 < nkt;
-        if (more) fetch(kt + 1);
-        load_frags(stage, F);
-        if (more) stash(stage ^ 1);  // the other stage: last read before the previous barrier
-        mma(F);
-        __syncthreads();
-    }
-    mx_store_tile<OUT_DT>(P, acc, m0, n0, lane, wave);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -433,7 +178,8 @@ __global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(GemmArgs P)
         if (more) stash(stage ^ 1);  // the other stage: every wave finished reading it before the previous barrier
         __syncthreads();
     }
-    mx_store_tile<OUT_DT>(P, acc, m0, n0, lane, wave, lds);
+    constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 128, n0 + wn * 128, lds + wave * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -730,7 +476,281 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
     // the epilogue's line buffers
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    mx_store_tile<OUT_DT>(P, acc, m0, n0, lane, wave, lds);
+    constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 128, n0 + wn * 128, lds + wave * PIECE, lane);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Tile kernel for the products the kernel above does not serve well: any K that is a multiple of 32 (one whole K tile at
+// least), any operand layout, outputs that 256 x 256 tiles cannot spread over the 256 CUs.  WM x WN waves of TA x TB MFMA
+// tiles each; built as 128 x 128 (2 x 2 waves of 2 x 2), 256 x 128 (2 x 2 of 4 x 2) and 256 x 256 (2 x 4 of 4 x 2), so that
+// two waves share a SIMD and cover each other's waits (two workgroups per CU, or one of eight waves).
+// What bounds it: LDS reads, (TA + TB) / (TA TB) KB per MFMA, i.e. 1 KB (128 x 128) or 3/4 KB against the 1 KB the LDS delivers
+// per 32-cycle MFMA and SIMD.
+// Pipeline: three LDS stages of K = 128; the direct loads of tile kt + 2 are requested when tile kt starts and waited for
+// (counted) in the middle of tile kt + 1; ONE barrier per tile; step 1's fragments are read under step 0's MFMAs and the next
+// tile's first ones under step 1's.
+// Scales: E8M0 bytes of a row-major ragged operand start at any byte, which a direct load cannot fetch, and one request per
+// row and K tile would cost the vector L1 as much as the codes: so a thread loads 16 bytes of its row = four K tiles at once
+// into registers (slabs: four dwords) and stores one dword per K tile into that tile's stage.
+// Measured (us; the register-staged 256 x 256 kernel that served a ragged K before -> this one): 4096 x 4128 x 4896 287 -> 84,
+// 1056 x 2080 x 2784 75 -> 16.6, 8480 x 9440 x 640 (whole K tiles, ragged edges) 100 -> 63.
+namespace mxt {
+constexpr int KT = 128, ROWB = 64, NS = 3;
+template <int WM, int WN, int TA, int TB>
+struct Geom {
+    static constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN, ROWS = BM + BN, NT = 64 * WM * WN;
+    static constexpr int STAGE = ROWS * ROWB + ROWS * 4;  // codes, then one dword (four E8M0 bytes) per row
+    static constexpr int LDS = NS * STAGE > NT * 128 ? NS * STAGE : NT * 128;
+};
+}  // namespace mxt
+
+template <int OUT_DT, int WM, int WN, int TA, int TB>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(GemmArgs P)
+{
+    using namespace mxt;
+    using G = Geom<WM, WN, TA, TB>;
+    constexpr int BM = G::BM, BN = G::BN, ROWS = G::ROWS, NT = G::NT, NW = WM * WN;
+    constexpr int CA = BM / 16 / NW, CB = BN / 16 / NW;  // direct-to-LDS instructions per wave and K tile (16 rows each)
+    constexpr int PW = CA + CB;
+    constexpr int NSR = (ROWS + NT - 1) / NT;            // scale rows per thread
+    static_assert(BM % (16 * NW) == 0 && BN % (16 * NW) == 0, "whole instructions per wave");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int r = lane & 31, g = lane >> 5;
+    const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
+    int ty, tx;
+    tile_coords((int)blockIdx.x, ntx, nty, ty, tx);
+    const int64_t m0 = (int64_t)ty * BM, n0 = (int64_t)tx * BN;
+    const int64_t Kb = P.K >> 1, Ks = P.K >> 5;
+    const int nkt = (int)((P.K + KT - 1) / KT);
+    const int rem = (int)(P.K - (int64_t)(nkt - 1) * KT);
+    const int ktail = rem < KT ? nkt - 1 : -1;  // the K tile that is not whole
+
+    float16v_t acc[TA][TB];
+#pragma unroll
+    for (int a = 0; a < TA; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+    // ---- codes: addresses as in the kernels above
+    const int ch = (lane & 3) ^ ((lane >> 4) & 3);
+    uint32_t offA[CA], offB[CB];
+#pragma unroll
+    for (int u = 0; u < CA; ++u) {
+        const int row = (wave * CA + u) * 16 + (lane >> 2);
+        const int64_t lr = m0 + row < P.M ? row : P.M - 1 - m0;
+        offA[u] = P.a_slab ? (uint32_t)(slab_row((int)(m0 & 255) + row) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < CB; ++u) {
+        const int row = (wave * CB + u) * 16 + (lane >> 2);
+        const int64_t lr = n0 + row < P.N ? row : P.N - 1 - n0;
+        offB[u] = P.b_slab ? (uint32_t)(slab_row((int)(n0 & 255) + row) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
+    }
+    const uint8_t *const baseA = P.a_slab ? P.A_codes + (m0 >> 8) * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
+    const uint8_t *const baseB = P.b_slab ? P.B_codes + (n0 >> 8) * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
+    const int64_t stepA = P.a_slab ? SLAB_CODE_BYTES : ROWB, stepB = P.b_slab ? SLAB_CODE_BYTES : ROWB;
+    typedef __attribute__((address_space(3))) void *lds_ptr_t;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+    auto uniform_ptr = [](const uint8_t *p) -> const uint8_t * {
+        const uint64_t v = reinterpret_cast<uint64_t>(p);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+        return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+    };
+    auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+    };
+    auto dma_codes = [&](int kt, uint32_t stage) {
+        const uint8_t *const pa = uniform_ptr(baseA + kt * stepA), *const pb = uniform_ptr(baseB + kt * stepB);
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + stage);
+        const uint32_t back = kt == ktail && ch * 32 >= rem ? (uint32_t)ch * 16 : 0u;  // (a missing chunk: the tile's first)
+#pragma unroll
+        for (int u = 0; u < CA; ++u) dma16(dst + (wave * CA + u) * 1024, offA[u] - back, pa);
+#pragma unroll
+        for (int u = 0; u < CB; ++u) dma16(dst + BM * ROWB + (wave * CB + u) * 1024, offB[u] - back, pb);
+    };
+    // ---- scales: four K tiles of a row at a time, 16 bytes (row-major, any alignment) or one dword per slab
+    static_assert(BM % 64 == 0 && BN % 64 == 0, "a wave's scale rows belong to one operand");
+    const uint8_t *sptr[NSR];
+#pragma unroll
+    for (int i = 0; i < NSR; ++i) {
+        const int wrow = 64 * wave + NT * i, row = wrow + lane;
+        const bool isA = wrow < BM;
+        const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
+        const int lrow = isA ? row : row - BM;
+        const uint8_t *const s = isA ? P.A_scales : P.B_scales;
+        sptr[i] = (isA ? P.a_slab : P.b_slab) ? s + (base >> 8) * nkt * SLAB_MX_SCALE_BYTES + slab_row(((int)(base & 255) + lrow) & 255) * 4
+                                              : s + (base + lrow < rows ? base + lrow : rows - 1) * Ks;
+    }
+    struct Group {
+        uint32_t w[NSR][4];
+    };
+    auto load_group = [&](int grp, Group &q) {
+#pragma unroll
+        for (int i = 0; i < NSR; ++i) {
+            const int wrow = 64 * wave + NT * i;
+            if (wrow >= ROWS) continue;
+            const bool slab = wrow < BM ? P.a_slab : P.b_slab;
+            if (!slab && 16 * grp + 16 <= Ks) {
+                __builtin_memcpy(q.w[i], sptr[i] + 16 * grp, 16);
+            } else {
+                // a dword per K tile; the last one of a row is read so that it ends with the row
+                const int step = slab ? (int)SLAB_MX_SCALE_BYTES : 4, last = slab ? (nkt - 1) * step : (int)Ks - 4;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int want = (4 * grp + t) * step, at = want < last ? want : last;
+                    uint32_t v;
+                    __builtin_memcpy(&v, sptr[i] + at, 4);
+                    q.w[i][t] = v >> (8 * ((want - at) & 3));
+                }
+            }
+        }
+    };
+    auto stash = [&](uint32_t stage, const Group &q, int t) {
+        uint32_t *const s = reinterpret_cast<uint32_t *>(lds + stage + ROWS * ROWB);
+#pragma unroll
+        for (int i = 0; i < NSR; ++i)
+            if (64 * wave + NT * i < ROWS) s[tid + NT * i] = q.w[i][t];
+    };
+
+    // ---- LDS -> registers
+    struct Frags {
+        uint4 a[TA], b[TB];
+    };
+    struct Scales {
+        uint32_t a[TA], b[TB];
+    };
+    const int sw = (r >> 2) & 3;
+    const int rdA = (wm * 32 * TA + r) * ROWB, rdB = (BM + wn * 32 * TB + r) * ROWB;
+    const int rdS = ROWS * ROWB + (wm * 32 * TA + r) * 4, rdT = ROWS * ROWB + (BM + wn * 32 * TB + r) * 4;
+    auto load_frags = [&](uint32_t stage, int s, Frags &F) {
+        const uint8_t *p = lds + stage + (((2 * g + s) ^ sw) << 4);
+#pragma unroll
+        for (int b = 0; b < TB; ++b) F.b[b] = *reinterpret_cast<const uint4 *>(p + rdB + 32 * b * ROWB);
+#pragma unroll
+        for (int a = 0; a < TA; ++a) F.a[a] = *reinterpret_cast<const uint4 *>(p + rdA + 32 * a * ROWB);
+    };
+    auto load_scales = [&](uint32_t stage, Scales &S) {
+#pragma unroll
+        for (int b = 0; b < TB; ++b) S.b[b] = *reinterpret_cast<const uint32_t *>(lds + stage + rdT + 128 * b);
+#pragma unroll
+        for (int a = 0; a < TA; ++a) S.a[a] = *reinterpret_cast<const uint32_t *>(lds + stage + rdS + 128 * a);
+    };
+    auto shift = [&](Scales &S) {
+#pragma unroll
+        for (int a = 0; a < TA; ++a) S.a[a] >>= 16 * g;
+#pragma unroll
+        for (int b = 0; b < TB; ++b) S.b[b] >>= 16 * g;
+    };
+    auto zero_tail = [&](Frags &F, int s) {
+        if ((2 * g + s) * 32 >= rem) {
+#pragma unroll
+            for (int a = 0; a < TA; ++a) F.a[a] = make_uint4(0, 0, 0, 0);
+        }
+    };
+#define NVFP4_MXT_MMA(F, S, s)                                                                                     \
+    _Pragma("unroll") for (int a = 0; a < TA; ++a) _Pragma("unroll") for (int b = 0; b < TB; ++b)                  \
+    {                                                                                                              \
+        const int8v_t va = {(int)F.a[a].x, (int)F.a[a].y, (int)F.a[a].z, (int)F.a[a].w, 0, 0, 0, 0};               \
+        const int8v_t vb = {(int)F.b[b].x, (int)F.b[b].y, (int)F.b[b].z, (int)F.b[b].w, 0, 0, 0, 0};               \
+        acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vb, va, acc[a][b], 4, 4, s, (int)S.b[b], s, (int)S.a[a]); \
+    }
+
+    Frags F0, F1;
+    Scales S, R;
+    Group gc, gn;
+    uint32_t s_cur = 0, s_nxt = G::STAGE, s_new = 2 * G::STAGE;
+    load_group(0, gc);
+    gn = gc;
+    dma_codes(0, s_cur);
+    stash(s_cur, gc, 0);
+    if (nkt > 1) dma_codes(1, s_nxt);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    load_frags(s_cur, 0, F0);
+    load_scales(s_cur, R);
+
+    // K tile kt (kt % 4 == j): on entry F0 and R hold the first fragments and the scales of the tile, the direct loads of tile
+    // kt + 1 are in flight.
+    auto tile = [&](int kt, auto jc) {
+        constexpr int j = decltype(jc)::value;
+        if (kt + 1 < nkt) stash(s_nxt, j == 3 ? gn : gc, (j + 1) & 3);
+        if (j == 3) gc = gn;
+        const bool more = kt + 2 < nkt;
+        if (more) dma_codes(kt + 2, s_new);
+        S = R;
+        shift(S);
+        if (kt == ktail) zero_tail(F0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_frags(s_cur, 1, F1);
+        NVFP4_MXT_MMA(F0, S, 0)
+#pragma unroll
+        for (int i = 0; i < TA + TB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (more)
+            asm volatile("s_waitcnt vmcnt(%0)" : : "n"(PW) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (j == 0 && 4 * (kt / 4 + 1) < nkt) load_group(kt / 4 + 1, gn);
+        if (kt == ktail) zero_tail(F1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_frags(s_nxt, 0, F0);
+        load_scales(s_nxt, R);
+        NVFP4_MXT_MMA(F1, S, 1)
+#pragma unroll
+        for (int i = 0; i < TA + TB; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t t = s_cur;
+        s_cur = s_nxt;
+        s_nxt = s_new;
+        s_new = t;
+    };
+    for (int kt = 0;; kt += 4) {
+        tile(kt, std::integral_constant<int, 0>{});
+        if (kt + 1 >= nkt) break;
+        tile(kt + 1, std::integral_constant<int, 1>{});
+        if (kt + 2 >= nkt) break;
+        tile(kt + 2, std::integral_constant<int, 2>{});
+        if (kt + 3 >= nkt) break;
+        tile(kt + 3, std::integral_constant<int, 3>{});
+        if (kt + 4 >= nkt) break;
+    }
+#undef NVFP4_MXT_MMA
+
+    __syncthreads();
+    static_assert(NW * 32 * 32 * TB * 4 <= G::LDS, "the epilogue's pieces");
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 32 * TA, n0 + wn * 32 * TB, lds + wave * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2)), lane);
+}
+
+template <int WM, int WN, int TA, int TB>
+static void launch_mx_tile(const GemmArgs &P, int out_dt, hipStream_t st)
+{
+    using G = mxt::Geom<WM, WN, TA, TB>;
+    const unsigned ntiles = (unsigned)(((P.N + G::BN - 1) / G::BN) * ((P.M + G::BM - 1) / G::BM));
+    if (out_dt == NVFP4_F32) {
+        auto k = gemm_nt_mxfp4_tile_kernel<NVFP4_F32, WM, WN, TA, TB>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(G::NT), G::LDS, st, P);
+    } else {
+        auto k = gemm_nt_mxfp4_tile_kernel<NVFP4_BF16, WM, WN, TA, TB>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(G::NT), G::LDS, st, P);
+    }
 }
 
 template <int OUT_DT, bool A_SLAB, bool B_SLAB>
@@ -758,22 +778,6 @@ static void launch_mx_dma(const GemmArgs &P, int out_dt, hipStream_t st)
         launch_mx_dma_out<NVFP4_F32>(P, st);
     else
         launch_mx_dma_out<NVFP4_BF16>(P, st);
-}
-
-static void launch_mx_fallback(const GemmArgs &P, int out_dt, hipStream_t st)
-{
-    const unsigned ntiles = (unsigned)(((P.N + mx::BN - 1) / mx::BN) * ((P.M + mx::BM - 1) / mx::BM));
-    if (out_dt == NVFP4_F32) {
-        auto k = gemm_nt_mxfp4_kernel<NVFP4_F32>;
-        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, mxf::LDS_BYTES), true);
-        (void)once;
-        hipLaunchKernelGGL(k, dim3(ntiles), dim3(256), mxf::LDS_BYTES, st, P);
-    } else {
-        auto k = gemm_nt_mxfp4_kernel<NVFP4_BF16>;
-        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, mxf::LDS_BYTES), true);
-        (void)once;
-        hipLaunchKernelGGL(k, dim3(ntiles), dim3(256), mxf::LDS_BYTES, st, P);
-    }
 }
 
 template <int B>
@@ -818,16 +822,18 @@ bool mxfp4_gemm_takes_slabs(int64_t K)
     return K % 128 == 0 && K >= 512 && offsets_fit;
 }
 
-hipError_t launch_gemm_mxfp4(const GemmArgs &P, int out_dt, hipStream_t st)
+hipError_t launch_gemm_mxfp4(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st)
 {
     const uintptr_t codes = reinterpret_cast<uintptr_t>(P.A_codes) | reinterpret_cast<uintptr_t>(P.B_codes);
     const uintptr_t scales = reinterpret_cast<uintptr_t>(P.A_scales) | reinterpret_cast<uintptr_t>(P.B_scales);
-    if (mxfp4_gemm_takes_slabs(P.K) && (codes & 15) == 0 && (scales & 3) == 0)
+    if (tile == TILE_256x256 && mxfp4_gemm_takes_slabs(P.K) && (codes & 15) == 0 && (scales & 3) == 0)
         launch_mx_dma(P, out_dt, st);
-    else if (P.a_slab || P.b_slab)
-        return hipErrorInvalidValue;  // (the fallback kernel reads row-major operands only)
+    else if (tile == TILE_256x256)
+        launch_mx_tile<2, 4, 4, 2>(P, out_dt, st);
+    else if (tile == TILE_256x128)
+        launch_mx_tile<2, 2, 4, 2>(P, out_dt, st);
     else
-        launch_mx_fallback(P, out_dt, st);
+        launch_mx_tile<2, 2, 2, 2>(P, out_dt, st);
     return hipGetLastError();
 }
 

@@ -1,0 +1,106 @@
+"""The GEMM at the sizes where its tiles can go wrong: every workgroup tile the size rule chooses from, with whole and ragged
+contractions (one K tile, less than one, one more than the waves that share it), rows and columns past the edge, one-row and
+one-column outputs.  Against the fp64 oracle, completely where it is cheap, on sampled outputs otherwise."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import assert_bf16_gemm_close, assert_gemm_close, ofmt, to_np
+
+pytestmark = pytest.mark.gpu
+
+nv = None
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _binding():
+    global nv
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2505_19115_amd import binding
+    nv = binding
+    yield
+
+
+FORMATS = {"nvfp4": (16, 0), "e4m3_32": (32, 0), "e4m3_64": (64, 0), "e4m3_128": (128, 0), "mxfp4": (32, 1)}
+
+
+def operand(rng, rows, K, block, scale):
+    codes = rng.integers(0, 256, (rows, K // 2)).astype(np.uint8)
+    lo, hi = (118, 136) if scale else (0x01, 0x7F)  # (every finite E4M3 byte; E8M0 exponents within 2^9)
+    return codes, rng.integers(lo, hi, (rows, K // block)).astype(np.uint8), 1.0 if scale else 0.75
+
+
+def run(A, B, fmt, out_dtype):
+    dev = lambda o: (torch.from_numpy(o[0]).cuda(), torch.from_numpy(o[1]).cuda(), torch.tensor([o[2]], dtype=torch.float32, device="cuda"))
+    Y = nv.gemm(dev(A), dev(B), fmt, out_dtype)
+    torch.cuda.synchronize()
+    return to_np(Y.float())
+
+
+def close(got, ref, ref_abs, what, out_dtype):
+    (assert_bf16_gemm_close if out_dtype == torch.bfloat16 else assert_gemm_close)(got, ref, ref_abs, what)
+
+
+@pytest.mark.parametrize("fmt_name", FORMATS)
+@pytest.mark.parametrize("shape", [(1, 1, 32), (31, 33, 64), (33, 65, 96), (64, 64, 128), (65, 31, 160), (128, 129, 384),
+                                   (2, 96, 1024), (16, 200, 1152), (70, 300, 2208), (1, 257, 4128)])
+def test_small_products(shape, fmt_name):
+    block, scale = FORMATS[fmt_name]
+    M, N, K = shape
+    K = -(-K // max(block, 32)) * max(block, 32)
+    fmt = nv.Format(block, scale, 1 - scale)
+    out_dtype = torch.float32 if (M + N) % 2 == 0 else torch.bfloat16
+    rng = np.random.default_rng(M + 7 * N + K)
+    A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
+    print(f"[case] gemm tile {fmt_name} {M}x{N}x{K} {out_dtype}", flush=True)
+    got = run(A, B, fmt, out_dtype)
+    of = ofmt(fmt)
+    close(got, oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"{fmt_name} {shape}", out_dtype)
+
+
+# (the tile each shape gets from the size rule, E4M3 / E8M0, is in its id)
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4", "e4m3_32"])
+@pytest.mark.parametrize("shape", [pytest.param((71, 4160, 32), id="32x64"), pytest.param((65, 4171, 1152), id="32x64-1152"),
+                                   pytest.param((65, 3036, 32), id="64x32"), pytest.param((300, 1100, 544), id="64x32-544"),
+                                   pytest.param((171, 2818, 32), id="64x64"), pytest.param((1200, 905, 640), id="64x64-or-128"),
+                                   pytest.param((257, 3401, 160), id="128-tail"), pytest.param((2081, 1100, 256), id="128"),
+                                   pytest.param((3666, 1043, 1696), id="128-or-256x128-tail"), pytest.param((3596, 1033, 1792), id="128-or-256x128"),
+                                   pytest.param((2720, 4358, 32), id="256-tail"), pytest.param((2841, 4235, 160), id="128-or-256-tail"),
+                                   pytest.param((2709, 4364, 128), id="256")])
+def test_every_tile_sampled(shape, fmt_name):
+    block, scale = FORMATS[fmt_name]
+    M, N, K = shape
+    fmt = nv.Format(block, scale, 1 - scale)
+    out_dtype = torch.float32 if K % 256 else torch.bfloat16
+    rng = np.random.default_rng(M + 7 * N + K)
+    A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
+    print(f"[case] gemm tile sampled {fmt_name} {M}x{N}x{K} {out_dtype}", flush=True)
+    got = run(A, B, fmt, out_dtype)
+    # random outputs, the first and last rows and columns, and the two rows and columns at every multiple of 32 of a band
+    edge = lambda n: np.unique(np.clip(np.concatenate([[0, n - 1, n - 2], np.arange(31, min(n, 520), 32), np.arange(32, min(n, 520), 32)]), 0, n - 1))
+    ii = np.concatenate([rng.integers(0, M, 2000), np.repeat(edge(M), 40), rng.integers(0, M, 40 * len(edge(N)))])
+    jj = np.concatenate([rng.integers(0, N, 2000), rng.integers(0, N, 40 * len(edge(M))), np.repeat(edge(N), 40)])
+    of = ofmt(fmt)
+    close(got[ii, jj], oracle.gemm_nt_sample(A, B, ii, jj, of), oracle.gemm_nt_sample(A, B, ii, jj, of, take_abs=True),
+          f"{fmt_name} {shape}", out_dtype)
+    assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
+def test_window_of_a_wider_output(fmt_name, out_dtype):
+    # an odd leading dimension rules wide stores out; columns beside the window stay untouched
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    rng = np.random.default_rng(5)
+    for M, N, K, ld in ((40, 70, 160, 73), (40, 72, 256, 80), (600, 610, 160, 611)):
+        A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
+        dev = lambda o: (torch.from_numpy(o[0]).cuda(), torch.from_numpy(o[1]).cuda(), torch.tensor([o[2]], dtype=torch.float32, device="cuda"))
+        print(f"[case] gemm window {fmt_name} {M}x{N}x{K} ldc={ld} {out_dtype}", flush=True)
+        out = torch.full((M, ld), -1.0, device="cuda", dtype=out_dtype)
+        nv.gemm(dev(A), dev(B), fmt, out=out[:, :N])
+        torch.cuda.synchronize()
+        of = ofmt(fmt)
+        close(to_np(out[:, :N].float()), oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"ldc {ld}", out_dtype)
+        assert bool((out[:, N:] == -1.0).all())
