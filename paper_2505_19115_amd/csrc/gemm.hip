@@ -83,8 +83,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     constexpr int VALU_PER_MFMA = (8 * (TA + TB) + TA * TB - 1) / (TA * TB);
     constexpr int A_BYTES = BM * KTB, B_BYTES = BN * KTB, SA_BYTES = BM * SROW, SB_BYTES = BN * SROW;
     constexpr int STAGE = A_BYTES + B_BYTES + SA_BYTES + SB_BYTES;
-    constexpr int CA = BM * 4 / NT, CB = BN * 4 / NT;  // 16-byte chunks per thread per tile
-    static_assert(BM * 4 % NT == 0 && BN * 4 % NT == 0 && BM * 4 >= NT && BN * 4 >= NT, "tile/thread mismatch");
+    constexpr int NW = WM * WN, NI = (BM + BN) / 16, CI = (NI + NW - 1) / NW;  // 16-row code loads per tile, per wave
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -120,20 +119,19 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     // 539 us, with the direct loads 190.)
     constexpr int NSR = (BM + BN + NT - 1) / NT;  // scale rows per thread
     uint64_t gs[NSR];
-    uint32_t offA[CA], offB[CB];  // byte offset of this thread's chunks inside a K tile column
+    uint32_t off[CI];  // byte offset of this thread's chunks inside a K tile column
     const int ch = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
-    for (int u = 0; u < CA; ++u) {
-        const int row = (wave * CA + u) * 16 + (lane >> 2);
-        const int64_t lr = m0 + row < P.M ? row : P.M - 1 - m0;  // row inside the tile, clamped
-        offA[u] = P.a_slab ? (uint32_t)(slab_row((int)(m0 & 255) + row) * 64 + ch * 16)  // (a slab holds all 256 rows: nothing to clamp)
-                           : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
-    }
-#pragma unroll
-    for (int u = 0; u < CB; ++u) {
-        const int row = (wave * CB + u) * 16 + (lane >> 2);
-        const int64_t lr = n0 + row < P.N ? row : P.N - 1 - n0;
-        offB[u] = P.b_slab ? (uint32_t)(slab_row((int)(n0 & 255) + row) * 64 + ch * 16) : (uint32_t)(lr * Kb + ch * 16);
+    for (int u = 0; u < CI; ++u) {
+        const int trow = (u * NW + wave) * 16 + (lane >> 2);  // row of the tile: A's, then B's
+        const bool isA = trow < BM;
+        const int row = isA ? trow : trow - BM;
+        const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
+        const int64_t lr = base + row < rows ? row : rows - 1 - base;  // row inside the tile, clamped
+        // (a tile that does not start at a slab may reach into the next one)
+        const int srow = (int)(base & 255) + (int)lr;
+        off[u] = (isA ? P.a_slab : P.b_slab) ? (uint32_t)((int64_t)(srow >> 8) * nkt * SLAB_CODE_BYTES + slab_row(srow & 255) * 64 + ch * 16)
+                                             : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
     }
     typedef __attribute__((address_space(3))) void *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
@@ -165,8 +163,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         srow_step[u] = SPT;
         if (!KTAIL && (isA ? P.a_slab : P.b_slab) && srow_on[u]) {
             const int64_t base = isA ? m0 : n0;
-            const int lrow = isA ? srow : srow - BM;
-            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + (base >> 8) * nkt * SLAB_SCALE_BYTES + slab_row((int)(base & 255) + lrow) * 8;
+            const int sr = (int)(base & 255) + (int)(gr - base);
+            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + ((base >> 8) + (sr >> 8)) * nkt * SLAB_SCALE_BYTES + slab_row(sr & 255) * 8;
             srow_step[u] = (int)SLAB_SCALE_BYTES;
         }
     }
@@ -182,9 +180,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         const bool tail = KTAIL && kt == nkt - 1;
         const uint32_t back = tail && ch * 32 >= rem ? (uint32_t)ch * 16 : 0u;  // (a chunk past K: the tile's first one)
 #pragma unroll
-        for (int u = 0; u < CA; ++u) dma16(dst + (wave * CA + u) * 1024, KTAIL ? offA[u] - back : offA[u], ua);
-#pragma unroll
-        for (int u = 0; u < CB; ++u) dma16(dst + A_BYTES + (wave * CB + u) * 1024, KTAIL ? offB[u] - back : offB[u], ub);
+        for (int u = 0; u < CI; ++u) {
+            const int i = u * NW + wave;
+            if (NI % NW == 0 || i < NI) dma16(dst + i * 1024, KTAIL ? off[u] - back : off[u], i < BM / 16 ? ua : ub);
+        }
 #pragma unroll
         for (int u = 0; u < NSR; ++u) {
             if (!srow_on[u]) continue;
@@ -412,6 +411,12 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
     if (tile == TILE_256x256) {
         if (ktail) launch_f16<B, 2, 4, 4, 2, true>(P, out_dt, st);
         else launch_f16<B, 2, 4, 4, 2, false>(P, out_dt, st);
+    } else if (tile == TILE_192x256) {
+        if (ktail) launch_f16<B, 2, 4, 3, 2, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 3, 2, false>(P, out_dt, st);
+    } else if (tile == TILE_128x256) {
+        if (ktail) launch_f16<B, 2, 4, 2, 2, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 2, 2, false>(P, out_dt, st);
     } else {
         if (ktail) launch_f16<B, 2, 2, 2, 2, true>(P, out_dt, st);
         else launch_f16<B, 2, 2, 2, 2, false>(P, out_dt, st);
@@ -430,6 +435,13 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 //    256 x 11008 x 4096                              47.1   51.8   50.1   33.0    34.7     77.6
 //   2048 x  4096 x 4096                             129.8  127.8  123.1   80.0    65.4     78.6
 //   4096 x  4096 x 4096                             248.3  248.3  248.9  155.4   124.8    108.0
+// and the two E4M3 tiles for products that leave a 256 x 256 grid short of the 256 CUs or just past a round of them (a 192-row
+// or 128-row tile of the same eight waves; more expansion work per product, less rounding up):
+//                                                  128x128  128x256  192x256  256x256
+//    512 x 11008 x 4096                              57.1     51.7     64.9     77.3
+//    777 x 12288 x 4096                              88.7    107.4     81.9     86.3
+//   2048 x  4096 x 11008                            156.8    153.0    174.7    203.2
+//   3072 x  8192 x 4096                             171.7    172.5    160.7    176.6
 // (two kernels before: 256 x 256 from 128 such tiles on, else 128 x 128, with a register-staged 128 x 128 for a ragged K:
 // 33.8, 84.5, 38.7, 81.2 and 108.0 us; 2080 x 2784 x 1056: 44.3 us, now 23.3.)
 struct TileCost {
@@ -437,11 +449,11 @@ struct TileCost {
     int fixed, tile, step, alone;       // ns, ns, ns, percent
 };
 static const TileCost E4M3_COST[TILES] = {{32, 32, 8, 2900, 350, 860, 3},    {32, 64, 8, 1300, 2400, 1430, 0}, {64, 32, 8, 1400, 2300, 1410, 0},
-                                          {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8}, {0, 0, 0, 0, 0, 0, 0},
-                                          {256, 256, 1, 0, 7900, 2560, 0}};
+                                          {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8}, {128, 256, 1, 3000, 1500, 1780, 0},
+                                          {192, 256, 1, 3000, 3000, 2380, 0},{0, 0, 0, 0, 0, 0, 0},             {256, 256, 1, 0, 7900, 2560, 0}};
 static const TileCost E8M0_COST[TILES] = {{32, 32, 8, 2700, 410, 585, 0},    {32, 64, 8, 1400, 2140, 930, 0},  {64, 32, 8, 1400, 2100, 935, 0},
-                                          {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {256, 128, 1, 2900, 3150, 556, 19},
-                                          {256, 256, 1, 0, 8500, 1000, 0}};
+                                          {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0},
+                                          {0, 0, 0, 0, 0, 0, 0},             {256, 128, 1, 2900, 3150, 556, 19}, {256, 256, 1, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {

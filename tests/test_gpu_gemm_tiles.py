@@ -67,7 +67,9 @@ def test_small_products(shape, fmt_name):
                                    pytest.param((257, 3401, 160), id="128-tail"), pytest.param((2081, 1100, 256), id="128"),
                                    pytest.param((3666, 1043, 1696), id="128-or-256x128-tail"), pytest.param((3596, 1033, 1792), id="128-or-256x128"),
                                    pytest.param((2720, 4358, 32), id="256-tail"), pytest.param((2841, 4235, 160), id="128-or-256-tail"),
-                                   pytest.param((2709, 4364, 128), id="256")])
+                                   pytest.param((2709, 4364, 128), id="256"),
+                                   pytest.param((2721, 1418, 128), id="128x256-or-any"), pytest.param((1618, 3033, 160), id="128x256-tail-or-any"),
+                                   pytest.param((2505, 3212, 256), id="192x256-or-any"), pytest.param((2373, 3777, 160), id="192x256-tail-or-any")])
 def test_every_tile_sampled(shape, fmt_name):
     block, scale = FORMATS[fmt_name]
     M, N, K = shape
@@ -104,3 +106,17 @@ def test_window_of_a_wider_output(fmt_name, out_dtype):
         of = ofmt(fmt)
         close(to_np(out[:, :N].float()), oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"ldc {ld}", out_dtype)
         assert bool((out[:, N:] == -1.0).all())
+
+
+# (a 192-row tile that starts in the middle of a slab reads the end of it and the beginning of the next)
+@pytest.mark.parametrize("shape", [pytest.param((2832, 3072, 256), id="192x256"), pytest.param((2352, 3200, 256), id="128x256")])
+def test_tiles_across_slabs(shape):
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    X, W = (torch.randn((n, K), generator=g, device="cuda") for n in (M, N))
+    print(f"[case] gemm tiles across slabs {M}x{N}x{K}", flush=True)
+    plain = nv.gemm(nv.quantize_dual(X)[0], nv.quantize_dual(W)[0], out_dtype=torch.float32)
+    for slabs in ((True, False), (False, True), (True, True)):
+        A, B = (nv.quantize_dual(t, slab_rows=s)[0] for t, s in ((X, slabs[0]), (W, slabs[1])))
+        assert torch.equal(nv.gemm(A, B, out_dtype=torch.float32, slabs=slabs, shape=shape), plain)
