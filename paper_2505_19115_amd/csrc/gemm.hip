@@ -83,7 +83,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     constexpr int VALU_PER_MFMA = (8 * (TA + TB) + TA * TB - 1) / (TA * TB);
     constexpr int A_BYTES = BM * KTB, B_BYTES = BN * KTB, SA_BYTES = BM * SROW, SB_BYTES = BN * SROW;
     constexpr int STAGE = A_BYTES + B_BYTES + SA_BYTES + SB_BYTES;
-    constexpr int NW = WM * WN, NI = (BM + BN) / 16, CI = (NI + NW - 1) / NW;  // 16-row code loads per tile, per wave
+    // Code loads of a tile, 16 rows each: A's pieces, then B's; CI per wave.  Where they divide evenly a wave takes
+    // consecutive pieces of A and of B, else the list is dealt out in turn.
+    constexpr int NW = WM * WN, NI = (BM + BN) / 16, CI = (NI + NW - 1) / NW, CA = BM / 16 / NW, CB = BN / 16 / NW;
+    constexpr bool EVEN = BM / 16 % NW == 0 && BN / 16 % NW == 0;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -119,19 +122,22 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     // 539 us, with the direct loads 190.)
     constexpr int NSR = (BM + BN + NT - 1) / NT;  // scale rows per thread
     uint64_t gs[NSR];
+    constexpr bool SPAN = BM == 192;  // A's rows may lie in two slabs
+    auto piece = [&](int u) { return !EVEN ? u * NW + wave : u < CA ? wave * CA + u : BM / 16 + wave * CB + u - CA; };
     uint32_t off[CI];  // byte offset of this thread's chunks inside a K tile column
     const int ch = (lane & 3) ^ ((lane >> 4) & 3);
 #pragma unroll
     for (int u = 0; u < CI; ++u) {
-        const int trow = (u * NW + wave) * 16 + (lane >> 2);  // row of the tile: A's, then B's
-        const bool isA = trow < BM;
+        const int trow = piece(u) * 16 + (lane >> 2);  // row of the tile: A's, then B's
+        const bool isA = EVEN ? u < CA : trow < BM;
         const int row = isA ? trow : trow - BM;
         const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
         const int64_t lr = base + row < rows ? row : rows - 1 - base;  // row inside the tile, clamped
-        // (a tile that does not start at a slab may reach into the next one)
-        const int srow = (int)(base & 255) + (int)lr;
-        off[u] = (isA ? P.a_slab : P.b_slab) ? (uint32_t)((int64_t)(srow >> 8) * nkt * SLAB_CODE_BYTES + slab_row(srow & 255) * 64 + ch * 16)
-                                             : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
+        // a slab holds all 256 rows of a 256- or 128-row tile: nothing to clamp; a 192-row tile may reach into the next one
+        const int srow = (int)(base & 255) + (int)(SPAN && isA ? lr : row);
+        const uint32_t slab_off = (uint32_t)(slab_row(SPAN && isA ? srow & 255 : srow) * 64 + ch * 16) +
+                                  (SPAN && isA && srow > 255 ? (uint32_t)nkt * (uint32_t)SLAB_CODE_BYTES : 0u);
+        off[u] = (isA ? P.a_slab : P.b_slab) ? slab_off : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
     }
     typedef __attribute__((address_space(3))) void *lds_ptr_t;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
@@ -163,8 +169,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         srow_step[u] = SPT;
         if (!KTAIL && (isA ? P.a_slab : P.b_slab) && srow_on[u]) {
             const int64_t base = isA ? m0 : n0;
-            const int sr = (int)(base & 255) + (int)(gr - base);
-            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + ((base >> 8) + (sr >> 8)) * nkt * SLAB_SCALE_BYTES + slab_row(sr & 255) * 8;
+            const int lrow = SPAN && isA ? (int)(gr - base) : isA ? srow : srow - BM;
+            const int sr = (int)(base & 255) + lrow;
+            const int64_t slab = SPAN ? (base >> 8) + (sr >> 8) : base >> 8;
+            srow_ptr[u] = (isA ? P.A_scales : P.B_scales) + slab * nkt * SLAB_SCALE_BYTES + slab_row(SPAN ? sr & 255 : sr) * 8;
             srow_step[u] = (int)SLAB_SCALE_BYTES;
         }
     }
@@ -181,8 +189,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         const uint32_t back = tail && ch * 32 >= rem ? (uint32_t)ch * 16 : 0u;  // (a chunk past K: the tile's first one)
 #pragma unroll
         for (int u = 0; u < CI; ++u) {
-            const int i = u * NW + wave;
-            if (NI % NW == 0 || i < NI) dma16(dst + i * 1024, KTAIL ? off[u] - back : off[u], i < BM / 16 ? ua : ub);
+            const int i = piece(u);
+            if (EVEN || i < NI) dma16(dst + i * 1024, KTAIL ? off[u] - back : off[u], (EVEN ? u < CA : i < BM / 16) ? ua : ub);
         }
 #pragma unroll
         for (int u = 0; u < NSR; ++u) {
