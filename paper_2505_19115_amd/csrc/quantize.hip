@@ -6,9 +6,9 @@
 //   rows kernel   : one lane = 8 consecutive elements of a row (one 16 B load for bf16), a
 //                   block of B elements = B/8 adjacent lanes, block maximum by DPP max across
 //                   those lanes, one 4 B store of 8 packed codes per lane.
-//   columns kernel: one lane = 16 consecutive rows x 8 consecutive columns held in registers.
+//   columns kernel: one lane = 16 or 8 consecutive rows x 8 consecutive columns held in registers.
 //                   Lanes that are adjacent in the wave hold vertically adjacent row groups of
-//                   the same 8 columns, so the four waves of a workgroup read 512 B (bf16)
+//                   the same 8 columns, so the waves of a workgroup read 512 B (bf16)
 //                   contiguous per row and a wave writes 64 B contiguous per output row of the
 //                   transposed code matrix, without staging through LDS.
 #include "kernels.h"
@@ -36,6 +36,22 @@ __device__ __forceinline__ float group_max(float a)
     if (L >= 8) a = dpp_max<0x141>(a);  // row_half_mirror      : swaps the two quads of 8 lanes
     if (L >= 16) a = dpp_max<0x140>(a); // row_mirror           : swaps the two halves of 16 lanes
     return a;
+}
+
+// Maximum of the two lanes D apart (lane ^ D; D = 8, 16 or 32), a >= 0.
+template <int D>
+__device__ __forceinline__ float lane_pair_max(float a)
+{
+    static_assert(D == 8 || D == 16 || D == 32, "");
+    if constexpr (D == 8) return dpp_max<0x128>(a);  // row_ror:8
+    const uint32_t u = f2u(a);
+    if constexpr (D == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return u2f(umax(p[0], p[1]));
+    } else {
+        const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return u2f(umax(p[0], p[1]));
+    }
 }
 
 // The quantizer streams: every input byte is read once and every output byte written once, so
@@ -193,8 +209,9 @@ __device__ __forceinline__ float chunk_amax_packed(const Chunk<DT> &c)
 // Per-tensor scale as the kernels see it: none, preset in memory, or the bit pattern of the
 // tensor maximum left by the amax kernel.
 // With n_partials > 0 the tensor maximum arrives as that many per-workgroup maxima and every
-// workgroup (256 threads, all of them must call this) folds them for itself: 2 KB from the L2 per
+// workgroup (NT threads, all of them must call this) folds them for itself: 2 KB from the L2 per
 // workgroup instead of a separate one-workgroup kernel between the maximum pass and the quantizer.
+template <int NT = 256>
 __device__ __forceinline__ float resolve_g(const QuantArgs &P)
 {
     if (P.g_mode == G_NONE) return 1.0f;
@@ -204,14 +221,14 @@ __device__ __forceinline__ float resolve_g(const QuantArgs &P)
     }
     const uint32_t *bits = reinterpret_cast<const uint32_t *>(P.g_src);
     if (P.n_partials == 0) return tensor_scale_from_amax(u2f(*bits));
-    __shared__ uint32_t fold[16];
+    __shared__ uint32_t fold[NT / 16];
     uint32_t m = 0;
-    for (int i = threadIdx.x; i < P.n_partials; i += 256) m = umax(m, bits[i]);
+    for (int i = threadIdx.x; i < P.n_partials; i += NT) m = umax(m, bits[i]);
     m = f2u(group_max<16>(u2f(m)));
     if ((threadIdx.x & 15) == 0) fold[threadIdx.x >> 4] = m;
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 16; ++t) m = umax(m, fold[t]);
+    for (int t = 0; t < NT / 16; ++t) m = umax(m, fold[t]);
     return tensor_scale_from_amax(u2f(m));
 }
 
@@ -224,7 +241,7 @@ __device__ __forceinline__ float resolve_g(const QuantArgs &P)
 // With E4M3 scales and a per-tensor g the multiplier q = 1 / (s * g) is a function of the scale byte alone: a
 // workgroup evaluates it once for each of the 127 finite bytes (the same multiply and correctly rounded division
 // every block would do) and the blocks then look it up, which takes ~12 instructions out of every block's path.
-// All 256 threads of the workgroup must call this (it ends in a barrier).  Returns false where no table applies.
+// All threads of the workgroup (128 or more) must call this (it ends in a barrier).  Returns false where no table applies.
 __shared__ float qtab[128];
 template <int SF, bool HW>
 __device__ __forceinline__ bool build_qtab(float g)
@@ -614,18 +631,29 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
 
 // ------------------------------------------------------------------ column-blocked quantizer
 
-// Lane tile: 16 rows x 8 columns.  Wave tile: (16 LV) rows x (8 * 64 / LV) columns, lanes with
-// consecutive ids stacked vertically; workgroup: 4 waves side by side.  LV = 8 gives 64-byte
-// runs per output row; measured on [8192, 8192] bf16: LV = 4 (32-byte runs) is 45 % slower,
-// LV = 16 (128-byte runs, 64-byte reads) no faster.
-template <int DT, int LV = 8>
+// Lane tile: RPL rows x 8 columns; a workgroup covers 128 rows x 256 columns, lanes with consecutive ids stacked
+// vertically, so that it reads 512 contiguous bytes (bf16) per row and writes 64 per output row.
+// RPL = 16 (4 waves) does the least work per element, RPL = 8 (8 waves: a block of 16 spans two lanes) has half the serial
+// chain per wave and half the registers.  What bounds a tensor of up to 512 tiles (2 per CU: 4 waves per SIMD, all resident at once) is that
+// chain: one batch of loads, the arithmetic, the stores.  What bounds a larger one in bf16 is the arithmetic, and binary32
+// tiles of 16 rows take 168-188 registers, two workgroups per CU.  us, RPL = 16 / 8, dual quantizer with row-major outputs:
+//                      bf16 RtN+RtN   bf16 SR+SR    MXFP4 bf16 SR+SR   f32 SR+SR     MXFP4 f32 SR+SR
+//     2048 x  4096     13.9 / 11.6    18.1 / 16.0   19.7 / 16.4        15.8 / 14.9   20.4 / 16.8
+//     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4        22.3 / 21.5   38.6 / 32.4
+//     4096 x 11008     43.6 / 43.8    56.8 / 58.4   57.2 / 57.8        63.0 / 62.0   115.8 / 93.7
+//     8192 x  8192     53.9 / 57.5    67.6 / 72.3   72.0 / 75.3        90.9 / 83.1   161.6 / 125.9
+static bool short_lane_tile(int dt, int64_t rows, int64_t cols)
+{
+    return dt == NVFP4_F32 || ((rows + 127) / 128) * ((cols + 255) / 256) <= 512;
+}
+template <int ROWS_PER_LANE>
 struct ColGeom {
-    static constexpr int RPL = 16;
-    static constexpr int LANES_V = LV;                 // lanes stacked vertically
+    static constexpr int RPL = ROWS_PER_LANE;
+    static constexpr int WG_ROWS = 128, WG_COLS = 256;
+    static constexpr int LANES_V = WG_ROWS / RPL;      // lanes stacked vertically
     static constexpr int LANES_H = 64 / LANES_V;       // column groups per wave
     static constexpr int WAVE_COLS = 8 * LANES_H;
-    static constexpr int WG_COLS = 4 * WAVE_COLS;
-    static constexpr int WG_ROWS = RPL * LANES_V;
+    static constexpr int NT = 64 * WG_COLS / WAVE_COLS;  // threads per workgroup
 };
 
 // 16 bits of the column c of a lane's 8 in row-major element order: from draw d0 when the 8
@@ -638,18 +666,18 @@ __device__ __forceinline__ uint32_t col_bits(const u32x4 &d0, const u32x4 &d1, u
     return pos < 8 ? sr_bits_of(d0, pos) : sr_bits_of(d1, pos - 8);
 }
 
-// Stochastic rounding of a lane's 16 x 8 tile through the hardware convert, two rows at a time
+// Stochastic rounding of a lane's RPL x 8 tile through the hardware convert, two rows at a time
 // (the byte select of the convert must be a constant, hence the recursion over row pairs).
 // ALIGNED (every row holds a whole number of draws and the lane's 8 columns are one of them): ctr is the draw
 // counter of row row0 + R at the lane's columns and cstep = cols / 8 the distance to the next row's, both carried
 // along instead of being recomputed from 64-bit element indices for every row.
 // MXS: q holds the converts' scale operands instead of multipliers.
-template <int DT, int RND, bool ALIGNED, int BL, int R, bool MXS>
-__device__ __forceinline__ void col_sr_hw(const QuantArgs &P, Chunk<DT> (&v)[16], float (&q)[8][16 / BL],
-                                          int64_t row0, int64_t col0, uint32_t (&weven)[8][2],
-                                          uint32_t (&wodd)[8][2], uint64_t ctr, uint64_t cstep)
+template <int DT, int RND, bool ALIGNED, int BL, int R, bool MXS, int RPL>
+__device__ __forceinline__ void col_sr_hw(const QuantArgs &P, Chunk<DT> (&v)[RPL], float (&q)[8][RPL / BL],
+                                          int64_t row0, int64_t col0, uint32_t (&weven)[8][RPL / 8],
+                                          uint32_t (&wodd)[8][RPL / 8], uint64_t ctr, uint64_t cstep)
 {
-    if constexpr (R < 16) {
+    if constexpr (R < RPL) {
         const uint64_t e0 = (uint64_t)(row0 + R) * (uint64_t)P.cols + (uint64_t)col0;
         const uint64_t e1 = e0 + (uint64_t)P.cols;
         const u32x4 z = {0, 0, 0, 0};
@@ -679,16 +707,16 @@ __device__ __forceinline__ void col_sr_hw(const QuantArgs &P, Chunk<DT> (&v)[16]
                                                             col_bits<ALIGNED>(b0, b1, sb, c));
             }
         }
-        col_sr_hw<DT, RND, ALIGNED, BL, R + 2, MXS>(P, v, q, row0, col0, weven, wodd, ctr + 2 * cstep, cstep);
+        col_sr_hw<DT, RND, ALIGNED, BL, R + 2, MXS, RPL>(P, v, q, row0, col0, weven, wodd, ctr + 2 * cstep, cstep);
     }
 }
 
-// Round-to-nearest of a lane's 16 x 8 tile through the hardware convert: rows R and R + 1 of a column share a
+// Round-to-nearest of a lane's RPL x 8 tile through the hardware convert: rows R and R + 1 of a column share a
 // byte, which the convert writes in place (its byte select must be a constant, hence the recursion over row pairs).
-template <int DT, int BL, int R, bool MXS>
-__device__ __forceinline__ void col_rtn_hw(Chunk<DT> (&v)[16], float (&q)[8][16 / BL], uint32_t (&words)[8][2])
+template <int DT, int BL, int R, bool MXS, int RPL>
+__device__ __forceinline__ void col_rtn_hw(Chunk<DT> (&v)[RPL], float (&q)[8][RPL / BL], uint32_t (&words)[8][RPL / 8])
 {
-    if constexpr (R < 16) {
+    if constexpr (R < RPL) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             if constexpr (MXS)
@@ -696,30 +724,34 @@ __device__ __forceinline__ void col_rtn_hw(Chunk<DT> (&v)[16], float (&q)[8][16 
             else
                 words[c][R / 8] = quant_pair_hw<(R % 8) / 2>(words[c][R / 8], v[R].get(c), v[R + 1].get(c), q[c][R / BL]);
         }
-        col_rtn_hw<DT, BL, R + 2, MXS>(v, q, words);
+        col_rtn_hw<DT, BL, R + 2, MXS, RPL>(v, q, words);
     }
 }
 
-// Where a lane's column-blocked outputs go in the slab layout: column c of the lane stores its 8 code bytes at
-// codes + 512 c and its scale byte at scales + 64 c (blocks of 16) or, from the lowest of the eight stacked lanes,
+// Where a lane's column-blocked outputs go in the slab layout: column c of the lane stores its RPL / 2 code bytes at
+// codes + 512 c and its scale byte at scales + 64 c (blocks of 16) or, from the lowest of the stacked lanes,
 // the column's four scale bytes at scales + 32 c (blocks of 32); the lane index is folded into the two pointers.
 struct ColSlab {
     uint8_t *codes, *scales;
 };
 
-template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int LV>
-__device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16], float g, float k, int64_t row0,
+// the codes of a lane's column: RPL rows, one nibble each
+template <int RPL>
+__device__ __forceinline__ void store_codes(uint8_t *p, const uint32_t (&w)[RPL / 8])
+{
+    if constexpr (RPL == 16) store8_stream(p, w[0], w[1]);
+    else store4_stream(p, w[0]);
+}
+
+template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int RPL>
+__device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[RPL], float g, float k, int64_t row0,
                                           int64_t col0, int ncol, int lv, const ColSlab *slab = nullptr);
 
 // ALIGNED: cols is a multiple of 8, so the 8 columns of a lane share one random draw per row.
-template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int LV = 8>
-__global__ __launch_bounds__(256) void quantize_cols_kernel(QuantArgs P)
+template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int RPL>
+__global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_cols_kernel(QuantArgs P)
 {
-    using G = ColGeom<DT, LV>;
-    constexpr int RPL = G::RPL;
-    constexpr int BL = B < RPL ? B : RPL;        // rows of one block held by this lane
-    constexpr int NB = RPL / BL;                 // blocks (or block parts) per lane per column
-    constexpr int LPB = B / BL;                  // lanes sharing one block
+    using G = ColGeom<RPL>;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lv = lane % G::LANES_V, lh = lane / G::LANES_V;
@@ -738,24 +770,23 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(QuantArgs P)
         else
             v[r].zero();
     }
-    const float g = resolve_g(P);
+    const float g = resolve_g<G::NT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *P.g_out = g;
-    cols_tile<DT, B, SF, RND, HW, ALIGNED, LV>(P, v, g, k, row0, col0, ncol, lv);
+    cols_tile<DT, B, SF, RND, HW, ALIGNED, RPL>(P, v, g, k, row0, col0, ncol, lv);
 }
 
-// The column-blocked quantization of one lane tile (16 rows x 8 columns in v): block maxima,
+// The column-blocked quantization of one lane tile (RPL rows x 8 columns in v): block maxima,
 // scale bytes, codes, and the stores into the transposed outputs.
-template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int LV>
-__device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16], float g, float k, int64_t row0,
+template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int RPL>
+__device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[RPL], float g, float k, int64_t row0,
                                           int64_t col0, int ncol, int lv, const ColSlab *slab)
 {
-    using G = ColGeom<DT, LV>;
-    constexpr int RPL = G::RPL;
-    constexpr int BL = B < RPL ? B : RPL;
-    constexpr int NB = RPL / BL;
-    constexpr int LPB = B / BL;
+    using G = ColGeom<RPL>;
+    constexpr int BL = B < RPL ? B : RPL;        // rows of one block held by this lane
+    constexpr int NB = RPL / BL;                 // blocks (or block parts) per lane per column
+    constexpr int LPB = B / BL;                  // lanes sharing one block
     const int64_t rows_half = P.rows >> 1;
     const int64_t nblk = P.rows / B;
 
@@ -812,7 +843,7 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16]
         for (int w = 0; w < RPL / 8; ++w) words[c][w] = 0;
 
     if (RND == NVFP4_RTN && HW) {
-        col_rtn_hw<DT, BL, 0, MXS>(v, q, words);
+        col_rtn_hw<DT, BL, 0, MXS, RPL>(v, q, words);
     } else if (RND == NVFP4_SR && HW) {
         // rows 2p and 2p+1 of a column share a byte: even rows go through slot 0, odd rows
         // through slot 1 of the convert, into two sets of words that are OR-ed at the end
@@ -822,7 +853,7 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16]
 #pragma unroll
             for (int w = 0; w < RPL / 8; ++w) wodd[c][w] = 0;
         const uint64_t cstep = (uint64_t)P.cols >> 3;
-        col_sr_hw<DT, RND, ALIGNED, BL, 0, MXS>(P, v, q, row0, col0, words, wodd, (uint64_t)row0 * cstep + ((uint64_t)col0 >> 3), cstep);
+        col_sr_hw<DT, RND, ALIGNED, BL, 0, MXS, RPL>(P, v, q, row0, col0, words, wodd, (uint64_t)row0 * cstep + ((uint64_t)col0 >> 3), cstep);
 #pragma unroll
         for (int c = 0; c < 8; ++c)
 #pragma unroll
@@ -856,18 +887,18 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16]
         }
     }
 
-    // Scale bytes, row-major [cols, rows / B]: the eight lanes stacked vertically hold consecutive bytes of a column's
-    // row (blocks of 16: one per lane, 8 per workgroup tile; blocks of 32: one per pair of lanes, 4 per tile).  Where
+    // Scale bytes, row-major [cols, rows / B]: the lanes stacked vertically hold consecutive bytes of a column's
+    // row (blocks of 16: 8 per workgroup tile; blocks of 32: 4), each in LPB adjacent lanes.  Where
     // the rows allow, four bytes are gathered into the lowest of their lanes through DPP row shifts (lane + n; every
     // lane takes part) and leave as one aligned dword instead of single bytes.
-    constexpr bool GATHER = RPL == 16 && LV == 8 && NB == 1 && (B == 16 || B == 32);
-    constexpr int GSTEP = B == 16 ? 1 : 2;  // lanes between consecutive bytes
+    constexpr bool GATHER = NB == 1 && (B == 16 || B == 32);
+    constexpr int GSTEP = LPB;  // lanes between consecutive bytes
     uint32_t sw[8];
     bool wide = false, owner = false;
     if constexpr (GATHER) {
         // (the whole 128-row tile inside the tensor, whole dwords per tile, aligned rows of the scale matrix)
         wide = (nblk & 3) == 0 && (reinterpret_cast<uintptr_t>(P.scales) & 3) == 0 && (row0 - lv * RPL) + G::WG_ROWS <= P.rows;
-        owner = (lv & (4 * GSTEP - 1)) == 0;  // blocks of 16: lanes 0 and 4 of the eight; blocks of 32: lane 0
+        owner = (lv & (4 * GSTEP - 1)) == 0;  // blocks of 16: two of the stacked lanes; blocks of 32: the lowest
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             sw[c] = sbytes[c][0];
@@ -876,18 +907,18 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16]
         }
     }
 
-    if (RPL == 16 && slab != nullptr) {
+    if (slab != nullptr) {
         // slab layout (the caller guarantees a lane tile entirely inside the tensor or entirely outside, blocks of
-        // 16 or 32): a store instruction of the wave writes 512 contiguous code bytes and 64 contiguous scale bytes
-        // (blocks of 16) or 32 contiguous scale bytes from its eight owner lanes (blocks of 32)
+        // 16 or 32): the stacked lanes of a column write its 64 code bytes of this K tile, the lane groups of two
+        // (four) waves 512 contiguous ones
         if (ncol == 8) {
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                store8_stream(slab->codes + 512 * c, words[c][0], words[c][1]);
+                store_codes<RPL>(slab->codes + 512 * c, words[c]);
                 if (B == 16) {
-                    slab->scales[64 * c] = (uint8_t)sbytes[c][0];
+                    if (lv % LPB == 0) slab->scales[64 * c] = (uint8_t)sbytes[c][0];
                 } else if (GATHER) {
-                    // blocks of 32: the lowest of the eight stacked lanes holds the column's four bytes of this K tile
+                    // blocks of 32: the lowest of the stacked lanes holds the column's four bytes of this K tile
                     if (owner) *reinterpret_cast<uint32_t *>(slab->scales + 32 * c) = sw[c];
                 }
             }
@@ -898,11 +929,7 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[16]
     for (int c = 0; c < 8; ++c) {
         if (c < ncol) {
             const int64_t col = col0 + c;
-            uint8_t *crow = P.codes + col * rows_half + (row0 >> 1);
-#pragma unroll
-            for (int h = 0; h < RPL / 16; ++h)
-                if (row0 + 16 * h < P.rows)
-                    store8_stream(crow + 8 * h, words[c][2 * h], words[c][2 * h + 1]);
+            if (row0 < P.rows) store_codes<RPL>(P.codes + col * rows_half + (row0 >> 1), words[c]);
             if (GATHER && wide) {
                 if (owner) *reinterpret_cast<uint32_t *>(P.scales + col * nblk + row0 / B) = sw[c];
             } else if (lv % LPB == 0) {
@@ -1015,20 +1042,20 @@ hipError_t launch_swiglu_bwd(const void *dH, const void *G, const void *U, int d
 // draws: seed_r for the row-blocked output, P.seed for the column-blocked one), each with its
 // own rounding mode (X is needed round-to-nearest along K for Eq. 4 and stochastically rounded
 // along M for Eq. 6).
-// Geometry of the columns kernel (lane = 16 rows x 8 columns, workgroup = 128 rows x 256
-// columns).  A row block of B = 16 or 32 columns spans 2 or 4 lanes that are 8 apart in the wave
-// (DPP row rotate / swizzle for the maximum).  The row-blocked codes of the tile (128 rows x 128
+// Geometry of the columns kernel (lane = RPL rows x 8 columns, workgroup = 128 rows x 256
+// columns).  A row block of B = 16 or 32 columns spans 2 or 4 lanes that are LANES_V apart in the wave
+// (DPP row rotate / lane swaps for the maximum).  The row-blocked codes of the tile (128 rows x 128
 // bytes) and its scale bytes are staged in LDS and written out 16 bytes per lane, so both outputs
 // leave in full lines although the lanes hold the data column-wise.
-// Host guarantees: rows % B == 0, cols % B == 0 (so a lane's 16 x 8 tile is entirely inside or
+// Host guarantees: rows % B == 0, cols % B == 0 (so a lane's RPL x 8 tile is entirely inside or
 // outside the tensor), 16-byte aligned rows of x.
-// One workgroup tile (128 rows x 256 columns at tile coordinates tx, ty; the lane's 16 x 8 part of it in v) through
+// One workgroup tile (128 rows x 256 columns at tile coordinates tx, ty; the lane's RPL x 8 part of it in v) through
 // both quantizers and out to memory.  Every thread of the workgroup must call it (barriers inside).
-template <int DT, int B, int SF, int RND_R, int RND_C>
-__device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16], float g, float k, int tx, int ty,
+template <int DT, int B, int SF, int RND_R, int RND_C, int RPL>
+__device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL], float g, float k, int tx, int ty,
                                           uint32_t *lds_codes, uint8_t *lds_scales)
 {
-    using G = ColGeom<DT, 8>;
+    using G = ColGeom<RPL>;
     constexpr int LPBR = B / 8;                  // lanes sharing one row block
     constexpr bool MXS = SF == NVFP4_SCALE_E8M0;  // block scale as the convert's scale operand
     constexpr int ROW_BYTES = G::WG_COLS / 2;    // 128 code bytes per tile row
@@ -1037,7 +1064,7 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16],
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lv = lane % G::LANES_V, lh = lane / G::LANES_V;
     const int64_t wrow0 = (int64_t)ty * G::WG_ROWS, wcol0 = (int64_t)tx * G::WG_COLS;
-    const int64_t row0 = wrow0 + lv * 16;
+    const int64_t row0 = wrow0 + lv * RPL;
     const int64_t col0 = wcol0 + wave * G::WAVE_COLS + lh * 8;
     const bool inside = row0 < P.rows && col0 < P.cols;
 
@@ -1045,42 +1072,40 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16],
     const uint64_t cstep_r = (uint64_t)P.cols >> 3;
     uint64_t ctr_r = (uint64_t)row0 * cstep_r + ((uint64_t)col0 >> 3);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < RPL; ++r) {
         float a = MXS ? chunk_amax_packed(v[r]) : chunk_amax(v[r]);
-        a = dpp_max<0x128>(a);  // row_ror:8 : lane ^ 8, the neighbouring column group
-        if (LPBR == 4) {
-            const uint32_t o = (uint32_t)__builtin_amdgcn_ds_swizzle((int)f2u(a), 0x401F);  // lane ^ 16
-            a = u2f(umax(f2u(a), o));
-        }
+        a = lane_pair_max<G::LANES_V>(a);  // the neighbouring column group
+        if (LPBR == 4) a = lane_pair_max<2 * G::LANES_V>(a);
         float q;
         const uint32_t sbyte = block_scale<SF, true, SF == NVFP4_SCALE_E4M3>(a, g, k, &q);
         if (MXS) q = mx_scale_operand(sbyte);
         // (cols is a multiple of the block, col0 of 8: the lane's 8 columns are one draw, cols / 8 draws per row)
         const uint32_t packed = chunk_codes_hw<DT, RND_R, MXS>(v[r], q, D.seed_r, ctr_r);
         ctr_r += cstep_r;
-        // tile row R = 16 lv + r holds 32 dwords; dword w is stored at w ^ (4 lv): the 16-byte
-        // chunk c of the row sits at chunk c ^ lv, which spreads the 8 rows a wave writes at a
+        // tile row R = RPL lv + r holds 32 dwords; dword w is stored at w ^ (4 lv % 32): the
+        // 16-byte chunk c of the row sits at chunk c ^ (lv % 8), which spreads the rows a wave writes at a
         // time over the banks
-        const int R = lv * 16 + r;
-        lds_codes[R * (ROW_BYTES / 4) + ((wave * 8 + lh) ^ (lv << 2))] = packed;
+        const int R = lv * RPL + r;
+        lds_codes[R * (ROW_BYTES / 4) + ((wave * G::LANES_H + lh) ^ ((lv & 7) << 2))] = packed;
         if ((lh & (LPBR - 1)) == 0) lds_scales[R * 16 + (wave * G::WAVE_COLS + lh * 8) / B] = (uint8_t)sbyte;
     }
 
     // (unpack the raw registers again below instead of keeping 128 floats alive)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r].launder();
+    for (int r = 0; r < RPL; ++r) v[r].launder();
 
     // column-blocked side: exactly the columns kernel's tile.  In the slab layout the workgroup's 256 columns are
     // one tile of operand rows and its 128 rows one K tile: it fills exactly one slab.
     ColSlab cs;
     if (D.slab_c) {
         const int64_t slab = (int64_t)tx * (P.rows / SLAB_K) + ty;
-        cs.codes = P.codes + slab * SLAB_CODE_BYTES + wave * 4096 + lane * 8;
-        // (tile column 64 wave + 8 lh + c sits at position 64 wave + 8 c + lh)
-        cs.scales = B == 16 ? P.scales + slab * SLAB_SCALE_BYTES + wave * 512 + lane
-                            : P.scales + slab * SLAB_MX_SCALE_BYTES + wave * 256 + lh * 4;
+        // (tile column 64 w + 8 j + c sits at position 64 w + 8 c + j; this lane's column group is 8 w + j)
+        const int cg = wave * G::LANES_H + lh, w = cg >> 3, j = cg & 7;
+        cs.codes = P.codes + slab * SLAB_CODE_BYTES + w * 4096 + j * 64 + lv * (RPL / 2);
+        cs.scales = B == 16 ? P.scales + slab * SLAB_SCALE_BYTES + w * 512 + j * 8 + lv * RPL / 16
+                            : P.scales + slab * SLAB_MX_SCALE_BYTES + w * 256 + j * 4;
     }
-    cols_tile<DT, B, SF, RND_C, true, true, 8>(P, v, g, k, row0, col0, inside ? 8 : 0, lv, D.slab_c ? &cs : nullptr);
+    cols_tile<DT, B, SF, RND_C, true, true, RPL>(P, v, g, k, row0, col0, inside ? 8 : 0, lv, D.slab_c ? &cs : nullptr);
 
     __syncthreads();
     if (D.slab_r) {
@@ -1090,10 +1115,10 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16],
         const int64_t slab0 = (wrow0 / SLAB_ROWS) * nkt + 2 * (int64_t)tx;
         const int half = (int)(wrow0 & 128);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int id = threadIdx.x + 256 * i, q = id >> 3, c = id & 7, R = slab_row(q);
+        for (int i = 0; i < 1024 / G::NT; ++i) {
+            const int id = threadIdx.x + G::NT * i, q = id >> 3, c = id & 7, R = slab_row(q);
             if (wrow0 + R < P.rows && wcol0 + c * 32 < P.cols) {
-                const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R >> 4)) << 2)]);
+                const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R / RPL & 7)) << 2)]);
                 const u32x4_t o = {w.x, w.y, w.z, w.w};
                 __builtin_nontemporal_store(o, reinterpret_cast<u32x4_t *>(D.codes_r + (slab0 + (c >> 2)) * SLAB_CODE_BYTES + (half + q) * 64 + (c & 3) * 16));
             }
@@ -1120,11 +1145,11 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16],
     const bool wide = (cpr & 15) == 0;  // rows of the code matrix are 16-byte aligned
     if (!D.slab_r) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int id = threadIdx.x + 256 * i, R = id >> 3, c = id & 7;
+        for (int i = 0; i < 1024 / G::NT; ++i) {
+            const int id = threadIdx.x + G::NT * i, R = id >> 3, c = id & 7;
             const int64_t row = wrow0 + R, col = wcol0 + c * 32;
             if (row < P.rows && col < P.cols) {
-                const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R >> 4)) << 2)]);
+                const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R / RPL & 7)) << 2)]);
                 uint8_t *dst = D.codes_r + row * cpr + (col >> 1);
                 if (col + 32 <= P.cols && wide) {
                     const u32x4_t o = {w.x, w.y, w.z, w.w};
@@ -1153,10 +1178,10 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[16],
     }
 }
 
-template <int DT, int B, int SF, int RND_R, int RND_C, int SRC = SRC_TENSOR>
-__global__ __launch_bounds__(256) void quantize_dual_kernel(DualArgs D)
+template <int DT, int B, int SF, int RND_R, int RND_C, int RPL, int SRC = SRC_TENSOR>
+__global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_dual_kernel(DualArgs D)
 {
-    using G = ColGeom<DT, 8>;
+    using G = ColGeom<RPL>;
     static_assert(B == 16 || B == 32, "row blocks must fit the 8 column groups of a wave");
     __shared__ __align__(16) uint32_t lds_codes[G::WG_ROWS * (G::WG_COLS / 2) / 4];
     __shared__ __align__(16) uint8_t lds_scales[G::WG_ROWS * 16];
@@ -1164,13 +1189,13 @@ __global__ __launch_bounds__(256) void quantize_dual_kernel(DualArgs D)
     const QuantArgs &P = D.c;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lv = lane % G::LANES_V, lh = lane / G::LANES_V;
-    const int64_t row0 = (int64_t)blockIdx.y * G::WG_ROWS + lv * 16;
+    const int64_t row0 = (int64_t)blockIdx.y * G::WG_ROWS + lv * RPL;
     const int64_t col0 = (int64_t)blockIdx.x * G::WG_COLS + wave * G::WAVE_COLS + lh * 8;
     const bool inside = row0 < P.rows && col0 < P.cols;
 
-    Chunk<DT> v[16];
+    Chunk<DT> v[RPL];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < RPL; ++r) {
         if (!inside)
             v[r].zero();
         else if (SRC == SRC_TENSOR)
@@ -1179,7 +1204,7 @@ __global__ __launch_bounds__(256) void quantize_dual_kernel(DualArgs D)
             swiglu_chunk<DT, SRC>(P.x, D.src_g, D.src_u, (row0 + r) * P.ld + col0, &v[r], &v[r]);
     }
 
-    const float g = resolve_g(P);
+    const float g = resolve_g<G::NT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, true>(g);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
@@ -1188,7 +1213,7 @@ __global__ __launch_bounds__(256) void quantize_dual_kernel(DualArgs D)
         *P.g_out = g_gemm;
         if (D.g_out2) *D.g_out2 = g_gemm;
     }
-    dual_tile<DT, B, SF, RND_R, RND_C>(D, v, g, k, (int)blockIdx.x, (int)blockIdx.y, lds_codes, lds_scales);
+    dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, (int)blockIdx.x, (int)blockIdx.y, lds_codes, lds_scales);
 }
 
 __global__ void saved_tag_kernel(TagArgs t, float *g1, float *g2)
@@ -1257,6 +1282,14 @@ hipError_t launch_tensor_amax_dense(const void *x, int dt, int64_t n_elements, u
     return launch_status();
 }
 
+template <int DT, int B, int SF, int RND, bool HW, bool ALIGNED, int RPL>
+static void launch_cols(const QuantArgs &P, hipStream_t st)
+{
+    using G = ColGeom<RPL>;
+    dim3 grid((unsigned)((P.cols + G::WG_COLS - 1) / G::WG_COLS), (unsigned)((P.rows + G::WG_ROWS - 1) / G::WG_ROWS));
+    hipLaunchKernelGGL((quantize_cols_kernel<DT, B, SF, RND, HW, ALIGNED, RPL>), grid, dim3(G::NT), 0, st, P);
+}
+
 template <int DT, int B, int SF, int RND, bool HW>
 static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
 {
@@ -1266,13 +1299,13 @@ static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
         hipLaunchKernelGGL((quantize_rows_kernel<DT, B, SF, RND, HW>), dim3((unsigned)((total + per - 1) / per)),
                            dim3(256), 0, st, P);
     } else {
-        using G = ColGeom<DT>;
-        dim3 grid((unsigned)((P.cols + G::WG_COLS - 1) / G::WG_COLS),
-                  (unsigned)((P.rows + G::WG_ROWS - 1) / G::WG_ROWS));
+        // (the cross-check formulation and stochastic rounding with unaligned draws have the 16-row tile only)
         if (RND == NVFP4_SR && (P.cols & 7) != 0)
-            hipLaunchKernelGGL((quantize_cols_kernel<DT, B, SF, RND, HW, RND == NVFP4_RTN>), grid, dim3(256), 0, st, P);
+            launch_cols<DT, B, SF, RND, HW, RND == NVFP4_RTN, 16>(P, st);
+        else if (HW && short_lane_tile(DT, P.rows, P.cols))
+            launch_cols<DT, B, SF, RND, HW, true, HW ? 8 : 16>(P, st);
         else
-            hipLaunchKernelGGL((quantize_cols_kernel<DT, B, SF, RND, HW, true>), grid, dim3(256), 0, st, P);
+            launch_cols<DT, B, SF, RND, HW, true, HW && DT == NVFP4_F32 ? 8 : 16>(P, st);
     }
 }
 
@@ -1320,35 +1353,42 @@ hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, i
     return launch_status();
 }
 
-template <int DT, int B, int SF>
+template <int DT, int B, int SF, int RPL>
 static void launch_dual_rnd(const DualArgs &D, int rnd_r, int rnd_c, hipStream_t st)
 {
-    using G = ColGeom<DT>;
+    using G = ColGeom<RPL>;
     dim3 grid((unsigned)((D.c.cols + G::WG_COLS - 1) / G::WG_COLS), (unsigned)((D.c.rows + G::WG_ROWS - 1) / G::WG_ROWS));
     if (rnd_r == NVFP4_SR && rnd_c == NVFP4_SR)
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR>), grid, dim3(256), 0, st, D);
+        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, RPL>), grid, dim3(G::NT), 0, st, D);
     else if (rnd_r == NVFP4_RTN && rnd_c == NVFP4_SR)
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_SR>), grid, dim3(256), 0, st, D);
+        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_SR, RPL>), grid, dim3(G::NT), 0, st, D);
     else
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_RTN>), grid, dim3(256), 0, st, D);
+        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_RTN, RPL>), grid, dim3(G::NT), 0, st, D);
 }
 
-template <int DT>
+template <int DT, int RPL>
 static void launch_dual_fmt(const DualArgs &D, int rnd_r, int rnd_c, int block, int sf, hipStream_t st)
 {
-    if (block == 16 && sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 16, NVFP4_SCALE_E4M3>(D, rnd_r, rnd_c, st);
-    else if (block == 16) launch_dual_rnd<DT, 16, NVFP4_SCALE_E8M0>(D, rnd_r, rnd_c, st);
-    else if (sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 32, NVFP4_SCALE_E4M3>(D, rnd_r, rnd_c, st);
-    else launch_dual_rnd<DT, 32, NVFP4_SCALE_E8M0>(D, rnd_r, rnd_c, st);
+    if (block == 16 && sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 16, NVFP4_SCALE_E4M3, RPL>(D, rnd_r, rnd_c, st);
+    else if (block == 16) launch_dual_rnd<DT, 16, NVFP4_SCALE_E8M0, RPL>(D, rnd_r, rnd_c, st);
+    else if (sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 32, NVFP4_SCALE_E4M3, RPL>(D, rnd_r, rnd_c, st);
+    else launch_dual_rnd<DT, 32, NVFP4_SCALE_E8M0, RPL>(D, rnd_r, rnd_c, st);
+}
+
+template <int DT, int B, int SF, int RPL>
+static void launch_swiglu_dual_rpl(const DualArgs &g, const DualArgs &u, hipStream_t st)
+{
+    using G = ColGeom<RPL>;
+    dim3 grid((unsigned)((g.c.cols + G::WG_COLS - 1) / G::WG_COLS), (unsigned)((g.c.rows + G::WG_ROWS - 1) / G::WG_ROWS));
+    hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, RPL, SRC_SWIGLU_DG>), grid, dim3(G::NT), 0, st, g);
+    hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, RPL, SRC_SWIGLU_DU>), grid, dim3(G::NT), 0, st, u);
 }
 
 template <int DT, int B, int SF>
 static void launch_swiglu_dual_fmt(const DualArgs &g, const DualArgs &u, hipStream_t st)
 {
-    using G = ColGeom<DT>;
-    dim3 grid((unsigned)((g.c.cols + G::WG_COLS - 1) / G::WG_COLS), (unsigned)((g.c.rows + G::WG_ROWS - 1) / G::WG_ROWS));
-    hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, SRC_SWIGLU_DG>), grid, dim3(256), 0, st, g);
-    hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, SRC_SWIGLU_DU>), grid, dim3(256), 0, st, u);
+    if (short_lane_tile(DT, g.c.rows, g.c.cols)) launch_swiglu_dual_rpl<DT, B, SF, 8>(g, u, st);
+    else launch_swiglu_dual_rpl<DT, B, SF, DT == NVFP4_F32 ? 8 : 16>(g, u, st);
 }
 
 hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, int sf, uint32_t *partials_g,
@@ -1407,10 +1447,12 @@ hipError_t launch_quantize_dual(const DualArgs &D, int dt, int rnd_r, int rnd_c,
 {
     // (SR rows with RtN columns is a combination no equation asks for: two kernels)
     if (quantize_dual_fused(dt, D.c.rows, D.c.cols, D.c.ld, block, hw_convert) && !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN)) {
-        if (dt == NVFP4_BF16)
-            launch_dual_fmt<NVFP4_BF16>(D, rnd_r, rnd_c, block, sf, st);
+        if (dt == NVFP4_F32)
+            launch_dual_fmt<NVFP4_F32, 8>(D, rnd_r, rnd_c, block, sf, st);
+        else if (short_lane_tile(dt, D.c.rows, D.c.cols))
+            launch_dual_fmt<NVFP4_BF16, 8>(D, rnd_r, rnd_c, block, sf, st);
         else
-            launch_dual_fmt<NVFP4_F32>(D, rnd_r, rnd_c, block, sf, st);
+            launch_dual_fmt<NVFP4_BF16, 16>(D, rnd_r, rnd_c, block, sf, st);
         return launch_status();
     }
     // other block sizes and ragged shapes: the two single-orientation kernels (they write the plain layout only)

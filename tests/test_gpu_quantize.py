@@ -330,3 +330,44 @@ def test_dual_orientation_strided_and_full_size():
         torch.cuda.synchronize()
         for a, b in ((qr, r1), (qc, c1)):
             assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+
+
+# The quantizers' lane tile is 8 rows up to 512 workgroup tiles of 128 x 256 and 16 rows beyond (bf16): a wide and a tall
+# tensor on each side of that line, with a last tile that is nearly empty.
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("shape", [(32, 512 * 256), (32, 512 * 256 + 32), (512 * 128, 32), (512 * 128 + 32, 32)])
+def test_both_lane_tiles(shape, fmt):
+    f = FORMATS[fmt]()
+    x = synth.student_t_outliers(*shape, seed=21, dtype=torch.bfloat16)
+    xg = x.cuda()
+    for rr, rc in ((nv.RTN, nv.RTN), (nv.SR, nv.SR)):
+        print(f"[case] lane tiles {shape} {fmt} {rr} {rc}", flush=True)
+        rows, cols = nv.quantize_dual(xg, rr, 5, rc, 6, f)
+        assert_quant_equal(rows, oracle.quantize(x, 1, rr, 5, ofmt(f)), f"{shape} rows")
+        want = oracle.quantize(x, 0, rc, 6, ofmt(f))
+        assert_quant_equal(cols, want, f"{shape} cols")
+        assert_quant_equal(nv.quantize(xg, 0, rc, 6, f), want, f"{shape} cols alone")
+
+
+def unslab(flat, rows, K, per_row):
+    """Slabs of 256 positions x per_row bytes per 128 contraction elements -> row-major [rows, K / 128 * per_row]."""
+    padded = -(-rows // 256) * 256
+    a = to_np(flat)[: padded * (K // 128) * per_row].reshape(padded // 256, K // 128, 256, per_row)
+    r = np.arange(256)
+    a = a[:, :, (r & ~63) | ((r & 7) << 3) | ((r >> 3) & 7), :]  # tile row r sits at this position
+    return a.transpose(0, 2, 1, 3).reshape(padded, -1)[:rows]
+
+
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape", [(384, 640), (128, 513 * 256)])
+def test_slab_outputs_of_both_lane_tiles(shape, dtype, fmt):
+    f = FORMATS[fmt]()
+    R, C = shape
+    xg = synth.student_t_outliers(R, C, seed=22, dtype=dtype).cuda()
+    print(f"[case] slab lane tiles {shape} {dtype} {fmt}", flush=True)
+    plain = nv.quantize_dual(xg, nv.SR, 5, nv.SR, 6, f)
+    slabs = nv.quantize_dual(xg, nv.SR, 5, nv.SR, 6, f, slab_rows=True, slab_cols=True)
+    for side, (rows, K) in enumerate(((R, C), (C, R))):
+        assert np.array_equal(unslab(slabs[side][0], rows, K, 64), to_np(plain[side][0])), f"codes of side {side}"
+        assert np.array_equal(unslab(slabs[side][1], rows, K, 128 // f.block), to_np(plain[side][1])), f"scales of side {side}"
