@@ -128,7 +128,7 @@ hipError_t amax_dense(const void *x, int dt, int64_t n_elements, uint32_t *parti
     return launch_tensor_amax_dense(x, dt, n_elements, dst, &g->n, st);
 }
 
-hipError_t run_quantize(const QuantPlan &q, const nvfp4_format *f, hipStream_t st)
+QuantArgs quant_args(const QuantPlan &q)
 {
     QuantArgs a;
     a.x = q.x;
@@ -142,7 +142,12 @@ hipError_t run_quantize(const QuantPlan &q, const nvfp4_format *f, hipStream_t s
     a.g_mode = q.g_mode;
     a.seed = q.seed;
     a.n_partials = q.n_partials;
-    return launch_quantize(a, q.dt, q.axis, q.rounding, f->block, f->scale, use_hw_convert(), st);
+    return a;
+}
+
+hipError_t run_quantize(const QuantPlan &q, const nvfp4_format *f, hipStream_t st)
+{
+    return launch_quantize(quant_args(q), q.dt, q.axis, q.rounding, f->block, f->scale, use_hw_convert(), st);
 }
 
 // What nvfp4_linear_fwd leaves for nvfp4_linear_bwd: {gX, gW}, then the transposed operands.
@@ -459,6 +464,9 @@ nvfp4_status quantize_impl(const void *x, int dt, int64_t rows, int64_t cols, in
                 if (amax_dense(x, dt, rows * cols, partials, 0, st, &g) != hipSuccess) return NVFP4_EHIP;
                 q.g_src = g.src;
                 q.n_partials = g.n;
+            } else if (!empty && tensor_amax_partials_only(rows, cols)) {
+                q.g_src = reinterpret_cast<const float *>(partials);
+                if (launch_tensor_amax_strided(x, dt, rows, cols, ld, partials, &q.n_partials, st) != hipSuccess) return NVFP4_EHIP;
             } else if (launch_tensor_amax(x, dt, rows, cols, ld, bits, partials, empty ? tensor_scale : nullptr, st) != hipSuccess) {
                 // (an empty tensor gets its scale (1) written there, by the fold alone; otherwise the quantizer writes it)
                 return NVFP4_EHIP;
@@ -542,6 +550,9 @@ nvfp4_status nvfp4_quantize_dual(const void *x, nvfp4_dtype dt_, int64_t rows, i
                 if (amax_dense(x, dt, rows * cols, partials, 0, st, &g) != hipSuccess) return NVFP4_EHIP;
                 d.c.g_src = g.src;
                 d.c.n_partials = g.n;
+            } else if (!empty && tensor_amax_partials_only(rows, cols)) {
+                d.c.g_src = reinterpret_cast<const float *>(partials);
+                if (launch_tensor_amax_strided(x, dt, rows, cols, ld, partials, &d.c.n_partials, st) != hipSuccess) return NVFP4_EHIP;
             } else if (launch_tensor_amax(x, dt, rows, cols, ld, bits, partials, empty ? tensor_scale : nullptr, st) != hipSuccess) {
                 return NVFP4_EHIP;
             }
@@ -659,9 +670,13 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
 
     const int gm = f->tensor_scale ? G_FROM_AMAX : G_NONE;
     GSource gx{reinterpret_cast<const float *>(amax + 0), 0}, gw{reinterpret_cast<const float *>(amax + 1), 0};
-    if (f->tensor_scale) {
+    if (f->tensor_scale && w_ops) {
         if (amax_dense(X, in_dt, M * K, partials, 0, st, &gx) != hipSuccess) return NVFP4_EHIP;
-        if (!w_ops && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
+    } else if (f->tensor_scale) {
+        uint32_t *const pw = partials + AMAX_DENSE_PARTIALS;
+        gx.src = reinterpret_cast<const float *>(partials);
+        gw.src = reinterpret_cast<const float *>(pw);
+        if (launch_tensor_amax_dense2(X, M * K, partials, &gx.n, W, N * K, pw, &gw.n, in_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
     int a_slab = 0, b_slab = 0;
     const bool t_fwd = gemm_takes_slabs(M, N, K, f->block, f->scale);
@@ -692,16 +707,20 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
         last.tag = saved_tag(M, N, K, f, bwd_seed, dx.slab_c != 0, w_ops ? false : dw.slab_c != 0, w_ops != nullptr);
         last.tag.dst = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(saved) + SAVED_TAG_OFFSET);
         saved_remember(saved, last.tag);
-        if (launch_quantize_dual(dx, in_dt, NVFP4_RTN, NVFP4_SR, f->block, f->scale, use_hw_convert(), st) != hipSuccess) return NVFP4_EHIP;
-        if (!w_ops) {
+        if (w_ops) {
+            if (launch_quantize_dual(dx, in_dt, NVFP4_RTN, NVFP4_SR, f->block, f->scale, use_hw_convert(), st) != hipSuccess) return NVFP4_EHIP;
+        } else {
             dw.slab_r = b_slab = sw && t_fwd;
-            if (launch_quantize_dual(dw, in_dt, NVFP4_RTN, NVFP4_RTN, f->block, f->scale, use_hw_convert(), st) != hipSuccess) return NVFP4_EHIP;
+            if (launch_quantize_dual_pair(dx, dw, in_dt, f->block, f->scale, use_hw_convert(), st) != hipSuccess) return NVFP4_EHIP;
         }
     } else {
         QuantPlan qx{X, in_dt, M, K, K, 1, NVFP4_RTN, 0, xc, xs, gx.src, ts + 0, gm, gx.n};
         QuantPlan qw{W, in_dt, N, K, K, 1, NVFP4_RTN, 0, const_cast<uint8_t *>(wc), const_cast<uint8_t *>(wsc), gw.src, ts + 1, gm, gw.n};
-        if (run_quantize(qx, f, st) != hipSuccess) return NVFP4_EHIP;
-        if (!w_ops && run_quantize(qw, f, st) != hipSuccess) return NVFP4_EHIP;
+        if (w_ops) {
+            if (run_quantize(qx, f, st) != hipSuccess) return NVFP4_EHIP;
+        } else {
+            if (launch_quantize_rows_pair(quant_args(qx), quant_args(qw), in_dt, f->block, f->scale, use_hw_convert(), st) != hipSuccess) return NVFP4_EHIP;
+        }
     }
     GemmArgs g{M, N, K, xc, xs, wc, wsc, ts, g_w, Y, N, a_slab, b_slab};
     return launch_gemm(g, f->block, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;

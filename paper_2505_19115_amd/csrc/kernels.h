@@ -114,6 +114,13 @@ hipError_t launch_tensor_amax(const void *x, int dt, int64_t rows, int64_t cols,
 // (the consuming quantizer folds them: QuantArgs::n_partials).  Returns their number in *n.
 constexpr int AMAX_DENSE_PARTIALS = 512;
 hipError_t launch_tensor_amax_dense(const void *x, int dt, int64_t n_elements, uint32_t *partials, int *n, hipStream_t st);
+// The same for two dense tensors of one element type in one launch.
+hipError_t launch_tensor_amax_dense2(const void *x0, int64_t n_elements0, uint32_t *partials0, int *n0, const void *x1,
+                                     int64_t n_elements1, uint32_t *partials1, int *n1, int dt, hipStream_t st);
+// The same for a tensor with a row pitch, where tensor_amax_partials_only() holds (32-bit chunk numbers); no fold kernel
+// either ([8192, 8192] bf16 with a pitch: one launch of 24 us instead of 22 + 5).
+bool tensor_amax_partials_only(int64_t rows, int64_t cols);
+hipError_t launch_tensor_amax_strided(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld, uint32_t *partials, int *n, hipStream_t st);
 hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, int block, int sf,
                            bool hw_convert, hipStream_t st);
 // Row-blocked and column-blocked quantization of one tensor; one fused kernel when
@@ -121,6 +128,10 @@ hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, i
 bool quantize_dual_fused(int dt, int64_t rows, int64_t cols, int64_t ld, int block, bool hw_convert);
 hipError_t launch_quantize_dual(const DualArgs &D, int dt, int rnd_rows, int rnd_cols, int block, int sf,
                                 bool hw_convert, hipStream_t st);
+// A forward call's X (rows round to nearest, columns stochastic) and W (round to nearest both ways): one launch where both are
+// small and served by the one-pass kernel, else two.  And the row-blocked side alone of both, round to nearest.
+hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int dt, int block, int sf, bool hw_convert, hipStream_t st);
+hipError_t launch_quantize_rows_pair(const QuantArgs &a, const QuantArgs &b, int dt, int block, int sf, bool hw_convert, hipStream_t st);
 // SwiGLU backward fused with the quantizers of its two results: one pass over dH, G, U leaves the partial maxima of
 // dG and dU (AMAX_DENSE_PARTIALS slots each, the counts come back in n_g / n_u; skipped without tensor scale), then one
 // dual-orientation pass per result re-evaluates it while loading.  g / u describe the outputs as for

@@ -500,32 +500,22 @@ __global__ __launch_bounds__(256) void amax_kernel(const void *x, int64_t cols, 
     }
 }
 
-// Dense tensors: a fixed grid of large workgroups strides over the chunks, one partial each.
+// A fixed grid of large workgroups strides over the chunks of one or two tensors (blockIdx.y), one partial each, which the
+// consumer folds.  A strided tensor is walked as its rows of ceil(cols / 8) chunks (32-bit chunk numbers: one division per
+// 16-byte load hides under the load).  Two tensors in one launch: a call on a small layer is bound by the launches in its
+// chain (2-4 us each), not by their work.
 constexpr int AMAX_DENSE_THREADS = 1024;
+struct AmaxArgs {
+    const void *x;
+    int64_t n;           // dense: elements
+    uint32_t rows, cpr;  // strided: rows, chunks per row
+    int64_t cols, ld;
+    uint32_t *part_out;
+    unsigned grid;
+};
 template <int DT>
-__global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_dense_kernel(const void *x, int64_t n, uint32_t *part_out)
+__device__ __forceinline__ void amax_store(float a, uint32_t *dst)
 {
-    const int64_t nchunk = n >> 3;
-    const int64_t stride = (int64_t)gridDim.x * (AMAX_DENSE_THREADS * AMAX_UNROLL);
-    float a = 0.0f;
-    for (int64_t base = (int64_t)blockIdx.x * (AMAX_DENSE_THREADS * AMAX_UNROLL) + threadIdx.x; base < nchunk; base += stride) {
-        Chunk<DT> v[AMAX_UNROLL];
-#pragma unroll
-        for (int u = 0; u < AMAX_UNROLL; ++u) {
-            const int64_t c = base + u * AMAX_DENSE_THREADS;
-            if (c < nchunk)
-                v[u].template load<false>(x, c * 8);
-            else
-                v[u].zero();
-        }
-#pragma unroll
-        for (int u = 0; u < AMAX_UNROLL; ++u) a = fmaxf(a, chunk_amax(v[u]));
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && (n & 7)) {
-        Chunk<DT> t;
-        t.load_partial(x, nchunk * 8, (int)(n & 7));
-        a = fmaxf(a, chunk_amax(t));
-    }
     a = group_max<16>(a);
     __shared__ uint32_t part[AMAX_DENSE_THREADS / 16];
     if ((threadIdx.x & 15) == 0) part[threadIdx.x >> 4] = f2u(a);
@@ -534,8 +524,60 @@ __global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_dense_kernel(const vo
         uint32_t m = 0;
 #pragma unroll
         for (int t = 0; t < AMAX_DENSE_THREADS / 16; ++t) m = umax(m, part[t]);
-        part_out[blockIdx.x] = m;
+        *dst = m;
     }
+}
+template <int DT>
+__global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_dense_kernel(AmaxArgs T0, AmaxArgs T1)
+{
+    const AmaxArgs &T = blockIdx.y == 0 ? T0 : T1;
+    if (blockIdx.x >= T.grid) return;
+    const int64_t nchunk = T.n >> 3;
+    const int64_t stride = (int64_t)T.grid * (AMAX_DENSE_THREADS * AMAX_UNROLL);
+    float a = 0.0f;
+    for (int64_t base = (int64_t)blockIdx.x * (AMAX_DENSE_THREADS * AMAX_UNROLL) + threadIdx.x; base < nchunk; base += stride) {
+        Chunk<DT> v[AMAX_UNROLL];
+#pragma unroll
+        for (int u = 0; u < AMAX_UNROLL; ++u) {
+            const int64_t c = base + u * AMAX_DENSE_THREADS;
+            if (c < nchunk)
+                v[u].template load<false>(T.x, c * 8);
+            else
+                v[u].zero();
+        }
+#pragma unroll
+        for (int u = 0; u < AMAX_UNROLL; ++u) a = fmaxf(a, chunk_amax(v[u]));
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (T.n & 7)) {
+        Chunk<DT> t;
+        t.load_partial(T.x, nchunk * 8, (int)(T.n & 7));
+        a = fmaxf(a, chunk_amax(t));
+    }
+    amax_store<DT>(a, T.part_out + blockIdx.x);
+}
+template <int DT>
+__global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_strided_kernel(AmaxArgs T)
+{
+    const int64_t total = (int64_t)T.rows * T.cpr;  // (below 2^31)
+    const int64_t stride = (int64_t)T.grid * (AMAX_DENSE_THREADS * AMAX_UNROLL);
+    float a = 0.0f;
+    for (int64_t base = (int64_t)blockIdx.x * (AMAX_DENSE_THREADS * AMAX_UNROLL) + threadIdx.x; base < total; base += stride) {
+        Chunk<DT> v[AMAX_UNROLL];
+#pragma unroll
+        for (int u = 0; u < AMAX_UNROLL; ++u) {
+            const int64_t id = base + u * AMAX_DENSE_THREADS;
+            v[u].zero();
+            if (id < total) {
+                const uint32_t row = (uint32_t)id / T.cpr, c = (uint32_t)id - row * T.cpr;
+                const int64_t off = (int64_t)row * T.ld + (int64_t)c * 8;
+                if ((int64_t)c * 8 + 8 <= T.cols) v[u].template load<false>(T.x, off);
+                else v[u].load_partial(T.x, off, (int)(T.cols & 7));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < AMAX_UNROLL; ++u) a = fmaxf(a, chunk_amax(v[u]));
+    }
+    amax_store<DT>(a, T.part_out + blockIdx.x);
 }
 
 // Folds n partial maxima into amax_bits[0]; with g_out != nullptr also writes the tensor scale.
@@ -562,13 +604,13 @@ __global__ __launch_bounds__(1024) void fold_amax_kernel(const uint32_t *partial
 constexpr int ROWS_UNROLL = 4;  // chunks per thread
 
 template <int DT, int B, int SF, int RND, bool HW>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
+__device__ __forceinline__ void rows_tile(const QuantArgs &P, const int64_t wg)
 {
     constexpr int LPB = B / 8;  // lanes per block
     constexpr bool MXS = HW && SF == NVFP4_SCALE_E8M0;  // block scale as the convert's scale operand
     const int64_t cpr = P.cols >> 3;
     const int64_t total = P.rows * cpr;
-    const int64_t base = (int64_t)blockIdx.x * (256 * ROWS_UNROLL) + threadIdx.x;
+    const int64_t base = wg * (256 * ROWS_UNROLL) + threadIdx.x;
     const bool dense = P.ld == P.cols;
     Chunk<DT> v[ROWS_UNROLL];
 #pragma unroll
@@ -589,7 +631,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
     const float g = resolve_g(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *P.g_out = g;
+    if (wg == 0 && threadIdx.x == 0) *P.g_out = g;
 #pragma unroll
     for (int u = 0; u < ROWS_UNROLL; ++u) {
         const int64_t id = base + u * 256;
@@ -629,6 +671,20 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
     }
 }
 
+template <int DT, int B, int SF, int RND, bool HW>
+__global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
+{
+    rows_tile<DT, B, SF, RND, HW>(P, blockIdx.x);
+}
+
+// Two tensors in one launch, round to nearest: the forward call's X and W.  The first `wgs` workgroups take the first.
+template <int DT, int B, int SF>
+__global__ __launch_bounds__(256) void quantize_rows_pair_kernel(QuantArgs P0, QuantArgs P1, unsigned wgs)
+{
+    const bool first = blockIdx.x < wgs;
+    rows_tile<DT, B, SF, NVFP4_RTN, true>(first ? P0 : P1, first ? blockIdx.x : blockIdx.x - wgs);
+}
+
 // ------------------------------------------------------------------ column-blocked quantizer
 
 // Lane tile: RPL rows x 8 columns; a workgroup covers 128 rows x 256 columns, lanes with consecutive ids stacked
@@ -642,6 +698,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(QuantArgs P)
 //     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4        22.3 / 21.5   38.6 / 32.4
 //     4096 x 11008     43.6 / 43.8    56.8 / 58.4   57.2 / 57.8        63.0 / 62.0   115.8 / 93.7
 //     8192 x  8192     53.9 / 57.5    67.6 / 72.3   72.0 / 75.3        90.9 / 83.1   161.6 / 125.9
+constexpr int64_t PAIR_TILES = 512;  // of X and W together: where both would take 8-row lane tiles, resident at once
 static bool short_lane_tile(int dt, int64_t rows, int64_t cols)
 {
     return dt == NVFP4_F32 || ((rows + 127) / 128) * ((cols + 255) / 256) <= 512;
@@ -1178,19 +1235,20 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL]
     }
 }
 
-template <int DT, int B, int SF, int RND_R, int RND_C, int RPL, int SRC = SRC_TENSOR>
-__global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_dual_kernel(DualArgs D)
+struct DualLds {
+    uint32_t codes[128 * 128 / 4];
+    uint8_t scales[128 * 16];
+};
+template <int DT, int B, int SF, int RND_R, int RND_C, int RPL, int SRC>
+__device__ __forceinline__ void dual_wg(const DualArgs &D, int tx, int ty, DualLds &lds)
 {
     using G = ColGeom<RPL>;
-    static_assert(B == 16 || B == 32, "row blocks must fit the 8 column groups of a wave");
-    __shared__ __align__(16) uint32_t lds_codes[G::WG_ROWS * (G::WG_COLS / 2) / 4];
-    __shared__ __align__(16) uint8_t lds_scales[G::WG_ROWS * 16];
-
+    static_assert(B == 16 || B == 32, "row blocks must fit the column groups of a wave");
     const QuantArgs &P = D.c;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lv = lane % G::LANES_V, lh = lane / G::LANES_V;
-    const int64_t row0 = (int64_t)blockIdx.y * G::WG_ROWS + lv * RPL;
-    const int64_t col0 = (int64_t)blockIdx.x * G::WG_COLS + wave * G::WAVE_COLS + lh * 8;
+    const int64_t row0 = (int64_t)ty * G::WG_ROWS + lv * RPL;
+    const int64_t col0 = (int64_t)tx * G::WG_COLS + wave * G::WAVE_COLS + lh * 8;
     const bool inside = row0 < P.rows && col0 < P.cols;
 
     Chunk<DT> v[RPL];
@@ -1207,13 +1265,34 @@ __global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_dual_kernel(DualArg
     const float g = resolve_g<G::NT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, true>(g);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    if (tx == 0 && ty == 0 && threadIdx.x == 0) {
         // (a `saved` buffer that is not the one this call expects poisons the scale the GEMMs will multiply by)
         const float g_gemm = tag_apply(D.tag) ? g : __builtin_nanf("");
         *P.g_out = g_gemm;
         if (D.g_out2) *D.g_out2 = g_gemm;
     }
-    dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, (int)blockIdx.x, (int)blockIdx.y, lds_codes, lds_scales);
+    dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, tx, ty, lds.codes, lds.scales);
+}
+
+template <int DT, int B, int SF, int RND_R, int RND_C, int RPL, int SRC = SRC_TENSOR>
+__global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_dual_kernel(DualArgs D)
+{
+    __shared__ __align__(16) DualLds lds;
+    dual_wg<DT, B, SF, RND_R, RND_C, RPL, SRC>(D, (int)blockIdx.x, (int)blockIdx.y, lds);
+}
+
+// X (round to nearest / stochastic) and W (round to nearest) of a forward call that saves both, in one launch: the first
+// `tiles` workgroups take X.
+template <int DT, int B, int SF>
+__global__ __launch_bounds__(ColGeom<8>::NT) void quantize_dual_pair_kernel(DualArgs X, DualArgs W, unsigned tiles, unsigned tx_x, unsigned tx_w)
+{
+    __shared__ __align__(16) DualLds lds;
+    if (blockIdx.x < tiles) {
+        dual_wg<DT, B, SF, NVFP4_RTN, NVFP4_SR, 8, SRC_TENSOR>(X, (int)(blockIdx.x % tx_x), (int)(blockIdx.x / tx_x), lds);
+    } else {
+        const unsigned id = blockIdx.x - tiles;
+        dual_wg<DT, B, SF, NVFP4_RTN, NVFP4_RTN, 8, SRC_TENSOR>(W, (int)(id % tx_w), (int)(id / tx_w), lds);
+    }
 }
 
 __global__ void saved_tag_kernel(TagArgs t, float *g1, float *g2)
@@ -1270,15 +1349,49 @@ hipError_t launch_tensor_amax(const void *x, int dt, int64_t rows, int64_t cols,
     return launch_status();
 }
 
+static unsigned amax_grid(int64_t chunks)
+{
+    const int64_t gx = (chunks + AMAX_DENSE_THREADS * AMAX_UNROLL - 1) / (AMAX_DENSE_THREADS * AMAX_UNROLL);
+    return (unsigned)(gx < 1 ? 1 : (gx > AMAX_DENSE_PARTIALS ? AMAX_DENSE_PARTIALS : gx));
+}
+static AmaxArgs amax_dense_args(const void *x, int64_t n, uint32_t *partials) { return {x, n, 0, 0, 0, 0, partials, amax_grid(n >> 3)}; }
+
 hipError_t launch_tensor_amax_dense(const void *x, int dt, int64_t n_elements, uint32_t *partials, int *n, hipStream_t st)
 {
-    int64_t gx = ((n_elements >> 3) + AMAX_DENSE_THREADS * AMAX_UNROLL - 1) / (AMAX_DENSE_THREADS * AMAX_UNROLL);
-    gx = gx < 1 ? 1 : (gx > AMAX_DENSE_PARTIALS ? AMAX_DENSE_PARTIALS : gx);
+    const AmaxArgs T = amax_dense_args(x, n_elements, partials);
     if (dt == NVFP4_BF16)
-        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_BF16>, dim3((unsigned)gx), dim3(AMAX_DENSE_THREADS), 0, st, x, n_elements, partials);
+        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_BF16>, dim3(T.grid), dim3(AMAX_DENSE_THREADS), 0, st, T, T);
     else
-        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_F32>, dim3((unsigned)gx), dim3(AMAX_DENSE_THREADS), 0, st, x, n_elements, partials);
-    *n = (int)gx;
+        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_F32>, dim3(T.grid), dim3(AMAX_DENSE_THREADS), 0, st, T, T);
+    *n = (int)T.grid;
+    return launch_status();
+}
+
+hipError_t launch_tensor_amax_dense2(const void *x0, int64_t n_elements0, uint32_t *partials0, int *n0, const void *x1,
+                                     int64_t n_elements1, uint32_t *partials1, int *n1, int dt, hipStream_t st)
+{
+    const AmaxArgs T0 = amax_dense_args(x0, n_elements0, partials0), T1 = amax_dense_args(x1, n_elements1, partials1);
+    const dim3 grid(T0.grid > T1.grid ? T0.grid : T1.grid, 2);
+    if (dt == NVFP4_BF16)
+        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_BF16>, grid, dim3(AMAX_DENSE_THREADS), 0, st, T0, T1);
+    else
+        hipLaunchKernelGGL(amax_dense_kernel<NVFP4_F32>, grid, dim3(AMAX_DENSE_THREADS), 0, st, T0, T1);
+    *n0 = (int)T0.grid;
+    *n1 = (int)T1.grid;
+    return launch_status();
+}
+
+bool tensor_amax_partials_only(int64_t rows, int64_t cols) { return rows * ((cols + 7) >> 3) < ((int64_t)1 << 31) - AMAX_DENSE_THREADS * AMAX_UNROLL * AMAX_DENSE_PARTIALS; }
+
+hipError_t launch_tensor_amax_strided(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld, uint32_t *partials, int *n, hipStream_t st)
+{
+    const int64_t cpr = (cols + 7) >> 3;
+    const AmaxArgs T = {x, 0, (uint32_t)rows, (uint32_t)cpr, cols, ld, partials, amax_grid(rows * cpr)};
+    if (dt == NVFP4_BF16)
+        hipLaunchKernelGGL(amax_strided_kernel<NVFP4_BF16>, dim3(T.grid), dim3(AMAX_DENSE_THREADS), 0, st, T);
+    else
+        hipLaunchKernelGGL(amax_strided_kernel<NVFP4_F32>, dim3(T.grid), dim3(AMAX_DENSE_THREADS), 0, st, T);
+    *n = (int)T.grid;
     return launch_status();
 }
 
@@ -1433,6 +1546,56 @@ hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, i
         else launch_swiglu_dual_fmt<NVFP4_F32, 32, NVFP4_SCALE_E8M0>(g, u, st);
     }
     return launch_status();
+}
+
+template <int DT, int B, int SF>
+static void launch_dual_pair_fmt(const DualArgs &x, const DualArgs &w, hipStream_t st)
+{
+    using G = ColGeom<8>;
+    auto across = [](const DualArgs &d) { return (unsigned)((d.c.cols + G::WG_COLS - 1) / G::WG_COLS); };
+    auto down = [](const DualArgs &d) { return (unsigned)((d.c.rows + G::WG_ROWS - 1) / G::WG_ROWS); };
+    const unsigned tiles = across(x) * down(x);
+    hipLaunchKernelGGL((quantize_dual_pair_kernel<DT, B, SF>), dim3(tiles + across(w) * down(w)), dim3(G::NT), 0, st, x, w, tiles, across(x), across(w));
+}
+
+hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int dt, int block, int sf, bool hw_convert, hipStream_t st)
+{
+    const int64_t tiles = ((x.c.rows + 127) / 128) * ((x.c.cols + 255) / 256) + ((w.c.rows + 127) / 128) * ((w.c.cols + 255) / 256);
+    const bool nv = block == 16 && sf == NVFP4_SCALE_E4M3, mxf = block == 32 && sf == NVFP4_SCALE_E8M0;
+    if (tiles <= PAIR_TILES && (nv || mxf) && quantize_dual_fused(dt, x.c.rows, x.c.cols, x.c.ld, block, hw_convert) &&
+        quantize_dual_fused(dt, w.c.rows, w.c.cols, w.c.ld, block, hw_convert)) {
+        if (dt == NVFP4_BF16 && nv) launch_dual_pair_fmt<NVFP4_BF16, 16, NVFP4_SCALE_E4M3>(x, w, st);
+        else if (dt == NVFP4_BF16) launch_dual_pair_fmt<NVFP4_BF16, 32, NVFP4_SCALE_E8M0>(x, w, st);
+        else if (nv) launch_dual_pair_fmt<NVFP4_F32, 16, NVFP4_SCALE_E4M3>(x, w, st);
+        else launch_dual_pair_fmt<NVFP4_F32, 32, NVFP4_SCALE_E8M0>(x, w, st);
+        return launch_status();
+    }
+    const hipError_t e = launch_quantize_dual(x, dt, NVFP4_RTN, NVFP4_SR, block, sf, hw_convert, st);
+    return e != hipSuccess ? e : launch_quantize_dual(w, dt, NVFP4_RTN, NVFP4_RTN, block, sf, hw_convert, st);
+}
+
+template <int DT>
+static void launch_rows_pair_dt(const QuantArgs &a, const QuantArgs &b, int block, int sf, unsigned wa, unsigned wb, hipStream_t st)
+{
+    const dim3 grid(wa + wb), wg(256);
+    if (sf == NVFP4_SCALE_E8M0) hipLaunchKernelGGL((quantize_rows_pair_kernel<DT, 32, NVFP4_SCALE_E8M0>), grid, wg, 0, st, a, b, wa);
+    else if (block == 16) hipLaunchKernelGGL((quantize_rows_pair_kernel<DT, 16, NVFP4_SCALE_E4M3>), grid, wg, 0, st, a, b, wa);
+    else if (block == 32) hipLaunchKernelGGL((quantize_rows_pair_kernel<DT, 32, NVFP4_SCALE_E4M3>), grid, wg, 0, st, a, b, wa);
+    else if (block == 64) hipLaunchKernelGGL((quantize_rows_pair_kernel<DT, 64, NVFP4_SCALE_E4M3>), grid, wg, 0, st, a, b, wa);
+    else hipLaunchKernelGGL((quantize_rows_pair_kernel<DT, 128, NVFP4_SCALE_E4M3>), grid, wg, 0, st, a, b, wa);
+}
+
+hipError_t launch_quantize_rows_pair(const QuantArgs &a, const QuantArgs &b, int dt, int block, int sf, bool hw_convert, hipStream_t st)
+{
+    auto wgs = [](const QuantArgs &P) { return (P.rows * (P.cols >> 3) + 256 * ROWS_UNROLL - 1) / (256 * ROWS_UNROLL); };
+    if (hw_convert && wgs(a) + wgs(b) < ((int64_t)1 << 31) && (sf == NVFP4_SCALE_E4M3 || block == 32)) {
+        const unsigned wa = (unsigned)wgs(a), wb = (unsigned)wgs(b);
+        if (dt == NVFP4_BF16) launch_rows_pair_dt<NVFP4_BF16>(a, b, block, sf, wa, wb, st);
+        else launch_rows_pair_dt<NVFP4_F32>(a, b, block, sf, wa, wb, st);
+        return launch_status();
+    }
+    const hipError_t e = launch_quantize(a, dt, 1, NVFP4_RTN, block, sf, hw_convert, st);
+    return e != hipSuccess ? e : launch_quantize(b, dt, 1, NVFP4_RTN, block, sf, hw_convert, st);
 }
 
 bool quantize_dual_fused(int dt, int64_t rows, int64_t cols, int64_t ld, int block, bool hw_convert)

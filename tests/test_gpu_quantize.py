@@ -371,3 +371,20 @@ def test_slab_outputs_of_both_lane_tiles(shape, dtype, fmt):
     for side, (rows, K) in enumerate(((R, C), (C, R))):
         assert np.array_equal(unslab(slabs[side][0], rows, K, 64), to_np(plain[side][0])), f"codes of side {side}"
         assert np.array_equal(unslab(slabs[side][1], rows, K, 128 // f.block), to_np(plain[side][1])), f"scales of side {side}"
+
+
+# The maximum pass over a tensor with a row pitch: rows that end inside a chunk of 8, one row, more chunks than one
+# pass of the grid takes; the largest magnitude sits in the first or the very last element, the gap beside the rows holds more.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape", [(16, 1, 8), (16, 7, 16), (1, 48, 64), (48, 2051, 2056), (4112, 4100, 4112)])
+def test_maximum_of_a_strided_tensor(shape, dtype):
+    rows, cols, ld = shape
+    axis = 1 if rows == 1 else 0
+    base = torch.full((rows, ld), 1e4, dtype=dtype)
+    base[:, :cols] = synth.normal(rows, cols, 1.0, 5, torch.float32).to(dtype)
+    for at in ((0, 0), (rows - 1, cols - 1)):
+        t = base.clone()
+        t[at] = -77.0
+        print(f"[case] strided maximum {shape} {dtype} {at}", flush=True)
+        got = nv.quantize(t.cuda()[:, :cols], axis, nv.RTN, 0, nv.NVFP4)
+        assert_quant_equal(got, oracle.quantize(t[:, :cols].contiguous(), axis, nv.RTN, 0, oracle.NVFP4), f"{shape} {at}")
