@@ -852,6 +852,9 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         d.slab_c = dy_slab_c;
         if (launch_quantize_dual(d, in_dt, NVFP4_SR, NVFP4_SR, f->block, f->scale, true, st) != hipSuccess) return NVFP4_EHIP;
     }
+    const GemmArgs g_dx{M, K, N, dyc, dys, wtc, wts, g_dy_r, g_w, dX, K, dy_slab_r, wt_slab};
+    const GemmArgs g_dw{N, K, M, dytc, dyts, xtc, xts, g_dy_c, g_x, dW, K, dy_slab_c, xt_slab};
+    const bool pair = dX && dW && gemm_pairs(g_dx, g_dw, f->scale);  // (then both run after the last quantizer)
     if (dX) {
         if (f->tensor_scale && !known && !have_wt && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
         // Eq. 5: dX[M, K] = Q_SR(dY)[M, N] * Q_RtN(W^T)[K, N]^T
@@ -860,8 +863,7 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!dual && !dyq && launch_saved_tag(tag, ts + 0, nullptr, st) != hipSuccess) return NVFP4_EHIP;
         if (!have_wt && run_quantize(qb, f, st) != hipSuccess) return NVFP4_EHIP;
-        GemmArgs g{M, K, N, dyc, dys, wtc, wts, g_dy_r, g_w, dX, K, dy_slab_r, wt_slab};
-        if (launch_gemm(g, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
+        if (!pair && launch_gemm(g_dx, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
     if (dW) {
         if (f->tensor_scale && !known && !have_xt && amax_dense(X, in_dt, M * K, partials, 2, st, &gx) != hipSuccess) return NVFP4_EHIP;
@@ -871,9 +873,9 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!dual && !dyq && launch_saved_tag(tag, ts + 2, nullptr, st) != hipSuccess) return NVFP4_EHIP;
         if (!have_xt && run_quantize(qb, f, st) != hipSuccess) return NVFP4_EHIP;
-        GemmArgs g{N, K, M, dytc, dyts, xtc, xts, g_dy_c, g_x, dW, K, dy_slab_c, xt_slab};
-        if (launch_gemm(g, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
+        if (!pair && launch_gemm(g_dw, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
+    if (pair && launch_gemm_pair(g_dx, g_dw, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     return NVFP4_OK;
 }
 

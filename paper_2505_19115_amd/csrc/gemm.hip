@@ -490,15 +490,43 @@ static int g_fp4_rescale_route = 0;  // (measured slower than the fp16 route: op
 void set_fp4_rescale_route(int on) { g_fp4_rescale_route = on; }
 int fp4_rescale_route() { return g_fp4_rescale_route; }
 
-hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)
+static hipError_t check_gemm(const GemmArgs &P, int block, int sf)
 {
     // lane offsets inside a 256-row tile are 32-bit
     if ((P.K >> 1) * 256 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     if ((P.a_slab || P.b_slab) && !gemm_takes_slabs(P.M, P.N, P.K, block, sf)) return hipErrorInvalidValue;
     if (sf == NVFP4_SCALE_E8M0 && block != 32) return hipErrorNotSupported;
+    return hipSuccess;
+}
+
+// (one workgroup per CU at most over both: two products that fill the chip by themselves gain nothing from sharing a launch)
+bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf)
+{
+    const GemmTile t = choose_gemm_tile(P0.M, P0.N, P0.K, sf);
+    if (t > TILE_64x64 || choose_gemm_tile(P1.M, P1.N, P1.K, sf) != t || g_fp4_rescale_route) return false;
+    const int bm = E4M3_COST[t].bm, bn = E4M3_COST[t].bn;
+    auto tiles = [&](const GemmArgs &P) { return ((P.M + bm - 1) / bm) * ((P.N + bn - 1) / bn); };
+    return tiles(P0) + tiles(P1) <= 256;
+}
+
+hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st)
+{
+    if (gemm_pairs(P0, P1, sf)) {
+        hipError_t e = check_gemm(P0, block, sf);
+        if (e == hipSuccess) e = check_gemm(P1, block, sf);
+        return e != hipSuccess ? e : launch_gemm_ksplit(P0, &P1, choose_gemm_tile(P0.M, P0.N, P0.K, sf), block, sf, out_dt, st);
+    }
+    const hipError_t e = launch_gemm(P0, block, sf, out_dt, st);
+    return e != hipSuccess ? e : launch_gemm(P1, block, sf, out_dt, st);
+}
+
+hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)
+{
+    const hipError_t e = check_gemm(P, block, sf);
+    if (e != hipSuccess) return e;
     if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
     const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);
-    if (tile <= TILE_64x64) return launch_gemm_ksplit(P, tile, block, sf, out_dt, st);
+    if (tile <= TILE_64x64) return launch_gemm_ksplit(P, nullptr, tile, block, sf, out_dt, st);
     if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(P, tile, out_dt, st);
     switch (block) {
     case 16: launch_f16_tile<16>(P, tile, out_dt, st); break;

@@ -144,11 +144,14 @@ hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, i
 // The same elementwise step with dG and dU stored as tensors of dt (n a multiple of 8).
 hipError_t launch_swiglu_bwd(const void *dH, const void *G, const void *U, int dt, int64_t n, void *dG, void *dU, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st);
+// Two independent products: one launch where gemm_pairs() holds (both small, the same tile), else two.
+bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf);
+hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st);
 // Workgroup tiles (rows x columns of the output) of the GEMM kernels: up to 64 x 64 in gemm_ksplit.hip (the waves of a
 // workgroup divide the contraction), the larger ones in gemm.hip (E4M3 scales) and gemm_mx.hip (E8M0).
 enum GemmTile { TILE_32x32, TILE_32x64, TILE_64x32, TILE_64x64, TILE_128x128, TILE_128x256, TILE_192x256, TILE_256x128, TILE_256x256, TILES };
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf);
-hipError_t launch_gemm_ksplit(const GemmArgs &P, GemmTile tile, int block, int sf, int out_dt, hipStream_t st);
+hipError_t launch_gemm_ksplit(const GemmArgs &P, const GemmArgs *P1, GemmTile tile, int block, int sf, int out_dt, hipStream_t st);
 hipError_t launch_gemm_mxfp4(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
 // E4M3 scales at blocks of 64 / 128 as unit-scale FP4 MFMAs per block + binary32 rescale (row-major operands, K % 128 == 0)
 bool fp4_rescale_gemm_applies(int64_t K, int block, const GemmArgs &P);

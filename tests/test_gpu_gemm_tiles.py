@@ -120,3 +120,20 @@ def test_tiles_across_slabs(shape):
     for slabs in ((True, False), (False, True), (True, True)):
         A, B = (nv.quantize_dual(t, slab_rows=s)[0] for t, s in ((X, slabs[0]), (W, slabs[1])))
         assert torch.equal(nv.gemm(A, B, out_dtype=torch.float32, slabs=slabs, shape=shape), plain)
+
+
+# A backward call that wants both gradients runs two small products in one launch, up to 256 workgroups in all (on that line,
+# one past it, and one tile each), with the same bits as the two products by themselves.
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("shape", [(32, 32, 32), (64, 256, 128), (96, 160, 1024), (64, 224, 896), (64, 224, 928)])
+def test_both_gradients_in_one_launch(shape, fmt_name):
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    M, N, K = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    X, W, dY = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (N, K), (M, N)))
+    print(f"[case] gradients in one launch {fmt_name} {shape}", flush=True)
+    dX, dW = nv.linear_bwd(dY, X, W, 3, fmt)
+    assert torch.equal(dX, nv.gemm(nv.quantize(dY, 1, nv.SR, 3, fmt), nv.quantize(W, 0, nv.RTN, 0, fmt), fmt))
+    assert torch.equal(dW, nv.gemm(nv.quantize(dY, 0, nv.SR, 4, fmt), nv.quantize(X, 0, nv.SR, 5, fmt), fmt))
