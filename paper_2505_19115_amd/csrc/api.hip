@@ -112,7 +112,7 @@ struct QuantPlan {
     int n_partials = 0;
 };
 
-// Where a quantizer finds the tensor maximum: one folded bit pattern (n == 0) or n partial maxima.
+// Where a quantizer finds the tensor maximum: one folded bit pattern (n == 0), n partial maxima, or (SELF_AMAX) the tensor.
 struct GSource {
     const float *src;
     int n;
@@ -123,6 +123,10 @@ constexpr size_t PARTIAL_SLOT = 4 * (size_t)AMAX_DENSE_PARTIALS;  // bytes of on
 // quantizers fold the partials themselves, so no fold kernel runs between the two.
 hipError_t amax_dense(const void *x, int dt, int64_t n_elements, uint32_t *partials, int slot, hipStream_t st, GSource *g)
 {
+    if (n_elements * (int64_t)elem_size(dt) <= SELF_AMAX_BYTES) {
+        *g = GSource{reinterpret_cast<const float *>(x), SELF_AMAX};
+        return hipSuccess;
+    }
     uint32_t *dst = partials + slot * AMAX_DENSE_PARTIALS;
     g->src = reinterpret_cast<const float *>(dst);
     return launch_tensor_amax_dense(x, dt, n_elements, dst, &g->n, st);
@@ -670,8 +674,10 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
 
     const int gm = f->tensor_scale ? G_FROM_AMAX : G_NONE;
     GSource gx{reinterpret_cast<const float *>(amax + 0), 0}, gw{reinterpret_cast<const float *>(amax + 1), 0};
-    if (f->tensor_scale && w_ops) {
+    const int64_t both_max = M > N ? M : N;
+    if (f->tensor_scale && (w_ops || both_max * K * (int64_t)elem_size(in_dt) <= SELF_AMAX_BYTES)) {
         if (amax_dense(X, in_dt, M * K, partials, 0, st, &gx) != hipSuccess) return NVFP4_EHIP;
+        if (!w_ops && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
     } else if (f->tensor_scale) {
         uint32_t *const pw = partials + AMAX_DENSE_PARTIALS;
         gx.src = reinterpret_cast<const float *>(partials);

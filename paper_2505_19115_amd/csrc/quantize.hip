@@ -211,7 +211,8 @@ __device__ __forceinline__ float chunk_amax_packed(const Chunk<DT> &c)
 // With n_partials > 0 the tensor maximum arrives as that many per-workgroup maxima and every
 // workgroup (NT threads, all of them must call this) folds them for itself: 2 KB from the L2 per
 // workgroup instead of a separate one-workgroup kernel between the maximum pass and the quantizer.
-template <int NT = 256>
+// n_partials < 0: a small dense tensor (SELF_AMAX_BYTES), whose maximum every workgroup takes for itself.
+template <int DT, int NT = 256>
 __device__ __forceinline__ float resolve_g(const QuantArgs &P)
 {
     if (P.g_mode == G_NONE) return 1.0f;
@@ -223,6 +224,28 @@ __device__ __forceinline__ float resolve_g(const QuantArgs &P)
     if (P.n_partials == 0) return tensor_scale_from_amax(u2f(*bits));
     __shared__ uint32_t fold[NT / 16];
     uint32_t m = 0;
+    if (P.n_partials < 0) {
+        const int n = (int)(P.rows * P.cols), nchunk = n >> 3;
+        float a = 0.0f;
+        for (int base = threadIdx.x; base < nchunk; base += 8 * NT) {
+            Chunk<DT> v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (base + u * NT < nchunk)
+                    v[u].template load<false>(P.x, (int64_t)(base + u * NT) * 8);
+                else
+                    v[u].zero();
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a = fmaxf(a, chunk_amax(v[u]));
+        }
+        if (threadIdx.x == 0 && (n & 7)) {
+            Chunk<DT> t;
+            t.load_partial(P.x, (int64_t)nchunk * 8, n & 7);
+            a = fmaxf(a, chunk_amax(t));
+        }
+        m = f2u(a);
+    }
     for (int i = threadIdx.x; i < P.n_partials; i += NT) m = umax(m, bits[i]);
     m = f2u(group_max<16>(u2f(m)));
     if ((threadIdx.x & 15) == 0) fold[threadIdx.x >> 4] = m;
@@ -628,7 +651,7 @@ __device__ __forceinline__ void rows_tile(const QuantArgs &P, const int64_t wg)
         }
     }
     // (after the loads are issued: folding the partial maxima then overlaps their latency)
-    const float g = resolve_g(P);
+    const float g = resolve_g<DT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
     if (wg == 0 && threadIdx.x == 0) *P.g_out = g;
@@ -827,7 +850,7 @@ __global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_cols_kernel(QuantAr
         else
             v[r].zero();
     }
-    const float g = resolve_g<G::NT>(P);
+    const float g = resolve_g<DT, G::NT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *P.g_out = g;
@@ -1262,7 +1285,7 @@ __device__ __forceinline__ void dual_wg(const DualArgs &D, int tx, int ty, DualL
             swiglu_chunk<DT, SRC>(P.x, D.src_g, D.src_u, (row0 + r) * P.ld + col0, &v[r], &v[r]);
     }
 
-    const float g = resolve_g<G::NT>(P);
+    const float g = resolve_g<DT, G::NT>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, true>(g);
     if (tx == 0 && ty == 0 && threadIdx.x == 0) {

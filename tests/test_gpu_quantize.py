@@ -388,3 +388,19 @@ def test_maximum_of_a_strided_tensor(shape, dtype):
         print(f"[case] strided maximum {shape} {dtype} {at}", flush=True)
         got = nv.quantize(t.cuda()[:, :cols], axis, nv.RTN, 0, nv.NVFP4)
         assert_quant_equal(got, oracle.quantize(t[:, :cols].contiguous(), axis, nv.RTN, 0, oracle.NVFP4), f"{shape} {at}")
+
+
+# Dense tensors of up to 128 KB have no maximum pass: on that line and one block past it, and with a last chunk that is not whole.
+@pytest.mark.parametrize("shape,dtype", [((16, 4096), torch.bfloat16), ((16, 4112), torch.bfloat16), ((16, 2048), torch.float32),
+                                         ((16, 2064), torch.float32), ((16, 16), torch.bfloat16), ((48, 8), torch.float32)])
+def test_maximum_of_a_small_tensor(shape, dtype):
+    for at in ((0, 0), (shape[0] - 1, shape[1] - 1)):
+        x = synth.normal(*shape, 1.0, 6, torch.float32).to(dtype)
+        x[at] = -77.0
+        print(f"[case] small maximum {shape} {dtype} {at}", flush=True)
+        run_both(x, 0, nv.SR, 9, nv.NVFP4, what=f"{shape} cols")
+        if shape[1] % 16 == 0:
+            run_both(x, 1, nv.SR, 9, nv.NVFP4, what=f"{shape} rows")
+            both = nv.quantize_dual(x.cuda(), nv.RTN, 0, nv.SR, 9, nv.NVFP4)
+            assert_quant_equal(both[0], oracle.quantize(x, 1, nv.RTN, 0, oracle.NVFP4), f"{shape} dual rows")
+            assert_quant_equal(both[1], oracle.quantize(x, 0, nv.SR, 9, oracle.NVFP4), f"{shape} dual cols")
