@@ -253,9 +253,13 @@ __device__ __forceinline__ void ksplit_tile(const GemmArgs &P, const int wg)
     int stage = 0;
     if (wave < nkt) fetch(wave, 0);
     for (int kt = wave; kt < nkt; kt += NW) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's loads of tile kt have landed
+        // this wave's loads of tile kt have landed, and its reads of the other stage (the last trip's) are done before fetch() has
+        // that stage overwritten
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         stash_scales(stage);
-        if (kt + NW < nkt) fetch(kt + NW, stage ^ 1);      // (the other stage was read to the end in the last trip)
+        if (kt + NW < nkt) fetch(kt + NW, stage ^ 1);
+        // (compute() reads scales that other lanes of the wave stored: the LDS keeps a wave's order, and so must the compiler)
+        asm volatile("" ::: "memory");
         compute(stage, kt == nkt - 1 && rem < KT);
         stage ^= 1;
     }
