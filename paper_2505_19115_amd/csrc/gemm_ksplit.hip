@@ -26,6 +26,7 @@ typedef int int8v_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float float2v_t __attribute__((ext_vector_type(2)));
+typedef float float4v_t __attribute__((ext_vector_type(4)));
 
 constexpr int KT = 128, KTB = 64;  // contraction elements and code bytes per row of a K tile
 constexpr int QUAD = 1024 + 16;    // LDS bytes between the float4 planes of a partial tile (64 lanes, shifted by four banks)
@@ -301,8 +302,9 @@ __device__ __forceinline__ void ksplit_tile(const GemmArgs &P, const int wg)
         if (OUT_DT == NVFP4_F32) {
             float *dst = reinterpret_cast<float *>(P.out) + grow * P.ldc + gcol;
             if (wide && gcol + 8 <= P.N) {
-                *reinterpret_cast<float4 *>(dst) = make_float4(y[0], y[1], y[2], y[3]);
-                *reinterpret_cast<float4 *>(dst + 4) = make_float4(y[4], y[5], y[6], y[7]);
+                // (vector values, not structs of four: see store_lines.h)
+                *reinterpret_cast<float4v_t *>(dst) = float4v_t{y[0], y[1], y[2], y[3]};
+                *reinterpret_cast<float4v_t *>(dst + 4) = float4v_t{y[4], y[5], y[6], y[7]};
             } else {
 #pragma unroll
                 for (int t = 0; t < 8; ++t)

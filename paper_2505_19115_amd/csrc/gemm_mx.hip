@@ -179,7 +179,8 @@ __global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(GemmArgs P)
         __syncthreads();
     }
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 128, n0 + wn * 128, lds + wave * PIECE, lane);
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -477,7 +478,8 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 128, n0 + wn * 128, lds + wave * PIECE, lane);
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    store_lines<OUT_DT, TA, TB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
