@@ -447,6 +447,10 @@ uint8_t nvfp4_host_round_sr(float m, uint32_t u16); /* m in [0, 6], 16 random bi
 void nvfp4_host_philox4x32_10(const uint32_t ctr[4], const uint32_t key[2], uint32_t out[4]);
 uint32_t nvfp4_host_sr_bits(uint64_t seed, uint64_t element_index);
 uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent byte */
+/* The workgroup tile that the size rule of nvfp4_gemm gives an M x N x K product of this format (of f, the scale type
+ * matters): rows * 65536 + columns of the output; 0 for sizes below 1 or a bad format.  Not a promise: the rule follows
+ * measurements. */
+int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* array forms: n inputs -> n outputs (host pointers) */
 void nvfp4_host_e4m3_encode_n(const float *r, int64_t n, uint8_t *out);
 void nvfp4_host_round_rtn_n(const float *m, int64_t n, uint8_t *out);

@@ -134,6 +134,8 @@ def _load() -> C.CDLL:
     L.nvfp4_host_sr_bits.argtypes = [u64, u64]
     L.nvfp4_host_e8m0_encode.restype = C.c_uint8
     L.nvfp4_host_e8m0_encode.argtypes = [C.c_float]
+    L.nvfp4_host_gemm_tile.restype = ci
+    L.nvfp4_host_gemm_tile.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_e4m3_encode_n.restype = None
     L.nvfp4_host_e4m3_encode_n.argtypes = [vp, i64, vp]
     L.nvfp4_host_round_rtn_n.restype = None
@@ -159,7 +161,7 @@ EXPORTS = (
     "nvfp4_gemm_slab", "nvfp4_gemm_takes_slabs", "nvfp4_slab_codes_bytes", "nvfp4_slab_scales_bytes",
     "nvfp4_linear_fwd", "nvfp4_linear_bwd", "nvfp4_host_e4m3_encode", "nvfp4_host_e4m3_decode",
     "nvfp4_host_round_rtn", "nvfp4_host_round_sr", "nvfp4_host_philox4x32_10",
-    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_e4m3_encode_n",
+    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_e4m3_encode_n",
     "nvfp4_host_round_rtn_n", "nvfp4_host_round_sr_n", "nvfp4_probe_mfma_rate",
     "nvfp4_quant_noise_workspace_bytes", "nvfp4_quant_noise", "nvfp4_quantize_static", "nvfp4_cross_check_switches",
     "nvfp4_weight_operands_bytes", "nvfp4_quantize_weight", "nvfp4_linear_fwd_wq", "nvfp4_linear_bwd_wq",
@@ -333,6 +335,13 @@ def gemm(A, B, fmt: Format = NVFP4, out_dtype: torch.dtype = torch.float32, out=
                                bsc.data_ptr(), ts.data_ptr(), out.data_ptr(), _dtype_tag(out),
                                out.stride(0), int(bool(slabs[0])), int(bool(slabs[1])), _stream()), "nvfp4_gemm")
     return out
+
+
+def gemm_tile(M: int, N: int, K: int, fmt: Format = NVFP4) -> tuple[int, int]:
+    """nvfp4_host_gemm_tile -> (rows, columns) of the workgroup tile the size rule gives this product."""
+    f = fmt.c()
+    t = lib.nvfp4_host_gemm_tile(M, N, K, C.byref(f))
+    return t >> 16, t & 0xFFFF
 
 
 def linear_fwd(X: torch.Tensor, W: torch.Tensor, fmt: Format = NVFP4,

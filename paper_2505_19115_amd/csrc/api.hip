@@ -586,6 +586,14 @@ int nvfp4_gemm_takes_slabs(int64_t M, int64_t N, int64_t K, const nvfp4_format *
     return check_format(f) == NVFP4_OK && M > 0 && N > 0 && K > 0 && gemm_takes_slabs(M, N, K, f->block, f->scale) ? 1 : 0;
 }
 
+int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
+{
+    if (check_format(f) != NVFP4_OK || M <= 0 || N <= 0 || K <= 0) return 0;
+    int rows, cols;
+    gemm_tile_size(choose_gemm_tile(M, N, K, f->scale), &rows, &cols);
+    return rows << 16 | cols;
+}
+
 size_t nvfp4_slab_codes_bytes(int64_t rows, int64_t K)
 {
     return rows <= 0 || K <= 0 ? 0 : (size_t)slab_rows_padded(rows) * (size_t)K / 2;

@@ -471,7 +471,7 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
     double best_time = 0;
     for (int t = 0; t < TILES; ++t) {
         const TileCost &c = cost[t];
-        if (c.bm == 0 || (t > TILE_64x64 && sf == NVFP4_SCALE_E8M0 && K < KT)) continue;  // (not built; needs one whole K tile)
+        if (c.bm == 0) continue;  // (not built)
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         if (tiles > 0x7FFFFFFF) continue;  // (more than a grid holds)
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
@@ -484,6 +484,13 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         }
     }
     return (GemmTile)best;
+}
+
+void gemm_tile_size(GemmTile t, int *rows, int *cols)
+{
+    const TileCost &c = E4M3_COST[t].bm ? E4M3_COST[t] : E8M0_COST[t];
+    *rows = c.bm;
+    *cols = c.bn;
 }
 
 static int g_fp4_rescale_route = 0;  // (measured slower than the fp16 route: opt-in)
@@ -504,7 +511,8 @@ bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf)
 {
     const GemmTile t = choose_gemm_tile(P0.M, P0.N, P0.K, sf);
     if (t > TILE_64x64 || choose_gemm_tile(P1.M, P1.N, P1.K, sf) != t || g_fp4_rescale_route) return false;
-    const int bm = E4M3_COST[t].bm, bn = E4M3_COST[t].bn;
+    int bm, bn;
+    gemm_tile_size(t, &bm, &bn);
     auto tiles = [&](const GemmArgs &P) { return ((P.M + bm - 1) / bm) * ((P.N + bn - 1) / bn); };
     return tiles(P0) + tiles(P1) <= 256;
 }

@@ -483,10 +483,10 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile kernel for the products the kernel above does not serve well: any K that is a multiple of 32 (one whole K tile at
-// least), any operand layout, outputs that 256 x 256 tiles cannot spread over the 256 CUs.  WM x WN waves of TA x TB MFMA
-// tiles each; built as 128 x 128 (2 x 2 waves of 2 x 2), 256 x 128 (2 x 2 of 4 x 2) and 256 x 256 (2 x 4 of 4 x 2), so that
-// two waves share a SIMD and cover each other's waits (two workgroups per CU, or one of eight waves).
+// Tile kernel for the products the kernel above does not serve well: any K that is a multiple of 32, any operand layout, outputs
+// that 256 x 256 tiles cannot spread over the 256 CUs.  WM x WN waves of TA x TB MFMA tiles each; built as 128 x 128 (2 x 2 waves
+// of 2 x 2), 256 x 128 (2 x 2 of 4 x 2) and 256 x 256 (2 x 4 of 4 x 2), so that two waves share a SIMD and cover each other's
+// waits (two workgroups per CU, or one of eight waves).
 // What bounds it: LDS reads, (TA + TB) / (TA TB) KB per MFMA, i.e. 1 KB (128 x 128) or 3/4 KB against the 1 KB the LDS delivers
 // per 32-cycle MFMA and SIMD.
 // Pipeline: three LDS stages of K = 128; the direct loads of tile kt + 2 are requested when tile kt starts and waited for
@@ -599,7 +599,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(Gem
             const int wrow = 64 * wave + NT * i;
             if (wrow >= ROWS) continue;
             const bool slab = wrow < BM ? P.a_slab : P.b_slab;
-            if (!slab && 16 * grp + 16 <= Ks) {
+            if (Ks < 4) {
+                // (less than one K tile: a row's one to three bytes)
+                uint32_t v = 0;
+                for (int t = 0; t < (int)Ks; ++t) v |= (uint32_t)sptr[i][t] << (8 * t);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q.w[i][t] = v;
+            } else if (!slab && 16 * grp + 16 <= Ks) {
                 __builtin_memcpy(q.w[i], sptr[i] + 16 * grp, 16);
             } else {
                 // a dword per K tile; the last one of a row is read so that it ends with the row

@@ -137,3 +137,17 @@ def test_both_gradients_in_one_launch(shape, fmt_name):
     dX, dW = nv.linear_bwd(dY, X, W, 3, fmt)
     assert torch.equal(dX, nv.gemm(nv.quantize(dY, 1, nv.SR, 3, fmt), nv.quantize(W, 0, nv.RTN, 0, fmt), fmt))
     assert torch.equal(dW, nv.gemm(nv.quantize(dY, 0, nv.SR, 4, fmt), nv.quantize(X, 0, nv.SR, 5, fmt), fmt))
+
+
+# MXFP4 contractions shorter than one K tile, on the large tiles
+@pytest.mark.parametrize("K", [32, 64, 96])
+@pytest.mark.parametrize("shape,tile", [((2052, 1990), (128, 128)), ((2720, 4358), (256, 256))])
+def test_mxfp4_short_contractions(shape, tile, K):
+    M, N = shape
+    assert nv.gemm_tile(M, N, K, nv.MXFP4) == tile
+    rng = np.random.default_rng(M + K)
+    A, B = operand(rng, M, K, 32, 1), operand(rng, N, K, 32, 1)
+    print(f"[case] short contraction {M}x{N}x{K}", flush=True)
+    got = run(A, B, nv.MXFP4, torch.float32)
+    of = ofmt(nv.MXFP4)
+    close(got, oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"K {K}", torch.float32)

@@ -315,3 +315,11 @@ def test_host_e8m0_matches_oracle_rule():
         x[0, 0] = v
         want = oracle.quantize(x, 1, oracle.RTN, 0, oracle.MXFP4)[1][0, 0]
         assert nv.lib.nvfp4_host_e8m0_encode(float(v)) == want, v
+
+
+def test_gemm_tile_rule():
+    E4, MX = nv.NVFP4, nv.MXFP4
+    assert nv.gemm_tile(0, 64, 64, E4) == (0, 0) and nv.gemm_tile(64, 64, 64, nv.Format(8, 0, 1)) == (0, 0)
+    # MXFP4 contractions shorter than a K tile have the large tiles too (on 64 x 64, 4096 x 11008 x 64 took 82 us, on 128 x 128 20)
+    for K in (32, 64, 96):
+        assert nv.gemm_tile(4096, 11008, K, MX) == (128, 128)
