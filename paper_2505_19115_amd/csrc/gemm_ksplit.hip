@@ -320,6 +320,9 @@ __device__ __forceinline__ void ksplit_tile(const GemmArgs &P, const int wg)
             uint16_t *dst = reinterpret_cast<uint16_t *>(P.out) + grow * P.ldc + gcol;
             if (wide && gcol + 8 <= P.N) {
                 *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+            } else if ((P.ldc & 3) == 0 && gcol + 8 <= P.N) {
+                *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
+                *reinterpret_cast<uint2 *>(dst + 4) = make_uint2(w[2], w[3]);
             } else {
 #pragma unroll
                 for (int t = 0; t < 8; ++t)

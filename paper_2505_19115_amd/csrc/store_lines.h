@@ -17,11 +17,12 @@ namespace nvfp4 {
 // 256 x 256 tiles) 151 us against 137.
 template <int OUT_DT, int TA, int TB, bool FULL, class ACC>
 __device__ __forceinline__ void store_lines_form(const GemmArgs &P, const ACC (&acc)[TA][TB], int64_t row0, int64_t col0, uint8_t *mine,
-                                                 unsigned lane, float gg, bool wide)
+                                                 unsigned lane, float gg, bool wide, bool half)
 {
     typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
     typedef float f2_t __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     constexpr int ESZ = OUT_DT == NVFP4_F32 ? 4 : 2, EPC = 16 / ESZ;   // element size, elements per piece
     constexpr int ROWB = 32 * TB * ESZ, CPR = ROWB / 16, SWZ = CPR - 1;  // bytes and pieces per row (CPR a power of two)
     constexpr int RPS = 64 / CPR;                                        // rows per store instruction
@@ -61,6 +62,9 @@ __device__ __forceinline__ void store_lines_form(const GemmArgs &P, const ACC (&
             } else if (grow0 + 32 * a + RPS * i < P.M) {
                 if (wide && gcol + EPC <= P.N) {
                     *reinterpret_cast<u32x4_t *>(dst) = v;
+                } else if (OUT_DT == NVFP4_BF16 && half && gcol + EPC <= P.N) {
+                    *reinterpret_cast<u32x2_t *>(dst) = v.xy;
+                    *reinterpret_cast<u32x2_t *>(dst + 8) = v.zw;
                 } else {
 #pragma unroll
                     for (int e = 0; e < EPC; ++e)
@@ -84,11 +88,12 @@ __device__ __forceinline__ void store_lines(const GemmArgs &P, const ACC (&acc)[
     asm volatile("" : "+v"(lane));
     const float gg = P.gA[0] * P.gB[0];
     const bool wide = P.ldc % (OUT_DT == NVFP4_F32 ? 4 : 8) == 0;
+    const bool half = P.ldc % 4 == 0;  // (bf16 rows start at multiples of 8 bytes: 303 x 6548 x 128 8.5 us in single elements)
     // (row0 and col0 are the same in the whole wave)
     if (wide && row0 + 32 * TA <= P.M && col0 + 32 * TB <= P.N)
-        store_lines_form<OUT_DT, TA, TB, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide);
+        store_lines_form<OUT_DT, TA, TB, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
     else
-        store_lines_form<OUT_DT, TA, TB, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide);
+        store_lines_form<OUT_DT, TA, TB, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
 }
 
 }  // namespace nvfp4
