@@ -435,33 +435,36 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 // busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves up to 64 x 64),
 //     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
 // Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
-// expansion, LDS reads).  The constants (nanoseconds) are fitted to 65 shapes from 5 x 192 x 256 to 11008 x 4096 x 4096, bf16
-// outputs, every tile timed on every shape; the choice is then within 0.4 % (E4M3) and 1.5 % (E8M0) of the best tile on
-// average.  E4M3 examples, us per tile choice:      32x32  32x64  64x32  64x64  128x128  256x256
-//     16 x 11008 x 4096                              11.0   10.3   16.4   13.6    32.0     76.3
-//     64 x  4096 x 11008                             14.2   19.8   20.1   28.7    78.8    194.1
-//    256 x 11008 x 4096                              47.1   51.8   50.1   33.0    34.7     77.6
-//   2048 x  4096 x 4096                             129.8  127.8  123.1   80.0    65.4     78.6
-//   4096 x  4096 x 4096                             248.3  248.3  248.9  155.4   124.8    108.0
-// and the two E4M3 tiles for products that leave a 256 x 256 grid short of the 256 CUs or just past a round of them (a 192-row
-// or 128-row tile of the same eight waves; more expansion work per product, less rounding up):
-//                                                  128x128  128x256  192x256  256x256
-//    512 x 11008 x 4096                              57.1     51.7     64.9     77.3
-//    777 x 12288 x 4096                              88.7    107.4     81.9     86.3
-//   2048 x  4096 x 11008                            156.8    153.0    174.7    203.2
-//   3072 x  8192 x 4096                             171.7    172.5    160.7    176.6
-// (two kernels before: 256 x 256 from 128 such tiles on, else 128 x 128, with a register-staged 128 x 128 for a ragged K:
-// 33.8, 84.5, 38.7, 81.2 and 108.0 us; 2080 x 2784 x 1056: 44.3 us, now 23.3.)
+// expansion, LDS reads).  The constants (nanoseconds) are fitted to every tile timed on 245 shapes from 9 x 162 x 768 to 11008 x 4096 x
+// 4096, row-major and in slabs, both output types (profiles/gemm_tiles.txt); the choice is then 1.0 / 1.2 % (E4M3, bf16 / f32 outputs)
+// and 1.5 / 1.6 % (E8M0) slower than the best tile on average.  E4M3, bf16 outputs, us per tile choice:
+//                              32x32  32x64  64x32  64x64  128x128  128x256  192x256  256x256
+//      16 x 11008 x  4096        9.8    9.1   16.3   12.7     31.8     47.8     62.1     75.8
+//      64 x  4096 x 11008       13.5   18.6   17.9   28.4     79.1    122.3    160.3    195.4
+//     256 x 11008 x  4096       45.2   50.9   49.7   32.8     34.6     50.8     65.8     77.8
+//     512 x 11008 x  4096       86.3   92.5   91.2   60.9     58.2     55.8     69.1     80.7
+//     777 x 12288 x  4096      153.6  161.2  164.9  101.1     91.3    110.4     84.1     93.8
+//    1056 x  2080 x  2784       32.0   40.5   39.9   28.1     27.6     37.3     49.7     59.2
+//    2048 x  4096 x  4096      133.2  140.2  136.5   84.3     67.5     64.9     78.4     91.1
+//    2048 x  4096 x 11008      319.6  300.3  284.1  210.9    173.8    163.7    191.0    222.8
+//    3072 x  8192 x  4096      394.5  414.3  399.1  240.5    187.2    190.7    174.8    195.7
+//    4096 x  4096 x  4096      266.1  279.8  273.5  163.7    128.2    128.0    155.2    110.7
+//    8192 x  8192 x   256      298.2  397.5  385.1  138.7     45.6     55.1     55.2     52.1
+//    4096 x 11008 x   512      239.5  286.9  272.2  102.2     51.7     61.8     60.6     56.0
+// (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
+// a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
     int bm, bn, kwaves;                 // tile, waves that divide the contraction
     int fixed, tile, step, alone;       // ns, ns, ns, percent
 };
-static const TileCost E4M3_COST[TILES] = {{32, 32, 8, 2900, 350, 860, 3},    {32, 64, 8, 1300, 2400, 1430, 0}, {64, 32, 8, 1400, 2300, 1410, 0},
-                                          {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8}, {128, 256, 1, 3000, 1500, 1780, 0},
-                                          {192, 256, 1, 3000, 3000, 2380, 0},{0, 0, 0, 0, 0, 0, 0},             {256, 256, 1, 0, 7900, 2560, 0}};
-static const TileCost E8M0_COST[TILES] = {{32, 32, 8, 2700, 410, 585, 0},    {32, 64, 8, 1400, 2140, 930, 0},  {64, 32, 8, 1400, 2100, 935, 0},
-                                          {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0},
-                                          {0, 0, 0, 0, 0, 0, 0},             {256, 128, 1, 2900, 3150, 556, 19}, {256, 256, 1, 0, 8500, 1000, 0}};
+static const TileCost E4M3_COST[TILES] = {
+    {32, 32, 8, 2900, 350, 860, 3},    {32, 64, 8, 1300, 2400, 1430, 0},   {64, 32, 8, 1400, 2300, 1410, 0},
+    {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8},  {128, 256, 1, 500, 3800, 1740, 0},
+    {192, 256, 1, 2500, 5200, 2330, 0}, {0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 0, 8500, 2650, 0}};
+static const TileCost E8M0_COST[TILES] = {
+    {32, 32, 8, 2700, 410, 585, 0},    {32, 64, 8, 1400, 2140, 930, 0},    {64, 32, 8, 1400, 2100, 935, 0},
+    {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 2900, 3150, 556, 30}, {256, 256, 1, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {

@@ -323,3 +323,9 @@ def test_gemm_tile_rule():
     # MXFP4 contractions shorter than a K tile have the large tiles too (on 64 x 64, 4096 x 11008 x 64 took 82 us, on 128 x 128 20)
     for K in (32, 64, 96):
         assert nv.gemm_tile(4096, 11008, K, MX) == (128, 128)
+    # short contractions with E4M3 scales: 128 x 256 tiles only pay where the products fill the time between their epilogues
+    # (8192 x 8192 x 256, bf16 outputs: 45.6 us on 128 x 128, 55 on the larger ones)
+    for M, N, K in ((8192, 8192, 128), (8192, 8192, 256), (4096, 11008, 128), (4096, 11008, 256), (8192, 4096, 256)):
+        assert nv.gemm_tile(M, N, K, E4) == (128, 128)
+    # MXFP4, 256 tiles of 256 x 128: one per CU, no faster than 256 x 256 and slower than 128 x 128
+    assert nv.gemm_tile(2048, 4096, 4096, MX) == (128, 128) and nv.gemm_tile(2048, 4096, 11008, MX) == (128, 128)
