@@ -454,29 +454,29 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
-    int bm, bn, kwaves;                 // tile, waves that divide the contraction
+    int bm, bn, kwaves, threads;        // tile, waves that divide the contraction, workgroup size
     int fixed, tile, step, alone;       // ns, ns, ns, percent
 };
 static const TileCost E4M3_COST[TILES] = {
-    {32, 32, 8, 2900, 350, 860, 3},    {32, 64, 8, 1300, 2400, 1430, 0},   {64, 32, 8, 1400, 2300, 1410, 0},
-    {64, 64, 4, 3800, 770, 1115, 3},   {128, 128, 1, 3700, 1200, 890, 8},  {128, 256, 1, 500, 3800, 1740, 0},
-    {192, 256, 1, 2500, 5200, 2330, 0}, {0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 0, 8500, 2650, 0}};
+    {32, 32, 8, 512, 2900, 350, 860, 3},    {32, 64, 8, 512, 1300, 2400, 1430, 0},   {64, 32, 8, 512, 1400, 2300, 1410, 0},
+    {64, 64, 4, 256, 3800, 770, 1115, 3},   {128, 128, 1, 256, 3700, 1200, 890, 8},  {128, 256, 1, 512, 500, 3800, 1740, 0},
+    {192, 256, 1, 512, 2500, 5200, 2330, 0}, {0, 0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 512, 0, 8500, 2650, 0}};
 static const TileCost E8M0_COST[TILES] = {
-    {32, 32, 8, 2700, 410, 585, 0},    {32, 64, 8, 1400, 2140, 930, 0},    {64, 32, 8, 1400, 2100, 935, 0},
-    {64, 64, 4, 3200, 910, 685, 0},    {128, 128, 1, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0},
-    {0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 2900, 3150, 556, 30}, {256, 256, 1, 0, 8500, 1000, 0}};
+    {32, 32, 8, 512, 2700, 410, 585, 0},    {32, 64, 8, 512, 1400, 2140, 930, 0},    {64, 32, 8, 512, 1400, 2100, 935, 0},
+    {64, 64, 4, 256, 3200, 910, 685, 0},    {128, 128, 1, 256, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {
     const TileCost *const cost = sf == NVFP4_SCALE_E8M0 ? E8M0_COST : E4M3_COST;
     const int64_t nkt = (K + KT - 1) / KT;
-    int best = TILE_32x32;
+    int best = TILE_256x256;
     double best_time = 0;
     for (int t = 0; t < TILES; ++t) {
         const TileCost &c = cost[t];
         if (c.bm == 0) continue;  // (not built)
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        if (tiles > 0x7FFFFFFF) continue;  // (more than a grid holds)
+        if (tiles * c.threads > 0xFFFFFFFF) continue;  // (the threads of a launch are counted in 32 bits)
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
         if (rounds == 1) time *= 1.0 + 0.01 * c.alone;

@@ -329,3 +329,17 @@ def test_gemm_tile_rule():
         assert nv.gemm_tile(M, N, K, E4) == (128, 128)
     # MXFP4, 256 tiles of 256 x 128: one per CU, no faster than 256 x 256 and slower than 128 x 128
     assert nv.gemm_tile(2048, 4096, 4096, MX) == (128, 128) and nv.gemm_tile(2048, 4096, 11008, MX) == (128, 128)
+
+
+def test_no_tile_beyond_the_launch_limit():
+    # a launch counts its threads in 32 bits, and no product that one of the tiles can serve may be given one that cannot
+    threads = {(32, 32): 512, (32, 64): 512, (64, 32): 512, (64, 64): 256, (128, 128): 256, (128, 256): 512, (192, 256): 512,
+               (256, 128): 256, (256, 256): 512}
+    for fmt in (nv.NVFP4, nv.MXFP4):
+        for M in (1, 64, 300, 4096, 1 << 18, 1 << 20, 1 << 24, 1 << 26, 1 << 28, (1 << 28) + 1, 1 << 30):
+            for N in (1, 32, 33, 64, 128, 300, 4096, 1 << 18):
+                for K in (32, 96, 128, 512, 1024, 4096, 16384):
+                    if M * N > 1 << 38:  # (more than 256 x 256 tiles can serve)
+                        continue
+                    t = nv.gemm_tile(M, N, K, fmt)
+                    assert -(-M // t[0]) * -(-N // t[1]) * threads[t] < 1 << 32, (M, N, K, t)
