@@ -212,7 +212,11 @@ __device__ __forceinline__ float chunk_amax_packed(const Chunk<DT> &c)
 // workgroup (NT threads, all of them must call this) folds them for itself: 2 KB from the L2 per
 // workgroup instead of a separate one-workgroup kernel between the maximum pass and the quantizer.
 // n_partials < 0: a small dense tensor (SELF_AMAX_BYTES), whose maximum every workgroup takes for itself.
-template <int DT, int NT = 256>
+// SELF = false leaves that form out, in kernels that no such tensor reaches: beside a lane tile of 16 rows its loads in flight cost
+// the registers of a whole wave per SIMD (129 instead of 126: a columns pass, bf16 SR, over 4096 x 8192 30.9 us instead of 26.1).
+// For the same reason binary32 chunks, twice the size, are four at a time, and kernels for E8M0 scales, whose formats have no tensor
+// scale, do without (MXFP4 rows, bf16 SR, 4096 x 11008: 24.4 us with it, 22.7 without).
+template <int DT, int NT = 256, bool SELF = true>
 __device__ __forceinline__ float resolve_g(const QuantArgs &P)
 {
     if (P.g_mode == G_NONE) return 1.0f;
@@ -224,20 +228,21 @@ __device__ __forceinline__ float resolve_g(const QuantArgs &P)
     if (P.n_partials == 0) return tensor_scale_from_amax(u2f(*bits));
     __shared__ uint32_t fold[NT / 16];
     uint32_t m = 0;
-    if (P.n_partials < 0) {
+    if (SELF && P.n_partials < 0) {
+        constexpr int U = DT == NVFP4_F32 ? 4 : 8;
         const int n = (int)(P.rows * P.cols), nchunk = n >> 3;
         float a = 0.0f;
-        for (int base = threadIdx.x; base < nchunk; base += 8 * NT) {
-            Chunk<DT> v[8];
+        for (int base = threadIdx.x; base < nchunk; base += U * NT) {
+            Chunk<DT> v[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (base + u * NT < nchunk)
                     v[u].template load<false>(P.x, (int64_t)(base + u * NT) * 8);
                 else
                     v[u].zero();
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a = fmaxf(a, chunk_amax(v[u]));
+            for (int u = 0; u < U; ++u) a = fmaxf(a, chunk_amax(v[u]));
         }
         if (threadIdx.x == 0 && (n & 7)) {
             Chunk<DT> t;
@@ -651,7 +656,7 @@ __device__ __forceinline__ void rows_tile(const QuantArgs &P, const int64_t wg)
         }
     }
     // (after the loads are issued: folding the partial maxima then overlaps their latency)
-    const float g = resolve_g<DT>(P);
+    const float g = resolve_g<DT, 256, SF == NVFP4_SCALE_E4M3>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
     if (wg == 0 && threadIdx.x == 0) *P.g_out = g;
@@ -850,7 +855,8 @@ __global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_cols_kernel(QuantAr
         else
             v[r].zero();
     }
-    const float g = resolve_g<DT, G::NT>(P);
+    // (tensors small enough to take their maximum here have few tiles, hence 8 rows per lane; the forms that only 16 rows serve aside)
+    const float g = resolve_g<DT, G::NT, SF == NVFP4_SCALE_E4M3 && (RPL == 8 || !HW || !ALIGNED)>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, HW>(g);
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *P.g_out = g;
@@ -1285,7 +1291,7 @@ __device__ __forceinline__ void dual_wg(const DualArgs &D, int tx, int ty, DualL
             swiglu_chunk<DT, SRC>(P.x, D.src_g, D.src_u, (row0 + r) * P.ld + col0, &v[r], &v[r]);
     }
 
-    const float g = resolve_g<DT, G::NT>(P);
+    const float g = resolve_g<DT, G::NT, SF == NVFP4_SCALE_E4M3 && RPL == 8 && SRC == SRC_TENSOR>(P);
     const float k = 1.0f / (6.0f * g);
     build_qtab<SF, true>(g);
     if (tx == 0 && ty == 0 && threadIdx.x == 0) {
@@ -1297,8 +1303,15 @@ __device__ __forceinline__ void dual_wg(const DualArgs &D, int tx, int ty, DualL
     dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, tx, ty, lds.codes, lds.scales);
 }
 
+// Waves per SIMD asked of the compiler with 16 rows per lane, where the registers lie within a few of the line (128 and 168 registers);
+// 0: as they come.
+constexpr int dual_waves(int dt, int b, int sf, int rnd_r, int rnd_c, int rpl)
+{
+    if (rpl != 16 || (b == 16 && sf == NVFP4_SCALE_E8M0)) return 0;
+    return dt == NVFP4_BF16 ? 4 : rnd_r == NVFP4_RTN && rnd_c == NVFP4_RTN ? 3 : 0;
+}
 template <int DT, int B, int SF, int RND_R, int RND_C, int RPL, int SRC = SRC_TENSOR>
-__global__ __launch_bounds__(ColGeom<RPL>::NT) void quantize_dual_kernel(DualArgs D)
+__global__ __launch_bounds__(ColGeom<RPL>::NT, dual_waves(DT, B, SF, RND_R, RND_C, RPL)) void quantize_dual_kernel(DualArgs D)
 {
     __shared__ __align__(16) DualLds lds;
     dual_wg<DT, B, SF, RND_R, RND_C, RPL, SRC>(D, (int)blockIdx.x, (int)blockIdx.y, lds);

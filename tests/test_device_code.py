@@ -1,5 +1,7 @@
-"""CPU-only checks of the compiled kernels: properties of this library's own gfx950 code that no result shows."""
+"""CPU-only checks of the compiled kernels: properties of this library's own gfx950 code that the tile rules and the output path
+count on and that no result shows (the pieces an output leaves in, registers that decide how many workgroups a CU holds)."""
 import os
+import re
 import shutil
 import struct
 import subprocess
@@ -15,7 +17,7 @@ MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 def code_object(source: str, tmp) -> str:
     """The gfx950 code object inside the object file that build() compiled from a source, as a file of its own."""
     obj = os.path.join(hip_build.OBJ, source + ".o")
-    for tool in ("llvm-objcopy", "llvm-objdump"):
+    for tool in ("llvm-objcopy", "llvm-objdump", "llvm-readelf"):
         if not shutil.which(os.path.join(LLVM, tool)):
             pytest.skip(f"{tool} is not installed")
     if not os.path.exists(obj):
@@ -36,6 +38,14 @@ def code_object(source: str, tmp) -> str:
     raise AssertionError("no gfx950 code object")
 
 
+def registers(source, tmp):
+    """Kernel name -> (vector registers, spilled ones)."""
+    notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object(source, tmp)], capture_output=True, text=True, check=True).stdout
+    found = re.findall(r"\.name:\s+(_ZN5nvfp4\S+).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", notes, re.S)
+    assert found
+    return {name: (int(v), int(s)) for name, v, s in found}
+
+
 @pytest.mark.parametrize("source", ["gemm", "gemm_mx", "gemm_ksplit"])
 def test_gemm_outputs_leave_in_whole_pieces(source, tmp_path):
     # A 16-byte piece whose store the compiler has split (its last word shared with the form for cut pieces) goes out as 12 + 4 bytes:
@@ -43,3 +53,34 @@ def test_gemm_outputs_leave_in_whole_pieces(source, tmp_path):
     asm = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", code_object(source, tmp_path)], capture_output=True, text=True, check=True).stdout
     assert asm.count("global_store_dwordx4") > 0
     assert asm.count("global_store_dwordx3") == 0
+
+
+def kernels(regs, kind):
+    """(template arguments, vector registers, spilled) of the kernels of a kind."""
+    for name, (v, s) in regs.items():
+        if kind in name:
+            yield tuple(int(x or y) for x, y in re.findall(r"Li(\d+)E|Lb(\d)E", name)), v, s
+
+
+def test_resident_workgroups_of_the_quantizers(tmp_path):
+    # 512 registers per SIMD: 128 are four waves, 168 three.  (Three registers above the line cost a columns pass 18 %.)
+    regs = registers("quantize", tmp_path)
+    seen = 0
+    for (dt, b, sf, rnd_r, rnd_c, rpl, src), v, s in kernels(regs, "quantize_dual_kernel"):
+        if rpl == 16 and dt == 1 and (b, sf) != (16, 1):
+            assert v <= 128 and s == 0, ("dual bf16", b, sf, rnd_r, rnd_c, src, v, s)
+            seen += 1
+        if rpl == 16 and dt == 0 and rnd_c == 0:
+            assert v <= 168 and s <= 2, ("dual f32 RtN", b, sf, v, s)
+            seen += 1
+        if rpl == 8:
+            assert v <= (170 if dt == 0 and sf == 1 else 128) and s == 0, ("dual, 8 rows", dt, b, sf, rnd_r, rnd_c, src, v, s)
+    assert seen >= 10
+    for (dt, b, sf, rnd, hw, aligned, rpl), v, s in kernels(regs, "quantize_cols_kernel"):
+        if rpl == 16 and dt == 1 and hw and aligned and not (b == 16 and sf == 1 and rnd == 0):
+            assert v <= 128 and s == 0, ("columns bf16", b, sf, rnd, v, s)
+        if rpl == 16 and dt == 0 and hw and rnd == 0 and (b >= 64 or sf == 1):
+            assert v <= 168 and s == 0, ("columns f32 RtN", b, sf, v, s)
+    for (dt, b, sf, rnd, hw), v, s in kernels(regs, "quantize_rows_kernel"):
+        if not (dt == 0 and sf == 1 and rnd == 1):
+            assert v <= 64 and s == 0, ("rows", dt, b, sf, rnd, hw, v, s)
