@@ -718,18 +718,40 @@ __global__ __launch_bounds__(256) void quantize_rows_pair_kernel(QuantArgs P0, Q
 // Lane tile: RPL rows x 8 columns; a workgroup covers 128 rows x 256 columns, lanes with consecutive ids stacked
 // vertically, so that it reads 512 contiguous bytes (bf16) per row and writes 64 per output row.
 // RPL = 16 (4 waves) does the least work per element, RPL = 8 (8 waves: a block of 16 spans two lanes) has half the serial
-// chain per wave and half the registers.  What bounds a tensor of up to 512 tiles (2 per CU: 4 waves per SIMD, all resident at once) is that
-// chain: one batch of loads, the arithmetic, the stores.  What bounds a larger one in bf16 is the arithmetic, and binary32
-// tiles of 16 rows take 168-188 registers, two workgroups per CU.  us, RPL = 16 / 8, dual quantizer with row-major outputs:
-//                      bf16 RtN+RtN   bf16 SR+SR    MXFP4 bf16 SR+SR   f32 SR+SR     MXFP4 f32 SR+SR
-//     2048 x  4096     13.9 / 11.6    18.1 / 16.0   19.7 / 16.4        15.8 / 14.9   20.4 / 16.8
-//     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4        22.3 / 21.5   38.6 / 32.4
-//     4096 x 11008     43.6 / 43.8    56.8 / 58.4   57.2 / 57.8        63.0 / 62.0   115.8 / 93.7
-//     8192 x  8192     53.9 / 57.5    67.6 / 72.3   72.0 / 75.3        90.9 / 83.1   161.6 / 125.9
+// chain per wave and half the registers, 512 tiles resident at once.
+// bf16: what bounds a tensor of up to 512 tiles is that chain (one batch of loads, the arithmetic, the stores), what bounds a larger
+// one the arithmetic.  us, RPL = 16 / 8, dual quantizer with row-major outputs:
+//                      bf16 RtN+RtN   bf16 SR+SR    MXFP4 bf16 SR+SR
+//     2048 x  4096     13.9 / 11.6    18.1 / 16.0   19.7 / 16.4
+//     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4
+//     4096 x 11008     43.6 / 43.8    56.8 / 58.4   57.2 / 57.8
+//     8192 x  8192     53.9 / 57.5    67.6 / 72.3   72.0 / 75.3
+// Binary32 tiles of 16 rows take 160 to 190 registers with E4M3 scales, and three workgroups per CU (768 tiles resident) where they
+// stay within 168: both sides RtN, RtN columns with blocks of 64 and 128 or E8M0 scales.  They are the faster ones
+//     from 257 to 512 tiles (all resident either way: the fewer instructions win)    columns, RtN duals into slabs, SwiGLU
+//     from 513 to 768 (one generation of them, two of the others)                    those of up to 168 registers, columns or slabs
+//     from 1025 to 1536 (two, or three as full as the others')                       RtN columns, duals into slabs, SwiGLU
+// and everywhere else 8 rows are, also for MXFP4 with SR, whose 16-row tiles take 285 registers.  us, RPL = 16 / 8, with the maximum
+// pass of the call (E4M3):
+//                      dual RtN+RtN slabs   dual SR+SR slabs   dual SR+SR     columns RtN, block 64   columns SR, block 16   MXFP4 SR+SR slabs
+//     3456 x  3072     25.7 / 26.2          31.6 / 31.1        32.6 / 31.6    23.6 / 25.0             27.6 / 29.1            36.1 / 27.4
+//     2048 x 11008     41.7 / 42.5          46.8 / 47.4        48.4 / 49.4    35.7 / 40.4             45.1 / 43.4            56.0 / 43.0
+//     8192 x  4096     62.1 / 57.8          67.6 / 62.3        68.9 / 62.0    53.2 / 50.6             59.5 / 56.6            78.4 / 56.3
+//     4096 x 11008     74.8 / 78.5          84.3 / 83.5        88.7 / 86.9    67.5 / 70.0             80.9 / 81.4           112.2 / 84.6
+//     8192 x  8192    113.5 / 107.7        118.1 / 112.6      121.5 / 114.3   97.1 / 95.9            114.3 / 104.6          155.8 / 111.7
+// (with the scale preset, dual SR+SR slabs, 4096 x 11008: 56.3 / 61.5; SwiGLU 3456 x 3072: 90.7 / 98.2, 4096 x 11008 335 / 346)
 constexpr int64_t PAIR_TILES = 512;  // of X and W together: where both would take 8-row lane tiles, resident at once
-static bool short_lane_tile(int dt, int64_t rows, int64_t cols)
+enum TileUse { COLUMNS, DUAL, DUAL_SLABS, SWIGLU };
+static bool short_lane_tile(int dt, int block, int sf, int rnd_r, int rnd_c, TileUse use, int64_t rows, int64_t cols)
 {
-    return dt == NVFP4_F32 || ((rows + 127) / 128) * ((cols + 255) / 256) <= 512;
+    const int64_t tiles = ((rows + 127) / 128) * ((cols + 255) / 256);
+    if (dt == NVFP4_BF16) return tiles <= 512;
+    const bool sr = rnd_c == NVFP4_SR;
+    if (use == DUAL || (sf == NVFP4_SCALE_E8M0 && sr) || tiles <= 256 || tiles > 1536) return true;
+    if (tiles <= 512) return use == DUAL_SLABS && sr;
+    if (tiles <= 768) return !(use == COLUMNS ? !sr && (block >= 64 || sf == NVFP4_SCALE_E8M0) : use == DUAL_SLABS && rnd_r == NVFP4_RTN && !sr);
+    if (tiles <= 1024) return true;
+    return use == COLUMNS && sr;
 }
 template <int ROWS_PER_LANE>
 struct ColGeom {
@@ -1451,10 +1473,10 @@ static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
         // (the cross-check formulation and stochastic rounding with unaligned draws have the 16-row tile only)
         if (RND == NVFP4_SR && (P.cols & 7) != 0)
             launch_cols<DT, B, SF, RND, HW, RND == NVFP4_RTN, 16>(P, st);
-        else if (HW && short_lane_tile(DT, P.rows, P.cols))
+        else if (HW && short_lane_tile(DT, B, SF, RND, RND, COLUMNS, P.rows, P.cols))
             launch_cols<DT, B, SF, RND, HW, true, HW ? 8 : 16>(P, st);
         else
-            launch_cols<DT, B, SF, RND, HW, true, HW && DT == NVFP4_F32 ? 8 : 16>(P, st);
+            launch_cols<DT, B, SF, RND, HW, true, HW && DT == NVFP4_F32 && SF == NVFP4_SCALE_E8M0 && RND == NVFP4_SR ? 8 : 16>(P, st);
     }
 }
 
@@ -1502,26 +1524,33 @@ hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, i
     return launch_status();
 }
 
-template <int DT, int B, int SF, int RPL>
-static void launch_dual_rnd(const DualArgs &D, int rnd_r, int rnd_c, hipStream_t st)
+template <int DT, int B, int SF, int RND_R, int RND_C>
+static void launch_dual_rpl(const DualArgs &D, hipStream_t st)
 {
-    using G = ColGeom<RPL>;
-    dim3 grid((unsigned)((D.c.cols + G::WG_COLS - 1) / G::WG_COLS), (unsigned)((D.c.rows + G::WG_ROWS - 1) / G::WG_ROWS));
-    if (rnd_r == NVFP4_SR && rnd_c == NVFP4_SR)
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_SR, NVFP4_SR, RPL>), grid, dim3(G::NT), 0, st, D);
-    else if (rnd_r == NVFP4_RTN && rnd_c == NVFP4_SR)
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_SR, RPL>), grid, dim3(G::NT), 0, st, D);
+    // (the binary32 kernels that no tensor takes with 16 rows are not built)
+    constexpr int LONG = DT == NVFP4_F32 && ((B == 16) != (SF == NVFP4_SCALE_E4M3) || (SF == NVFP4_SCALE_E8M0 && RND_C == NVFP4_SR)) ? 8 : 16;
+    const unsigned gx = (unsigned)((D.c.cols + 255) / 256), gy = (unsigned)((D.c.rows + 127) / 128);
+    if (short_lane_tile(DT, B, SF, RND_R, RND_C, D.slab_r || D.slab_c ? DUAL_SLABS : DUAL, D.c.rows, D.c.cols))
+        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, 8>), dim3(gx, gy), dim3(ColGeom<8>::NT), 0, st, D);
     else
-        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, NVFP4_RTN, NVFP4_RTN, RPL>), grid, dim3(G::NT), 0, st, D);
+        hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, LONG>), dim3(gx, gy), dim3(ColGeom<LONG>::NT), 0, st, D);
 }
 
-template <int DT, int RPL>
+template <int DT, int B, int SF>
+static void launch_dual_rnd(const DualArgs &D, int rnd_r, int rnd_c, hipStream_t st)
+{
+    if (rnd_r == NVFP4_SR && rnd_c == NVFP4_SR) launch_dual_rpl<DT, B, SF, NVFP4_SR, NVFP4_SR>(D, st);
+    else if (rnd_r == NVFP4_RTN && rnd_c == NVFP4_SR) launch_dual_rpl<DT, B, SF, NVFP4_RTN, NVFP4_SR>(D, st);
+    else launch_dual_rpl<DT, B, SF, NVFP4_RTN, NVFP4_RTN>(D, st);
+}
+
+template <int DT>
 static void launch_dual_fmt(const DualArgs &D, int rnd_r, int rnd_c, int block, int sf, hipStream_t st)
 {
-    if (block == 16 && sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 16, NVFP4_SCALE_E4M3, RPL>(D, rnd_r, rnd_c, st);
-    else if (block == 16) launch_dual_rnd<DT, 16, NVFP4_SCALE_E8M0, RPL>(D, rnd_r, rnd_c, st);
-    else if (sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 32, NVFP4_SCALE_E4M3, RPL>(D, rnd_r, rnd_c, st);
-    else launch_dual_rnd<DT, 32, NVFP4_SCALE_E8M0, RPL>(D, rnd_r, rnd_c, st);
+    if (block == 16 && sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 16, NVFP4_SCALE_E4M3>(D, rnd_r, rnd_c, st);
+    else if (block == 16) launch_dual_rnd<DT, 16, NVFP4_SCALE_E8M0>(D, rnd_r, rnd_c, st);
+    else if (sf == NVFP4_SCALE_E4M3) launch_dual_rnd<DT, 32, NVFP4_SCALE_E4M3>(D, rnd_r, rnd_c, st);
+    else launch_dual_rnd<DT, 32, NVFP4_SCALE_E8M0>(D, rnd_r, rnd_c, st);
 }
 
 template <int DT, int B, int SF, int RPL>
@@ -1536,8 +1565,8 @@ static void launch_swiglu_dual_rpl(const DualArgs &g, const DualArgs &u, hipStre
 template <int DT, int B, int SF>
 static void launch_swiglu_dual_fmt(const DualArgs &g, const DualArgs &u, hipStream_t st)
 {
-    if (short_lane_tile(DT, g.c.rows, g.c.cols)) launch_swiglu_dual_rpl<DT, B, SF, 8>(g, u, st);
-    else launch_swiglu_dual_rpl<DT, B, SF, DT == NVFP4_F32 ? 8 : 16>(g, u, st);
+    if (short_lane_tile(DT, B, SF, NVFP4_SR, NVFP4_SR, SWIGLU, g.c.rows, g.c.cols)) launch_swiglu_dual_rpl<DT, B, SF, 8>(g, u, st);
+    else launch_swiglu_dual_rpl<DT, B, SF, DT == NVFP4_F32 && SF == NVFP4_SCALE_E8M0 ? 8 : 16>(g, u, st);
 }
 
 hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, int sf, uint32_t *partials_g,
@@ -1646,12 +1675,8 @@ hipError_t launch_quantize_dual(const DualArgs &D, int dt, int rnd_r, int rnd_c,
 {
     // (SR rows with RtN columns is a combination no equation asks for: two kernels)
     if (quantize_dual_fused(dt, D.c.rows, D.c.cols, D.c.ld, block, hw_convert) && !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN)) {
-        if (dt == NVFP4_F32)
-            launch_dual_fmt<NVFP4_F32, 8>(D, rnd_r, rnd_c, block, sf, st);
-        else if (short_lane_tile(dt, D.c.rows, D.c.cols))
-            launch_dual_fmt<NVFP4_BF16, 8>(D, rnd_r, rnd_c, block, sf, st);
-        else
-            launch_dual_fmt<NVFP4_BF16, 16>(D, rnd_r, rnd_c, block, sf, st);
+        if (dt == NVFP4_F32) launch_dual_fmt<NVFP4_F32>(D, rnd_r, rnd_c, block, sf, st);
+        else launch_dual_fmt<NVFP4_BF16>(D, rnd_r, rnd_c, block, sf, st);
         return launch_status();
     }
     // other block sizes and ragged shapes: the two single-orientation kernels (they write the plain layout only)

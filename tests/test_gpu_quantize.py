@@ -332,7 +332,7 @@ def test_dual_orientation_strided_and_full_size():
             assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
 
 
-# The quantizers' lane tile is 8 rows up to 512 workgroup tiles of 128 x 256 and 16 rows beyond (bf16): a wide and a tall
+# The quantizers' lane tile of a bf16 tensor is 8 rows up to 512 workgroup tiles of 128 x 256 and 16 rows beyond: a wide and a tall
 # tensor on each side of that line, with a last tile that is nearly empty.
 @pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
 @pytest.mark.parametrize("shape", [(32, 512 * 256), (32, 512 * 256 + 32), (512 * 128, 32), (512 * 128 + 32, 32)])
@@ -347,6 +347,29 @@ def test_both_lane_tiles(shape, fmt):
         want = oracle.quantize(x, 0, rc, 6, ofmt(f))
         assert_quant_equal(cols, want, f"{shape} cols")
         assert_quant_equal(nv.quantize(xg, 0, rc, 6, f), want, f"{shape} cols alone")
+
+
+# Binary32: 16 rows between 257 and 768 and between 1025 and 1536 tiles for some formats, roundings and outputs, 8 elsewhere.  The
+# plain dual pass always takes 8, so it is what the other forms are compared with (and the oracle, on the smallest).
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4", "e4m3_64"])
+@pytest.mark.parametrize("tiles", [256, 257, 512, 513, 768, 769, 1024, 1025, 1536, 1537])
+def test_lane_tiles_of_binary32(tiles, fmt):
+    f = nv.Format(64, 0, 1) if fmt == "e4m3_64" else FORMATS[fmt]()
+    R, C = tiles * 128, 128
+    xg = torch.randn((R, C), generator=torch.Generator(device="cuda").manual_seed(tiles), device="cuda")
+    print(f"[case] binary32 lane tiles {tiles} {fmt}", flush=True)
+    for rr, rc in ((nv.RTN, nv.RTN), (nv.RTN, nv.SR), (nv.SR, nv.SR)):
+        cols = nv.quantize(xg, 0, rc, 6, f)
+        if tiles in (257, 513) and rr == rc:
+            assert_quant_equal(cols, oracle.quantize(xg.cpu(), 0, rc, 6, ofmt(f)), f"{tiles} tiles, columns")
+        if fmt == "e4m3_64":
+            continue
+        plain = nv.quantize_dual(xg, rr, 5, rc, 6, f)
+        assert torch.equal(cols[0], plain[1][0]) and torch.equal(cols[1], plain[1][1])
+        slabs = nv.quantize_dual(xg, rr, 5, rc, 6, f, slab_rows=True, slab_cols=True)
+        for side, (rows, K) in enumerate(((R, C), (C, R))):
+            assert np.array_equal(unslab(slabs[side][0], rows, K, 64), to_np(plain[side][0])), f"codes of side {side}"
+            assert np.array_equal(unslab(slabs[side][1], rows, K, 128 // f.block), to_np(plain[side][1])), f"scales of side {side}"
 
 
 def unslab(flat, rows, K, per_row):
