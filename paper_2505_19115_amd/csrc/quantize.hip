@@ -87,6 +87,8 @@ struct Chunk<NVFP4_BF16> {
     {
         raw = load16<STREAM>(reinterpret_cast<const uint16_t *>(x) + off);
     }
+    // (from any element on)
+    __device__ __forceinline__ void load_unaligned(const void *x, int64_t off) { __builtin_memcpy(&raw, reinterpret_cast<const uint16_t *>(x) + off, 16); }
     __device__ __forceinline__ void load_partial(const void *x, int64_t off, int n)
     {
         const uint16_t *p = reinterpret_cast<const uint16_t *>(x) + off;
@@ -133,6 +135,12 @@ struct Chunk<NVFP4_F32> {
         const uint4 a = load16<STREAM>(p), b = load16<STREAM>(p + 4);
         lo = make_float4(u2f(a.x), u2f(a.y), u2f(a.z), u2f(a.w));
         hi = make_float4(u2f(b.x), u2f(b.y), u2f(b.z), u2f(b.w));
+    }
+    __device__ __forceinline__ void load_unaligned(const void *x, int64_t off)
+    {
+        const float *p = reinterpret_cast<const float *>(x) + off;
+        __builtin_memcpy(&lo, p, 16);
+        __builtin_memcpy(&hi, p + 4, 16);
     }
     __device__ __forceinline__ void load_partial(const void *x, int64_t off, int n)
     {
@@ -583,23 +591,35 @@ __global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_dense_kernel(AmaxArgs
     }
     amax_store<DT>(a, T.part_out + blockIdx.x);
 }
+// The last chunk of a row that ends inside one is moved back to end with the row: a maximum may see elements twice, and every chunk
+// is one wide load then.  (Element by element, the ends kept the loads around them from being in flight together: binary32 [2432, 6980]
+// 14.6 us; rows shorter than a chunk still go that way.)
 template <int DT>
 __global__ __launch_bounds__(AMAX_DENSE_THREADS) void amax_strided_kernel(AmaxArgs T)
 {
     const int64_t total = (int64_t)T.rows * T.cpr;  // (below 2^31)
     const int64_t stride = (int64_t)T.grid * (AMAX_DENSE_THREADS * AMAX_UNROLL);
     float a = 0.0f;
+    if (T.cols < 8) {
+        for (int64_t row = (int64_t)blockIdx.x * AMAX_DENSE_THREADS + threadIdx.x; row < T.rows; row += (int64_t)T.grid * AMAX_DENSE_THREADS) {
+            Chunk<DT> v;
+            v.load_partial(T.x, row * T.ld, (int)T.cols);
+            a = fmaxf(a, chunk_amax(v));
+        }
+        amax_store<DT>(a, T.part_out + blockIdx.x);
+        return;
+    }
     for (int64_t base = (int64_t)blockIdx.x * (AMAX_DENSE_THREADS * AMAX_UNROLL) + threadIdx.x; base < total; base += stride) {
         Chunk<DT> v[AMAX_UNROLL];
 #pragma unroll
         for (int u = 0; u < AMAX_UNROLL; ++u) {
             const int64_t id = base + u * AMAX_DENSE_THREADS;
-            v[u].zero();
             if (id < total) {
                 const uint32_t row = (uint32_t)id / T.cpr, c = (uint32_t)id - row * T.cpr;
-                const int64_t off = (int64_t)row * T.ld + (int64_t)c * 8;
-                if ((int64_t)c * 8 + 8 <= T.cols) v[u].template load<false>(T.x, off);
-                else v[u].load_partial(T.x, off, (int)(T.cols & 7));
+                const int64_t col = (int64_t)c * 8 + 8 <= T.cols ? (int64_t)c * 8 : T.cols - 8;
+                v[u].load_unaligned(T.x, (int64_t)row * T.ld + col);
+            } else {
+                v[u].zero();
             }
         }
 #pragma unroll

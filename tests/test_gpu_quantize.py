@@ -396,10 +396,10 @@ def test_slab_outputs_of_both_lane_tiles(shape, dtype, fmt):
         assert np.array_equal(unslab(slabs[side][1], rows, K, 128 // f.block), to_np(plain[side][1])), f"scales of side {side}"
 
 
-# The maximum pass over a tensor with a row pitch: rows that end inside a chunk of 8, one row, more chunks than one
-# pass of the grid takes; the largest magnitude sits in the first or the very last element, the gap beside the rows holds more.
+# The maximum pass over a tensor with a row pitch: rows shorter than a chunk of 8, of one chunk, that end inside one, one row, more
+# chunks than one pass of the grid takes; the largest magnitude sits in the first or the very last element, the gap beside the rows holds more.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("shape", [(16, 1, 8), (16, 7, 16), (1, 48, 64), (48, 2051, 2056), (4112, 4100, 4112)])
+@pytest.mark.parametrize("shape", [(16, 1, 8), (16, 7, 16), (16, 8, 16), (16, 9, 16), (32, 15, 16), (1, 48, 64), (48, 2051, 2056), (4112, 4100, 4112)])
 def test_maximum_of_a_strided_tensor(shape, dtype):
     rows, cols, ld = shape
     axis = 1 if rows == 1 else 0
