@@ -93,8 +93,8 @@ def test_random_codes_and_scales(shape):
 @pytest.mark.parametrize("shape", [(2900, 3000, 256), (2560, 3330, 512), (4100, 8200, 256), (3000, 2900, 384)],
                          ids=["144 ragged tiles, 2 K tiles", "140 tiles, 4 K tiles", "561 tiles", "3 K tiles"])
 def test_large_tile_kernel_ragged_edges(shape):
-    # >= 128 tiles of 256 x 256 select the 8-wave kernel: edge tiles (clamped rows, element-wise stores),
-    # even and odd numbers of K tiles, more tiles than CUs
+    # 128 and more tiles of 256 x 256: the eight-wave kernel (its 192-row tile, 128 x 128 tiles for 4100 x 8200 x 256; which tile each
+    # size takes is in test_gpu_gemm_tiles.py): edge tiles (clamped rows, cut pieces), even and odd numbers of K tiles, more tiles than CUs
     M, N, K = shape
     rng = np.random.default_rng(M + N + K)
     A, B = random_operand(rng, M, K, lo=0x30, hi=0x48, g=0.5), random_operand(rng, N, K, lo=0x30, hi=0x48, g=0.25)
@@ -468,7 +468,7 @@ def mx_operand(rng, rows, K, lo=112, hi=142):
 
 @pytest.mark.parametrize("shape", [(256, 256, 256), (200, 136, 512), (1, 1, 32), (130, 257, 96), (384, 512, 1024),
                                    (300, 520, 1280), (64, 64, 160),
-                                   # K a multiple of 128: the four-stage direct-to-LDS kernel with 1, 2, 3, 4, 5 K tiles
+                                   # K a multiple of 128: 1, 2, 3, 4, 5 K tiles
                                    (256, 512, 128), (1, 1, 128), (257, 300, 256), (130, 257, 384), (512, 256, 512),
                                    (260, 252, 640)])
 def test_mxfp4_random_codes_and_scales(shape):
@@ -641,7 +641,7 @@ def test_large_tile_bf16_output_with_padded_rows(pad):
     M, N, K = 2816, 3072, 256
     rng = np.random.default_rng(77 + pad)
     A, B = random_operand(rng, M, K, lo=0x30, hi=0x48, g=0.5), random_operand(rng, N, K, lo=0x30, hi=0x48, g=0.25)
-    for fmt, a, b in ((nv.NVFP4, A, B), (nv.MXFP4, mx_operand(rng, M, 512), mx_operand(rng, N, 512))):  # (K = 512: the direct-to-LDS MXFP4 kernel)
+    for fmt, a, b in ((nv.NVFP4, A, B), (nv.MXFP4, mx_operand(rng, M, 512), mx_operand(rng, N, 512))):
         print(f"[case] padded bf16 output pad={pad} fmt={fmt}", flush=True)
         buf = torch.full((M, N + pad), -3.0, dtype=torch.bfloat16, device="cuda")
         nv.gemm(dev(a), dev(b), fmt, out=buf[:, :N])

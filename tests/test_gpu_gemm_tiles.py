@@ -1,6 +1,8 @@
 """The GEMM at the sizes where its tiles can go wrong: every workgroup tile the size rule chooses from, with whole and ragged
 contractions (one K tile, less than one, one more than the waves that share it), rows and columns past the edge, one-row and
 one-column outputs.  Against the fp64 oracle, completely where it is cheap, on sampled outputs otherwise."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -59,21 +61,30 @@ def test_small_products(shape, fmt_name):
     close(got, oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"{fmt_name} {shape}", out_dtype)
 
 
-# (the tile each shape gets from the size rule, E4M3 / E8M0, is in its id)
+# The tile each shape gets from the size rule, E4M3 and E8M0 scales: asserted, so that a change of the rule moves no test in silence.
+# Between them: every tile of both kinds, each with whole K tiles and with a K tail, rows and columns past the edge.
+SAMPLED = [((71, 4160, 32), (32, 64), (32, 64)), ((65, 4171, 1152), (32, 64), (32, 64)),
+           ((65, 3036, 32), (64, 32), (64, 32)), ((300, 1100, 544), (64, 32), (64, 32)), ((100, 3000, 1024), (64, 32), (64, 32)),
+           ((171, 2818, 32), (64, 64), (64, 64)), ((1200, 905, 640), (32, 32), (128, 128)), ((241, 268, 32), (32, 32), (32, 32)),
+           ((257, 3401, 160), (128, 128), (128, 128)), ((2081, 1100, 256), (128, 128), (128, 128)),
+           ((3666, 1043, 1696), (64, 64), (128, 128)), ((3596, 1033, 1792), (64, 64), (128, 128)),
+           ((8195, 1802, 160), None, (256, 128)), ((7171, 2050, 256), None, (256, 128)),
+           ((2721, 1418, 128), (128, 256), (128, 128)), ((1618, 3033, 160), (128, 256), (128, 128)),
+           ((2505, 3212, 256), (192, 256), (128, 128)), ((2373, 3777, 160), (192, 256), (128, 128)),
+           ((2841, 4235, 160), (192, 256), (256, 256)),
+           # 256 x 256; in E8M0 the direct-to-LDS kernel takes K = 640 and 1024, the tile kernel the others
+           ((2720, 4358, 32), (256, 256), (256, 256)), ((3900, 4080, 160), (256, 256), (256, 256)), ((2709, 4364, 128), (256, 256), (256, 256)),
+           ((4030, 4050, 384), (256, 256), (256, 256)), ((3900, 4090, 640), (256, 256), (256, 256)), ((3900, 4080, 1024), (256, 256), (256, 256))]
+
+
 @pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4", "e4m3_32"])
-@pytest.mark.parametrize("shape", [pytest.param((71, 4160, 32), id="32x64"), pytest.param((65, 4171, 1152), id="32x64-1152"),
-                                   pytest.param((65, 3036, 32), id="64x32"), pytest.param((300, 1100, 544), id="64x32-544"),
-                                   pytest.param((171, 2818, 32), id="64x64"), pytest.param((1200, 905, 640), id="64x64-or-128"),
-                                   pytest.param((257, 3401, 160), id="128-tail"), pytest.param((2081, 1100, 256), id="128"),
-                                   pytest.param((3666, 1043, 1696), id="128-or-256x128-tail"), pytest.param((3596, 1033, 1792), id="128-or-256x128"),
-                                   pytest.param((2720, 4358, 32), id="256-tail"), pytest.param((2841, 4235, 160), id="128-or-256-tail"),
-                                   pytest.param((2709, 4364, 128), id="256"),
-                                   pytest.param((2721, 1418, 128), id="128x256-or-any"), pytest.param((1618, 3033, 160), id="128x256-tail-or-any"),
-                                   pytest.param((2505, 3212, 256), id="192x256-or-any"), pytest.param((2373, 3777, 160), id="192x256-tail-or-any")])
-def test_every_tile_sampled(shape, fmt_name):
+@pytest.mark.parametrize("shape,e4m3_tile,e8m0_tile", SAMPLED, ids=["x".join(map(str, c[0])) for c in SAMPLED])
+def test_every_tile_sampled(shape, e4m3_tile, e8m0_tile, fmt_name):
     block, scale = FORMATS[fmt_name]
     M, N, K = shape
     fmt = nv.Format(block, scale, 1 - scale)
+    want = e8m0_tile if scale else e4m3_tile
+    assert want is None or nv.gemm_tile(M, N, K, fmt) == want
     out_dtype = torch.float32 if K % 256 else torch.bfloat16
     rng = np.random.default_rng(M + 7 * N + K)
     A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
@@ -139,6 +150,39 @@ def test_both_gradients_in_one_launch(shape, fmt_name):
     assert torch.equal(dW, nv.gemm(nv.quantize(dY, 0, nv.SR, 4, fmt), nv.quantize(X, 0, nv.SR, 5, fmt), fmt))
 
 
+# The large kernels' outputs with every kind of row: 16-byte aligned ones with a gap (ldc), ones that start at multiples of 8 bytes
+# (bf16, ldc = 4 mod 8) and of one element, at the edges of the output and inside.
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("shape,e4m3_tile,e8m0_tile", [((3900, 4090, 640), (256, 256), (256, 256)), ((4030, 4050, 384), (256, 256), (256, 256)),
+                                                       ((2505, 3212, 256), (192, 256), (128, 128)), ((2081, 1100, 256), (128, 128), (128, 128))])
+def test_large_tiles_in_windows_of_wider_outputs(shape, e4m3_tile, e8m0_tile, fmt_name, out_dtype):
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    M, N, K = shape
+    assert nv.gemm_tile(M, N, K, fmt) == (e8m0_tile if scale else e4m3_tile)
+    rng = np.random.default_rng(M)
+    A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
+    dev = lambda o: (torch.from_numpy(o[0]).cuda(), torch.from_numpy(o[1]).cuda(), torch.tensor([o[2]], dtype=torch.float32, device="cuda"))
+    a, b = dev(A), dev(B)
+    ii, jj = rng.integers(0, M, 3000), rng.integers(0, N, 3000)
+    ii[:1500], jj[1000:2500] = rng.integers(M - 260, M, 1500), rng.integers(N - 260, N, 1500)
+    of = ofmt(fmt)
+    ref, ref_abs = oracle.gemm_nt_sample(A, B, ii, jj, of), oracle.gemm_nt_sample(A, B, ii, jj, of, take_abs=True)
+    first = None
+    for ld in (-(-N // 8) * 8 + 8, -(-N // 8) * 8 + 4, (N | 1) + 2):
+        print(f"[case] gemm windows {fmt_name} {M}x{N}x{K} ldc={ld} {out_dtype}", flush=True)
+        out = torch.full((M, ld), -1.0, device="cuda", dtype=out_dtype)
+        nv.gemm(a, b, fmt, out=out[:, :N])
+        torch.cuda.synchronize()
+        got = out[:, :N].float()
+        assert bool((out[:, N:] == -1.0).all()), "columns outside the window were written"
+        if first is None:
+            first = got
+            close(to_np(got)[ii, jj], ref, ref_abs, f"ldc {ld}", out_dtype)
+        assert torch.equal(got, first)
+
+
 # MXFP4 contractions shorter than one K tile, on the large tiles
 @pytest.mark.parametrize("K", [32, 64, 96])
 @pytest.mark.parametrize("shape,tile", [((2052, 1990), (128, 128)), ((2720, 4358), (256, 256))])
@@ -151,3 +195,38 @@ def test_mxfp4_short_contractions(shape, tile, K):
     got = run(A, B, nv.MXFP4, torch.float32)
     of = ofmt(nv.MXFP4)
     close(got, oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"K {K}", torch.float32)
+
+
+# Operands in slabs on tiles other than the 256 x 256 they were made for: the same bits as row-major operands.
+@pytest.mark.parametrize("fmt_name,shape,tile", [("nvfp4", (16, 32768, 1024), (32, 32)), ("nvfp4", (50, 32800, 1024), (64, 64)),
+                                                 ("mxfp4", (40, 2080, 1024), (32, 32)), ("mxfp4", (70, 4100, 1024), (32, 64)),
+                                                 ("mxfp4", (100, 3000, 1024), (64, 32)), ("mxfp4", (33, 8200, 512), (64, 64)),
+                                                 ("mxfp4", (2048, 4096, 1024), (128, 128)), ("mxfp4", (7171, 2050, 512), (256, 128)),
+                                                 ("mxfp4", (3900, 4080, 640), (256, 256))])
+def test_slab_operands_on_every_tile(fmt_name, shape, tile):
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    M, N, K = shape
+    assert nv.gemm_tile(M, N, K, fmt) == tile
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    # (rows padded to whole blocks for the quantizer; the product takes the first M and N of them)
+    X, W = (torch.randn((-(-n // block) * block, K), generator=g, device="cuda") for n in (M, N))
+    ops = [(nv.quantize_dual(t, fmt=fmt)[0], nv.quantize_dual(t, fmt=fmt, slab_rows=True)[0]) for t in (X, W)]
+    print(f"[case] slabs {fmt_name} {M}x{N}x{K}", flush=True)
+    plain = nv.gemm(ops[0][0], ops[1][0], fmt, shape=shape)
+    for slabs in ((True, False), (False, True), (True, True)):
+        assert torch.equal(nv.gemm(ops[0][slabs[0]], ops[1][slabs[1]], fmt, slabs=slabs, shape=shape), plain), slabs
+
+
+def test_packed_weights_of_a_wide_projection():
+    # 16 tokens against a vocabulary-sized weight: its packed operand is in slabs (128 output tiles of 256 x 256), the product runs on
+    # a tile whose waves divide the contraction
+    M, N, K = 16, 32768, 512
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X, W = (torch.randn((n, K), generator=g, device="cuda").to(torch.bfloat16) for n in (M, N))
+    assert nv.gemm_tile(M, N, K)[0] <= 64 and nv.lib.nvfp4_gemm_takes_slabs(M, N, K, ctypes.byref(nv.NVFP4.c()))
+    Y = nv.linear_fwd(X, None, w_operands=nv.quantize_weight(W, M), N=N)
+    assert torch.equal(Y, nv.linear_fwd(X, W))
+    assert torch.equal(Y, nv.gemm(nv.quantize(X), nv.quantize(W)))
