@@ -25,8 +25,6 @@ namespace nvfp4 {
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float float2v_t __attribute__((ext_vector_type(2)));
 
 constexpr int KT = 128;      // contraction elements per LDS tile
 constexpr int KTB = KT / 2;  // bytes of codes per row per tile
@@ -52,13 +50,6 @@ __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
     r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
     r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
     return r;
-}
-
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f)
-{
-    uint32_t u = f2u(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
 }
 
 // Tile geometry.  A workgroup is WM x WN waves; a wave owns (32 TA) x (32 TB) outputs as
@@ -522,13 +513,9 @@ bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf)
 
 hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st)
 {
-    if (gemm_pairs(P0, P1, sf)) {
-        hipError_t e = check_gemm(P0, block, sf);
-        if (e == hipSuccess) e = check_gemm(P1, block, sf);
-        return e != hipSuccess ? e : launch_gemm_ksplit(P0, &P1, choose_gemm_tile(P0.M, P0.N, P0.K, sf), block, sf, out_dt, st);
-    }
-    const hipError_t e = launch_gemm(P0, block, sf, out_dt, st);
-    return e != hipSuccess ? e : launch_gemm(P1, block, sf, out_dt, st);
+    hipError_t e = check_gemm(P0, block, sf);
+    if (e == hipSuccess) e = check_gemm(P1, block, sf);
+    return e != hipSuccess ? e : launch_gemm_ksplit(P0, &P1, choose_gemm_tile(P0.M, P0.N, P0.K, sf), block, sf, out_dt, st);
 }
 
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)

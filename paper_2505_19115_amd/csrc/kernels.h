@@ -149,7 +149,7 @@ hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, i
 // The same elementwise step with dG and dU stored as tensors of dt (n a multiple of 8).
 hipError_t launch_swiglu_bwd(const void *dH, const void *G, const void *U, int dt, int64_t n, void *dG, void *dU, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st);
-// Two independent products: one launch where gemm_pairs() holds (both small, the same tile), else two.
+// Two independent products in one launch, where gemm_pairs() holds (both small, the same tile).
 bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf);
 hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st);
 // Workgroup tiles (rows x columns of the output) of the GEMM kernels: up to 64 x 64 in gemm_ksplit.hip (the waves of a
