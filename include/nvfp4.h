@@ -152,9 +152,9 @@ nvfp4_status nvfp4_quantize(const void *x, nvfp4_dtype dt, int64_t rows, int64_t
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as
  * nvfp4_quantize without `workspace`: the scratch (header + per-workgroup partial maxima of the tensor-maximum
  * pass) is a 65792-byte array inside the library's device image, one per GPU, held until the process ends.  The
- * call allocates nothing.  Limit: any dense tensor (ld == cols) fits; a strided one needs one partial maximum per
- * 8192-element span of a row and at most 16384 of them (e.g. 16384 rows of up to 8192 columns) -- beyond that the
- * call returns NVFP4_EWORKSPACE and enqueues nothing.  With NVFP4_PRESET_TSCALE or a format without tensor scale
+ * call allocates nothing.  Limit: any dense tensor (ld == cols) is accepted; a strided one with at most 16384
+ * 8192-element spans of rows (e.g. 16384 rows of up to 8192 columns) -- beyond that the call returns
+ * NVFP4_EWORKSPACE and enqueues nothing.  With NVFP4_PRESET_TSCALE or a format without tensor scale
  * the array is not touched.  Every call on a GPU shares that GPU's array: calls whose kernels may overlap on one
  * GPU (different streams, or threads) race on it and must be ordered by the caller; calls on one stream are safe.
  * Nothing in the array has to start at zero (every partial maximum is written before it is read).

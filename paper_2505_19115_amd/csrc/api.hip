@@ -282,8 +282,9 @@ nvfp4_status static_scratch(void **out)
     return NVFP4_OK;
 }
 
-// Scratch bytes nvfp4_quantize really touches for this tensor: a dense tensor leaves at most AMAX_DENSE_PARTIALS
-// partial maxima, a strided one one per 8192-element span of a row.
+// Scratch bytes that nvfp4_quantize_static asks for: AMAX_DENSE_PARTIALS partial maxima of a dense tensor, one per 8192-element span
+// of a row of a strided one.  (Strided tensors leave AMAX_DENSE_PARTIALS too, up to the size of tensor_amax_partials_only(); the
+// documented limit of that entry is kept.)
 size_t quantize_scratch_need(int64_t rows, int64_t cols, int64_t ld)
 {
     if (rows <= 0 || cols <= 0 || ld == cols) return WS_HEADER + PARTIAL_SLOT;

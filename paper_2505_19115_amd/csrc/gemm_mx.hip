@@ -821,8 +821,8 @@ hipError_t launch_gemm_fp4_rescale(const GemmArgs &P, int block, int out_dt, hip
     return hipGetLastError();
 }
 
-// The shapes the direct-to-LDS kernel serves (given 16-byte aligned codes and 4-byte aligned scales); it is also the
-// kernel that can read the codes of an operand from slabs.
+// The contractions whose operands come as slabs: those that the four-stage direct-to-LDS kernel, which they were made for, can walk
+// (with 16-byte aligned codes and 4-byte aligned scales).  The other tiles read them too.
 bool mxfp4_gemm_takes_slabs(int64_t K)
 {
     // lane offsets of the direct-to-LDS loads are 32-bit and relative to the tile's first row

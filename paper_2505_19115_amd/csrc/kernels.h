@@ -88,8 +88,8 @@ struct GemmArgs {
     int64_t ldc;
     int a_slab = 0, b_slab = 0;  // operand stored in the slab layout (only where gemm_takes_slabs() holds)
 };
-// True when launch_gemm() runs the 256 x 256 direct-to-LDS kernel for this problem, the one that can read operands
-// in the slab layout.
+// True for the products whose operands the dual quantizer hands over as slabs (and nvfp4_gemm_slab() accepts): NVFP4 with at least
+// 128 output tiles of 256 x 256, MXFP4 with K >= 512, K a multiple of 128 in both.  Every tile of the GEMM kernels reads slabs.
 bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf);
 
 // Tensor maximum: one partial per workgroup into `partials` (tensor_amax_partials() entries),
@@ -165,7 +165,7 @@ hipError_t launch_gemm_fp4_rescale(const GemmArgs &P, int block, int out_dt, hip
 // Which of the two exact routes launch_gemm() takes for those formats: 0 = expanded to fp16 (the NVFP4 kernel), 1 = this one
 void set_fp4_rescale_route(int on);
 int fp4_rescale_route();
-bool mxfp4_gemm_takes_slabs(int64_t K);  // MXFP4: the codes of an operand may come as slabs (its scales stay row-major)
+bool mxfp4_gemm_takes_slabs(int64_t K);  // the MXFP4 part of gemm_takes_slabs()
 // Noise statistics: per-workgroup partial pairs (quant_noise_partials() of them), folded into sums[2].
 int64_t quant_noise_partials(int64_t rows, int64_t cols, int axis);
 hipError_t launch_quant_noise(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld, int axis, int block, int sf,
