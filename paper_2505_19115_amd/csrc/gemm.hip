@@ -52,12 +52,63 @@ __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
     return r;
 }
 
-// Tile geometry.  A workgroup is WM x WN waves; a wave owns (32 TA) x (32 TB) outputs as
+// Sums of two halves of a workgroup (SIDE waves each, wave `w` of one facing wave `w` of the other) over the same N x TB tiles:
+// the lower half keeps the first (N + 1) / 2 tile rows, the upper half the rest, each sends the other what it does not keep
+// through the LDS (64 lanes x float4 per accumulator quarter: 1 KB, no bank conflicts).
+template <int N, int TB, int SIDE>
+__device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float16_t (&kept)[(N + 1) / 2][TB], uint8_t *lds, bool upper, int w,
+                                            int lane)
+{
+    constexpr int LO = (N + 1) / 2, HI = N - LO, ROW = TB * 4096;
+    uint8_t *const from_lower = lds + w * (HI * ROW) + lane * 16, *const from_upper = lds + SIDE * (HI * ROW) + w * (LO * ROW) + lane * 16;
+    const uint8_t *const theirs = upper ? from_lower : from_upper;
+    uint8_t *const ours = upper ? from_upper : from_lower;
+    // (what goes and what stays is chosen by value: a choice between array elements would put the accumulators into memory)
+#pragma unroll
+    for (int a = 0; a < LO; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+            if (a < HI || upper) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = acc[a][b][4 * q + e], hi = a < HI ? acc[LO + a < N ? LO + a : 0][b][4 * q + e] : 0.0f;
+                        y[e] = upper ? lo : hi;
+                        kept[a][b][4 * q + e] = upper ? hi : lo;
+                    }
+                    *reinterpret_cast<float4 *>(ours + (a * TB + b) * 4096 + 1024 * q) = make_float4(y[0], y[1], y[2], y[3]);
+                }
+            } else {
+                kept[a][b] = acc[a][b];
+            }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < LO; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+            if (a < HI || !upper) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 o = *reinterpret_cast<const float4 *>(theirs + (a * TB + b) * 4096 + 1024 * q);
+                    kept[a][b][4 * q] += o.x; kept[a][b][4 * q + 1] += o.y; kept[a][b][4 * q + 2] += o.z; kept[a][b][4 * q + 3] += o.w;
+                }
+            }
+    __syncthreads();
+}
+
+// Tile geometry.  A workgroup is KG groups of WM x WN waves; a wave owns (32 TA) x (32 TB) outputs as
 // TA x TB MFMA tiles.  The production shape is 2 x 4 waves of 4 x 2 tiles: 256 x 256 per
 // workgroup, 128 accumulator registers per wave, so TWO waves fit on every SIMD.  That is
 // the point of the shape: measured on gfx950, one wave alone issues a VALU instruction only
 // every ~8 cycles, two waves per SIMD reach the full rate of one per 4 cycles, and the
 // operand expansion costs 8 (TA + TB) / (TA TB) = 6 VALU instructions per 32-cycle MFMA.
+// KG = 4 serves products with fewer 128 x 128 tiles than CUs, where one workgroup of four waves leaves each SIMD a single wave:
+// four groups of 1 x 2 waves multiply every fourth K tile each, with their own stages and the large tile's wave shape, and add
+// their sums through the LDS at the end.  1056 x 2080 x 2784: 128 x 128 26.2 us, 96 x 128 with four groups 21.7; 256 x 11008 x 4096:
+// 30.7 -> 28.8; 1536 x 1536 x 6144: 45.0 -> 34.3.  (Two groups of 1 x 4 waves on 128 x 256 were no faster than eight waves of 64 x 64:
+// 4096 x 4096 x 11008 315 and 312 us; a chip filled either way is bound by its power, not by the expansion.)
 //
 // Per 128-wide K tile the 64 code bytes of each operand row sit in LDS as four 16-byte chunks
 // and its 8 block scales as fp16 values (scale * 2^-8; for blocks wider than 16 the value is
@@ -65,10 +116,10 @@ __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
 // 32 codes = two 16-element blocks; dword t (0..3) of the chunk feeds one MFMA step and
 // belongs to block t / 2.  A and B use the same assignment of contraction indices to (lane
 // half, step), which is all the instruction requires.
-template <int B, int WM, int WN, int TA, int TB, int OUT_DT, bool KTAIL>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
+template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL>
+__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmArgs P)
 {
-    constexpr int NT = 64 * WM * WN;
+    constexpr int NT = 64 * WM * WN;  // threads of a group
     constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
     constexpr int SPT = KT / B;  // scale bytes per row per tile in global memory
     constexpr int VALU_PER_MFMA = (8 * (TA + TB) + TA * TB - 1) / (TA * TB);
@@ -80,8 +131,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     constexpr bool EVEN = BM / 16 % NW == 0 && BN / 16 % NW == 0;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = KG == 1 ? 0 : wave_wg / NW, wave = wave_wg - group * NW, tid = wave * 64 + lane;  // (inside the group from here on)
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 31, h = lane >> 5;
     const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
@@ -113,7 +165,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     // 539 us, with the direct loads 190.)
     constexpr int NSR = (BM + BN + NT - 1) / NT;  // scale rows per thread
     uint64_t gs[NSR];
-    constexpr bool SPAN = BM == 192;  // A's rows may lie in two slabs
+    constexpr bool SPAN = 256 % BM != 0;  // A's rows may lie in two slabs
     auto piece = [&](int u) { return !EVEN ? u * NW + wave : u < CA ? wave * CA + u : BM / 16 + wave * CB + u - CA; };
     uint32_t off[CI];  // byte offset of this thread's chunks inside a K tile column
     const int ch = (lane & 3) ^ ((lane >> 4) & 3);
@@ -124,14 +176,15 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         const int row = isA ? trow : trow - BM;
         const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
         const int64_t lr = base + row < rows ? row : rows - 1 - base;  // row inside the tile, clamped
-        // a slab holds all 256 rows of a 256- or 128-row tile: nothing to clamp; a 192-row tile may reach into the next one
+        // a slab holds all rows of a 256- or 128-row tile: nothing to clamp; one of 160 or 192 rows may reach into the next slab
         const int srow = (int)(base & 255) + (int)(SPAN && isA ? lr : row);
         const uint32_t slab_off = (uint32_t)(slab_row(SPAN && isA ? srow & 255 : srow) * 64 + ch * 16) +
                                   (SPAN && isA && srow > 255 ? (uint32_t)nkt * (uint32_t)SLAB_CODE_BYTES : 0u);
         off[u] = (isA ? P.a_slab : P.b_slab) ? slab_off : (uint32_t)(lr * Kb + ch * 16);  // (relative to the tile's first row: 32 bits suffice)
     }
     typedef __attribute__((address_space(3))) void *lds_ptr_t;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+    uint8_t *const stages = lds + group * (2 * STAGE);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)stages;
     // wave-uniform 64-bit value -> scalar registers
     auto uniform_ptr = [](const uint8_t *p) -> const uint8_t * {
         const uint64_t v = reinterpret_cast<uint64_t>(p);
@@ -172,8 +225,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     const uint8_t *baseB = P.b_slab ? P.B_codes + (n0 >> 8) * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
     const int64_t stepA = P.a_slab ? SLAB_CODE_BYTES : KTB, stepB = P.b_slab ? SLAB_CODE_BYTES : KTB;
     const int rem = KTAIL ? (int)(P.K - (int64_t)(nkt - 1) * KT) : KT;  // elements of the last K tile
-    // tile kt: codes -> LDS stage `stage` (direct); scale bytes -> registers
-    auto fetch = [&](int kt, int stage) {
+    // the group's step j (K tile j KG + group): codes -> LDS stage `stage` (direct); scale bytes -> registers.  A K tile past the
+    // last one is the last one again with zero scales: every group takes the same steps and meets the same barriers.
+    const int steps = (nkt + KG - 1) / KG;
+    auto fetch = [&](int j, int stage) {
+        const int kj = j * KG + group;
+        const bool absent = KG > 1 && kj >= nkt;
+        const int kt = absent ? nkt - 1 : kj;
         const uint8_t *ua = uniform_ptr(baseA + kt * stepA), *ub = uniform_ptr(baseB + kt * stepB);
         const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + stage * STAGE);
         const bool tail = KTAIL && kt == nkt - 1;
@@ -187,7 +245,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
         for (int u = 0; u < NSR; ++u) {
             if (!srow_on[u]) continue;
             const uint8_t *sp = srow_ptr[u] + (int64_t)kt * srow_step[u];
-            if (tail) {
+            if (absent) {
+                gs[u] = 0;
+            } else if (tail) {
                 uint64_t sv = 0;  // zero scales past K
 #pragma unroll
                 for (int t = 0; t < SPT; ++t)
@@ -211,7 +271,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     // because fp16's bias is E4M3's plus 8) of the chunk's two 16-element blocks; a wave reads
     // 32 consecutive rows of one chunk.  For blocks wider than 16 the value is repeated.
     auto stash = [&](int stage) {
-        uint8_t *base = lds + stage * STAGE;
+        uint8_t *base = stages + stage * STAGE;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's direct-to-LDS loads have landed
         uint32_t *sS = reinterpret_cast<uint32_t *>(base + A_BYTES + B_BYTES);
 #pragma unroll
@@ -243,7 +303,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     for (int p = 0; p < 2; ++p) coff[p] = swz(r, 2 * p + h);
     const int soff = (h * (BM + BN) + r) * 4;
     auto load_codes = [&](int stage, int p, Codes &Q) {
-        const uint8_t *sA = lds + stage * STAGE + coff[p], *sB = sA + A_BYTES;
+        const uint8_t *sA = stages + stage * STAGE + coff[p], *sB = sA + A_BYTES;
 #pragma unroll
         for (int a = 0; a < TA; ++a)
             Q.ca[a] = *reinterpret_cast<const uint4 *>(sA + (wm * 32 * TA + 32 * a) * KTB);
@@ -252,7 +312,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
             Q.cb[b] = *reinterpret_cast<const uint4 *>(sB + (wn * 32 * TB + 32 * b) * KTB);
     };
     auto load_scales = [&](int stage, int p, Scales &S) {
-        const uint8_t *sS = lds + stage * STAGE + A_BYTES + B_BYTES + soff + 2 * p * (BM + BN) * 4;
+        const uint8_t *sS = stages + stage * STAGE + A_BYTES + B_BYTES + soff + 2 * p * (BM + BN) * 4;
 #pragma unroll
         for (int a = 0; a < TA; ++a) S.sa[a] = *reinterpret_cast<const uint32_t *>(sS + (wm * 32 * TA + 32 * a) * 4);
 #pragma unroll
@@ -337,11 +397,11 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
     }
     // two tiles per trip so that the LDS stage (and with it every LDS offset) is a constant
     int kt = 0;
-    for (; kt + 2 < nkt; kt += 2) {
+    for (; kt + 2 < steps; kt += 2) {
         NVFP4_TILE(0, kt)
         NVFP4_TILE(1, kt + 1)
     }
-    if (kt + 1 < nkt) {
+    if (kt + 1 < steps) {
         NVFP4_TILE(0, kt)
         ++kt;
     }
@@ -365,28 +425,58 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_nt_f16_kernel(GemmArgs P)
 
     // epilogue.  The MFMA's first operand is the B (N-side) fragment, so a lane holds four consecutive columns of one row.
     __syncthreads();  // every wave has read the last K tile: the stages may be overwritten
-    constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 32 * TA, n0 + wn * 32 * TB, lds + wave * PIECE, lane);
+    const int64_t row0 = m0 + wm * 32 * TA, col0 = n0 + wn * 32 * TB;
+    uint8_t *const mine = lds + wave_wg * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2));
+    if constexpr (KG == 1) {
+        store_lines<OUT_DT, TA, TB>(P, acc, row0, col0, mine, lane);
+    } else {
+        // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the tile rows
+        constexpr int LO = (TA + 1) / 2, HI = TA - LO;
+        float16_t half[LO][TB];
+        if constexpr (KG == 2) {
+            fold_groups<TA, TB, NW>(acc, half, lds, group != 0, wave, lane);
+            if (LO == HI || group == 0) {
+                store_lines<OUT_DT, LO, TB>(P, half, row0 + group * 32 * LO, col0, mine, lane);
+            } else {
+                float16_t rest[HI][TB];
+#pragma unroll
+                for (int a = 0; a < HI; ++a)
+#pragma unroll
+                    for (int b = 0; b < TB; ++b) rest[a][b] = half[a][b];
+                store_lines<OUT_DT, HI, TB>(P, rest, row0 + 32 * LO, col0, mine, lane);
+            }
+        } else {
+            static_assert(KG == 4 && LO == 2, "four groups, three or four tile rows");
+            float16_t last[1][TB];
+            fold_groups<TA, TB, 2 * NW>(acc, half, lds, group >= 2, (group & 1) * NW + wave, lane);
+            fold_groups<LO, TB, 2 * NW>(half, last, lds, group & 1, (group >> 1) * NW + wave, lane);
+            // (of three tile rows the last group gets none)
+            const int row = (group >> 1) * LO + (group & 1);
+            if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, 1, TB>(P, last, row0 + row * 32, col0, mine, lane);
+        }
+    }
 }
 
-template <int B, int WM, int WN, int TA, int TB, bool KTAIL>
+template <int B, int WM, int WN, int TA, int TB, int KG, bool KTAIL>
 static void launch_f16(const GemmArgs &P, int out_dt, hipStream_t st)
 {
-    constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
-    // two stages, or the epilogue's pieces (one per wave, 32 rows of fp32)
-    constexpr int STAGES = 2 * ((BM + BN) * KTB + (BM + BN) * SROW), PIECES = WM * WN * 32 * 32 * TB * 4;
-    constexpr int LDS_BYTES = STAGES > PIECES ? STAGES : PIECES;
+    constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN, NT = 64 * WM * WN * KG;
+    // two stages per group, what a fold of the groups exchanges, or the epilogue's pieces (one per wave, 32 rows of fp32)
+    constexpr int STAGES = KG * 2 * ((BM + BN) * KTB + (BM + BN) * SROW), PIECES = NT / 64 * 32 * 32 * TB * 4;
+    constexpr int FOLD = KG == 1 ? 0 : KG / 2 * BM * BN * 4;
+    constexpr int LDS_BYTES = STAGES > PIECES ? (STAGES > FOLD ? STAGES : FOLD) : (PIECES > FOLD ? PIECES : FOLD);
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
     const unsigned ntiles = (unsigned)(((P.N + BN - 1) / BN) * ((P.M + BM - 1) / BM));
     if (out_dt == NVFP4_F32) {
-        auto k = gemm_nt_f16_kernel<B, WM, WN, TA, TB, NVFP4_F32, KTAIL>;
+        auto k = gemm_nt_f16_kernel<B, WM, WN, TA, TB, KG, NVFP4_F32, KTAIL>;
         static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES), true);
         (void)once;
-        hipLaunchKernelGGL(k, dim3(ntiles), dim3(64 * WM * WN), LDS_BYTES, st, P);
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(NT), LDS_BYTES, st, P);
     } else {
-        auto k = gemm_nt_f16_kernel<B, WM, WN, TA, TB, NVFP4_BF16, KTAIL>;
+        auto k = gemm_nt_f16_kernel<B, WM, WN, TA, TB, KG, NVFP4_BF16, KTAIL>;
         static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES), true);
         (void)once;
-        hipLaunchKernelGGL(k, dim3(ntiles), dim3(64 * WM * WN), LDS_BYTES, st, P);
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(NT), LDS_BYTES, st, P);
     }
 }
 
@@ -408,40 +498,45 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 {
     const bool ktail = (P.K % KT) != 0;
     if (tile == TILE_256x256) {
-        if (ktail) launch_f16<B, 2, 4, 4, 2, true>(P, out_dt, st);
-        else launch_f16<B, 2, 4, 4, 2, false>(P, out_dt, st);
+        if (ktail) launch_f16<B, 2, 4, 4, 2, 1, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 4, 2, 1, false>(P, out_dt, st);
     } else if (tile == TILE_192x256) {
-        if (ktail) launch_f16<B, 2, 4, 3, 2, true>(P, out_dt, st);
-        else launch_f16<B, 2, 4, 3, 2, false>(P, out_dt, st);
+        if (ktail) launch_f16<B, 2, 4, 3, 2, 1, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 3, 2, 1, false>(P, out_dt, st);
     } else if (tile == TILE_128x256) {
-        if (ktail) launch_f16<B, 2, 4, 2, 2, true>(P, out_dt, st);
-        else launch_f16<B, 2, 4, 2, 2, false>(P, out_dt, st);
+        if (ktail) launch_f16<B, 2, 4, 2, 2, 1, true>(P, out_dt, st);
+        else launch_f16<B, 2, 4, 2, 2, 1, false>(P, out_dt, st);
+    } else if (tile == TILE_128x128_K4) {
+        if (ktail) launch_f16<B, 1, 2, 4, 2, 4, true>(P, out_dt, st);
+        else launch_f16<B, 1, 2, 4, 2, 4, false>(P, out_dt, st);
+    } else if (tile == TILE_96x128_K4) {
+        if (ktail) launch_f16<B, 1, 2, 3, 2, 4, true>(P, out_dt, st);
+        else launch_f16<B, 1, 2, 3, 2, 4, false>(P, out_dt, st);
     } else {
-        if (ktail) launch_f16<B, 2, 2, 2, 2, true>(P, out_dt, st);
-        else launch_f16<B, 2, 2, 2, 2, false>(P, out_dt, st);
+        if (ktail) launch_f16<B, 2, 2, 2, 2, 1, true>(P, out_dt, st);
+        else launch_f16<B, 2, 2, 2, 2, 1, false>(P, out_dt, st);
     }
 }
 
 // Which workgroup tile computes an M x N x K product: the one whose estimated time is least.  With R = the tiles of the
-// busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves up to 64 x 64),
+// busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves or groups of waves),
 //     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
 // Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
 // expansion, LDS reads).  The constants (nanoseconds) are fitted to every tile timed on 245 shapes from 9 x 162 x 768 to 11008 x 4096 x
-// 4096, row-major and in slabs, both output types (profiles/gemm_tiles.txt); the choice is then 1.0 / 1.2 % (E4M3, bf16 / f32 outputs)
+// 4096, row-major and in slabs, both output types (profiles/gemm_tiles.txt); the choice is then 0.7 / 1.1 % (E4M3, bf16 / f32 outputs)
 // and 1.5 / 1.6 % (E8M0) slower than the best tile on average.  E4M3, bf16 outputs, us per tile choice:
-//                              32x32  32x64  64x32  64x64  128x128  128x256  192x256  256x256
-//      16 x 11008 x  4096        9.8    9.1   16.3   12.7     31.8     47.8     62.1     75.8
-//      64 x  4096 x 11008       13.5   18.6   17.9   28.4     79.1    122.3    160.3    195.4
-//     256 x 11008 x  4096       45.2   50.9   49.7   32.8     34.6     50.8     65.8     77.8
-//     512 x 11008 x  4096       86.3   92.5   91.2   60.9     58.2     55.8     69.1     80.7
-//     777 x 12288 x  4096      153.6  161.2  164.9  101.1     91.3    110.4     84.1     93.8
-//    1056 x  2080 x  2784       32.0   40.5   39.9   28.1     27.6     37.3     49.7     59.2
-//    2048 x  4096 x  4096      133.2  140.2  136.5   84.3     67.5     64.9     78.4     91.1
-//    2048 x  4096 x 11008      319.6  300.3  284.1  210.9    173.8    163.7    191.0    222.8
-//    3072 x  8192 x  4096      394.5  414.3  399.1  240.5    187.2    190.7    174.8    195.7
-//    4096 x  4096 x  4096      266.1  279.8  273.5  163.7    128.2    128.0    155.2    110.7
-//    8192 x  8192 x   256      298.2  397.5  385.1  138.7     45.6     55.1     55.2     52.1
-//    4096 x 11008 x   512      239.5  286.9  272.2  102.2     51.7     61.8     60.6     56.0
+//                                 32x32     64x64  96x128K4   128x128 128x128K4   128x256   192x256   256x256
+//       64 x  4096 x 11008            11.7      27.0      51.6      76.5      60.9     120.1     158.0     193.7
+//      256 x 11008 x  4096            43.5      30.7      46.9      31.8      28.8      47.7      63.0      76.3
+//      512 x 11008 x  4096            82.0      57.4      72.3      55.1      58.2      50.1      63.4      77.6
+//      777 x 12288 x  4096           144.1     100.1      96.0      85.3      88.5     104.1      79.2      83.2
+//     1056 x  2080 x  2784            29.7      26.6      21.7      26.1      25.3      36.4      49.7      58.4
+//     2048 x  4096 x  4096           120.3      80.0      74.2      63.6      62.8      61.7      67.3      77.0
+//     2048 x  4096 x 11008           315.8     207.3     182.3     167.1     155.1     156.3     172.0     199.7
+//     3072 x  8192 x  4096           358.1     234.2     199.7     183.2     185.3     181.7     163.6     175.6
+//     4096 x  4096 x  4096           239.8     157.7     146.5     123.2     125.8     120.9     140.6     104.1
+//     8192 x  8192 x   256           287.3     130.6     138.0      46.6     125.8      52.3      49.9      47.6
+//     4096 x 11008 x   512           221.9      93.5      97.7      50.5      89.6      57.3      53.8      50.3
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
@@ -450,12 +545,14 @@ struct TileCost {
 };
 static const TileCost E4M3_COST[TILES] = {
     {32, 32, 8, 512, 2900, 350, 860, 3},    {32, 64, 8, 512, 1300, 2400, 1430, 0},   {64, 32, 8, 512, 1400, 2300, 1410, 0},
-    {64, 64, 4, 256, 3800, 770, 1115, 3},   {128, 128, 1, 256, 3700, 1200, 890, 8},  {128, 256, 1, 512, 500, 3800, 1740, 0},
-    {192, 256, 1, 512, 2500, 5200, 2330, 0}, {0, 0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 512, 0, 8500, 2650, 0}};
+    {64, 64, 4, 256, 3800, 770, 1115, 3},   {96, 128, 4, 512, 2000, 5600, 2600, 0},  {128, 128, 1, 256, 3700, 1200, 890, 8},
+    {128, 128, 4, 512, 2300, 5070, 3350, 0}, {128, 256, 1, 512, 500, 3800, 1740, 0}, {192, 256, 1, 512, 2500, 5200, 2330, 0},
+    {0, 0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 512, 0, 8500, 2650, 0}};
 static const TileCost E8M0_COST[TILES] = {
     {32, 32, 8, 512, 2700, 410, 585, 0},    {32, 64, 8, 512, 1400, 2140, 930, 0},    {64, 32, 8, 512, 1400, 2100, 935, 0},
-    {64, 64, 4, 256, 3200, 910, 685, 0},    {128, 128, 1, 256, 3200, 1390, 356, 28}, {0, 0, 0, 0, 0, 0, 0, 0},
-    {0, 0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
+    {64, 64, 4, 256, 3200, 910, 685, 0},    {0, 0, 0, 0, 0, 0, 0, 0},                {128, 128, 1, 256, 3200, 1390, 356, 28},
+    {0, 0, 0, 0, 0, 0, 0, 0},               {0, 0, 0, 0, 0, 0, 0, 0},                {0, 0, 0, 0, 0, 0, 0, 0},
+    {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {

@@ -153,8 +153,9 @@ hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStre
 bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf);
 hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st);
 // Workgroup tiles (rows x columns of the output) of the GEMM kernels: up to 64 x 64 in gemm_ksplit.hip (the waves of a
-// workgroup divide the contraction), the larger ones in gemm.hip (E4M3 scales) and gemm_mx.hip (E8M0).
-enum GemmTile { TILE_32x32, TILE_32x64, TILE_64x32, TILE_64x64, TILE_128x128, TILE_128x256, TILE_192x256, TILE_256x128, TILE_256x256, TILES };
+// workgroup divide the contraction), the larger ones in gemm.hip (E4M3 scales; K4: four groups of waves divide the contraction) and
+// gemm_mx.hip (E8M0).
+enum GemmTile { TILE_32x32, TILE_32x64, TILE_64x32, TILE_64x64, TILE_96x128_K4, TILE_128x128, TILE_128x128_K4, TILE_128x256, TILE_192x256, TILE_256x128, TILE_256x256, TILES };
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf);
 void gemm_tile_size(GemmTile t, int *rows, int *cols);
 hipError_t launch_gemm_ksplit(const GemmArgs &P, const GemmArgs *P1, GemmTile tile, int block, int sf, int out_dt, hipStream_t st);

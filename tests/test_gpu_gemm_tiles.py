@@ -230,3 +230,16 @@ def test_packed_weights_of_a_wide_projection():
     Y = nv.linear_fwd(X, None, w_operands=nv.quantize_weight(W, M), N=N)
     assert torch.equal(Y, nv.linear_fwd(X, W))
     assert torch.equal(Y, nv.gemm(nv.quantize(X), nv.quantize(W)))
+
+
+# Tiles whose four groups of waves take every fourth K tile: all four remainders of the K tiles (the groups without a K tile in the
+# last step add zeros), with and without a K tail, rows and columns past the edge.
+FOUR_GROUPS = [((2631, 769, 1312), (96, 128)), ((1704, 1157, 1440), (96, 128)), ((1179, 1726, 2176), (96, 128)), ((1173, 1690, 2112), (96, 128)),
+               ((1863, 1601, 2496), (128, 128)), ((1921, 1553, 3328), (128, 128))]
+
+
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "e4m3_64"])
+@pytest.mark.parametrize("shape,tile", FOUR_GROUPS, ids=["x".join(map(str, c[0])) for c in FOUR_GROUPS])
+def test_four_groups_sampled(shape, tile, fmt_name):
+    M, N, K = shape
+    test_every_tile_sampled((M, N, -(-K // FORMATS[fmt_name][0]) * FORMATS[fmt_name][0]), tile, None, fmt_name)
