@@ -182,7 +182,9 @@ def _torch_dtype(tag: int) -> torch.dtype:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream's handle without a torch.cuda.Stream around it: 0.2 us instead of 2.8, of the 14 that the host spent on a
+    # decode call of two launches (asked anew on every call: the stream and the device are the caller's to change)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(code: int, where: str) -> None:
