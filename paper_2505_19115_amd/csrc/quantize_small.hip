@@ -1,0 +1,203 @@
+// Quantizer kernel for small tensors (small_tensor()): one or two tensors, one or both orientations, in one launch.
+#include <type_traits>
+
+#include "quantize_tile.h"
+
+namespace nvfp4 {
+
+// A tensor of a few workgroup tiles is quantized by a few waves, and what bounds it is one wave's serial chain: 64 elements per lane
+// along one axis, then along the other, at the 8 cycles per instruction of a wave that is alone on its SIMD (dual SR+SR of 64 x 256:
+// 11.7 us, here 3.6).  Here the two orientations are separate jobs of one launch and a lane holds as little as the blocks allow: 8 elements of a row,
+// or one block of a column.  The draws of a column's block (one per row and 8 columns) are shared by the wave through LDS.
+constexpr int SMALL_NT = 512;
+struct SmallJob {
+    QuantArgs q;   // q.g_out null: another job of the tensor writes the scale
+    int axis, rounding;
+    unsigned wgs;
+    float *g_out2;
+    TagArgs tag;
+};
+
+// Column of its group of 64 that a lane holds.  bf16: two lanes 32 apart share a dword of two columns (below).
+template <int DT>
+__device__ __forceinline__ int lane_column(int lane) { return DT == NVFP4_BF16 ? 2 * (lane & 31) + (lane >> 5) : lane; }
+
+// The lane's column of B rows from row0 on (whole groups of 64 columns or their first 8 n).  bf16 columns come two to a dword: the lower
+// half of the wave loads the even rows, the upper half the odd ones, and each lane takes its 16 bits of both (one element per load, 64 x 256
+// took 4.5 us instead of 3.6).
+template <int DT, int B>
+__device__ __forceinline__ void load_column(const QuantArgs &P, int64_t row0, int64_t col0, int lane, bool live, float (&v)[B])
+{
+    if constexpr (DT == NVFP4_BF16) {
+        const int odd = lane >> 5;
+        const uint16_t *const p = reinterpret_cast<const uint16_t *>(P.x) + (row0 + odd) * P.ld + col0 + 2 * (lane & 31);
+        uint32_t w[B / 2];
+#pragma unroll
+        for (int r = 0; r < B / 2; ++r) w[r] = live ? *reinterpret_cast<const uint32_t *>(p + 2 * r * P.ld) : 0u;
+#pragma unroll
+        for (int r = 0; r < B / 2; ++r) {
+            const auto both = __builtin_amdgcn_permlane32_swap(w[r], w[r], false, false);
+            v[2 * r] = u2f(odd ? both[0] & 0xFFFF0000u : both[0] << 16);
+            v[2 * r + 1] = u2f(odd ? both[1] & 0xFFFF0000u : both[1] << 16);
+        }
+    } else {
+        const float *const p = reinterpret_cast<const float *>(P.x) + row0 * P.ld + col0 + lane;
+#pragma unroll
+        for (int r = 0; r < B; ++r) v[r] = live ? p[r * P.ld] : 0.0f;
+    }
+}
+
+// One lane = one block of B rows of one column, a wave = 64 columns, the waves of a workgroup one below the other, so that the 8 or 16
+// code bytes that they store to an output row make up one line; row-major outputs, cols a multiple of 8.
+template <int DT, int B, int SF, int RND>
+__device__ __forceinline__ float cols_small(const QuantArgs &P, const unsigned wg, uint32_t *draws)
+{
+    constexpr bool MXS = SF == NVFP4_SCALE_E8M0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned groups = (unsigned)((P.cols + 63) / 64), nblk = (unsigned)(P.rows / B);
+    const unsigned band = wg / groups, blk = band * (SMALL_NT / 64) + wave;
+    const int64_t row0 = (int64_t)blk * B, col0 = (int64_t)(wg - band * groups) * 64, col = col0 + lane_column<DT>(lane);
+    const bool live = blk < nblk && col < P.cols;  // (of two lanes that share a dword both or neither: cols is even)
+    float v[B];
+    load_column<DT, B>(P, row0, col0, lane, live, v);
+    uint16_t *const mine = reinterpret_cast<uint16_t *>(draws) + wave * (B * 64);  // [row][column]
+    if (RND == NVFP4_SR) {
+#pragma unroll
+        for (int i = 0; i < B / 8; ++i) {
+            const int r = lane / 8 + 8 * i, cg = lane % 8;
+            const u32x4 d = sr_draw(P.seed, (uint64_t)(row0 + r) * ((uint64_t)P.cols >> 3) + ((uint64_t)col0 >> 3) + cg);
+            *reinterpret_cast<uint4 *>(mine + r * 64 + cg * 8) = make_uint4(d.x, d.y, d.z, d.w);
+        }
+        asm volatile("" ::: "memory");  // (other lanes of the wave read them below: the LDS keeps a wave's order, and so must the compiler)
+    }
+    const float g = resolve_g<DT, SMALL_NT, SF == NVFP4_SCALE_E4M3>(P);
+    const float k = 1.0f / (6.0f * g);
+    float a = 0.0f, q;
+#pragma unroll
+    for (int r = 0; r < B; ++r) a = fmaxf(a, fabsf(v[r]));
+    const uint32_t sbyte = block_scale<SF, true, false>(a, g, k, &q);
+    if (MXS) q = mx_scale_operand(sbyte);
+    uint32_t words[B / 8];
+#pragma unroll
+    for (int w = 0; w < B / 8; ++w) {
+        uint32_t lo = 0, hi = 0;
+        auto pair = [&](auto byte) {
+            constexpr int BYTE = decltype(byte)::value;
+            const int r = 8 * w + 2 * BYTE;
+            const float x0 = MXS ? v[r] : v[r] * q, x1 = MXS ? v[r + 1] : v[r + 1] * q;
+            if constexpr (RND == NVFP4_RTN) {
+                lo = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(lo, x0, x1, MXS ? q : 1.0f, BYTE);
+            } else {
+                const uint32_t s0 = sr_seed_first(mine[r * 64 + lane_column<DT>(lane)]), s1 = sr_seed_first(mine[(r + 1) * 64 + lane_column<DT>(lane)]);
+                lo = sr_scaled<BYTE>(lo, x0, s0, MXS ? q : 1.0f);
+                hi = sr_scaled<BYTE>(hi, x1, s1, MXS ? q : 1.0f);
+            }
+        };
+        pair(std::integral_constant<int, 0>());
+        pair(std::integral_constant<int, 1>());
+        pair(std::integral_constant<int, 2>());
+        pair(std::integral_constant<int, 3>());
+        words[w] = lo | (hi << 4);
+    }
+    if (live) {
+        uint8_t *const dst = P.codes + col * (P.rows >> 1) + (row0 >> 1);
+#pragma unroll
+        for (int w = 0; w < B / 8; w += 2) *reinterpret_cast<uint2 *>(dst + 4 * w) = make_uint2(words[w], words[w + 1]);
+        P.scales[col * (int64_t)nblk + blk] = (uint8_t)sbyte;
+    }
+    return g;
+}
+
+template <int DT, int B, int SF>
+__global__ __launch_bounds__(SMALL_NT) void quantize_small_kernel(SmallJob j0, SmallJob j1, SmallJob j2, SmallJob j3)
+{
+    __shared__ __align__(16) uint32_t draws[SMALL_NT / 64 * B * 32];
+    unsigned wg = blockIdx.x;
+    const unsigned e0 = j0.wgs, e1 = e0 + j1.wgs, e2 = e1 + j2.wgs;
+    const SmallJob &J = wg < e0 ? j0 : wg < e1 ? j1 : wg < e2 ? j2 : j3;
+    wg -= wg < e0 ? 0 : wg < e1 ? e0 : wg < e2 ? e1 : e2;
+    float g;
+    if (J.axis == 1)
+        g = J.rounding == NVFP4_RTN ? rows_tile<DT, B, SF, NVFP4_RTN, true, SMALL_NT, 1>(J.q, wg) : rows_tile<DT, B, SF, NVFP4_SR, true, SMALL_NT, 1>(J.q, wg);
+    else
+        g = J.rounding == NVFP4_RTN ? cols_small<DT, B, SF, NVFP4_RTN>(J.q, wg, draws) : cols_small<DT, B, SF, NVFP4_SR>(J.q, wg, draws);
+    if (wg == 0 && threadIdx.x == 0 && J.q.g_out) {
+        // (a `saved` buffer that is not the one this call expects poisons the scale the GEMMs will multiply by)
+        const float g_gemm = tag_apply(J.tag) ? g : __builtin_nanf("");
+        *J.q.g_out = g_gemm;
+        if (J.g_out2) *J.g_out2 = g_gemm;
+    }
+}
+
+// ------------------------------------------------------------------ host side
+
+// Tensors that go through quantize_small_kernel, in elements.  Its lanes reload nothing and share nothing between the orientations, so a
+// large tensor is read twice by its dual form and stored in smaller pieces; us, the other kernels / this one, scale preset, blocks of 16:
+//                  bf16 rows SR  columns RtN  columns SR   RtN+RtN      SR+SR         binary32 rows SR  columns SR   RtN+RtN      SR+SR
+//     64 x  256     3.6 / 3.0    5.5 / 3.1    7.6 / 3.7    6.7 / 3.0   10.4 / 3.6       3.4 / 3.0    7.5 / 3.4    6.6 / 2.9   10.3 / 3.4
+//   1024 x 1024     3.7 / 3.2    6.4 / 3.9    8.4 / 4.5    9.0 / 4.4   12.6 / 5.2       3.7 / 3.4    9.9 / 4.3    9.7 / 4.2   12.9 / 4.9
+//   1024 x 2048     3.8 / 3.9    6.5 / 4.3    8.5 / 4.9    9.3 / 5.1   13.0 / 6.1       4.1 / 4.2   10.1 / 4.8    9.9 / 5.2   13.2 / 6.2
+//   2048 x 2048     4.6 / 5.3    8.8 / 5.8   10.5 / 6.4   11.0 / 8.0   14.8 / 8.9       6.0 / 5.6   10.6 / 6.5   10.7 / 8.8   14.2 / 9.8
+//   2080 x 2784     5.7 / 6.6    9.8 / 7.5   12.0 / 8.2   12.4 / 11.6  16.5 / 12.7      7.3 / 7.2   12.0 / 8.3   11.9 / 13.3  15.6 / 14.7
+//   2048 x 4096     6.6 / 8.6    9.2 / 8.5   11.0 / 9.4   11.6 / 13.6  15.6 / 15.6      9.0 / 9.7   11.6 / 9.9   11.5 / 18.5  14.9 / 19.4
+//   4096 x 4096     9.8 / 14.8  11.4 / 15.2  15.6 / 15.8  15.1 / 28.0  22.5 / 31.4     15.6 / 17.8  19.6 / 18.5  20.1 / 35.5  22.0 / 36.2
+// (MXFP4: the same lines, columns SR of 4096 x 4096 binary32 21.9 / 16.2.)
+bool small_tensor(int dt, const QuantArgs &P, int block, bool hw, SmallUse use)
+{
+    const bool bf16 = dt == NVFP4_BF16;
+    const int64_t M = 1 << 20, most = use == SMALL_ROWS ? (bf16 ? M : 4 * M) : use == SMALL_COLUMNS ? (bf16 ? 8 * M : 16 * M) : 4 * M;
+    return hw && (block == 16 || block == 32) && (P.cols & 7) == 0 && P.rows * P.cols <= most;
+}
+static SmallJob small_job(const QuantArgs &q, int axis, int rounding, int block)
+{
+    SmallJob j = {q, axis, rounding, 0, nullptr, {}};
+    constexpr int WAVES = SMALL_NT / 64;
+    j.wgs = (unsigned)(axis == 1 ? (q.rows * (q.cols >> 3) + SMALL_NT - 1) / SMALL_NT : (q.rows / block + WAVES - 1) / WAVES * ((q.cols + 63) / 64));
+    return j;
+}
+// the jobs of a dual quantization (row-major outputs): rows, which also write the scale, and columns
+static void small_dual_jobs(const DualArgs &D, int rnd_r, int rnd_c, int block, SmallJob *j)
+{
+    QuantArgs r = D.c;
+    r.codes = D.codes_r;
+    r.scales = D.scales_r;
+    r.seed = D.seed_r;
+    j[0] = small_job(r, 1, rnd_r, block);
+    j[0].g_out2 = D.g_out2;
+    j[0].tag = D.tag;
+    QuantArgs c = D.c;
+    c.g_out = nullptr;
+    j[1] = small_job(c, 0, rnd_c, block);
+}
+template <int DT>
+static void launch_small_dt(const SmallJob (&j)[4], int block, int sf, hipStream_t st)
+{
+    const dim3 grid(j[0].wgs + j[1].wgs + j[2].wgs + j[3].wgs), wg(SMALL_NT);
+    if (block == 16 && sf == NVFP4_SCALE_E4M3) hipLaunchKernelGGL((quantize_small_kernel<DT, 16, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    else if (block == 16) hipLaunchKernelGGL((quantize_small_kernel<DT, 16, NVFP4_SCALE_E8M0>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    else if (sf == NVFP4_SCALE_E4M3) hipLaunchKernelGGL((quantize_small_kernel<DT, 32, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    else hipLaunchKernelGGL((quantize_small_kernel<DT, 32, NVFP4_SCALE_E8M0>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+}
+static hipError_t launch_small(const SmallJob (&j)[4], int dt, int block, int sf, hipStream_t st)
+{
+    if (dt == NVFP4_BF16) launch_small_dt<NVFP4_BF16>(j, block, sf, st);
+    else launch_small_dt<NVFP4_F32>(j, block, sf, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_quantize_small(const QuantArgs &P, const QuantArgs *P1, int dt, int axis, int rounding, int block, int sf, hipStream_t st)
+{
+    SmallJob j[4] = {small_job(P, axis, rounding, block)};
+    if (P1) j[1] = small_job(*P1, axis, rounding, block);
+    return launch_small(j, dt, block, sf, st);
+}
+
+hipError_t launch_quantize_small_dual(const DualArgs &D, const DualArgs *W, int dt, int rnd_r, int rnd_c, int block, int sf, hipStream_t st)
+{
+    SmallJob j[4] = {};
+    small_dual_jobs(D, rnd_r, rnd_c, block, j);
+    if (W) small_dual_jobs(*W, NVFP4_RTN, NVFP4_RTN, block, j + 2);
+    return launch_small(j, dt, block, sf, st);
+}
+
+}  // namespace nvfp4

@@ -427,3 +427,41 @@ def test_maximum_of_a_small_tensor(shape, dtype):
             both = nv.quantize_dual(x.cuda(), nv.RTN, 0, nv.SR, 9, nv.NVFP4)
             assert_quant_equal(both[0], oracle.quantize(x, 1, nv.RTN, 0, oracle.NVFP4), f"{shape} dual rows")
             assert_quant_equal(both[1], oracle.quantize(x, 0, nv.SR, 9, oracle.NVFP4), f"{shape} dual cols")
+
+
+SMALL_FORMATS = ["nvfp4", "mxfp4", "e4m3_b32"]
+
+
+def _quantize_all(x_cpu, x, f, axes, dual, what):
+    for axis in axes:
+        for rounding in (nv.RTN, nv.SR):
+            print(f"[case] {what} {tuple(x.shape)} {x.dtype} axis={axis} rounding={rounding}", flush=True)
+            assert_quant_equal(nv.quantize(x, axis, rounding, 31, f), oracle.quantize(x_cpu, axis, rounding, 31, ofmt(f)), f"{what} {axis} {rounding}")
+    if dual:
+        for rr, rc in ((nv.RTN, nv.RTN), (nv.RTN, nv.SR), (nv.SR, nv.SR), (nv.SR, nv.RTN)):
+            print(f"[case] {what} {tuple(x.shape)} {x.dtype} dual {rr} {rc}", flush=True)
+            qr, qc = nv.quantize_dual(x, rr, 32, rc, 33, f)
+            assert_quant_equal(qr, oracle.quantize(x_cpu, 1, rr, 32, ofmt(f)), f"{what} dual rows {rr}")
+            assert_quant_equal(qc, oracle.quantize(x_cpu, 0, rc, 33, ofmt(f)), f"{what} dual columns {rc}")
+
+
+# The kernel for small tensors at its edges: one block, blocks short of a workgroup's eight, columns short of a group of 64, a row
+# pitch; along rows cols has to be whole blocks, down columns only a multiple of 8.
+@pytest.mark.parametrize("fmt", SMALL_FORMATS)
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,cols,pitch", [(32, 32, 32), (32, 8, 8), (160, 72, 88), (288, 96, 96), (96, 1160, 1160), (1024, 1024, 1032)])
+def test_small_tensors(rows, cols, pitch, dtype, fmt):
+    f = FORMATS[fmt]()
+    big = synth.student_t_outliers(rows, pitch, seed=rows + cols, dtype=dtype)
+    whole = cols % f.block == 0
+    _quantize_all(big[:, :cols].contiguous(), big.cuda()[:, :cols], f, (1, 0) if whole else (0,), whole, f"small {fmt}")
+
+
+# Just past the sizes that it takes: the kernels for larger tensors with rows and columns past the edge of their tiles.
+@pytest.mark.parametrize("fmt", SMALL_FORMATS)
+@pytest.mark.parametrize("rows,cols,dtype,axes,dual", [(1120, 1056, torch.bfloat16, (1,), False), (2080, 2080, torch.float32, (1,), True),
+                                                       (2080, 2080, torch.bfloat16, (), True), (2080, 4120, torch.bfloat16, (0,), False),
+                                                       (4128, 4104, torch.float32, (0,), False)])
+def test_past_the_small_tensors(rows, cols, dtype, axes, dual, fmt):
+    x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(rows + cols)) * 0.02).to(dtype)
+    _quantize_all(x, x.cuda(), FORMATS[fmt](), axes, dual, f"large {fmt}")
