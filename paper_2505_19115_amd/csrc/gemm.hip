@@ -588,11 +588,16 @@ static int g_fp4_rescale_route = 0;  // (measured slower than the fp16 route: op
 void set_fp4_rescale_route(int on) { g_fp4_rescale_route = on; }
 int fp4_rescale_route() { return g_fp4_rescale_route; }
 
+bool gemm_reads_slabs(int64_t K, int block, int sf)
+{
+    return sf == NVFP4_SCALE_E8M0 ? block == 32 && mxfp4_gemm_takes_slabs(K) : block == 16 && K % KT == 0;
+}
+
 static hipError_t check_gemm(const GemmArgs &P, int block, int sf)
 {
     // lane offsets inside a 256-row tile are 32-bit
     if ((P.K >> 1) * 256 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    if ((P.a_slab || P.b_slab) && !gemm_takes_slabs(P.M, P.N, P.K, block, sf)) return hipErrorInvalidValue;
+    if ((P.a_slab || P.b_slab) && !gemm_reads_slabs(P.K, block, sf)) return hipErrorInvalidValue;
     if (sf == NVFP4_SCALE_E8M0 && block != 32) return hipErrorNotSupported;
     return hipSuccess;
 }

@@ -86,11 +86,13 @@ struct GemmArgs {
     const float *gA, *gB;  // per-tensor scales of the two operands (device)
     void *out;
     int64_t ldc;
-    int a_slab = 0, b_slab = 0;  // operand stored in the slab layout (only where gemm_takes_slabs() holds)
+    int a_slab = 0, b_slab = 0;  // operand stored in the slab layout (only where gemm_reads_slabs() holds)
 };
 // True for the products whose operands the dual quantizer hands over as slabs (and nvfp4_gemm_slab() accepts): NVFP4 with at least
 // 128 output tiles of 256 x 256, MXFP4 with K >= 512, K a multiple of 128 in both.  Every tile of the GEMM kernels reads slabs.
 bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf);
+// What the kernels can read as slabs: contractions of whole K tiles in the two formats, whatever the number of output tiles.
+bool gemm_reads_slabs(int64_t K, int block, int sf);
 
 // Tensor maximum: one partial per workgroup into `partials` (tensor_amax_partials() entries),
 // then folded into amax_bits[0] (bit pattern of max|x|) and, if g_out is given, into the scale.

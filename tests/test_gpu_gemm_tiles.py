@@ -243,3 +243,24 @@ FOUR_GROUPS = [((2631, 769, 1312), (96, 128)), ((1704, 1157, 1440), (96, 128)), 
 def test_four_groups_sampled(shape, tile, fmt_name):
     M, N, K = shape
     test_every_tile_sampled((M, N, -(-K // FORMATS[fmt_name][0]) * FORMATS[fmt_name][0]), tile, None, fmt_name)
+
+
+# Packed weights of more than a few million elements are slabs also where a few tokens meet them: every small tile, the other operand
+# row-major, output columns that end inside a slab; the bits of the calls that quantize W themselves.
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("M", [32, 64, 160, 320])
+def test_weight_slabs_with_few_tokens(M, fmt_name):
+    N, K, seed = 2080, 2176, 5
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    X, W, dY = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (N, K), (M, N)))
+    print(f"[case] weight slabs {fmt_name} {M}x{N}x{K}", flush=True)
+    wq = nv.quantize_weight(W, M, fmt)
+    saved = torch.empty(nv.linear_saved_bytes(M, N, K, fmt), dtype=torch.uint8, device="cuda")
+    Y = nv.linear_fwd(X, None, fmt, w_operands=wq, N=N, saved=saved, bwd_seed=seed)
+    assert torch.equal(Y, nv.linear_fwd(X, W, fmt))
+    got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K, w_operands=wq)
+    for a, b in zip(got, nv.linear_bwd(dY, X, W, seed, fmt)):
+        assert torch.equal(a, b)
