@@ -512,8 +512,9 @@ __device__ __forceinline__ float rows_tile(const QuantArgs &P, const int64_t wg)
         if (id < total) {
             int64_t off = id * 8;
             if (!dense) {
-                const int64_t i = id / cpr;
-                off = i * P.ld + (id - i * cpr) * 8;
+                // (a 64-bit division per chunk costs more than the chunk's arithmetic)
+                const int64_t i = total <= 0xFFFFFFFF ? (int64_t)((uint32_t)id / (uint32_t)cpr) : id / cpr;
+                off += i * (P.ld - P.cols);
             }
             v[u].template load<true>(P.x, off);
         } else {
