@@ -200,8 +200,8 @@ __global__ __launch_bounds__(256) void quantize_rows_pair_kernel(QuantArgs P0, Q
 // vertically, so that it reads 512 contiguous bytes (bf16) per row and writes 64 per output row.
 // RPL = 16 (4 waves) does the least work per element, RPL = 8 (8 waves: a block of 16 spans two lanes) has half the serial
 // chain per wave and half the registers, 512 tiles resident at once.
-// bf16: what bounds a tensor of up to 512 tiles is that chain (one batch of loads, the arithmetic, the stores), what bounds a larger
-// one the arithmetic.  us, RPL = 16 / 8, dual quantizer with row-major outputs:
+// bf16: what bounds a tensor of up to 512 tiles is that chain (one batch of loads, the arithmetic, the stores); larger ones are streamed
+// (streams()).  us, RPL = 16 / 8, dual quantizer with row-major outputs:
 //                      bf16 RtN+RtN   bf16 SR+SR    MXFP4 bf16 SR+SR
 //     2048 x  4096     13.9 / 11.6    18.1 / 16.0   19.7 / 16.4
 //     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4
@@ -531,6 +531,105 @@ __device__ __forceinline__ void cols_tile(const QuantArgs &P, Chunk<DT> (&v)[RPL
     }
 }
 
+// ------------------------------------------------------------------ bf16 tensors of many tiles: the next tile in flight
+
+// The 16 x 8 lane tiles of one wave, one workgroup tile after the other, each requested before the one in hand is worked on.  The kernels
+// above load, compute and store, one tile per wave: two generations of waves that do each of the three at the same time, 70 % of a
+// wave's life spent waiting for memory.  The first LR rows of the next tile go from memory straight into a piece of LDS that only
+// this wave uses (global_load_lds: 1 KB per row, 16 bytes per lane, read back by the lane that fetched them: no barriers), the others
+// into registers.  Whole tiles in registers take 240 and more of them, whole tiles in LDS leave room for two workgroups per CU.
+template <int LR>
+struct TileStream {
+    using G = ColGeom<16>;
+    static constexpr int LDS_BYTES = G::NT / 64 * LR * 1024;
+    const uint8_t *mine;  // this lane's 16 bytes of row 0
+    uint32_t lds_wave;    // LDS address of the wave's piece
+    int lv, lcol;         // the lane's tile: rows 16 lv .. of the workgroup tile, columns lcol ..
+    Chunk<NVFP4_BF16> rest[16 - LR];
+
+    __device__ __forceinline__ TileStream(uint8_t *lds)
+    {
+        typedef __attribute__((address_space(3))) void *lds_ptr_t;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        mine = lds + wave * (LR * 1024) + (threadIdx.x & 63) * 16;
+        lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)lds + wave * (LR * 1024));
+        place(threadIdx.x);
+    }
+    // (also once per tile, from a thread index that the compiler cannot trace back: what derives from it is then computed again instead of
+    // kept from tile to tile, dual RtN+RtN with 15 rows in LDS 186 -> 116 registers)
+    __device__ __forceinline__ void place(int tid)
+    {
+        lv = (tid & 63) % G::LANES_V;
+        lcol = (tid >> 6) * G::WAVE_COLS + (tid & 63) / G::LANES_V * 8;
+    }
+    // (rows is a multiple of 16 and cols of 8: a lane tile is inside or outside as a whole)
+    __device__ __forceinline__ bool inside(const QuantArgs &P, int tx, int ty) const
+    {
+        return (int64_t)ty * G::WG_ROWS + lv * 16 < P.rows && (int64_t)tx * G::WG_COLS + lcol < P.cols;
+    }
+    // A lane outside the tensor fetches the workgroup tile's first lane tile, which is inside.
+    __device__ __forceinline__ void request(const QuantArgs &P, int tx, int ty)
+    {
+        const uint16_t *base = reinterpret_cast<const uint16_t *>(P.x) + (int64_t)ty * G::WG_ROWS * P.ld + (int64_t)tx * G::WG_COLS;
+        const uint32_t off = inside(P, tx, ty) ? (uint32_t)(lv * 16 * P.ld + lcol) : 0u;  // elements; the byte offset has 32 bits (streams())
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (r < LR)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds_wave + r * 1024), "v"(off * 2u), "s"(base) : "memory");
+            else
+                rest[r < LR ? 0 : r - LR].template load<true>(base, off);
+            base += P.ld;
+        }
+    }
+    // The tile requested last; its LDS may be written again afterwards.  (Waits for the stores of the tile before as well: counting those
+    // out changed no time.)
+    __device__ __forceinline__ void take(bool live, Chunk<NVFP4_BF16> (&v)[16])
+    {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            if (r < LR) v[r].raw = *reinterpret_cast<const uint4 *>(mine + r * 1024);
+            else v[r] = rest[r < LR ? 0 : r - LR];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (!live) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r].zero();
+        }
+    }
+};
+// Workgroups per CU, and rows in LDS that leave room for them: three need 168 registers or fewer, and 53 KB of LDS each, of which the
+// dual kernel's own output takes 18.
+constexpr int STREAM_WGS = 3, COLS_LDS_ROWS = 12, DUAL_LDS_ROWS = 8;
+
+template <int B, int SF, int RND>
+__global__ __launch_bounds__(ColGeom<16>::NT, STREAM_WGS) void quantize_cols_stream_kernel(QuantArgs P, unsigned gx, unsigned tiles)
+{
+    using G = ColGeom<16>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t stream_lds[];
+    TileStream<COLS_LDS_ROWS> T(stream_lds);
+    unsigned id = blockIdx.x;
+    T.request(P, (int)(id % gx), (int)(id / gx));
+    const float g = resolve_g<NVFP4_BF16, G::NT, false>(P);
+    const float k = 1.0f / (6.0f * g);
+    build_qtab<SF, true>(g);
+    if (id == 0 && threadIdx.x == 0) *P.g_out = g;
+    for (bool more = true; more;) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        T.place(tid);
+        const int tx = (int)(id % gx), ty = (int)(id / gx);
+        const bool live = T.inside(P, tx, ty);
+        Chunk<NVFP4_BF16> v[16];
+        T.take(live, v);
+        id += gridDim.x;
+        more = id < tiles;
+        if (more) T.request(P, (int)(id % gx), (int)(id / gx));
+        cols_tile<NVFP4_BF16, B, SF, RND, true, true, 16>(P, v, g, k, (int64_t)ty * G::WG_ROWS + T.lv * 16, (int64_t)tx * G::WG_COLS + T.lcol,
+                                                         live ? 8 : 0, T.lv);
+    }
+}
+
 // ------------------------------------------------------------------ SwiGLU backward as a tile source
 
 // Where the dual quantizer's tile comes from: a tensor in memory, or dG / dU of the SwiGLU backward evaluated from
@@ -641,7 +740,7 @@ hipError_t launch_swiglu_bwd(const void *dH, const void *G, const void *U, int d
 // One workgroup tile (128 rows x 256 columns at tile coordinates tx, ty; the lane's RPL x 8 part of it in v) through
 // both quantizers and out to memory.  Every thread of the workgroup must call it (barriers inside).
 template <int DT, int B, int SF, int RND_R, int RND_C, int RPL>
-__device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL], float g, float k, int tx, int ty,
+__device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL], float g, float k, int tx, int ty, const int tid,
                                           uint32_t *lds_codes, uint8_t *lds_scales)
 {
     using G = ColGeom<RPL>;
@@ -650,7 +749,7 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL]
     constexpr int ROW_BYTES = G::WG_COLS / 2;    // 128 code bytes per tile row
     constexpr int ROW_SC = G::WG_COLS / B;       // scale bytes per tile row
     const QuantArgs &P = D.c;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int lv = lane % G::LANES_V, lh = lane / G::LANES_V;
     const int64_t wrow0 = (int64_t)ty * G::WG_ROWS, wcol0 = (int64_t)tx * G::WG_COLS;
     const int64_t row0 = wrow0 + lv * RPL;
@@ -705,15 +804,15 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL]
         const int half = (int)(wrow0 & 128);
 #pragma unroll
         for (int i = 0; i < 1024 / G::NT; ++i) {
-            const int id = threadIdx.x + G::NT * i, q = id >> 3, c = id & 7, R = slab_row(q);
+            const int id = tid + G::NT * i, q = id >> 3, c = id & 7, R = slab_row(q);
             if (wrow0 + R < P.rows && wcol0 + c * 32 < P.cols) {
                 const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R / RPL & 7)) << 2)]);
                 const u32x4_t o = {w.x, w.y, w.z, w.w};
                 __builtin_nontemporal_store(o, reinterpret_cast<u32x4_t *>(D.codes_r + (slab0 + (c >> 2)) * SLAB_CODE_BYTES + (half + q) * 64 + (c & 3) * 16));
             }
         }
-        if (threadIdx.x < G::WG_ROWS) {
-            const int q = threadIdx.x, R = slab_row(q);
+        if (tid < G::WG_ROWS) {
+            const int q = tid, R = slab_row(q);
             if (wrow0 + R < P.rows) {
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(&lds_scales[R * 16]);
                 if (B == 16) {
@@ -735,7 +834,7 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL]
     if (!D.slab_r) {
 #pragma unroll
         for (int i = 0; i < 1024 / G::NT; ++i) {
-            const int id = threadIdx.x + G::NT * i, R = id >> 3, c = id & 7;
+            const int id = tid + G::NT * i, R = id >> 3, c = id & 7;
             const int64_t row = wrow0 + R, col = wcol0 + c * 32;
             if (row < P.rows && col < P.cols) {
                 const uint4 w = *reinterpret_cast<const uint4 *>(&lds_codes[R * (ROW_BYTES / 4) + ((c ^ (R / RPL & 7)) << 2)]);
@@ -750,8 +849,8 @@ __device__ __forceinline__ void dual_tile(const DualArgs &D, Chunk<DT> (&v)[RPL]
             }
         }
     }
-    if (threadIdx.x < G::WG_ROWS) {
-        const int R = threadIdx.x;
+    if (tid < G::WG_ROWS) {
+        const int R = tid;
         const int64_t row = wrow0 + R, nsc = P.cols / B, s0 = wcol0 / B;
         if (row < P.rows && s0 < nsc) {
             uint8_t *dst = D.scales_r + row * nsc + s0;
@@ -803,7 +902,7 @@ __device__ __forceinline__ void dual_wg(const DualArgs &D, int tx, int ty, DualL
         *P.g_out = g_gemm;
         if (D.g_out2) *D.g_out2 = g_gemm;
     }
-    dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, tx, ty, lds.codes, lds.scales);
+    dual_tile<DT, B, SF, RND_R, RND_C, RPL>(D, v, g, k, tx, ty, (int)threadIdx.x, lds.codes, lds.scales);
 }
 
 // Waves per SIMD asked of the compiler with 16 rows per lane, where the registers lie within a few of the line (128 and 168 registers);
@@ -818,6 +917,39 @@ __global__ __launch_bounds__(ColGeom<RPL>::NT, dual_waves(DT, B, SF, RND_R, RND_
 {
     __shared__ __align__(16) DualLds lds;
     dual_wg<DT, B, SF, RND_R, RND_C, RPL, SRC>(D, (int)blockIdx.x, (int)blockIdx.y, lds);
+}
+
+template <int B, int SF, int RND_R, int RND_C>
+__global__ __launch_bounds__(ColGeom<16>::NT, STREAM_WGS) void quantize_dual_stream_kernel(DualArgs D, unsigned gx, unsigned tiles)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t stream_lds[];
+    __shared__ __align__(16) DualLds lds;
+    const QuantArgs &P = D.c;
+    TileStream<DUAL_LDS_ROWS> T(stream_lds);
+    unsigned id = blockIdx.x;
+    T.request(P, (int)(id % gx), (int)(id / gx));
+    const float g = resolve_g<NVFP4_BF16, ColGeom<16>::NT, false>(P);
+    const float k = 1.0f / (6.0f * g);
+    build_qtab<SF, true>(g);
+    if (id == 0 && threadIdx.x == 0) {
+        // (a `saved` buffer that is not the one this call expects poisons the scale the GEMMs will multiply by)
+        const float g_gemm = tag_apply(D.tag) ? g : __builtin_nanf("");
+        *P.g_out = g_gemm;
+        if (D.g_out2) *D.g_out2 = g_gemm;
+    }
+    for (bool more = true; more;) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        T.place(tid);
+        const int tx = (int)(id % gx), ty = (int)(id / gx);
+        Chunk<NVFP4_BF16> v[16];
+        T.take(T.inside(P, tx, ty), v);
+        __syncthreads();  // (every wave has stored its share of the codes that the tile before left in lds)
+        id += gridDim.x;
+        more = id < tiles;
+        if (more) T.request(P, (int)(id % gx), (int)(id / gx));
+        dual_tile<NVFP4_BF16, B, SF, RND_R, RND_C, 16>(D, v, g, k, tx, ty, tid, lds.codes, lds.scales);
+    }
 }
 
 // X (round to nearest / stochastic) and W (round to nearest) of a forward call that saves both, in one launch: the first
@@ -942,6 +1074,30 @@ static void launch_cols(const QuantArgs &P, hipStream_t st)
     hipLaunchKernelGGL((quantize_cols_kernel<DT, B, SF, RND, HW, ALIGNED, RPL>), grid, dim3(G::NT), 0, st, P);
 }
 
+// bf16 tensors of more than 512 workgroup tiles go through the streaming kernels (their lane tiles are whole, and the byte offset of a row
+// inside a workgroup tile has 32 bits).  us, one tile per workgroup with 16 rows per lane / streaming, scale preset:
+//                     columns                      dual, row-major                            dual, slabs
+//                     RtN          SR              RtN+RtN       RtN+SR        SR+SR           RtN+RtN       RtN+SR        SR+SR
+//     3072 x  6144    17.1 / 15.0  22.9 / 16.6     21.8 / 17.3   27.8 / 22.6   33.8 / 28.5     (host)        27.5 / 23.0   33.1 / 28.0
+//     4096 x  8192    20.4 / 20.8  27.9 / 23.8     26.7 / 23.8   34.7 / 30.8   42.7 / 39.2     26.2 / 23.8   34.3 / 30.8   42.4 / 38.7
+//     4096 x 11008    36.5 / 32.2  45.2 / 36.0     44.9 / 38.6   53.6 / 47.6   60.7 / 57.3     41.9 / 33.7   49.1 / 43.4   57.2 / 53.7
+//     8192 x  8192    44.5 / 41.6  54.8 / 45.9     55.2 / 51.8   63.6 / 54.7   75.7 / 73.8     52.3 / 42.9   61.4 / 52.6   75.3 / 70.7
+//     8192 x 12288    68.9 / 60.5  82.8 / 68.0     85.3 / 83.9   94.9 / 93.3   111 / 107       74.4 / 65.2   88.0 / 84.6   109 / 104
+//    16384 x  8192    84.8 / 81.6  104 / 87.9      110 / 114     124 / 123     143 / 138       97.4 / 86.0   116 / 109     138 / 135
+//    16384 x 12288     129 / 126   150 / 133       164 / 170     176 / 176     199 / 203       142 / 128     161 / 156     189 / 191
+// (MXFP4 alike.)  Above 3072 tiles row-major duals have many generations of workgroups, whose phases drift apart by themselves, and
+// keep those of one tile.  Handing each workgroup tiles one below the other instead of 768 apart: 8192 x 8192 dual RtN+RtN 72.
+static bool streams(const QuantArgs &P) { return (P.cols & 7) == 0 && P.ld <= (1 << 22); }
+constexpr int64_t STREAM_ROW_MAJOR_TILES = 3072;
+template <typename K, typename A>
+static void launch_stream(K kernel, const A &args, const QuantArgs &P, int lds, hipStream_t st)
+{
+    using G = ColGeom<16>;
+    const unsigned gx = (unsigned)((P.cols + G::WG_COLS - 1) / G::WG_COLS), tiles = gx * (unsigned)((P.rows + G::WG_ROWS - 1) / G::WG_ROWS);
+    // (as many workgroups as are resident at once)
+    hipLaunchKernelGGL(kernel, dim3(tiles < 256 * STREAM_WGS ? tiles : 256 * STREAM_WGS), dim3(G::NT), lds, st, args, gx, tiles);
+}
+
 template <int DT, int B, int SF, int RND, bool HW>
 static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
 {
@@ -956,6 +1112,11 @@ static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
             launch_cols<DT, B, SF, RND, HW, RND == NVFP4_RTN, 16>(P, st);
         else if (HW && short_lane_tile(DT, B, SF, RND, RND, COLUMNS, P.rows, P.cols))
             launch_cols<DT, B, SF, RND, HW, true, HW ? 8 : 16>(P, st);
+        else if constexpr (HW && DT == NVFP4_BF16 && RND == NVFP4_SR) {
+            if (streams(P)) launch_stream(quantize_cols_stream_kernel<B, SF, RND>, P, P, TileStream<COLS_LDS_ROWS>::LDS_BYTES, st);
+            else launch_cols<DT, B, SF, RND, HW, true, 8>(P, st);
+        } else if (HW && DT == NVFP4_BF16 && streams(P))
+            launch_stream(quantize_cols_stream_kernel<B, SF, RND>, P, P, TileStream<COLS_LDS_ROWS>::LDS_BYTES, st);
         else
             launch_cols<DT, B, SF, RND, HW, true, HW && DT == NVFP4_F32 && SF == NVFP4_SCALE_E8M0 && RND == NVFP4_SR ? 8 : 16>(P, st);
     }
@@ -1014,6 +1175,8 @@ static void launch_dual_rpl(const DualArgs &D, hipStream_t st)
     const unsigned gx = (unsigned)((D.c.cols + 255) / 256), gy = (unsigned)((D.c.rows + 127) / 128);
     if (short_lane_tile(DT, B, SF, RND_R, RND_C, D.slab_r || D.slab_c ? DUAL_SLABS : DUAL, D.c.rows, D.c.cols))
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, 8>), dim3(gx, gy), dim3(ColGeom<8>::NT), 0, st, D);
+    else if (DT == NVFP4_BF16 && streams(D.c) && (D.slab_r || D.slab_c || (int64_t)gx * gy <= STREAM_ROW_MAJOR_TILES))
+        launch_stream(quantize_dual_stream_kernel<B, SF, RND_R, RND_C>, D, D.c, TileStream<DUAL_LDS_ROWS>::LDS_BYTES, st);
     else
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, LONG>), dim3(gx, gy), dim3(ColGeom<LONG>::NT), 0, st, D);
 }

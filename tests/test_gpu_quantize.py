@@ -465,3 +465,28 @@ def test_small_tensors(rows, cols, pitch, dtype, fmt):
 def test_past_the_small_tensors(rows, cols, dtype, axes, dual, fmt):
     x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(rows + cols)) * 0.02).to(dtype)
     _quantize_all(x, x.cuda(), FORMATS[fmt](), axes, dual, f"large {fmt}")
+
+
+# bf16 tensors of more than 512 workgroup tiles (128 x 256) are walked by a fixed number of workgroups, 768 of them, each with its next
+# tile in flight: a single tile each, some with two, some with three; one row or one column of tiles, all of them cut short; a row pitch.
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4", "e4m3_b32", "e4m3_b64"])
+@pytest.mark.parametrize("rows,cols,pitch", [(64, 205056, 205056), (102464, 96, 104), (204864, 64, 64), (67584, 64, 128)])
+def test_tensors_of_many_tiles(rows, cols, pitch, fmt):
+    f = FORMATS[fmt]()
+    x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(rows + cols)) * 0.02).to(torch.bfloat16)
+    big = torch.full((rows, pitch), float("nan"), dtype=torch.bfloat16, device="cuda")
+    big[:, :cols] = x.cuda()
+    _quantize_all(x, big[:, :cols], f, (0,), f.block <= 32, f"many tiles {fmt}")
+
+
+@pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
+def test_slabs_of_many_tiles(fmt):
+    f, rows, cols = FORMATS[fmt](), 128, 205056
+    x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(7)) * 0.02).to(torch.bfloat16).cuda()
+    for rr, rc in ((nv.RTN, nv.RTN), (nv.RTN, nv.SR), (nv.SR, nv.SR)):
+        print(f"[case] slabs of many tiles {fmt} {rr} {rc}", flush=True)
+        plain = nv.quantize_dual(x, rr, 5, rc, 6, f)
+        slabs = nv.quantize_dual(x, rr, 5, rc, 6, f, slab_rows=True, slab_cols=True)
+        for side, (outer, K) in enumerate(((rows, cols), (cols, rows))):
+            assert np.array_equal(unslab(slabs[side][0], outer, K, 64), to_np(plain[side][0])), f"codes of side {side}"
+            assert np.array_equal(unslab(slabs[side][1], outer, K, 128 // f.block), to_np(plain[side][1])), f"scales of side {side}"
