@@ -966,6 +966,56 @@ __global__ __launch_bounds__(ColGeom<8>::NT) void quantize_dual_pair_kernel(Dual
     }
 }
 
+// The same for bf16 tensors of many tiles: one run of tiles over both tensors, X's first.
+template <int B, int SF>
+__global__ __launch_bounds__(ColGeom<16>::NT, STREAM_WGS) void quantize_dual_stream_pair_kernel(DualArgs X, DualArgs W, unsigned gx, unsigned tiles_x, unsigned gw,
+                                                                                                unsigned tiles)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t stream_lds[];
+    __shared__ __align__(16) DualLds lds;
+    TileStream<DUAL_LDS_ROWS> T(stream_lds);
+    unsigned id = blockIdx.x;
+    auto request = [&]() {
+        if (id < tiles_x) T.request(X.c, (int)(id % gx), (int)(id / gx));
+        else T.request(W.c, (int)((id - tiles_x) % gw), (int)((id - tiles_x) / gw));
+    };
+    request();
+    const float g_x = resolve_g<NVFP4_BF16, ColGeom<16>::NT, false>(X.c);
+    __syncthreads();  // (both folds use the same LDS)
+    const float g_w = resolve_g<NVFP4_BF16, ColGeom<16>::NT, false>(W.c);
+    if (id == 0 && threadIdx.x == 0) {
+        const float to_x = tag_apply(X.tag) ? g_x : __builtin_nanf(""), to_w = tag_apply(W.tag) ? g_w : __builtin_nanf("");
+        *X.c.g_out = to_x;
+        if (X.g_out2) *X.g_out2 = to_x;
+        *W.c.g_out = to_w;
+        if (W.g_out2) *W.g_out2 = to_w;
+    }
+    Chunk<NVFP4_BF16> v[16];
+    int tid;
+    auto next = [&](const DualArgs &D, int tx, int ty) {
+        tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        T.place(tid);
+        T.take(T.inside(D.c, tx, ty), v);
+        __syncthreads();  // (every wave has stored its share of the codes that the tile before left in lds)
+        id += gridDim.x;
+        if (id < tiles) request();
+    };
+    build_qtab<SF, true>(g_x);
+    while (id < tiles_x) {
+        const int tx = (int)(id % gx), ty = (int)(id / gx);
+        next(X, tx, ty);
+        dual_tile<NVFP4_BF16, B, SF, NVFP4_RTN, NVFP4_SR, 16>(X, v, g_x, 1.0f / (6.0f * g_x), tx, ty, tid, lds.codes, lds.scales);
+    }
+    __syncthreads();  // (the table of X is no longer read)
+    build_qtab<SF, true>(g_w);
+    while (id < tiles) {
+        const int tx = (int)((id - tiles_x) % gw), ty = (int)((id - tiles_x) / gw);
+        next(W, tx, ty);
+        dual_tile<NVFP4_BF16, B, SF, NVFP4_RTN, NVFP4_RTN, 16>(W, v, g_w, 1.0f / (6.0f * g_w), tx, ty, tid, lds.codes, lds.scales);
+    }
+}
+
 __global__ void saved_tag_kernel(TagArgs t, float *g1, float *g2)
 {
     if (!tag_apply(t)) {
@@ -1089,6 +1139,20 @@ static void launch_cols(const QuantArgs &P, hipStream_t st)
 // keep those of one tile.  Handing each workgroup tiles one below the other instead of 768 apart: 8192 x 8192 dual RtN+RtN 72.
 static bool streams(const QuantArgs &P) { return (P.cols & 7) == 0 && P.ld <= (1 << 22); }
 constexpr int64_t STREAM_ROW_MAJOR_TILES = 3072;
+// Right behind its maximum pass much of the tensor comes from the last-level cache, there is less latency to hide, and dual kernels with
+// stochastic rounding are bound by their arithmetic, for which four waves per SIMD are better than three.  us, one tile per workgroup /
+// streaming, maximum pass included:   RtN+RtN slabs   RtN+SR slabs   SR+SR slabs    columns RtN    columns SR
+//     2048 x 11008                    28.7 / 28.1     34.4 / 34.3    40.2 / 39.2    25.2 / 23.8    31.2 / 29.5
+//     4608 x  8192                    44.4 / 41.4     51.6 / 51.4    60.8 / 59.6    38.2 / 33.8    46.3 / 42.4
+//     4096 x 11008                    50.8 / 50.2     59.4 / 61.5    69.6 / 70.4    45.5 / 42.2    55.8 / 52.1
+//     8192 x  8192                    69.0 / 65.4     80.2 / 82.8    94.3 / 94.2    58.0 / 54.1    71.3 / 68.0
+//     8192 x 12288                    98.8 / 96.0      112 / 116      131 / 136     84.0 / 78.8     101 / 95.9
+constexpr int64_t STREAM_CACHED_SR_TILES = 1152;
+static bool streams_dual(const DualArgs &D, int rnd_c, int64_t tiles)
+{
+    const bool cached = D.c.g_mode != G_NONE && D.c.g_mode != G_PRESET;
+    return streams(D.c) && (D.slab_r || D.slab_c || tiles <= STREAM_ROW_MAJOR_TILES) && !(cached && rnd_c == NVFP4_SR && tiles > STREAM_CACHED_SR_TILES);
+}
 template <typename K, typename A>
 static void launch_stream(K kernel, const A &args, const QuantArgs &P, int lds, hipStream_t st)
 {
@@ -1175,7 +1239,7 @@ static void launch_dual_rpl(const DualArgs &D, hipStream_t st)
     const unsigned gx = (unsigned)((D.c.cols + 255) / 256), gy = (unsigned)((D.c.rows + 127) / 128);
     if (short_lane_tile(DT, B, SF, RND_R, RND_C, D.slab_r || D.slab_c ? DUAL_SLABS : DUAL, D.c.rows, D.c.cols))
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, 8>), dim3(gx, gy), dim3(ColGeom<8>::NT), 0, st, D);
-    else if (DT == NVFP4_BF16 && streams(D.c) && (D.slab_r || D.slab_c || (int64_t)gx * gy <= STREAM_ROW_MAJOR_TILES))
+    else if (DT == NVFP4_BF16 && streams_dual(D, RND_C, (int64_t)gx * gy))
         launch_stream(quantize_dual_stream_kernel<B, SF, RND_R, RND_C>, D, D.c, TileStream<DUAL_LDS_ROWS>::LDS_BYTES, st);
     else
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, LONG>), dim3(gx, gy), dim3(ColGeom<LONG>::NT), 0, st, D);
@@ -1258,6 +1322,17 @@ hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, i
     return launch_status();
 }
 
+template <int B, int SF>
+static void launch_dual_stream_pair(const DualArgs &x, const DualArgs &w, hipStream_t st)
+{
+    using G = ColGeom<16>;
+    auto across = [](const DualArgs &d) { return (unsigned)((d.c.cols + G::WG_COLS - 1) / G::WG_COLS); };
+    auto down = [](const DualArgs &d) { return (unsigned)((d.c.rows + G::WG_ROWS - 1) / G::WG_ROWS); };
+    const unsigned tiles_x = across(x) * down(x), tiles = tiles_x + across(w) * down(w);
+    hipLaunchKernelGGL((quantize_dual_stream_pair_kernel<B, SF>), dim3(tiles < 256 * STREAM_WGS ? tiles : 256 * STREAM_WGS), dim3(G::NT),
+                       TileStream<DUAL_LDS_ROWS>::LDS_BYTES, st, x, w, across(x), tiles_x, across(w), tiles);
+}
+
 template <int DT, int B, int SF>
 static void launch_dual_pair_fmt(const DualArgs &x, const DualArgs &w, hipStream_t st)
 {
@@ -1276,8 +1351,15 @@ hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int d
     }
     const int64_t tiles = ((x.c.rows + 127) / 128) * ((x.c.cols + 255) / 256) + ((w.c.rows + 127) / 128) * ((w.c.cols + 255) / 256);
     const bool nv = block == 16 && sf == NVFP4_SCALE_E4M3, mxf = block == 32 && sf == NVFP4_SCALE_E8M0;
-    if (tiles <= PAIR_TILES && (nv || mxf) && quantize_dual_fused(dt, x.c.rows, x.c.cols, x.c.ld, block, hw_convert) &&
-        quantize_dual_fused(dt, w.c.rows, w.c.cols, w.c.ld, block, hw_convert)) {
+    const bool fused = (nv || mxf) && quantize_dual_fused(dt, x.c.rows, x.c.cols, x.c.ld, block, hw_convert) &&
+                       quantize_dual_fused(dt, w.c.rows, w.c.cols, w.c.ld, block, hw_convert);
+    const bool slabs = (x.slab_r || x.slab_c) && (w.slab_r || w.slab_c);
+    if (fused && dt == NVFP4_BF16 && tiles > PAIR_TILES && tiles < ((int64_t)1 << 31) && (slabs || tiles <= STREAM_ROW_MAJOR_TILES) && streams(x.c) && streams(w.c)) {
+        if (nv) launch_dual_stream_pair<16, NVFP4_SCALE_E4M3>(x, w, st);
+        else launch_dual_stream_pair<32, NVFP4_SCALE_E8M0>(x, w, st);
+        return launch_status();
+    }
+    if (fused && tiles <= PAIR_TILES) {
         if (dt == NVFP4_BF16 && nv) launch_dual_pair_fmt<NVFP4_BF16, 16, NVFP4_SCALE_E4M3>(x, w, st);
         else if (dt == NVFP4_BF16) launch_dual_pair_fmt<NVFP4_BF16, 32, NVFP4_SCALE_E8M0>(x, w, st);
         else if (nv) launch_dual_pair_fmt<NVFP4_F32, 16, NVFP4_SCALE_E4M3>(x, w, st);

@@ -264,3 +264,24 @@ def test_weight_slabs_with_few_tokens(M, fmt_name):
     got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K, w_operands=wq)
     for a, b in zip(got, nv.linear_bwd(dY, X, W, seed, fmt)):
         assert torch.equal(a, b)
+
+
+# bf16 X and W of together more than 512 quantizer tiles (128 x 256) are one run of tiles over both tensors: the change from X to W in a
+# workgroup's first, second and third tile, tiles past the edges of both; row-major and slabs; the bits of the calls that quantize alone.
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("M,N,K", [(160, 8224, 4224), (2080, 4128, 4224), (12320, 288, 2176), (23328, 416, 2336)])
+def test_saved_operands_of_many_tiles(M, N, K, fmt_name):
+    seed = 11
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    X, W, dY = (torch.randn(s, generator=g, device="cuda").bfloat16() for s in ((M, K), (N, K), (M, N)))
+    W *= 0.02
+    print(f"[case] saved operands of many tiles {fmt_name} {M}x{N}x{K}", flush=True)
+    saved = torch.empty(nv.linear_saved_bytes(M, N, K, fmt), dtype=torch.uint8, device="cuda")
+    Y = nv.linear_fwd(X, W, fmt, saved=saved, bwd_seed=seed)
+    assert torch.equal(Y, nv.linear_fwd(X, W, fmt))
+    got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K)
+    for a, b in zip(got, nv.linear_bwd(dY, X, W, seed, fmt)):
+        assert torch.equal(a, b)
