@@ -210,7 +210,7 @@ __device__ __forceinline__ float chunk_amax_packed(const Chunk<DT> &c)
 // workgroup instead of a separate one-workgroup kernel between the maximum pass and the quantizer.
 // n_partials < 0: a small dense tensor (SELF_AMAX_BYTES), whose maximum every workgroup takes for itself.
 // SELF = false leaves that form out, in kernels that no such tensor reaches: beside a lane tile of 16 rows its loads in flight cost
-// the registers of a whole wave per SIMD (129 instead of 126: a columns pass, bf16 SR, over 4096 x 8192 30.1 us instead of 25.8, over
+// the registers of a whole wave per SIMD (129 instead of 126: a columns pass of one tile per workgroup, bf16 SR, over 4096 x 8192 30.1 us instead of 25.8, over
 // 8192 x 8192 53.0 instead of 51.6; 4096 x 11008, 1376 tiles, 1.8 rounds of three
 // workgroups per CU or 1.3 of four, took 41.9 instead of 43.7).  Binary32 chunks, twice the size, are four at a time, and kernels for E8M0 scales, whose formats have no tensor
 // scale, do without; neither changed a time (MXFP4 rows, bf16 SR, 4096 x 11008: 20.8 us both ways).
