@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     // the next LDS read.  Here the destination stage is not read before the explicit wait and the
     // barrier in stash().
     auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
     };
     const uint8_t *srow_ptr[NSR];
     int srow_step[NSR];  // bytes from one K tile's scales of the row to the next

@@ -137,7 +137,7 @@ __device__ __forceinline__ void ksplit_tile(const GemmArgs &P, const int wg)
     };
     // inline assembly for the reason given in gemm.hip: the stage is read only after the explicit wait below
     auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
     };
     uint64_t gs[NSR];  // the fetched K tile's scale bytes of this lane's rows
     auto fetch = [&](int kt, int stage) {

@@ -281,7 +281,13 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
     const uint32_t scale_dst = __builtin_amdgcn_readfirstlane(lds0 + SCALES0 + wave * 1024);
     const uint32_t dump_dst = __builtin_amdgcn_readfirstlane(lds0 + DUMP0 + wave * 1024);
     auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
+    };
+    // dma16_chosen: for an address that was selected right before.  The compiler selects 64-bit values in vector registers and reads the
+    // lane back, and the load has to come five wait states after that read, which the compiler does not put into inline assembly.
+    // (tests/test_device_code.py has every such load's distance; waiting at all of them costs the small MXFP4 products 3 %.)
+    auto dma16_chosen = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
     };
     // codes of K tile kt: tile + kt * step (row-major: 64 bytes further along every row; slabs: the next 16 KB slab)
     const uint8_t *tileA = A_SLAB ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
     auto group_start = [&](int G) -> int { return 16 * G + 16 <= Ks ? 16 * G : (int)Ks - 16; };
     // keeps the number of loads per tile constant (the counted waits rely on it): one request, lands in the dump
     // (the first bytes of A's codes: a valid address in both layouts)
-    auto dma_filler = [&]() { dma16(dump_dst, 0u, uniform_ptr(tileA)); };
+    auto dma_filler = [&]() { dma16_chosen(dump_dst, 0u, uniform_ptr(tileA)); };
     // row-major scales, group G.  part 0: this wave's 64 A rows, part 1: its 64 B rows
     auto dma_scales = [&](int G, int part) {
         if ((part == 0 && A_SLAB) || (part == 1 && B_SLAB)) {
@@ -312,7 +318,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
             return;
         }
         const uint8_t *base = (part ? tileSB : tileSA) + group_start(G);
-        dma16(scale_dst + (G & 1) * SBUF + part * (BM * 16), part ? offSB : offSA, uniform_ptr(base));
+        dma16_chosen(scale_dst + (G & 1) * SBUF + part * (BM * 16), part ? offSB : offSA, uniform_ptr(base));
     };
     // scale slabs of K tile kt (real: kt < nkt): wave 0 fetches A's, wave 1 B's, 16 bytes per lane, into stage
     // kt % 4 of that operand's part of the first scale buffer; the other waves (and a wave whose operand is
@@ -322,7 +328,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
     auto dma_scale_slab = [&](int kt, bool real) {
         const bool go = slab_loader && real;
         const uint8_t *base = go ? (wave == 0 ? tileSA : tileSB) + (int64_t)kt * SLAB_MX_SCALE_BYTES : tileA;
-        dma16(go ? slab_scale_dst + (uint32_t)(kt & (NS - 1)) * 1024 : dump_dst, go ? (uint32_t)lane * 16 : 0u, uniform_ptr(base));
+        dma16_chosen(go ? slab_scale_dst + (uint32_t)(kt & (NS - 1)) * 1024 : dump_dst, go ? (uint32_t)lane * 16 : 0u, uniform_ptr(base));
     };
 
     // ---- LDS -> registers
@@ -566,7 +572,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(Gem
         return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
     };
     auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
     };
     auto dma_codes = [&](int kt, uint32_t stage) {
         const uint8_t *const pa = uniform_ptr(baseA + kt * stepA), *const pb = uniform_ptr(baseB + kt * stepB);

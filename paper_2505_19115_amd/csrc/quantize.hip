@@ -575,7 +575,7 @@ struct TileStream {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             if (r < LR)
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds_wave + r * 1024), "v"(off * 2u), "s"(base) : "memory");
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(lds_wave + r * 1024), "v"(off * 2u), "s"(base) : "memory", "m0");
             else
                 rest[r < LR ? 0 : r - LR].template load<true>(base, off);
             base += P.ld;

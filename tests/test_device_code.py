@@ -46,6 +46,47 @@ def registers(source, tmp):
     return {name: (int(v), int(s)) for name, v, s in found}
 
 
+def unwaited_loads(asm):
+    """(number of direct-to-LDS loads, the kernels of those whose address registers a lane read wrote fewer than five wait states before)."""
+    kernel, before, loads, unwaited = "", [], 0, []
+    for line in asm.splitlines():
+        head = re.match(r"^[0-9a-f]+ <(.*)>:", line)
+        if head:
+            kernel, before = head.group(1), []
+            continue
+        ins = line.split("//")[0].strip()
+        if not ins:
+            continue
+        if ins.startswith("global_load_lds"):
+            loads += 1
+            first, last = map(int, re.search(r"s\[(\d+):(\d+)\]", ins).groups())
+            states = 0
+            for prev in reversed(before):
+                if states >= 5:
+                    break
+                written = re.match(r"v_read(?:first)?lane_b32 s(\d+)", prev)
+                if written and first <= int(written.group(1)) <= last:
+                    unwaited.append(kernel)
+                    break
+                states += int(prev.split()[1]) + 1 if prev.startswith("s_nop") else 1
+        before = before[-5:] + [ins]
+    return loads, unwaited
+
+
+def test_unwaited_loads_are_found():
+    text = "0000 <k>:\n v_readfirstlane_b32 s1, v3\n s_mov_b32 m0, s28\n s_nop {}\n global_load_lds_dwordx4 v4, s[0:1]\n"
+    assert unwaited_loads(text.format(2)) == (1, ["k"]) and unwaited_loads(text.format(3)) == (1, [])
+
+
+# A scalar register that a vector instruction wrote may be the address of a vector memory instruction five wait states later.  The compiler
+# keeps that by itself, but not for the loads in inline assembly, whose own first instructions have to be the wait.
+@pytest.mark.parametrize("source", ["quantize", "gemm", "gemm_mx", "gemm_ksplit"])
+def test_direct_loads_wait_for_their_address(source, tmp_path):
+    asm = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", code_object(source, tmp_path)], capture_output=True, text=True, check=True).stdout
+    loads, unwaited = unwaited_loads(asm)
+    assert loads > 0 and not unwaited
+
+
 @pytest.mark.parametrize("source", ["gemm", "gemm_mx", "gemm_ksplit"])
 def test_gemm_outputs_leave_in_whole_pieces(source, tmp_path):
     # A 16-byte piece whose store the compiler has split (its last word shared with the form for cut pieces) goes out as 12 + 4 bytes:
