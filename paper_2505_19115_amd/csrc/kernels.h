@@ -130,11 +130,12 @@ bool tensor_amax_partials_only(int64_t rows, int64_t cols);
 hipError_t launch_tensor_amax_strided(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld, uint32_t *partials, int *n, hipStream_t st);
 hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, int block, int sf,
                            bool hw_convert, hipStream_t st);
-// Tensors that quantize_small.hip serves (its kernel splits them finer): one orientation of one or two tensors, and both
-// orientations of one tensor or of a forward call's X and W (W round to nearest).  Row-major outputs.
+// Tensors that quantize_small.hip serves (its kernels split them finer): rows of one tensor or of two (P1: both round to nearest), columns
+// of one, and both orientations of one tensor or of a forward call's X and W (W round to nearest).  Row-major outputs.
 enum SmallUse { SMALL_ROWS, SMALL_COLUMNS, SMALL_DUAL };
 bool small_tensor(int dt, const QuantArgs &P, int block, bool hw_convert, SmallUse use);
-hipError_t launch_quantize_small(const QuantArgs &P, const QuantArgs *P1, int dt, int axis, int rounding, int block, int sf, hipStream_t st);
+hipError_t launch_quantize_small_rows(const QuantArgs &P, const QuantArgs *P1, int dt, int rounding, int block, int sf, hipStream_t st);
+hipError_t launch_quantize_small_columns(const QuantArgs &P, int dt, int rounding, int block, int sf, hipStream_t st);
 hipError_t launch_quantize_small_dual(const DualArgs &D, const DualArgs *W, int dt, int rnd_r, int rnd_c, int block, int sf, hipStream_t st);
 // Row-blocked and column-blocked quantization of one tensor; one fused kernel when
 // quantize_dual_fused() holds, else the two single-orientation kernels.

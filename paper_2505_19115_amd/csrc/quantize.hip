@@ -1223,7 +1223,8 @@ static void launch_q_fmt(const QuantArgs &P, int axis, int rounding, int block, 
 hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, int block, int sf,
                            bool hw_convert, hipStream_t st)
 {
-    if (small_tensor(dt, P, block, hw_convert, axis == 1 ? SMALL_ROWS : SMALL_COLUMNS)) return launch_quantize_small(P, nullptr, dt, axis, rounding, block, sf, st);
+    if (axis == 1 && small_tensor(dt, P, block, hw_convert, SMALL_ROWS)) return launch_quantize_small_rows(P, nullptr, dt, rounding, block, sf, st);
+    if (axis == 0 && small_tensor(dt, P, block, hw_convert, SMALL_COLUMNS)) return launch_quantize_small_columns(P, dt, rounding, block, sf, st);
     if (dt == NVFP4_BF16)
         launch_q_fmt<NVFP4_BF16>(P, axis, rounding, block, sf, hw_convert, st);
     else
@@ -1384,7 +1385,7 @@ static void launch_rows_pair_dt(const QuantArgs &a, const QuantArgs &b, int bloc
 hipError_t launch_quantize_rows_pair(const QuantArgs &a, const QuantArgs &b, int dt, int block, int sf, bool hw_convert, hipStream_t st)
 {
     if (small_tensor(dt, a, block, hw_convert, SMALL_ROWS) && small_tensor(dt, b, block, hw_convert, SMALL_ROWS))
-        return launch_quantize_small(a, &b, dt, 1, NVFP4_RTN, block, sf, st);
+        return launch_quantize_small_rows(a, &b, dt, NVFP4_RTN, block, sf, st);
     auto wgs = [](const QuantArgs &P) { return (P.rows * (P.cols >> 3) + 256 * ROWS_UNROLL - 1) / (256 * ROWS_UNROLL); };
     if (hw_convert && wgs(a) + wgs(b) < ((int64_t)1 << 31) && (sf == NVFP4_SCALE_E4M3 || block == 32)) {
         const unsigned wa = (unsigned)wgs(a), wb = (unsigned)wgs(b);

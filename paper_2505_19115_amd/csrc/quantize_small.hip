@@ -1,4 +1,4 @@
-// Quantizer kernel for small tensors (small_tensor()): one or two tensors, one or both orientations, in one launch.
+// Quantizer kernels for small tensors (small_tensor()): columns or both orientations of one or two tensors, and rows, in one launch.
 #include <type_traits>
 
 #include "quantize_tile.h"
@@ -129,6 +129,30 @@ __global__ __launch_bounds__(SMALL_NT) void quantize_small_kernel(SmallJob j0, S
     }
 }
 
+// Rows of one tensor, or of two (round to nearest; the first `wgs` workgroups take the first), by themselves: a chunk per lane as above.  At
+// 2-3 us what counts is what a launch brings along, so these have neither the other kernel's four jobs nor its 16 or 32 KB of LDS.  GPU
+// time, us, bf16 RtN / SR, the kernel with four chunks per thread / the jobs kernel / this one:
+//              NVFP4                                          NVFP4, scale preset                           MXFP4
+//      1 x 64  2.62 / 3.04 / 2.36   3.32 / 3.28 / 2.53        2.00 / 2.37 / 1.86   2.73 / 2.59 / 1.91       1.85 / 2.13 / 1.82   2.46 / 2.41 / 1.86
+//     64 x 256 3.33 / 3.36 / 2.87   3.88 / 3.56 / 3.01        2.75 / 2.55 / 2.13   3.30 / 2.74 / 2.24       2.14 / 2.25 / 1.99   2.80 / 2.59 / 2.06
+//   1024 x 512 5.85 / 5.61 / 5.03   6.37 / 5.84 / 5.31        2.95 / 2.64 / 2.20   3.49 / 2.93 / 2.45       2.51 / 2.34 / 2.03   3.07 / 2.76 / 2.35
+// (workgroups of 256: 16 x 4096 NVFP4 4.3 instead of 3.8, which take the maximum of the whole tensor in each; elsewhere alike.)
+template <int DT, int B, int SF, int RND>
+__global__ __launch_bounds__(SMALL_NT) void quantize_small_rows_kernel(QuantArgs P)
+{
+    const float g = rows_tile<DT, B, SF, RND, true, SMALL_NT, 1>(P, blockIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *P.g_out = g;
+}
+template <int DT, int B, int SF>
+__global__ __launch_bounds__(SMALL_NT) void quantize_small_rows_pair_kernel(QuantArgs P0, QuantArgs P1, unsigned wgs)
+{
+    const bool first = blockIdx.x < wgs;
+    const QuantArgs &P = first ? P0 : P1;
+    const unsigned wg = first ? blockIdx.x : blockIdx.x - wgs;
+    const float g = rows_tile<DT, B, SF, NVFP4_RTN, true, SMALL_NT, 1>(P, wg);
+    if (wg == 0 && threadIdx.x == 0) *P.g_out = g;
+}
+
 // ------------------------------------------------------------------ host side
 
 // Tensors that go through quantize_small_kernel, in elements.  Its lanes reload nothing and share nothing between the orientations, so a
@@ -141,7 +165,8 @@ __global__ __launch_bounds__(SMALL_NT) void quantize_small_kernel(SmallJob j0, S
 //   2080 x 2784     5.7 / 6.6    9.8 / 7.5   12.0 / 8.2   12.4 / 11.6  16.5 / 12.7      7.3 / 7.2   12.0 / 8.3   11.9 / 13.3  15.6 / 14.7
 //   2048 x 4096     6.6 / 8.6    9.2 / 8.5   11.0 / 9.4   11.6 / 13.6  15.6 / 15.6      9.0 / 9.7   11.6 / 9.9   11.5 / 18.5  14.9 / 19.4
 //   4096 x 4096     9.8 / 14.8  11.4 / 15.2  15.6 / 15.8  15.1 / 28.0  22.5 / 31.4     15.6 / 17.8  19.6 / 18.5  20.1 / 35.5  22.0 / 36.2
-// (MXFP4: the same lines, columns SR of 4096 x 4096 binary32 21.9 / 16.2.)
+// (MXFP4: the same lines, columns SR of 4096 x 4096 binary32 21.9 / 16.2.  The rows as jobs of the columns' kernel; by themselves, as they
+// are launched now, 0.4 us less.)
 bool small_tensor(int dt, const QuantArgs &P, int block, bool hw, SmallUse use)
 {
     const bool bf16 = dt == NVFP4_BF16;
@@ -185,10 +210,32 @@ static hipError_t launch_small(const SmallJob (&j)[4], int dt, int block, int sf
     return hipGetLastError();
 }
 
-hipError_t launch_quantize_small(const QuantArgs &P, const QuantArgs *P1, int dt, int axis, int rounding, int block, int sf, hipStream_t st)
+template <int DT, int B, int SF>
+static void launch_small_rows(const QuantArgs &P, const QuantArgs *P1, int rounding, hipStream_t st)
 {
-    SmallJob j[4] = {small_job(P, axis, rounding, block)};
-    if (P1) j[1] = small_job(*P1, axis, rounding, block);
+    const unsigned w0 = small_job(P, 1, rounding, B).wgs, w1 = P1 ? small_job(*P1, 1, rounding, B).wgs : 0;
+    if (P1) hipLaunchKernelGGL((quantize_small_rows_pair_kernel<DT, B, SF>), dim3(w0 + w1), dim3(SMALL_NT), 0, st, P, *P1, w0);
+    else if (rounding == NVFP4_RTN) hipLaunchKernelGGL((quantize_small_rows_kernel<DT, B, SF, NVFP4_RTN>), dim3(w0), dim3(SMALL_NT), 0, st, P);
+    else hipLaunchKernelGGL((quantize_small_rows_kernel<DT, B, SF, NVFP4_SR>), dim3(w0), dim3(SMALL_NT), 0, st, P);
+}
+template <int DT>
+static void launch_small_rows_dt(const QuantArgs &P, const QuantArgs *P1, int rounding, int block, int sf, hipStream_t st)
+{
+    if (block == 16 && sf == NVFP4_SCALE_E4M3) launch_small_rows<DT, 16, NVFP4_SCALE_E4M3>(P, P1, rounding, st);
+    else if (block == 16) launch_small_rows<DT, 16, NVFP4_SCALE_E8M0>(P, P1, rounding, st);
+    else if (sf == NVFP4_SCALE_E4M3) launch_small_rows<DT, 32, NVFP4_SCALE_E4M3>(P, P1, rounding, st);
+    else launch_small_rows<DT, 32, NVFP4_SCALE_E8M0>(P, P1, rounding, st);
+}
+hipError_t launch_quantize_small_rows(const QuantArgs &P, const QuantArgs *P1, int dt, int rounding, int block, int sf, hipStream_t st)
+{
+    if (dt == NVFP4_BF16) launch_small_rows_dt<NVFP4_BF16>(P, P1, rounding, block, sf, st);
+    else launch_small_rows_dt<NVFP4_F32>(P, P1, rounding, block, sf, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_quantize_small_columns(const QuantArgs &P, int dt, int rounding, int block, int sf, hipStream_t st)
+{
+    const SmallJob j[4] = {small_job(P, 0, rounding, block)};
     return launch_small(j, dt, block, sf, st);
 }
 

@@ -125,3 +125,11 @@ def test_resident_workgroups_of_the_quantizers(tmp_path):
     for (dt, b, sf, rnd, hw), v, s in kernels(regs, "quantize_rows_kernel"):
         if not (dt == 0 and sf == 1 and rnd == 1):
             assert v <= 64 and s == 0, ("rows", dt, b, sf, rnd, hw, v, s)
+
+
+def test_rows_of_small_tensors_bring_little_along(tmp_path):
+    # 2 us of row quantization: with the LDS and the four jobs of the kernel for both orientations, decode calls took 0.4 us longer
+    notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object("quantize_small", tmp_path)], capture_output=True, text=True, check=True).stdout
+    rows = [int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", k).group(1)) for k in notes.split("  - .agpr_count") if "quantize_small_rows" in k]
+    assert len(rows) == 2 * 4 * 3  # (element types, formats; round to nearest, stochastic, two tensors)
+    assert max(rows) <= 1024
