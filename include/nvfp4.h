@@ -451,6 +451,8 @@ uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent 
  * matters): rows * 65536 + columns of the output; 0 for sizes below 1 or a bad format.  Not a promise: the rule follows
  * measurements. */
 int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
+/* Into how many parts the waves of that tile's workgroup divide the contraction (1: not at all); 0 as above. */
+int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* array forms: n inputs -> n outputs (host pointers) */
 void nvfp4_host_e4m3_encode_n(const float *r, int64_t n, uint8_t *out);
 void nvfp4_host_round_rtn_n(const float *m, int64_t n, uint8_t *out);

@@ -603,6 +603,12 @@ int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
     return rows << 16 | cols;
 }
 
+int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
+{
+    if (check_format(f) != NVFP4_OK || M <= 0 || N <= 0 || K <= 0) return 0;
+    return gemm_tile_split(choose_gemm_tile(M, N, K, f->scale));
+}
+
 size_t nvfp4_slab_codes_bytes(int64_t rows, int64_t K)
 {
     return rows <= 0 || K <= 0 ? 0 : (size_t)slab_rows_padded(rows) * (size_t)K / 2;

@@ -565,6 +565,11 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         if (c.bm == 0) continue;  // (not built)
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         if (tiles * c.threads > 0xFFFFFFFF) continue;  // (the threads of a launch are counted in 32 bits)
+        // (the four-group tiles hold a whole CU each: beyond one round of them their times lie up to 12 % below and 23 % above the estimate's
+        // other choice.  us, that choice / 96 x 128 with four groups: 1376 x 2432 x 12032, one round of 128 x 128, 99.6 / 81.6; two rounds
+        // 6464 x 800 x 9856 139.1 / 127.2, 3072 x 1792 x 8256 102.2 / 121.7, 2377 x 1793 x 7552 with blocks of 64 92.9 / 109.2; three
+        // 1280 x 6816 x 5760 103.3 / 118.8, 1381 x 5979 x 8800 167.4 / 202.9)
+        if ((t == TILE_96x128_K4 || t == TILE_128x128_K4) && tiles > 256) continue;
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
         if (rounds == 1) time *= 1.0 + 0.01 * c.alone;
@@ -583,6 +588,8 @@ void gemm_tile_size(GemmTile t, int *rows, int *cols)
     *rows = c.bm;
     *cols = c.bn;
 }
+
+int gemm_tile_split(GemmTile t) { return E4M3_COST[t].bm ? E4M3_COST[t].kwaves : E8M0_COST[t].kwaves; }
 
 static int g_fp4_rescale_route = 0;  // (measured slower than the fp16 route: opt-in)
 void set_fp4_rescale_route(int on) { g_fp4_rescale_route = on; }

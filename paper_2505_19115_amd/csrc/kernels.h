@@ -167,6 +167,7 @@ hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, i
 enum GemmTile { TILE_32x32, TILE_32x64, TILE_64x32, TILE_64x64, TILE_96x128_K4, TILE_128x128, TILE_128x128_K4, TILE_128x256, TILE_192x256, TILE_256x128, TILE_256x256, TILES };
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf);
 void gemm_tile_size(GemmTile t, int *rows, int *cols);
+int gemm_tile_split(GemmTile t);  // parts into which the waves of its workgroup divide the contraction
 hipError_t launch_gemm_ksplit(const GemmArgs &P, const GemmArgs *P1, GemmTile tile, int block, int sf, int out_dt, hipStream_t st);
 hipError_t launch_gemm_mxfp4(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
 // E4M3 scales at blocks of 64 / 128 as unit-scale FP4 MFMAs per block + binary32 rescale (row-major operands, K % 128 == 0)

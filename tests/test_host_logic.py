@@ -331,6 +331,17 @@ def test_gemm_tile_rule():
     assert nv.gemm_tile(2048, 4096, 4096, MX) == (128, 128) and nv.gemm_tile(2048, 4096, 11008, MX) == (128, 128)
 
 
+def test_four_group_tiles_take_one_round():
+    four = lambda M, N, K: nv.gemm_split(M, N, K, nv.NVFP4) == 4 and nv.gemm_tile(M, N, K, nv.NVFP4) in ((96, 128), (128, 128))
+    for M, N, K in ((1056, 2080, 2784), (1536, 1536, 6144), (1376, 2432, 12032), (704, 4832, 4992), (192, 11424, 2432)):
+        assert four(M, N, K), (M, N, K)
+    # with more than one workgroup per CU they were slower than the tile without groups by as much as 23 %
+    for M, N, K in ((3072, 1792, 8256), (2377, 1793, 7552), (1968, 2752, 6720), (1280, 6816, 5760), (1381, 5979, 8800), (2400, 3680, 11392),
+                    (672, 11008, 4096), (3355, 5317, 10016)):
+        assert not four(M, N, K), (M, N, K)
+    assert nv.gemm_split(16, 4096, 4096) == 8 and nv.gemm_split(4096, 4096, 4096) == 1 and nv.gemm_split(0, 1, 1) == 0
+
+
 def test_no_tile_beyond_the_launch_limit():
     # a launch counts its threads in 32 bits, and no product that one of the tiles can serve may be given one that cannot
     threads = {(32, 32): 512, (32, 64): 512, (64, 32): 512, (64, 64): 256, (128, 128): 256, (128, 256): 512, (192, 256): 512,
