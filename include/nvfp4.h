@@ -453,6 +453,10 @@ uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent 
 int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* Into how many parts the waves of that tile's workgroup divide the contraction (1: not at all); 0 as above. */
 int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
+/* 1 if nvfp4_quantize down the columns (both = 0) or nvfp4_quantize_dual (both = 1) of a bf16 tensor walks its tiles with
+ * resident workgroups, the next tile in flight (flags as in those calls; rounding_rows counts for both = 1).  Not a promise. */
+int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols,
+                                const nvfp4_format *f, uint32_t flags);
 /* array forms: n inputs -> n outputs (host pointers) */
 void nvfp4_host_e4m3_encode_n(const float *r, int64_t n, uint8_t *out);
 void nvfp4_host_round_rtn_n(const float *m, int64_t n, uint8_t *out);

@@ -609,6 +609,17 @@ int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f
     return gemm_tile_split(choose_gemm_tile(M, N, K, f->scale));
 }
 
+int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols, const nvfp4_format *f, uint32_t flags)
+{
+    if (check_format(f) != NVFP4_OK || rows <= 0 || cols <= 0 || ld < cols) return 0;
+    QuantArgs P;
+    P.rows = rows;
+    P.cols = cols;
+    P.ld = ld;
+    const bool slabs = both && (flags & (NVFP4_SLAB_ROWS | NVFP4_SLAB_COLS)), cached = f->tensor_scale && !(flags & NVFP4_PRESET_TSCALE);
+    return quantize_streams(P, f->block, f->scale, both != 0, rounding_rows, rounding_cols, slabs, cached, use_hw_convert()) ? 1 : 0;
+}
+
 size_t nvfp4_slab_codes_bytes(int64_t rows, int64_t K)
 {
     return rows <= 0 || K <= 0 ? 0 : (size_t)slab_rows_padded(rows) * (size_t)K / 2;

@@ -130,6 +130,9 @@ bool tensor_amax_partials_only(int64_t rows, int64_t cols);
 hipError_t launch_tensor_amax_strided(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld, uint32_t *partials, int *n, hipStream_t st);
 hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, int block, int sf,
                            bool hw_convert, hipStream_t st);
+// Whether the resident workgroups of a streaming kernel walk this bf16 tensor (columns, or both orientations); cached: right behind its
+// maximum pass.
+bool quantize_streams(const QuantArgs &P, int block, int sf, bool both, int rnd_r, int rnd_c, bool slabs, bool cached, bool hw_convert);
 // Tensors that quantize_small.hip serves (its kernels split them finer): rows of one tensor or of two (P1: both round to nearest), columns
 // of one, and both orientations of one tensor or of a forward call's X and W (W round to nearest).  Row-major outputs.
 enum SmallUse { SMALL_ROWS, SMALL_COLUMNS, SMALL_DUAL };

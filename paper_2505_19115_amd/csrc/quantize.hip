@@ -1124,8 +1124,8 @@ static void launch_cols(const QuantArgs &P, hipStream_t st)
     hipLaunchKernelGGL((quantize_cols_kernel<DT, B, SF, RND, HW, ALIGNED, RPL>), grid, dim3(G::NT), 0, st, P);
 }
 
-// bf16 tensors of more than 512 workgroup tiles go through the streaming kernels (their lane tiles are whole, and the byte offset of a row
-// inside a workgroup tile has 32 bits).  us, one tile per workgroup with 16 rows per lane / streaming, scale preset:
+// bf16 tensors of more than 512 workgroup tiles may go through the streaming kernels (their lane tiles are whole, and the byte offset of a
+// row inside a workgroup tile has 32 bits).  us, NVFP4, one tile per workgroup with 16 rows per lane / streaming, scale preset:
 //                     columns                      dual, row-major                            dual, slabs
 //                     RtN          SR              RtN+RtN       RtN+SR        SR+SR           RtN+RtN       RtN+SR        SR+SR
 //     3072 x  6144    17.1 / 15.0  22.9 / 16.6     21.8 / 17.3   27.8 / 22.6   33.8 / 28.5     (host)        27.5 / 23.0   33.1 / 28.0
@@ -1135,9 +1135,50 @@ static void launch_cols(const QuantArgs &P, hipStream_t st)
 //     8192 x 12288    68.9 / 60.5  82.8 / 68.0     85.3 / 83.9   94.9 / 93.3   111 / 107       74.4 / 65.2   88.0 / 84.6   109 / 104
 //    16384 x  8192    84.8 / 81.6  104 / 87.9      110 / 114     124 / 123     143 / 138       97.4 / 86.0   116 / 109     138 / 135
 //    16384 x 12288     129 / 126   150 / 133       164 / 170     176 / 176     199 / 203       142 / 128     161 / 156     189 / 191
-// (MXFP4 alike.)  Above 3072 tiles row-major duals have many generations of workgroups, whose phases drift apart by themselves, and
-// keep those of one tile.  Handing each workgroup tiles one below the other instead of 768 apart: 8192 x 8192 dual RtN+RtN 72.
+// The same in MXFP4:
+//     3072 x  6144    17.9 / 16.0  20.1 / 16.0     22.9 / 19.3   27.0 / 22.4   33.6 / 27.6     (host)        26.8 / 26.1   32.7 / 27.9
+//     4096 x 11008    34.1 / 29.1  37.8 / 34.3     43.8 / 40.6   50.1 / 42.9   58.9 / 52.0     40.2 / 33.5   47.4 / 39.5   57.3 / 50.2
+//     8192 x  8192    43.4 / 42.2  48.6 / 46.1     58.3 / 56.4   62.9 / 54.7   72.1 / 64.4     51.3 / 47.9   58.7 / 50.1   70.9 / 62.9
+//    16384 x 12288     126 / 126   129 / 129       169 / 168     181 / 182     193 / 192       137 / 130     156 / 141     182 / 177
+// Handing each workgroup tiles one below the other instead of 768 apart: 8192 x 8192 dual RtN+RtN 72.
+// Sizes between these have cut tiles, row pitches and rounds of all kinds.  Streaming / one tile per workgroup, mean over 10 to 50 random
+// shapes each (preset: scale given or none, the tensor comes from memory; cached: right behind its maximum pass):
+//     tiles                        513-768  -1024  -1152  -1536  -2048  -3072  -4096  -5000
+//     columns RtN  NVFP4  preset      1.00   1.06   0.86   0.93   0.98   0.98   1.04   1.08
+//                         cached      0.99   1.04   0.91   0.96   0.99   0.97   0.96   0.98
+//                  MXFP4              0.97   1.06   0.86   0.94   1.02   1.03   1.08   1.13
+//              E4M3, 64   preset      1.06   1.09   1.10   1.02   1.05   1.10   1.17   1.24
+//                         cached      1.02   1.03   0.99   0.99   0.99   1.01   1.05   1.07
+//              E8M0, 16               1.00   1.04   0.96   1.01   1.03   1.05   1.07   1.09
+//     columns SR   NVFP4  preset      0.83   0.89   0.78   0.86   0.97   0.94   0.98   1.03
+//                         cached      0.92   0.96   0.88   0.90   1.00   0.95   0.95   0.93
+//                  MXFP4              0.87   0.94   0.87   0.95   0.96   1.01   1.06   1.05
+//              E4M3, 64   preset      0.85   0.90   0.82   0.88   0.97   1.04   1.09   1.18
+//                         cached      0.93   0.96   0.89   0.94   0.98   0.95   0.94   0.95
+//         rows 64 beyond 128 preset   0.92   1.03   0.98   1.02   1.15
+//                         cached      0.93   0.99   0.92   1.01   1.10   1.10   1.15   1.15
+//     RtN+RtN rows NVFP4  preset      0.88   1.04   0.84   0.93   1.01   1.01
+//                         cached      0.96   0.99   0.89   0.95   0.99   0.97
+//                  MXFP4              1.03   1.07   0.91   0.95   0.98   0.99
+//     RtN+SR rows  MXFP4              0.84   0.94   0.84   0.93   0.96   0.97
+//     RtN+RtN slabs NVFP4 preset      0.99   1.03   0.83   0.90   0.94   0.92   0.93   0.95
+//                  MXFP4              0.99   1.02   0.89   0.90   0.97   0.95   0.98   0.98
+//     (slabs with stochastic rounding, MXFP4: 0.83 to 0.99 in every column)
+// One tile per workgroup holds 1024 at once and is in its first round up to there, streaming holds 768.  Wide blocks leave their scale
+// bytes one by one, with rows of an odd multiple of 64 each run of codes cuts two lines, and a walk waits for its stores.  With many
+// tiles one workgroup's phases drift apart from the next one's by themselves.
 static bool streams(const QuantArgs &P) { return (P.cols & 7) == 0 && P.ld <= (1 << 22); }
+static bool behind_maximum(const QuantArgs &P) { return P.g_mode != G_NONE && P.g_mode != G_PRESET; }
+static int64_t workgroup_tiles(int64_t rows, int64_t cols) { return ((rows + 127) / 128) * ((cols + 255) / 256); }
+constexpr int64_t ONE_ROUND_TILES = 1024, STREAM_ROUND_TILES = 768;
+constexpr bool columns_streamable(int block, int sf, int rnd) { return rnd == NVFP4_SR || (block <= 32 && !(block == 16 && sf == NVFP4_SCALE_E8M0)); }
+static bool streams_columns(const QuantArgs &P, int block, int sf, int rnd, bool cached)
+{
+    const int64_t tiles = workgroup_tiles(P.rows, P.cols);
+    if (!columns_streamable(block, sf, rnd) || !streams(P)) return false;
+    if (rnd == NVFP4_SR) return (block <= 32 || P.rows % 128 == 0) && (cached || tiles <= (sf == NVFP4_SCALE_E4M3 && block <= 32 ? 4096 : 2048));
+    return (tiles <= STREAM_ROUND_TILES || tiles > ONE_ROUND_TILES) && (cached || tiles <= (sf == NVFP4_SCALE_E4M3 ? 2048 : 1536));
+}
 constexpr int64_t STREAM_ROW_MAJOR_TILES = 3072;
 // Right behind its maximum pass much of the tensor comes from the last-level cache, there is less latency to hide, and dual kernels with
 // stochastic rounding are bound by their arithmetic, for which four waves per SIMD are better than three.  us, one tile per workgroup /
@@ -1148,10 +1189,22 @@ constexpr int64_t STREAM_ROW_MAJOR_TILES = 3072;
 //     8192 x  8192                    69.0 / 65.4     80.2 / 82.8    94.3 / 94.2    58.0 / 54.1    71.3 / 68.0
 //     8192 x 12288                    98.8 / 96.0      112 / 116      131 / 136     84.0 / 78.8     101 / 95.9
 constexpr int64_t STREAM_CACHED_SR_TILES = 1152;
-static bool streams_dual(const DualArgs &D, int rnd_c, int64_t tiles)
+static bool streams_dual(const QuantArgs &P, int block, int sf, int rnd_c, bool slabs, bool cached)
 {
-    const bool cached = D.c.g_mode != G_NONE && D.c.g_mode != G_PRESET;
-    return streams(D.c) && (D.slab_r || D.slab_c || tiles <= STREAM_ROW_MAJOR_TILES) && !(cached && rnd_c == NVFP4_SR && tiles > STREAM_CACHED_SR_TILES);
+    const int64_t tiles = workgroup_tiles(P.rows, P.cols);
+    if (!streams(P) || (cached && rnd_c == NVFP4_SR && tiles > STREAM_CACHED_SR_TILES)) return false;
+    if (slabs) return rnd_c == NVFP4_SR || cached || tiles <= STREAM_ROUND_TILES || tiles > ONE_ROUND_TILES;
+    // (blocks of 16 with E8M0 scales: the kernel of one tile takes too many registers for 1024 at once, 0.83 in that column)
+    const bool one_round = tiles <= ONE_ROUND_TILES && !(block == 16 && sf == NVFP4_SCALE_E8M0);
+    if (rnd_c == NVFP4_RTN && (tiles > STREAM_ROUND_TILES ? one_round : sf == NVFP4_SCALE_E8M0)) return false;
+    return tiles <= STREAM_ROW_MAJOR_TILES;
+}
+bool quantize_streams(const QuantArgs &P, int block, int sf, bool both, int rnd_r, int rnd_c, bool slabs, bool cached, bool hw_convert)
+{
+    if (!hw_convert || short_lane_tile(NVFP4_BF16, block, sf, rnd_r, rnd_c, COLUMNS, P.rows, P.cols)) return false;
+    if (!both) return !small_tensor(NVFP4_BF16, P, block, true, SMALL_COLUMNS) && streams_columns(P, block, sf, rnd_c, cached);
+    return (slabs || !small_tensor(NVFP4_BF16, P, block, true, SMALL_DUAL)) && quantize_dual_fused(NVFP4_BF16, P.rows, P.cols, P.ld, block, true) &&
+           !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN) && streams_dual(P, block, sf, rnd_c, slabs, cached);
 }
 template <typename K, typename A>
 static void launch_stream(K kernel, const A &args, const QuantArgs &P, int lds, hipStream_t st)
@@ -1176,12 +1229,10 @@ static void launch_q(const QuantArgs &P, int axis, hipStream_t st)
             launch_cols<DT, B, SF, RND, HW, RND == NVFP4_RTN, 16>(P, st);
         else if (HW && short_lane_tile(DT, B, SF, RND, RND, COLUMNS, P.rows, P.cols))
             launch_cols<DT, B, SF, RND, HW, true, HW ? 8 : 16>(P, st);
-        else if constexpr (HW && DT == NVFP4_BF16 && RND == NVFP4_SR) {
-            if (streams(P)) launch_stream(quantize_cols_stream_kernel<B, SF, RND>, P, P, TileStream<COLS_LDS_ROWS>::LDS_BYTES, st);
-            else launch_cols<DT, B, SF, RND, HW, true, 8>(P, st);
-        } else if (HW && DT == NVFP4_BF16 && streams(P))
-            launch_stream(quantize_cols_stream_kernel<B, SF, RND>, P, P, TileStream<COLS_LDS_ROWS>::LDS_BYTES, st);
-        else
+        else if constexpr (HW && DT == NVFP4_BF16 && columns_streamable(B, SF, RND)) {
+            if (streams_columns(P, B, SF, RND, behind_maximum(P))) launch_stream(quantize_cols_stream_kernel<B, SF, RND>, P, P, TileStream<COLS_LDS_ROWS>::LDS_BYTES, st);
+            else launch_cols<DT, B, SF, RND, HW, true, 16>(P, st);
+        } else
             launch_cols<DT, B, SF, RND, HW, true, HW && DT == NVFP4_F32 && SF == NVFP4_SCALE_E8M0 && RND == NVFP4_SR ? 8 : 16>(P, st);
     }
 }
@@ -1240,7 +1291,7 @@ static void launch_dual_rpl(const DualArgs &D, hipStream_t st)
     const unsigned gx = (unsigned)((D.c.cols + 255) / 256), gy = (unsigned)((D.c.rows + 127) / 128);
     if (short_lane_tile(DT, B, SF, RND_R, RND_C, D.slab_r || D.slab_c ? DUAL_SLABS : DUAL, D.c.rows, D.c.cols))
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, 8>), dim3(gx, gy), dim3(ColGeom<8>::NT), 0, st, D);
-    else if (DT == NVFP4_BF16 && streams_dual(D, RND_C, (int64_t)gx * gy))
+    else if (DT == NVFP4_BF16 && streams_dual(D.c, B, SF, RND_C, D.slab_r || D.slab_c, behind_maximum(D.c)))
         launch_stream(quantize_dual_stream_kernel<B, SF, RND_R, RND_C>, D, D.c, TileStream<DUAL_LDS_ROWS>::LDS_BYTES, st);
     else
         hipLaunchKernelGGL((quantize_dual_kernel<DT, B, SF, RND_R, RND_C, LONG>), dim3(gx, gy), dim3(ColGeom<LONG>::NT), 0, st, D);

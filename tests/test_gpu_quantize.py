@@ -467,21 +467,38 @@ def test_past_the_small_tensors(rows, cols, dtype, axes, dual, fmt):
     _quantize_all(x, x.cuda(), FORMATS[fmt](), axes, dual, f"large {fmt}")
 
 
-# bf16 tensors of more than 512 workgroup tiles (128 x 256) are walked by a fixed number of workgroups, 768 of them, each with its next
-# tile in flight: a single tile each, some with two, some with three; one row or one column of tiles, all of them cut short; a row pitch.
+# bf16 tensors of more than 512 workgroup tiles (128 x 256), most of which are walked by a fixed number of workgroups, 768 of them, each
+# with its next tile in flight: a single tile each, some with two, some with three; one row or one column of tiles, all of them cut short;
+# a row pitch.  The others of these calls keep one tile per workgroup.
+def _streams(rows, cols, pitch, f, both, rr, rc):
+    return nv.quantize_streams(rows, cols, pitch, both, rr, rc, f)
+
+
 @pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4", "e4m3_b32", "e4m3_b64"])
-@pytest.mark.parametrize("rows,cols,pitch", [(64, 205056, 205056), (102464, 96, 104), (204864, 64, 64), (67584, 64, 128)])
+@pytest.mark.parametrize("rows,cols,pitch", [(64, 205056, 205056), (102464, 96, 104), (135424, 64, 64), (204864, 64, 64), (67584, 64, 128)])
 def test_tensors_of_many_tiles(rows, cols, pitch, fmt):
     f = FORMATS[fmt]()
+    tiles = -(-rows // 128) * -(-cols // 256)
+    # (columns of up to 8M elements go to the kernel for small tensors; to nearest, blocks of 64 and MXFP4's 1601 tiles are not walked)
+    assert _streams(rows, cols, pitch, f, False, 0, nv.SR) == (rows * cols > 8 << 20 if f.block <= 32 else rows % 128 == 0)
+    if tiles in (1058, 1601):
+        assert _streams(rows, cols, pitch, f, False, 0, nv.RTN) == (f.block <= 32 and (tiles == 1058 or f.scale == nv.SCALE_E4M3))
+        assert f.block > 32 or _streams(rows, cols, pitch, f, True, nv.RTN, nv.RTN)
+    if f.block <= 32 and tiles <= 1152:
+        assert _streams(rows, cols, pitch, f, True, nv.RTN, nv.SR) and _streams(rows, cols, pitch, f, True, nv.SR, nv.SR)
     x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(rows + cols)) * 0.02).to(torch.bfloat16)
     big = torch.full((rows, pitch), float("nan"), dtype=torch.bfloat16, device="cuda")
     big[:, :cols] = x.cuda()
     _quantize_all(x, big[:, :cols], f, (0,), f.block <= 32, f"many tiles {fmt}")
 
 
+# (one tile each, or two and three)
 @pytest.mark.parametrize("fmt", ["nvfp4", "mxfp4"])
-def test_slabs_of_many_tiles(fmt):
-    f, rows, cols = FORMATS[fmt](), 128, 205056
+@pytest.mark.parametrize("rows", [128, 256])
+def test_slabs_of_many_tiles(rows, fmt):
+    f, cols = FORMATS[fmt](), 205056
+    walked = [nv.quantize_streams(rows, cols, cols, True, rr, rc, f, nv.SLAB_ROWS | nv.SLAB_COLS) for rr, rc in ((nv.RTN, nv.RTN), (nv.RTN, nv.SR), (nv.SR, nv.SR))]
+    assert walked == ([True, fmt == "mxfp4", fmt == "mxfp4"] if rows == 256 else [fmt == "nvfp4", True, True])
     x = (torch.randn((rows, cols), generator=torch.Generator().manual_seed(7)) * 0.02).to(torch.bfloat16).cuda()
     for rr, rc in ((nv.RTN, nv.RTN), (nv.RTN, nv.SR), (nv.SR, nv.SR)):
         print(f"[case] slabs of many tiles {fmt} {rr} {rc}", flush=True)
