@@ -106,9 +106,12 @@ __device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float
 // operand expansion costs 8 (TA + TB) / (TA TB) = 6 VALU instructions per 32-cycle MFMA.
 // KG = 4 serves products with fewer 128 x 128 tiles than CUs, where one workgroup of four waves leaves each SIMD a single wave:
 // four groups of 1 x 2 waves multiply every fourth K tile each, with their own stages and the large tile's wave shape, and add
-// their sums through the LDS at the end.  1056 x 2080 x 2784: 128 x 128 26.2 us, 96 x 128 with four groups 21.7; 256 x 11008 x 4096:
-// 30.7 -> 28.8; 1536 x 1536 x 6144: 45.0 -> 34.3.  (Two groups of 1 x 4 waves on 128 x 256 were no faster than eight waves of 64 x 64:
-// 4096 x 4096 x 11008 315 and 312 us; a chip filled either way is bound by its power, not by the expansion.)
+// their sums through the LDS at the end.  1056 x 2080 x 2784: 128 x 128 26.2 us, 96 x 128 with four groups 21.7; 1536 x 1536 x 6144:
+// 64 x 64 45.0, 96 x 128 with four groups 34.3.  (256 x 11008 x 4096 stays on 64 x 64: 30.7, the estimates lie 4 % apart, 128 x 128 with
+// four groups 28.8.  Two groups of 1 x 4 waves on 128 x 256 were no faster than eight waves of 64 x 64: 4096 x 4096 x 11008 315 and 312 us;
+// a chip filled either way is bound by its power, not by the expansion.)
+// With blocks of 32 to 128 the 128 x 128 form spills up to 7 registers and still takes 0.65 to 0.9 of the time of the tile it replaces
+// (2164 x 1618 x 11520, blocks of 64, 129.9 -> 94.5 us; blocks of 16 100.7 -> 86.0).
 //
 // Per 128-wide K tile the 64 code bytes of each operand row sit in LDS as four 16-byte chunks
 // and its 8 block scales as fp16 values (scale * 2^-8; for blocks wider than 16 the value is
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
         const int row = isA ? trow : trow - BM;
         const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
         const int64_t lr = base + row < rows ? row : rows - 1 - base;  // row inside the tile, clamped
-        // a slab holds all rows of a 256- or 128-row tile: nothing to clamp; one of 160 or 192 rows may reach into the next slab
+        // a slab holds all rows of a 256- or 128-row tile: nothing to clamp; one of 96 or 192 rows may reach into the next slab
         const int srow = (int)(base & 255) + (int)(SPAN && isA ? lr : row);
         const uint32_t slab_off = (uint32_t)(slab_row(SPAN && isA ? srow & 255 : srow) * 64 + ch * 16) +
                                   (SPAN && isA && srow > 255 ? (uint32_t)nkt * (uint32_t)SLAB_CODE_BYTES : 0u);
@@ -432,28 +435,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     } else {
         // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the tile rows
         constexpr int LO = (TA + 1) / 2, HI = TA - LO;
-        float16_t half[LO][TB];
-        if constexpr (KG == 2) {
-            fold_groups<TA, TB, NW>(acc, half, lds, group != 0, wave, lane);
-            if (LO == HI || group == 0) {
-                store_lines<OUT_DT, LO, TB>(P, half, row0 + group * 32 * LO, col0, mine, lane);
-            } else {
-                float16_t rest[HI][TB];
-#pragma unroll
-                for (int a = 0; a < HI; ++a)
-#pragma unroll
-                    for (int b = 0; b < TB; ++b) rest[a][b] = half[a][b];
-                store_lines<OUT_DT, HI, TB>(P, rest, row0 + 32 * LO, col0, mine, lane);
-            }
-        } else {
-            static_assert(KG == 4 && LO == 2, "four groups, three or four tile rows");
-            float16_t last[1][TB];
-            fold_groups<TA, TB, 2 * NW>(acc, half, lds, group >= 2, (group & 1) * NW + wave, lane);
-            fold_groups<LO, TB, 2 * NW>(half, last, lds, group & 1, (group >> 1) * NW + wave, lane);
-            // (of three tile rows the last group gets none)
-            const int row = (group >> 1) * LO + (group & 1);
-            if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, 1, TB>(P, last, row0 + row * 32, col0, mine, lane);
-        }
+        static_assert(KG == 4 && LO == 2, "four groups, three or four tile rows");
+        float16_t half[LO][TB], last[1][TB];
+        fold_groups<TA, TB, 2 * NW>(acc, half, lds, group >= 2, (group & 1) * NW + wave, lane);
+        fold_groups<LO, TB, 2 * NW>(half, last, lds, group & 1, (group >> 1) * NW + wave, lane);
+        // (of three tile rows the last group gets none)
+        const int row = (group >> 1) * LO + (group & 1);
+        if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, 1, TB>(P, last, row0 + row * 32, col0, mine, lane);
     }
 }
 

@@ -200,8 +200,8 @@ __global__ __launch_bounds__(256) void quantize_rows_pair_kernel(QuantArgs P0, Q
 // vertically, so that it reads 512 contiguous bytes (bf16) per row and writes 64 per output row.
 // RPL = 16 (4 waves) does the least work per element, RPL = 8 (8 waves: a block of 16 spans two lanes) has half the serial
 // chain per wave and half the registers, 512 tiles resident at once.
-// bf16: what bounds a tensor of up to 512 tiles is that chain (one batch of loads, the arithmetic, the stores); larger ones are streamed
-// (streams()).  us, RPL = 16 / 8, dual quantizer with row-major outputs:
+// bf16: what bounds a tensor of up to 512 tiles is that chain (one batch of loads, the arithmetic, the stores); larger ones have
+// 16 rows, one tile per workgroup or streamed (streams()).  us, RPL = 16 / 8, dual quantizer with row-major outputs:
 //                      bf16 RtN+RtN   bf16 SR+SR    MXFP4 bf16 SR+SR
 //     2048 x  4096     13.9 / 11.6    18.1 / 16.0   19.7 / 16.4
 //     4096 x  4096     18.2 / 15.2    25.1 / 21.9   26.9 / 23.4
