@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2505_19115_amd import binding as nv
@@ -27,6 +28,20 @@ def test_library_exports_every_declared_symbol():
     for name in declared:
         assert hasattr(raw, name), name
     assert declared == set(nv.EXPORTS)
+
+
+def test_stream_handle(monkeypatch):
+    # the current device's current stream, also from a torch without the raw handle; a process without a GPU gets torch's own error
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(nv, "_raw_stream", lambda device: 100 + device)
+    assert nv._stream() == 103
+    monkeypatch.setattr(nv, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
+    assert nv._stream() == 7
+    monkeypatch.undo()
+    if not torch.cuda.is_available():
+        with pytest.raises((RuntimeError, AssertionError)):
+            nv._stream()
 
 
 def test_sizes():
