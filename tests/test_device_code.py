@@ -127,6 +127,30 @@ def test_resident_workgroups_of_the_quantizers(tmp_path):
             assert v <= 64 and s == 0, ("rows", dt, b, sf, rnd, hw, v, s)
 
 
+def test_resident_workgroups_of_the_streaming_quantizers(tmp_path):
+    # three workgroups of four waves per CU: 168 registers
+    regs = registers("quantize", tmp_path)
+    columns = list(kernels(regs, "quantize_cols_stream_kernel"))
+    duals = list(kernels(regs, "quantize_dual_stream_kernel"))
+    pairs = list(kernels(regs, "quantize_dual_stream_pair_kernel"))
+    assert {a for a, _, _ in columns} == {(16, 0, 0), (16, 0, 1), (16, 1, 1), (32, 0, 0), (32, 0, 1), (32, 1, 0), (32, 1, 1), (64, 0, 1), (64, 1, 1), (128, 0, 1), (128, 1, 1)}
+    assert len(duals) == 4 * 3 and {a for a, _, _ in pairs} == {(16, 0), (32, 1)}
+    for args, v, s in columns + duals + pairs:
+        # (blocks of 16 with E8M0 scales, both sides to nearest: on the line, with ten spilled)
+        assert v <= 168 and s <= (10 if args == (16, 1, 0, 0) else 0), (args, v, s)
+
+
+def test_registers_of_small_tensors_and_four_groups(tmp_path):
+    # workgroups of eight waves: two per SIMD need 256 registers (four groups of waves, one workgroup per CU), four 128 (small tensors)
+    for args, v, s in kernels(registers("quantize_small", tmp_path), "quantize_small"):
+        assert v <= 128 and s == 0, (args, v, s)
+    four = [(args, v, s) for args, v, s in kernels(registers("gemm", tmp_path), "gemm_nt_f16_kernel") if args[5] == 4]
+    assert len(four) == 4 * 2 * 2 * 2  # (blocks, tiles, output types, K tail)
+    for (block, wm, wn, ta, tb, groups, out, tail), v, s in four:
+        # (128 x 128 with blocks of 32 to 128 spills a few)
+        assert v <= 256 and s <= (7 if ta == 4 and block > 16 else 0), (block, ta, out, tail, v, s)
+
+
 def test_rows_of_small_tensors_bring_little_along(tmp_path):
     # 2 us of row quantization: with the LDS and the four jobs of the kernel for both orientations, decode calls took 0.4 us longer
     notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object("quantize_small", tmp_path)], capture_output=True, text=True, check=True).stdout

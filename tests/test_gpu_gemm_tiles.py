@@ -85,7 +85,13 @@ def test_every_tile_sampled(shape, e4m3_tile, e8m0_tile, fmt_name):
     fmt = nv.Format(block, scale, 1 - scale)
     want = e8m0_tile if scale else e4m3_tile
     assert want is None or nv.gemm_tile(M, N, K, fmt) == want
-    out_dtype = torch.float32 if K % 256 else torch.bfloat16
+    check_sampled(shape, fmt_name, torch.float32 if K % 256 else torch.bfloat16)
+
+
+def check_sampled(shape, fmt_name, out_dtype):
+    block, scale = FORMATS[fmt_name]
+    M, N, K = shape
+    fmt = nv.Format(block, scale, 1 - scale)
     rng = np.random.default_rng(M + 7 * N + K)
     A, B = operand(rng, M, K, block, scale), operand(rng, N, K, block, scale)
     print(f"[case] gemm tile sampled {fmt_name} {M}x{N}x{K} {out_dtype}", flush=True)
@@ -199,6 +205,7 @@ def test_mxfp4_short_contractions(shape, tile, K):
 
 # Operands in slabs on tiles other than the 256 x 256 they were made for: the same bits as row-major operands.
 @pytest.mark.parametrize("fmt_name,shape,tile", [("nvfp4", (16, 32768, 1024), (32, 32)), ("nvfp4", (50, 32800, 1024), (64, 64)),
+                                                 ("nvfp4", (96, 32700, 2048), (96, 128)), ("nvfp4", (128, 32768, 4096), (128, 128)),
                                                  ("mxfp4", (40, 2080, 1024), (32, 32)), ("mxfp4", (70, 4100, 1024), (32, 64)),
                                                  ("mxfp4", (100, 3000, 1024), (64, 32)), ("mxfp4", (33, 8200, 512), (64, 64)),
                                                  ("mxfp4", (2048, 4096, 1024), (128, 128)), ("mxfp4", (7171, 2050, 512), (256, 128)),
@@ -207,7 +214,7 @@ def test_slab_operands_on_every_tile(fmt_name, shape, tile):
     block, scale = FORMATS[fmt_name]
     fmt = nv.Format(block, scale, 1 - scale)
     M, N, K = shape
-    assert nv.gemm_tile(M, N, K, fmt) == tile
+    assert nv.gemm_tile(M, N, K, fmt) == tile and (fmt_name == "mxfp4" or nv.gemm_split(M, N, K, fmt) > 1)
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     # (rows padded to whole blocks for the quantizer; the product takes the first M and N of them)
@@ -232,35 +239,53 @@ def test_packed_weights_of_a_wide_projection():
     assert torch.equal(Y, nv.gemm(nv.quantize(X), nv.quantize(W)))
 
 
-# Tiles whose four groups of waves take every fourth K tile: all four remainders of the K tiles (the groups without a K tile in the
-# last step add zeros), with and without a K tail, rows and columns past the edge.
-FOUR_GROUPS = [((2631, 769, 1312), (96, 128)), ((1704, 1157, 1440), (96, 128)), ((1179, 1726, 2176), (96, 128)), ((1173, 1690, 2112), (96, 128)),
-               ((1863, 1601, 2496), (128, 128)), ((1921, 1553, 3328), (128, 128))]
+# Tiles whose four groups of waves take every fourth K tile: every remainder of the K tiles (the groups without a K tile in the last step
+# add zeros), with whole K tiles and with a K tail, rows and columns past the edge, both output types.
+FOUR_GROUPS = [((2970, 641, 1536), (96, 128)), ((1667, 1175, 1472), (96, 128)), ((2970, 642, 2176), (96, 128)), ((1798, 1098, 2112), (96, 128)),
+               ((708, 2692, 1792), (96, 128)), ((716, 2689, 1728), (96, 128)), ((2955, 648, 1408), (96, 128)), ((646, 2971, 1344), (96, 128)),
+               ((3081, 963, 2560), (128, 128)), ((1106, 2689, 2496), (128, 128)), ((1222, 2442, 5248), (128, 128)), ((2890, 1028, 5184), (128, 128)),
+               ((2232, 1351, 4352), (128, 128)), ((1930, 1553, 4288), (128, 128)), ((1094, 2713, 3456), (128, 128)), ((1094, 2760, 3392), (128, 128))]
 
 
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("fmt_name", ["nvfp4", "e4m3_64"])
 @pytest.mark.parametrize("shape,tile", FOUR_GROUPS, ids=["x".join(map(str, c[0])) for c in FOUR_GROUPS])
-def test_four_groups_sampled(shape, tile, fmt_name):
-    M, N, K = shape
-    test_every_tile_sampled((M, N, -(-K // FORMATS[fmt_name][0]) * FORMATS[fmt_name][0]), tile, None, fmt_name)
+def test_four_groups_sampled(shape, tile, fmt_name, out_dtype):
+    assert nv.gemm_tile(*shape) == tile and nv.gemm_split(*shape) == 4
+    check_sampled(shape, fmt_name, out_dtype)
 
 
-# Packed weights of more than a few million elements are slabs also where a few tokens meet them: every small tile, the other operand
-# row-major, output columns that end inside a slab; the bits of the calls that quantize W themselves.
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["e4m3_32", "e4m3_128"])
+@pytest.mark.parametrize("shape,tile", [((2955, 648, 1408), (96, 128)), ((1094, 2713, 3456), (128, 128))])
+def test_four_groups_of_other_blocks(shape, tile, fmt_name, out_dtype):
+    assert nv.gemm_tile(*shape) == tile and nv.gemm_split(*shape) == 4
+    check_sampled(shape, fmt_name, out_dtype)
+
+
+# Packed weights of more than a few million elements are slabs also where few tokens meet them: every tile of up to 64 x 64 and both with
+# four groups, the other operand row-major, output columns that end inside a slab; the bits of the calls that quantize W themselves.
+FEW_TOKENS = [((32, 2080, 2176), (32, 32), 8), ((160, 2080, 2176), (64, 32), 8), ((224, 2080, 2176), (32, 64), 8), ((320, 2080, 2176), (64, 64), 4),
+              ((992, 2080, 2176), (96, 128), 4), ((1504, 2080, 4096), (128, 128), 4)]
+
+
 @pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4"])
-@pytest.mark.parametrize("M", [32, 64, 160, 320])
-def test_weight_slabs_with_few_tokens(M, fmt_name):
-    N, K, seed = 2080, 2176, 5
+@pytest.mark.parametrize("shape,tile,split", FEW_TOKENS, ids=["x".join(map(str, c[0])) for c in FEW_TOKENS])
+def test_weight_slabs_with_few_tokens(shape, tile, split, fmt_name):
+    (M, N, K), seed = shape, 5
     block, scale = FORMATS[fmt_name]
     fmt = nv.Format(block, scale, 1 - scale)
+    if fmt_name == "nvfp4" or M <= 320:
+        assert nv.gemm_tile(M, N, K, fmt) == tile and nv.gemm_split(M, N, K, fmt) == split
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     X, W, dY = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (N, K), (M, N)))
     print(f"[case] weight slabs {fmt_name} {M}x{N}x{K}", flush=True)
     wq = nv.quantize_weight(W, M, fmt)
     saved = torch.empty(nv.linear_saved_bytes(M, N, K, fmt), dtype=torch.uint8, device="cuda")
-    Y = nv.linear_fwd(X, None, fmt, w_operands=wq, N=N, saved=saved, bwd_seed=seed)
-    assert torch.equal(Y, nv.linear_fwd(X, W, fmt))
+    for out_dtype in (torch.float32, torch.bfloat16):
+        Y = nv.linear_fwd(X, None, fmt, out_dtype, w_operands=wq, N=N, saved=saved, bwd_seed=seed)
+        assert torch.equal(Y, nv.linear_fwd(X, W, fmt, out_dtype))
     got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K, w_operands=wq)
     for a, b in zip(got, nv.linear_bwd(dY, X, W, seed, fmt)):
         assert torch.equal(a, b)

@@ -380,13 +380,17 @@ def test_which_quantizers_stream():
 
 def test_no_tile_beyond_the_launch_limit():
     # a launch counts its threads in 32 bits, and no product that one of the tiles can serve may be given one that cannot
-    threads = {(32, 32): 512, (32, 64): 512, (64, 32): 512, (64, 64): 256, (128, 128): 256, (128, 256): 512, (192, 256): 512,
-               (256, 128): 256, (256, 256): 512}
+    # (rows, columns, parts of the contraction -> threads)
+    threads = {(32, 32, 8): 512, (32, 64, 8): 512, (64, 32, 8): 512, (64, 64, 4): 256, (96, 128, 4): 512, (128, 128, 1): 256, (128, 128, 4): 512,
+               (128, 256, 1): 512, (192, 256, 1): 512, (256, 128, 1): 256, (256, 256, 1): 512}
+    seen = set()
     for fmt in (nv.NVFP4, nv.MXFP4):
-        for M in (1, 64, 300, 4096, 1 << 18, 1 << 20, 1 << 24, 1 << 26, 1 << 28, (1 << 28) + 1, 1 << 30):
-            for N in (1, 32, 33, 64, 128, 300, 4096, 1 << 18):
-                for K in (32, 96, 128, 512, 1024, 4096, 16384):
+        for M in (1, 64, 300, 2700, 2970, 4096, 1 << 18, 1 << 20, 1 << 24, 1 << 26, 1 << 28, (1 << 28) + 1, 1 << 30):
+            for N in (1, 32, 33, 64, 128, 300, 641, 1093, 4096, 1 << 18):
+                for K in (32, 96, 128, 512, 1024, 1536, 2560, 4096, 16384):
                     if M * N > 1 << 38:  # (more than 256 x 256 tiles can serve)
                         continue
-                    t = nv.gemm_tile(M, N, K, fmt)
+                    t = nv.gemm_tile(M, N, K, fmt) + (nv.gemm_split(M, N, K, fmt),)
+                    seen.add(t)
                     assert -(-M // t[0]) * -(-N // t[1]) * threads[t] < 1 << 32, (M, N, K, t)
+    assert {(96, 128, 4), (128, 128, 4), (128, 128, 1), (256, 256, 1)} <= seen
