@@ -190,9 +190,10 @@ def main() -> int:
                  "one_stream_ms" if args.streams >= 2 else "mlp_graph_2_streams_ms": round(other_ms, 3)}
 
     # ---- the same step composed from the single entry points (tensor-maximum pass + dual quantizer through
-    # nvfp4_quantize_dual with slab outputs, GEMMs through nvfp4_gemm_slab): exactly the kernels of the fused
-    # calls, in their order, with an event pair around every GEMM, so that the three GEMM shapes are timed
-    # INSIDE the step (the clock a GEMM sees depends on what ran just before it) and the parts can be added up
+    # nvfp4_quantize_dual with slab outputs, GEMMs through nvfp4_gemm_slab): the GEMMs of the fused calls on the
+    # same operands, behind the same passes over the tensors (the fused forward call makes those over X and W as
+    # one launch each), with an event pair around every GEMM, so that the three GEMM shapes are timed INSIDE the
+    # step (the clock a GEMM sees depends on what ran just before it) and the parts can be added up
     def composed(fmt):
         parts = []
         for name, N, K, X, W, dY, wf, wb, Y, dX, dW, saved in data:
@@ -250,8 +251,9 @@ def main() -> int:
         out["gemm_ms_per_step"] = round(total, 3)
         out["composed_step_ms"] = round(plain_ms, 3)
         out["other_kernels_ms_per_step"] = round(plain_ms - total, 3)
-        out["how"] = ("the step composed from nvfp4_quantize_dual (maximum pass + dual quantizer, slab outputs) and nvfp4_gemm_slab: the same "
-                      "kernels in the same order as the fused calls; event pair around each GEMM; M x N x K of the GEMM (contraction last)")
+        out["how"] = ("the step composed from nvfp4_quantize_dual (maximum pass + dual quantizer, slab outputs) and nvfp4_gemm_slab: the GEMM "
+                      "launches of the fused calls on the same operands, behind the same passes over X, W and dY, which a fused forward call makes "
+                      "over X and W at once; event pair around each GEMM; M x N x K of the GEMM (contraction last)")
         return out
 
     in_step = in_step_gemm_times(nv.NVFP4, PEAK_F16_TFLOPS)
