@@ -185,16 +185,18 @@ def _torch_dtype(tag: int) -> torch.dtype:
     return torch.float32 if tag == F32 else torch.bfloat16
 
 
-# (torch's own way to the raw handle, without a public name; a torch that lacks it goes through the Stream object)
+# (torch's own ways to the device's number and the raw handle, without public names; a torch that lacks them goes through the Stream object)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream() -> int:
     # the current stream's handle without a torch.cuda.Stream around it: 0.2 us instead of 2.8, of the 14 that the host spent on a
-    # decode call of two launches (asked anew on every call: the stream and the device are the caller's to change)
-    if _raw_stream is None:
+    # decode call of two launches (asked anew on every call: the stream and the device are the caller's to change; torch.cuda.current_device()
+    # instead of the raw one, which initializes as well, 0.3)
+    if _raw_device is None or _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_raw_device())
 
 
 def _check(code: int, where: str) -> None:

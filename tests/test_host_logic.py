@@ -32,15 +32,17 @@ def test_library_exports_every_declared_symbol():
 
 def test_stream_handle(monkeypatch):
     # the current device's current stream, also from a torch without the raw handle; a process without a GPU gets torch's own error
-    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
+    monkeypatch.setattr(nv, "_raw_device", lambda: 3)
     monkeypatch.setattr(nv, "_raw_stream", lambda device: 100 + device)
     assert nv._stream() == 103
-    monkeypatch.setattr(nv, "_raw_stream", None)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
-    assert nv._stream() == 7
+    for lacking in ("_raw_device", "_raw_stream"):
+        with monkeypatch.context() as m:
+            m.setattr(nv, lacking, None)
+            assert nv._stream() == 7
     monkeypatch.undo()
     if not torch.cuda.is_available():
-        with pytest.raises((RuntimeError, AssertionError)):
+        with pytest.raises((RuntimeError, AssertionError), match="GPU|HIP|CUDA"):
             nv._stream()
 
 
