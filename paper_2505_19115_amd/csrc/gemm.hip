@@ -110,7 +110,7 @@ __device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float
 // 64 x 64 45.0, 96 x 128 with four groups 34.3.  (256 x 11008 x 4096 stays on 64 x 64: 30.7, the estimates lie 4 % apart, 128 x 128 with
 // four groups 28.8.  Two groups of 1 x 4 waves on 128 x 256 were no faster than eight waves of 64 x 64: 4096 x 4096 x 11008 315 and 312 us;
 // a chip filled either way is bound by its power, not by the expansion.)
-// With blocks of 32 to 128 the 128 x 128 form spills up to 7 registers and still takes 0.65 to 0.9 of the time of the tile it replaces
+// With blocks of 32 to 128 the 128 x 128 form takes 0.65 to 0.9 of the time of the tile it replaces
 // (2164 x 1618 x 11520, blocks of 64, 129.9 -> 94.5 us; blocks of 16 100.7 -> 86.0).
 //
 // Per 128-wide K tile the 64 code bytes of each operand row sit in LDS as four 16-byte chunks
@@ -125,6 +125,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     constexpr int NT = 64 * WM * WN;  // threads of a group
     constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
     constexpr int SPT = KT / B;  // scale bytes per row per tile in global memory
+    // A row-major row's scale bytes come 8 at a time: those of WINDOW K tiles.  A request per row costs the vector L1 the same for 1 byte
+    // as for 8, and of a K tail the bytes past the row are shifted out below instead of left out one by one, which was a chain of 8
+    // loads at the end of the walk.  us, a request per row and K tile / a window: 4096 x 4096 x 11008 blocks of 64 284 / 271, of 32
+    // 278 / 267; with a K tail (f32 outputs) 1056 x 2080 x 2784 blocks of 16 25.4 / 21.6, of 32 24.7 / 21.1, 1056 x 2784 x 2080 22.7 / 21.2.
+    // (16 bytes, two K tiles, at a time for blocks of 16: a few more registers and branches, 1056 x 2080 x 2816 23.1 instead of 21.4.)
+    constexpr int WINDOW = 8 / SPT;
+    constexpr bool WINDOWS = KTAIL || WINDOW > 1;  // (without a K tail a window of blocks of 16 is a K tile's 8 bytes, here or in a slab)
     constexpr int VALU_PER_MFMA = (8 * (TA + TB) + TA * TB - 1) / (TA * TB);
     constexpr int A_BYTES = BM * KTB, B_BYTES = BN * KTB, SA_BYTES = BM * SROW, SB_BYTES = BN * SROW;
     constexpr int STAGE = A_BYTES + B_BYTES + SA_BYTES + SB_BYTES;
@@ -159,7 +166,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     // Rows past the matrix edge are clamped to the last row (their products land in outputs
     // that are never stored), so the code loads carry no predicate.  A K tail (K not a
     // multiple of 128) is handled through the scales alone: a chunk past K is replaced by the
-    // tile's first one and meets zero scales.
+    // tile's first one and meets the zeros that follow the row's last scale byte.
     // The codes go from global memory straight into LDS (global_load_lds, 16
     // bytes per lane): a wave instruction fills 1 KB = 16 consecutive tile rows, lane i landing at
     // byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
@@ -231,6 +238,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     // the group's step j (K tile j KG + group): codes -> LDS stage `stage` (direct); scale bytes -> registers.  A K tile past the
     // last one is the last one again with zero scales: every group takes the same steps and meets the same barriers.
     const int steps = (nkt + KG - 1) / KG;
+    // first byte of the window that K tile kt lies in: the last one ends with the row, also if that is shorter
+    auto window = [&](int kt) { return kt / WINDOW * 8 + 8 < (int)Ks ? kt / WINDOW * 8 : (int)Ks - 8; };
     auto fetch = [&](int j, int stage) {
         const int kj = j * KG + group;
         const bool absent = KG > 1 && kj >= nkt;
@@ -247,25 +256,14 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
 #pragma unroll
         for (int u = 0; u < NSR; ++u) {
             if (!srow_on[u]) continue;
-            const uint8_t *sp = srow_ptr[u] + (int64_t)kt * srow_step[u];
-            if (absent) {
+            if constexpr (!WINDOWS) {
+                gs[u] = *reinterpret_cast<const uint64_t *>(srow_ptr[u] + (int64_t)kt * srow_step[u]);
+            } else if (Ks >= 8) {
+                // (the groups' K tiles lie KG apart: a window each)
+                if (WINDOW == 1 || KG > 1 || j == 0 || kt % WINDOW == 0) __builtin_memcpy(&gs[u], srow_ptr[u] + window(kt), 8);
+            } else if (j == 0) {
                 gs[u] = 0;
-            } else if (tail) {
-                uint64_t sv = 0;  // zero scales past K
-#pragma unroll
-                for (int t = 0; t < SPT; ++t)
-                    if (t * B < rem) sv |= (uint64_t)sp[t] << (8 * t);
-                gs[u] = sv;
-            } else if (KTAIL) {
-                // (the scale rows of a ragged K start at any byte)
-                uint64_t sv = 0;
-                __builtin_memcpy(&sv, sp, SPT);
-                gs[u] = sv;
-            } else {
-                if (SPT == 8) gs[u] = *reinterpret_cast<const uint64_t *>(sp);
-                else if (SPT == 4) gs[u] = *reinterpret_cast<const uint32_t *>(sp);
-                else if (SPT == 2) gs[u] = *reinterpret_cast<const uint16_t *>(sp);
-                else gs[u] = *sp;
+                for (int t = 0; t < (int)Ks; ++t) gs[u] = gs[u] >> 8 | (uint64_t)srow_ptr[u][t] << 56;
             }
         }
     };
@@ -273,21 +271,28 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     // scales (byte << 7 = fp16(scale * 2^-8), exact for normal and subnormal E4M3 bytes alike
     // because fp16's bias is E4M3's plus 8) of the chunk's two 16-element blocks; a wave reads
     // 32 consecutive rows of one chunk.  For blocks wider than 16 the value is repeated.
-    auto stash = [&](int stage) {
+    auto stash = [&](int stage, int j) {
         uint8_t *base = stages + stage * STAGE;
+        const int kj = j * KG + group;
+        // bits of the window in front of the K tile's scales; what follows the row is shifted in as zeros, and all of a K tile past the
+        // last one is
+        const int at = WINDOWS ? 8 * (kj * SPT - window(kj)) : (KG == 1 || kj < nkt) ? 0 : 64;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's direct-to-LDS loads have landed
         uint32_t *sS = reinterpret_cast<uint32_t *>(base + A_BYTES + B_BYTES);
 #pragma unroll
         for (int u = 0; u < NSR; ++u) {
             if (!srow_on[u]) continue;
+            // (a window of one K tile is not used again: shifted where it is, and only if it has to be)
+            if (WINDOW == 1 && at) gs[u] = at < 64 ? gs[u] >> at : 0;
+            const uint64_t w = WINDOW == 1 ? gs[u] : at < 64 ? gs[u] >> at : 0;
+            const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int c = 0; c < 4; ++c) {
                 // bytes i0, i1 of the staged scale bytes -> (b0 << 7) | (b1 << 23): one byte permute
                 // (b0 into byte 0, b1 into byte 2, zeros between) and one shift
-                const int i0 = (32 * j) / B, i1 = (32 * j + 16) / B;  // (constants after unrolling)
-                const uint32_t lo = (uint32_t)gs[u], hi = (uint32_t)(gs[u] >> 32);
+                const int i0 = (32 * c) / B, i1 = (32 * c + 16) / B;  // (constants after unrolling)
                 const uint32_t sel = 0x0C000C00u | (uint32_t)i0 | ((uint32_t)i1 << 16);
-                sS[j * (BM + BN) + tid + NT * u] = __builtin_amdgcn_perm(hi, lo, sel) << 7;
+                sS[c * (BM + BN) + tid + NT * u] = __builtin_amdgcn_perm(hi, lo, sel) << 7;
             }
         }
     };
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     Scales S0, S1;
     Frags F0, F1;
     fetch(0, 0);
-    stash(0);
+    stash(0, 0);
     __syncthreads();
     load_codes(0, 0, Ca);
     load_scales(0, 0, S0);
@@ -390,7 +395,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
         NVFP4_STEP(Cb, S1, 0, F0, F1)             \
         NVFP4_STEP(Cb, S1, 1, F1, F0)             \
         NVFP4_STEP(Cb, S1, 2, F0, F1)             \
-        stash((stage) ^ 1);                       \
+        stash((stage) ^ 1, (kt) + 1);             \
         __syncthreads();                          \
         load_codes((stage) ^ 1, 0, Ca);           \
         load_scales((stage) ^ 1, 0, S0);          \

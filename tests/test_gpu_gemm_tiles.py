@@ -263,6 +263,18 @@ def test_four_groups_of_other_blocks(shape, tile, fmt_name, out_dtype):
     check_sampled(shape, fmt_name, out_dtype)
 
 
+# Row-major scales are fetched 8 bytes of a row at a time, the last 8 ending with the row: rows of fewer than 8 bytes, of 8, of one more,
+# of whole windows and one K tile past them, at every block size.
+@pytest.mark.parametrize("fmt_name,K", [("nvfp4", 32), ("nvfp4", 96), ("nvfp4", 160), ("nvfp4", 288), ("e4m3_32", 32), ("e4m3_32", 224),
+                                        ("e4m3_32", 256), ("e4m3_32", 288), ("e4m3_32", 640), ("e4m3_64", 64), ("e4m3_64", 448),
+                                        ("e4m3_64", 512), ("e4m3_64", 576), ("e4m3_64", 1152), ("e4m3_128", 128), ("e4m3_128", 896),
+                                        ("e4m3_128", 1024), ("e4m3_128", 1152), ("e4m3_128", 2176)])
+@pytest.mark.parametrize("M,N,tile", [(2720, 4358, (256, 256)), (1056, 2080, None)])
+def test_windows_of_row_major_scales(M, N, tile, fmt_name, K):
+    assert nv.gemm_tile(M, N, K) == (tile or ((128, 128) if K < 2176 else (96, 128)))
+    check_sampled((M, N, K), fmt_name, torch.float32)
+
+
 # Packed weights of more than a few million elements are slabs also where few tokens meet them: every tile of up to 64 x 64 and both with
 # four groups, the other operand row-major, output columns that end inside a slab; the bits of the calls that quantize W themselves.
 FEW_TOKENS = [((32, 2080, 2176), (32, 32), 8), ((160, 2080, 2176), (64, 32), 8), ((224, 2080, 2176), (32, 64), 8), ((320, 2080, 2176), (64, 64), 4),
