@@ -710,17 +710,7 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
     const int gm = f->tensor_scale ? G_FROM_AMAX : G_NONE;
     GSource gx{reinterpret_cast<const float *>(amax + 0), 0}, gw{reinterpret_cast<const float *>(amax + 1), 0};
     const int64_t both_max = M > N ? M : N;
-    if (f->tensor_scale && (w_ops || both_max * K * (int64_t)elem_size(in_dt) <= SELF_AMAX_BYTES)) {
-        if (amax_dense(X, in_dt, M * K, partials, 0, st, &gx) != hipSuccess) return NVFP4_EHIP;
-        if (!w_ops && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
-    } else if (f->tensor_scale) {
-        uint32_t *const pw = partials + AMAX_DENSE_PARTIALS;
-        gx.src = reinterpret_cast<const float *>(partials);
-        gw.src = reinterpret_cast<const float *>(pw);
-        if (launch_tensor_amax_dense2(X, M * K, partials, &gx.n, W, N * K, pw, &gw.n, in_dt, st) != hipSuccess) return NVFP4_EHIP;
-    }
     int a_slab = 0, b_slab = 0;
-    const bool t_fwd = gemm_takes_slabs(M, N, K, f->block, f->scale);
     if (w_ops) {
         // W as quantized once for all micro-batches of the optimizer step: no pass over W here
         const WeightLayout WL = weight_layout(w_ops, N, K, f->block);
@@ -731,7 +721,22 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
         g_w = WL.g;
         b_slab = w_slab;
         if (xw_scales_out && hipMemcpyAsync(xw_scales_out + 1, WL.g, sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return NVFP4_EHIP;
+        // a small X of few rows: one launch quantizes it and multiplies
+        const GemmArgs thin{M, N, K, nullptr, nullptr, wc, wsc, nullptr, g_w, Y, N, 0, b_slab};
+        if (!saved && use_hw_convert() && (f->tensor_scale != 0) == (f->scale == NVFP4_SCALE_E4M3) && gemm_is_thin(thin, f->block, f->scale) &&
+            thin_takes_tensor(M, K, in_dt))
+            return launch_gemm_thin_tensor(thin, X, in_dt, ts, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }
+    if (f->tensor_scale && (w_ops || both_max * K * (int64_t)elem_size(in_dt) <= SELF_AMAX_BYTES)) {
+        if (amax_dense(X, in_dt, M * K, partials, 0, st, &gx) != hipSuccess) return NVFP4_EHIP;
+        if (!w_ops && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
+    } else if (f->tensor_scale) {
+        uint32_t *const pw = partials + AMAX_DENSE_PARTIALS;
+        gx.src = reinterpret_cast<const float *>(partials);
+        gw.src = reinterpret_cast<const float *>(pw);
+        if (launch_tensor_amax_dense2(X, M * K, partials, &gx.n, W, N * K, pw, &gw.n, in_dt, st) != hipSuccess) return NVFP4_EHIP;
+    }
+    const bool t_fwd = gemm_takes_slabs(M, N, K, f->block, f->scale);
     if (saved) {
         // one pass over X and one over W also leave what Eqs. 5-6 need of them: Q_SR(X^T) with
         // the backward call's third stream, and Q_RtN(W^T)

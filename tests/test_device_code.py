@@ -157,3 +157,14 @@ def test_rows_of_small_tensors_bring_little_along(tmp_path):
     rows = [int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", k).group(1)) for k in notes.split("  - .agpr_count") if "quantize_small_rows" in k]
     assert len(rows) == 2 * 4 * 3  # (element types, formats; round to nearest, stochastic, two tensors)
     assert max(rows) <= 1024
+
+
+def test_few_rows_kernels(tmp_path):
+    # the direct loads' waits as above; workgroups of 16 waves, four per SIMD: 128 registers
+    asm = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", code_object("gemm_thin", tmp_path)], capture_output=True, text=True, check=True).stdout
+    loads, unwaited = unwaited_loads(asm)
+    assert loads > 0 and not unwaited
+    thin = list(kernels(registers("gemm_thin", tmp_path), "gemm_nt_thin_kernel"))
+    assert len(thin) == 3 * 2 * 7 * 2  # (A packed, binary32, bf16; formats; tiles; output types)
+    for args, v, s in thin:
+        assert v <= 128 and s == 0, (args, v, s)
