@@ -11,11 +11,11 @@ namespace nvfp4 {
 // element by element, so a tile at the edge of a ragged output keeps wide stores everywhere else.
 // No wave may still read `mine`, no load may still write it.  The lane coordinates are re-derived from an opaque copy so
 // that none of the addressing is computed before the K loop and kept in registers across it.
-// Two forms, for a wave's part inside the output (the usual case: no predicate, nothing between the LDS reads and the stores) and
+// Forms for a wave's part inside the output (the usual case: no predicate, nothing between the LDS reads and the stores; streaming or not) and
 // for one at its edge, and pieces as vector values: in one form, with pieces as structs of four words, the compiler stored the last
 // word of a piece apart, sharing that store with the cut pieces, and binary32 rows left in 12 + 4 bytes: 8192 x 8192 x 1024 (E4M3,
 // 256 x 256 tiles) 151 us against 137.
-template <int OUT_DT, int TA, int TB, bool FULL, class ACC>
+template <int OUT_DT, int TA, int TB, bool FULL, bool STREAM, class ACC>
 __device__ __forceinline__ void store_lines_form(const GemmArgs &P, const ACC (&acc)[TA][TB], int64_t row0, int64_t col0, uint8_t *mine,
                                                  unsigned lane, float gg, bool wide, bool half)
 {
@@ -57,7 +57,9 @@ __device__ __forceinline__ void store_lines_form(const GemmArgs &P, const ACC (&
             const unsigned rowl = rowl0 + RPS * i;
             const u32x4_t v = *reinterpret_cast<const u32x4_t *>(mine + rowl * ROWB + ((c ^ (rowl & SWZ)) << 4));
             uint8_t *const dst = dst0 + (int64_t)(32 * a + RPS * i) * P.ldc * ESZ;
-            if (FULL) {
+            if (FULL && STREAM) {
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(dst));
+            } else if (FULL) {
                 *reinterpret_cast<u32x4_t *>(dst) = v;
             } else if (grow0 + 32 * a + RPS * i < P.M) {
                 if (wide && gcol + EPC <= P.N) {
@@ -90,10 +92,11 @@ __device__ __forceinline__ void store_lines(const GemmArgs &P, const ACC (&acc)[
     const bool wide = P.ldc % (OUT_DT == NVFP4_F32 ? 4 : 8) == 0;
     const bool half = P.ldc % 4 == 0;  // (bf16 rows start at multiples of 8 bytes: 303 x 6548 x 128 8.5 us in single elements)
     // (row0 and col0 are the same in the whole wave)
-    if (wide && row0 + 32 * TA <= P.M && col0 + 32 * TB <= P.N)
-        store_lines_form<OUT_DT, TA, TB, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
-    else
-        store_lines_form<OUT_DT, TA, TB, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+    if (wide && row0 + 32 * TA <= P.M && col0 + 32 * TB <= P.N) {
+        if (P.stream) store_lines_form<OUT_DT, TA, TB, true, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+        else store_lines_form<OUT_DT, TA, TB, true, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+    } else
+        store_lines_form<OUT_DT, TA, TB, false, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
 }
 
 }  // namespace nvfp4
