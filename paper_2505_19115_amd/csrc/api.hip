@@ -876,6 +876,21 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         tag.chk = reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(saved) + SAVED_TAG_OFFSET);
         if (!saved_matches(saved, tag)) return NVFP4_EINVAL;
     }
+    // W and X down their columns, where those operands are not at hand.  Small ones go with dY in one launch: each by itself leaves CUs idle
+    // (us, forward and backward, NVFP4, tensor scales handed over, a launch each / one: 64 x 256 x 128 bf16 21.4 / 15.4, 512 x 1024 x 1024 40.1 /
+    // 32.4, 1056 x 2080 x 2784 binary32 112.0 / 104.9, 2048 x 2048 x 1024 84.1 / 77.0).
+    QuantPlan qw{W, in_dt, N, K, K, 0, NVFP4_RTN, 0, wtc, wts, gw.src, ts + 1, gm_xw, gw.n};
+    QuantPlan qx{X, in_dt, M, K, K, 0, NVFP4_SR, seed + 2, xtc, xts, gx.src, ts + 3, gm_xw, gx.n};
+    auto maximum = [&](QuantPlan &q, int slot) {
+        GSource g{q.g_src, q.n_partials};
+        const hipError_t e = amax_dense(q.x, in_dt, q.rows * q.cols, partials, slot, st, &g);
+        q.g_src = g.src;
+        q.n_partials = g.n;
+        return e;
+    };
+    const bool w_max = f->tensor_scale && !known && dX && !have_wt, x_max = f->tensor_scale && !known && dW && !have_xt;
+    auto small = [&](const QuantPlan &q) { return small_tensor(in_dt, quant_args(q), f->block, use_hw_convert(), SMALL_COLUMNS); };
+    bool together = dual && !dy_slab_r && !dy_slab_c && !(have_wt && have_xt) && (have_wt || small(qw)) && (have_xt || small(qx));
     if (dual) {
         DualArgs d;
         d.tag = tag;
@@ -896,29 +911,34 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         d.g_out2 = ts + 2;
         d.slab_r = dy_slab_r;
         d.slab_c = dy_slab_c;
-        if (launch_quantize_dual(d, in_dt, NVFP4_SR, NVFP4_SR, f->block, f->scale, true, st) != hipSuccess) return NVFP4_EHIP;
+        together = together && small_tensor(in_dt, d.c, f->block, true, SMALL_DUAL);
+        if (together) {
+            if ((w_max && maximum(qw, 1) != hipSuccess) || (x_max && maximum(qx, 2) != hipSuccess)) return NVFP4_EHIP;
+            const QuantArgs aw = quant_args(qw), ax = quant_args(qx);
+            if (launch_quantize_small_backward(d, have_wt ? nullptr : &aw, have_xt ? nullptr : &ax, in_dt, f->block, f->scale, st) != hipSuccess) return NVFP4_EHIP;
+        } else if (launch_quantize_dual(d, in_dt, NVFP4_SR, NVFP4_SR, f->block, f->scale, true, st) != hipSuccess) {
+            return NVFP4_EHIP;
+        }
     }
     const GemmArgs g_dx{M, K, N, dyc, dys, wtc, wts, g_dy_r, g_w, dX, K, dy_slab_r, wt_slab};
     const GemmArgs g_dw{N, K, M, dytc, dyts, xtc, xts, g_dy_c, g_x, dW, K, dy_slab_c, xt_slab};
     const bool pair = dX && dW && gemm_pairs(g_dx, g_dw, f->scale);  // (then both run after the last quantizer)
     if (dX) {
-        if (f->tensor_scale && !known && !have_wt && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
+        if (w_max && !together && maximum(qw, 1) != hipSuccess) return NVFP4_EHIP;
         // Eq. 5: dX[M, K] = Q_SR(dY)[M, N] * Q_RtN(W^T)[K, N]^T
         QuantPlan qa{dY, in_dt, M, N, N, 1, NVFP4_SR, seed, dyc, dys, gdy.src, ts + 0, gm, gdy.n};
-        QuantPlan qb{W, in_dt, N, K, K, 0, NVFP4_RTN, 0, wtc, wts, gw.src, ts + 1, gm_xw, gw.n};
         if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!dual && !dyq && launch_saved_tag(tag, ts + 0, nullptr, st) != hipSuccess) return NVFP4_EHIP;
-        if (!have_wt && run_quantize(qb, f, st) != hipSuccess) return NVFP4_EHIP;
+        if (!have_wt && !together && run_quantize(qw, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!pair && launch_gemm(g_dx, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
     if (dW) {
-        if (f->tensor_scale && !known && !have_xt && amax_dense(X, in_dt, M * K, partials, 2, st, &gx) != hipSuccess) return NVFP4_EHIP;
+        if (x_max && !together && maximum(qx, 2) != hipSuccess) return NVFP4_EHIP;
         // Eq. 6: dW[N, K] = Q_SR(dY^T)[N, M] * Q_SR(X^T)[K, M]^T
         QuantPlan qa{dY, in_dt, M, N, N, 0, NVFP4_SR, seed + 1, dytc, dyts, gdy.src, ts + 2, gm, gdy.n};
-        QuantPlan qb{X, in_dt, M, K, K, 0, NVFP4_SR, seed + 2, xtc, xts, gx.src, ts + 3, gm_xw, gx.n};
         if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!dual && !dyq && launch_saved_tag(tag, ts + 2, nullptr, st) != hipSuccess) return NVFP4_EHIP;
-        if (!have_xt && run_quantize(qb, f, st) != hipSuccess) return NVFP4_EHIP;
+        if (!have_xt && !together && run_quantize(qx, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!pair && launch_gemm(g_dw, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
     if (pair && launch_gemm_pair(g_dx, g_dw, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;

@@ -141,6 +141,9 @@ bool small_tensor(int dt, const QuantArgs &P, int block, bool hw_convert, SmallU
 hipError_t launch_quantize_small_rows(const QuantArgs &P, const QuantArgs *P1, int dt, int rounding, int block, int sf, hipStream_t st);
 hipError_t launch_quantize_small_columns(const QuantArgs &P, int dt, int rounding, int block, int sf, hipStream_t st);
 hipError_t launch_quantize_small_dual(const DualArgs &D, const DualArgs *W, int dt, int rnd_r, int rnd_c, int block, int sf, hipStream_t st);
+// A backward call's small tensors in one launch: both orientations of dY (stochastic), the columns of W (to nearest) and of X (stochastic);
+// W or X may be missing.
+hipError_t launch_quantize_small_backward(const DualArgs &dY, const QuantArgs *W, const QuantArgs *X, int dt, int block, int sf, hipStream_t st);
 // Row-blocked and column-blocked quantization of one tensor; one fused kernel when
 // quantize_dual_fused() holds, else the two single-orientation kernels.
 bool quantize_dual_fused(int dt, int64_t rows, int64_t cols, int64_t ld, int block, bool hw_convert);

@@ -247,4 +247,13 @@ hipError_t launch_quantize_small_dual(const DualArgs &D, const DualArgs *W, int 
     return launch_small(j, dt, block, sf, st);
 }
 
+hipError_t launch_quantize_small_backward(const DualArgs &dY, const QuantArgs *W, const QuantArgs *X, int dt, int block, int sf, hipStream_t st)
+{
+    SmallJob j[4] = {};
+    small_dual_jobs(dY, NVFP4_SR, NVFP4_SR, block, j);
+    if (W) j[2] = small_job(*W, 0, NVFP4_RTN, block);
+    if (X) j[3] = small_job(*X, 0, NVFP4_SR, block);
+    return launch_small(j, dt, block, sf, st);
+}
+
 }  // namespace nvfp4

@@ -322,3 +322,28 @@ def test_saved_operands_of_many_tiles(M, N, K, fmt_name):
     got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K)
     for a, b in zip(got, nv.linear_bwd(dY, X, W, seed, fmt)):
         assert torch.equal(a, b)
+
+
+# A backward call that has neither W^T nor X^T quantizes all three tensors in one launch where they are small: on the lines of that
+# (4M elements of dY, 8M of bf16 W and X, 16M of binary32) and past them, one of the three past, odd sizes; maxima taken, scales handed
+# over, W's operands at hand.  The bits of the separate calls.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "mxfp4", "e4m3_32", "e4m3_64"])
+@pytest.mark.parametrize("shape", [(64, 64, 64), (192, 320, 1088), (1056, 416, 2080), (2048, 2048, 64), (2048, 2112, 64), (64, 2048, 4096), (64, 2112, 4096),
+                                   (2112, 64, 4096)])
+def test_small_tensors_of_a_backward_call(shape, fmt_name, dtype):
+    block, scale = FORMATS[fmt_name]
+    fmt = nv.Format(block, scale, 1 - scale)
+    M, N, K = (-(-n // max(block, 32)) * max(block, 32) for n in shape)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    X, W, dY = (torch.randn(s, generator=g, device="cuda").to(dtype) for s in ((M, K), (N, K), (M, N)))
+    seed = 21
+    print(f"[case] small backward {fmt_name} {M}x{N}x{K} {dtype}", flush=True)
+    dX = nv.gemm(nv.quantize(dY, 1, nv.SR, seed, fmt), nv.quantize(W, 0, nv.RTN, 0, fmt), fmt)
+    dW = nv.gemm(nv.quantize(dY, 0, nv.SR, seed + 1, fmt), nv.quantize(X, 0, nv.SR, seed + 2, fmt), fmt)
+    scales = torch.empty(2, device="cuda")
+    nv.linear_fwd(X, W, fmt, scales_out=scales)
+    for kw in ({}, dict(xw_scales=scales), dict(w_operands=nv.quantize_weight(W, M, fmt))):
+        got = nv.linear_bwd(dY, X, W, seed, fmt, **kw)
+        assert torch.equal(got[0], dX) and torch.equal(got[1], dW), list(kw)
