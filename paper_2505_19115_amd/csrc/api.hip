@@ -89,6 +89,18 @@ bool dual_writes_slabs(const nvfp4_format *f, int dt, int64_t rows, int64_t cols
            quantize_dual_fused(dt, rows, cols, cols, f->block, use_hw_convert()) && !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN);
 }
 
+// The same for the tensors of a training call.  MXFP4 products take slabs from K = 512 on, however few their rows are, but tensors that the
+// kernels for small ones serve are quantized by those, row-major.  us, forward and backward, operands saved by the forward call, slabs /
+// row-major: 64 x 1024 x 1024 bf16 31.3 / 22.7, 512 x 1024 x 1024 38.8 / 30.0, binary32 41.3 / 27.6, 2048 x 2048 x 2048 72.8 / 66.3, 1024 x 2048 x
+// 4096 (W and X^T in slabs) 69.7 / 66.7; only tensor scales handed over: 512 x 1024 x 1024 45.2 / 25.6, 2048 x 2048 x 2048 80.7 / 62.6.
+bool training_slabs(const nvfp4_format *f, int dt, int64_t rows, int64_t cols, int rnd_r, int rnd_c)
+{
+    QuantArgs t;
+    t.rows = rows;
+    t.cols = cols;
+    return dual_writes_slabs(f, dt, rows, cols, rnd_r, rnd_c) && !(f->scale == NVFP4_SCALE_E8M0 && small_tensor(dt, t, f->block, use_hw_convert(), SMALL_DUAL));
+}
+
 // An empty tensor (rows or cols 0) may come with a null data pointer.
 nvfp4_status check_tensor(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld)
 {
@@ -744,7 +756,7 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
         DualArgs dx{{X, M, K, K, L.xtc, L.xts, gx.src, ts + 0, gm, bwd_seed + 2, gx.n}, xc, xs, 0, L.g + 0};
         DualArgs dw{{W, N, K, K, L.wtc, L.wts, gw.src, ts + 1, gm, 0, gw.n}, const_cast<uint8_t *>(wc), const_cast<uint8_t *>(wsc), 0, L.g + 1};
         // row-blocked sides feed this call's GEMM, Q(X^T) the update GEMM (Eq. 6), Q(W^T) the input-gradient GEMM (Eq. 5)
-        const bool sx = dual_writes_slabs(f, in_dt, M, K, NVFP4_RTN, NVFP4_SR), sw = dual_writes_slabs(f, in_dt, N, K, NVFP4_RTN, NVFP4_RTN);
+        const bool sx = training_slabs(f, in_dt, M, K, NVFP4_RTN, NVFP4_SR), sw = training_slabs(f, in_dt, N, K, NVFP4_RTN, NVFP4_RTN);
         dx.slab_r = a_slab = sx && t_fwd;
         dx.slab_c = sx && gemm_takes_slabs(N, K, M, f->block, f->scale);
         dw.slab_c = sw && gemm_takes_slabs(M, K, N, f->block, f->scale);
@@ -853,7 +865,7 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
     const bool dual = !dyq && dX && dW && quantize_dual_fused(in_dt, M, N, N, f->block, use_hw_convert());
     // layouts: dY's two sides as this call's dual pass writes them, W^T and X^T as the forward call wrote them
     const bool t_dx = gemm_takes_slabs(M, K, N, f->block, f->scale), t_dw = gemm_takes_slabs(N, K, M, f->block, f->scale);
-    const bool sdy = dual && dual_writes_slabs(f, in_dt, M, N, NVFP4_SR, NVFP4_SR);
+    const bool sdy = dual && training_slabs(f, in_dt, M, N, NVFP4_SR, NVFP4_SR);
     int dy_slab_r = sdy && t_dx, dy_slab_c = sdy && t_dw;
     const float *g_dy_r = ts + 0, *g_dy_c = ts + 2;  // written by this call's quantizers of dY
     if (dyq) {
@@ -868,8 +880,8 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
     } else if (f->tensor_scale) {
         if (amax_dense(dY, in_dt, M * N, partials, 0, st, &gdy) != hipSuccess) return NVFP4_EHIP;
     }
-    const int wt_slab = w_ops ? (int)wq_wt_slab : (int)(saved && t_dx && dual_writes_slabs(f, in_dt, N, K, NVFP4_RTN, NVFP4_RTN));
-    const int xt_slab = saved && t_dw && dual_writes_slabs(f, in_dt, M, K, NVFP4_RTN, NVFP4_SR);
+    const int wt_slab = w_ops ? (int)wq_wt_slab : (int)(saved && t_dx && training_slabs(f, in_dt, N, K, NVFP4_RTN, NVFP4_RTN));
+    const int xt_slab = saved && t_dw && training_slabs(f, in_dt, M, K, NVFP4_RTN, NVFP4_SR);
     TagArgs tag;
     if (saved) {
         tag = saved_tag(M, N, K, f, seed, xt_slab != 0, w_ops ? false : wt_slab != 0, w_ops != nullptr);

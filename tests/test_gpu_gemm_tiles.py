@@ -347,3 +347,25 @@ def test_small_tensors_of_a_backward_call(shape, fmt_name, dtype):
     for kw in ({}, dict(xw_scales=scales), dict(w_operands=nv.quantize_weight(W, M, fmt))):
         got = nv.linear_bwd(dY, X, W, seed, fmt, **kw)
         assert torch.equal(got[0], dX) and torch.equal(got[1], dW), list(kw)
+
+
+# MXFP4 tensors of up to 4M elements keep their rows in training calls whose products could take slabs (contractions of 512 and more): on
+# that line and past it, one operand on each side of it, operands handed over by the forward call.
+@pytest.mark.parametrize("shape", [(512, 512, 512), (96, 1024, 640), (2048, 2048, 2048), (2048, 2080, 2048), (2080, 512, 2048), (512, 2080, 2048)])
+def test_small_mxfp4_training_tensors(shape):
+    M, N, K = shape
+    fmt, seed = nv.MXFP4, 9
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N)
+    X, W, dY = (torch.randn(s, generator=g, device="cuda").bfloat16() for s in ((M, K), (N, K), (M, N)))
+    print(f"[case] small MXFP4 training {M}x{N}x{K}", flush=True)
+    Yr = nv.gemm(nv.quantize(X, fmt=fmt), nv.quantize(W, fmt=fmt), fmt)
+    dX = nv.gemm(nv.quantize(dY, 1, nv.SR, seed, fmt), nv.quantize(W, 0, nv.RTN, 0, fmt), fmt)
+    dW = nv.gemm(nv.quantize(dY, 0, nv.SR, seed + 1, fmt), nv.quantize(X, 0, nv.SR, seed + 2, fmt), fmt)
+    wq = nv.quantize_weight(W, M, fmt)
+    for kw in ({}, dict(w_operands=wq)):
+        saved = torch.empty(nv.linear_saved_bytes(M, N, K, fmt), dtype=torch.uint8, device="cuda")
+        Y = nv.linear_fwd(X, None if kw else W, fmt, saved=saved, bwd_seed=seed, N=N, **kw)
+        got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K, **kw)
+        for a, b in zip((Y, *got), (Yr, dX, dW)):
+            assert torch.equal(a, b), list(kw)
