@@ -739,6 +739,24 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
             thin_takes_tensor(M, K, in_dt))
             return launch_gemm_thin_tensor(thin, X, in_dt, ts, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }
+    if (!w_ops && use_hw_convert() && small_forward_takes(M, N, K, in_dt, f->block, f->scale)) {
+        // a layer of a small network: everything in one launch, row-major (no product of this size takes slabs)
+        SmallForward S{};
+        S.P = GemmArgs{M, N, K, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, Y, N};
+        S.X = X;
+        S.W = W;
+        S.scales = ts;
+        S.tensor_scale = f->tensor_scale;
+        if (!saved) return launch_small_forward(S, nullptr, nullptr, in_dt, f->block, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
+        const SavedLayout L = saved_layout(saved, M, N, K, f->block);
+        const QuantArgs cx{X, M, K, K, L.xtc, L.xts, reinterpret_cast<const float *>(X), nullptr, gm, bwd_seed + 2, SELF_AMAX};
+        const QuantArgs cw{W, N, K, K, L.wtc, L.wts, reinterpret_cast<const float *>(W), nullptr, gm, 0, SELF_AMAX};
+        S.saved_scales = L.g;
+        S.tag = saved_tag(M, N, K, f, bwd_seed, false, false);
+        S.tag.dst = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(saved) + SAVED_TAG_OFFSET);
+        saved_remember(saved, S.tag);
+        return launch_small_forward(S, &cx, &cw, in_dt, f->block, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
+    }
     if (f->tensor_scale && (w_ops || both_max * K * (int64_t)elem_size(in_dt) <= SELF_AMAX_BYTES)) {
         if (amax_dense(X, in_dt, M * K, partials, 0, st, &gx) != hipSuccess) return NVFP4_EHIP;
         if (!w_ops && amax_dense(W, in_dt, N * K, partials, 1, st, &gw) != hipSuccess) return NVFP4_EHIP;
@@ -887,6 +905,16 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         tag = saved_tag(M, N, K, f, seed, xt_slab != 0, w_ops ? false : wt_slab != 0, w_ops != nullptr);
         tag.chk = reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(saved) + SAVED_TAG_OFFSET);
         if (!saved_matches(saved, tag)) return NVFP4_EINVAL;
+    }
+    if (dual && have_wt && have_xt && !wt_slab && !xt_slab && use_hw_convert() && small_backward_takes(M, N, K, in_dt, f->block, f->scale)) {
+        SmallBackward S{};
+        S.dx = GemmArgs{M, K, N, nullptr, nullptr, wtc, wts, nullptr, g_w, dX, K};
+        S.dw = GemmArgs{N, K, M, nullptr, nullptr, xtc, xts, nullptr, g_x, dW, K};
+        S.dY = QuantArgs{dY, M, N, N, nullptr, nullptr, nullptr, nullptr, gm, seed + 1};
+        S.seed_rows = seed;
+        S.tensor_scale = f->tensor_scale;
+        S.tag = tag;
+        return launch_small_backward(S, in_dt, f->block, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }
     // W and X down their columns, where those operands are not at hand.  Small ones go with dY in one launch: each by itself leaves CUs idle
     // (us, forward and backward, NVFP4, tensor scales handed over, a launch each / one: 64 x 256 x 128 bf16 21.4 / 15.4, 512 x 1024 x 1024 40.1 /

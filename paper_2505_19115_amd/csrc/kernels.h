@@ -165,6 +165,41 @@ hipError_t launch_swiglu_bwd_dual(DualArgs &g, DualArgs &u, int dt, int block, i
 // The same elementwise step with dG and dU stored as tensors of dt (n a multiple of 8).
 hipError_t launch_swiglu_bwd(const void *dH, const void *G, const void *U, int dt, int64_t n, void *dG, void *dU, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st);
+// One orientation of a tensor as part of a launch of the kernels for small tensors
+struct SmallJob {
+    QuantArgs q;   // q.g_out null: another job of the tensor writes the scale
+    int axis, rounding;
+    unsigned wgs;
+    float *g_out2;
+    TagArgs tag;
+};
+// A forward call, and a backward call on saved operands, in one launch, for layers of a small network (fused_small.hip): row-major operands.
+// cx, cw: the columns of X (stochastic) and of W (to nearest) that a forward call leaves for the backward one, or null.
+struct SmallForward {
+    GemmArgs P;          // sizes and output
+    const void *X, *W;
+    float *scales, *saved_scales;  // {gX, gW}; the second may be null
+    int tensor_scale;    // the format has one (taken from the tensors)
+    TagArgs tag;
+    SmallJob cx, cw;     // from here on set by the launcher
+    unsigned tiles;
+    uint32_t row_mul;
+    int lds_aux;
+};
+struct SmallBackward {
+    GemmArgs dx, dw;     // (A is not read)
+    QuantArgs dY;        // tensor and the columns' seed
+    uint64_t seed_rows;
+    int tensor_scale;
+    TagArgs tag;
+    unsigned tiles;      // from here on set by the launcher
+    uint32_t row_mul;
+    int lds_aux;
+};
+bool small_forward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf);
+bool small_backward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf);
+hipError_t launch_small_forward(SmallForward S, const QuantArgs *cx, const QuantArgs *cw, int dt, int block, int sf, int out_dt, hipStream_t st);
+hipError_t launch_small_backward(SmallBackward S, int dt, int block, int sf, int out_dt, hipStream_t st);
 // Two independent products in one launch, where gemm_pairs() holds (both small, the same tile).
 bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf);
 hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st);

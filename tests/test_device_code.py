@@ -168,3 +168,11 @@ def test_few_rows_kernels(tmp_path):
     assert len(thin) == 3 * 2 * 7 * 2  # (A packed, binary32, bf16; formats; tiles; output types)
     for args, v, s in thin:
         assert v <= 128 and s == 0, (args, v, s)
+
+
+def test_fused_layers_registers(tmp_path):
+    # workgroups of eight waves, one per CU: 256 registers
+    fused = list(kernels(registers("fused_small", tmp_path), "small_"))
+    assert len(fused) == 2 * 2 * 2 * 2  # (directions, element types, formats, output types)
+    for args, v, s in fused:
+        assert v <= 256 and s == 0, (args, v, s)
