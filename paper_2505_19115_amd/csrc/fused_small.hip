@@ -146,7 +146,7 @@ __device__ __forceinline__ void multiply(const GemmArgs &P, uint8_t *lds, int64_
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
     for (int kt = wave; kt < nkt; kt += NW) ksplit_compute<SF, TA, TB, NW>(lds + kt * G::STAGE, kt == nkt - 1 && rem < ks::KT, rem, acc, lane);
-    ksplit_finish<SF, TA, TB, NW, OUT_DT>(P, acc, lds, m0, n0, gg);
+    ksplit_finish<SF, TA, TB, NW, OUT_DT>(P, acc, lds, m0, n0, [&]() { return gg; });
 }
 
 }  // namespace fs

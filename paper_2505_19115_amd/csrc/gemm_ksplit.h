@@ -121,8 +121,9 @@ __device__ __forceinline__ void ksplit_compute(const uint8_t *stage, bool tail, 
     }
 }
 
-template <int SF, int TA, int TB, int NW, int OUT_DT>
-__device__ __forceinline__ void ksplit_finish(const GemmArgs &P, const ks::float16_t (&acc)[TA][TB], uint8_t *lds, int64_t m0, int64_t n0, float gg)
+// (scale() gives the product of the tensor scales, which is not needed, and in the kernels on packed operands not loaded, before the sums)
+template <int SF, int TA, int TB, int NW, int OUT_DT, class SCALE>
+__device__ __forceinline__ void ksplit_finish(const GemmArgs &P, const ks::float16_t (&acc)[TA][TB], uint8_t *lds, int64_t m0, int64_t n0, SCALE scale)
 {
     using namespace ks;
     using G = Geom<SF, TA, TB, NW>;
@@ -143,6 +144,7 @@ __device__ __forceinline__ void ksplit_finish(const GemmArgs &P, const ks::float
                         make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
     }
     __syncthreads();
+    const float gg = scale();
     // one thread sums 8 consecutive columns of a row over the waves, in their order
     constexpr int CPR = BN / 8;
     const bool wide = (OUT_DT == NVFP4_F32 ? (P.ldc & 3) : (P.ldc & 7)) == 0;

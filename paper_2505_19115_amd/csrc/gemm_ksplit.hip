@@ -155,7 +155,7 @@ __device__ __forceinline__ void ksplit_tile(const GemmArgs &P, const int wg)
         stage ^= 1;
     }
 
-    ksplit_finish<SF, TA, TB, NW, OUT_DT>(P, acc, lds, m0, n0, P.gA[0] * P.gB[0]);
+    ksplit_finish<SF, TA, TB, NW, OUT_DT>(P, acc, lds, m0, n0, [&]() { return P.gA[0] * P.gB[0]; });
 }
 
 // One product, or two that do not depend on each other (a backward call's dX and dW) in one launch: the first `tiles`
