@@ -960,24 +960,26 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
             return NVFP4_EHIP;
         }
     }
+    if (!dual && !dyq) {
+        // dY's two sides by themselves, one behind the other (the second finds the tensor in the last-level cache)
+        QuantPlan rows{dY, in_dt, M, N, N, 1, NVFP4_SR, seed, dyc, dys, gdy.src, ts + 0, gm, gdy.n};
+        QuantPlan columns{dY, in_dt, M, N, N, 0, NVFP4_SR, seed + 1, dytc, dyts, gdy.src, ts + 2, gm, gdy.n};
+        if (dX && run_quantize(rows, f, st) != hipSuccess) return NVFP4_EHIP;
+        if (dW && run_quantize(columns, f, st) != hipSuccess) return NVFP4_EHIP;
+        if (launch_saved_tag(tag, dX ? ts + 0 : nullptr, dW ? ts + 2 : nullptr, st) != hipSuccess) return NVFP4_EHIP;
+    }
     const GemmArgs g_dx{M, K, N, dyc, dys, wtc, wts, g_dy_r, g_w, dX, K, dy_slab_r, wt_slab};
     const GemmArgs g_dw{N, K, M, dytc, dyts, xtc, xts, g_dy_c, g_x, dW, K, dy_slab_c, xt_slab};
     const bool pair = dX && dW && gemm_pairs(g_dx, g_dw, f->scale);  // (then both run after the last quantizer)
     if (dX) {
         if (w_max && !together && maximum(qw, 1) != hipSuccess) return NVFP4_EHIP;
         // Eq. 5: dX[M, K] = Q_SR(dY)[M, N] * Q_RtN(W^T)[K, N]^T
-        QuantPlan qa{dY, in_dt, M, N, N, 1, NVFP4_SR, seed, dyc, dys, gdy.src, ts + 0, gm, gdy.n};
-        if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
-        if (!dual && !dyq && launch_saved_tag(tag, ts + 0, nullptr, st) != hipSuccess) return NVFP4_EHIP;
         if (!have_wt && !together && run_quantize(qw, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!pair && launch_gemm(g_dx, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }
     if (dW) {
         if (x_max && !together && maximum(qx, 2) != hipSuccess) return NVFP4_EHIP;
         // Eq. 6: dW[N, K] = Q_SR(dY^T)[N, M] * Q_SR(X^T)[K, M]^T
-        QuantPlan qa{dY, in_dt, M, N, N, 0, NVFP4_SR, seed + 1, dytc, dyts, gdy.src, ts + 2, gm, gdy.n};
-        if (!dual && !dyq && run_quantize(qa, f, st) != hipSuccess) return NVFP4_EHIP;
-        if (!dual && !dyq && launch_saved_tag(tag, ts + 2, nullptr, st) != hipSuccess) return NVFP4_EHIP;
         if (!have_xt && !together && run_quantize(qx, f, st) != hipSuccess) return NVFP4_EHIP;
         if (!pair && launch_gemm(g_dw, f->block, f->scale, out_dt, st) != hipSuccess) return NVFP4_EHIP;
     }

@@ -1395,6 +1395,23 @@ static void launch_dual_pair_fmt(const DualArgs &x, const DualArgs &w, hipStream
     hipLaunchKernelGGL((quantize_dual_pair_kernel<DT, B, SF>), dim3(tiles + across(w) * down(w)), dim3(G::NT), 0, st, x, w, tiles, across(x), across(w));
 }
 
+// The two single-orientation passes of a dual quantization; each writes one of the scale's destinations.
+static QuantArgs row_side(const DualArgs &D)
+{
+    QuantArgs r = D.c;
+    r.codes = D.codes_r;
+    r.scales = D.scales_r;
+    r.seed = D.seed_r;
+    return r;
+}
+static hipError_t launch_column_side(const DualArgs &D, int dt, int rounding, int block, int sf, bool hw_convert, hipStream_t st)
+{
+    QuantArgs c = D.c;
+    if (D.g_out2) c.g_out = D.g_out2;
+    const hipError_t e = launch_quantize(c, dt, 0, rounding, block, sf, hw_convert, st);
+    return e != hipSuccess ? e : launch_saved_tag(D.tag, D.c.g_out, D.g_out2, st);
+}
+
 hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int dt, int block, int sf, bool hw_convert, hipStream_t st)
 {
     if (!(x.slab_r || x.slab_c || w.slab_r || w.slab_c) && small_tensor(dt, x.c, block, hw_convert, SMALL_DUAL) && small_tensor(dt, w.c, block, hw_convert, SMALL_DUAL) &&
@@ -1417,6 +1434,13 @@ hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int d
         else if (nv) launch_dual_pair_fmt<NVFP4_F32, 16, NVFP4_SCALE_E4M3>(x, w, st);
         else launch_dual_pair_fmt<NVFP4_F32, 32, NVFP4_SCALE_E8M0>(x, w, st);
         return launch_status();
+    }
+    if (!quantize_dual_fused(dt, x.c.rows, x.c.cols, x.c.ld, block, hw_convert) && !quantize_dual_fused(dt, w.c.rows, w.c.cols, w.c.ld, block, hw_convert)) {
+        // (wide blocks) the rows of both in one launch, then the columns of each
+        if (x.slab_r || x.slab_c || w.slab_r || w.slab_c) return hipErrorInvalidValue;
+        hipError_t e = launch_quantize_rows_pair(row_side(x), row_side(w), dt, block, sf, hw_convert, st);
+        if (e == hipSuccess) e = launch_column_side(x, dt, NVFP4_SR, block, sf, hw_convert, st);
+        return e != hipSuccess ? e : launch_column_side(w, dt, NVFP4_RTN, block, sf, hw_convert, st);
     }
     const hipError_t e = launch_quantize_dual(x, dt, NVFP4_RTN, NVFP4_SR, block, sf, hw_convert, st);
     return e != hipSuccess ? e : launch_quantize_dual(w, dt, NVFP4_RTN, NVFP4_RTN, block, sf, hw_convert, st);
@@ -1467,20 +1491,8 @@ hipError_t launch_quantize_dual(const DualArgs &D, int dt, int rnd_r, int rnd_c,
     }
     // other block sizes and ragged shapes: the two single-orientation kernels (they write the plain layout only)
     if (D.slab_r || D.slab_c) return hipErrorInvalidValue;
-    QuantArgs r = D.c;
-    r.codes = D.codes_r;
-    r.scales = D.scales_r;
-    r.seed = D.seed_r;
-    r.g_out = D.c.g_out;
-    hipError_t e = launch_quantize(r, dt, 1, rnd_r, block, sf, hw_convert, st);
-    if (e != hipSuccess) return e;
-    e = launch_quantize(D.c, dt, 0, rnd_c, block, sf, hw_convert, st);
-    if (e != hipSuccess) return e;
-    if (D.g_out2) {
-        e = hipMemcpyAsync(D.g_out2, D.c.g_out, sizeof(float), hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return e;
-    }
-    return launch_saved_tag(D.tag, D.c.g_out, D.g_out2, st);
+    const hipError_t e = launch_quantize(row_side(D), dt, 1, rnd_r, block, sf, hw_convert, st);
+    return e != hipSuccess ? e : launch_column_side(D, dt, rnd_c, block, sf, hw_convert, st);
 }
 
 hipError_t launch_saved_tag(const TagArgs &t, float *g1, float *g2, hipStream_t st)
