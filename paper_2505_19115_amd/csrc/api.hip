@@ -98,7 +98,7 @@ bool training_slabs(const nvfp4_format *f, int dt, int64_t rows, int64_t cols, i
     QuantArgs t;
     t.rows = rows;
     t.cols = cols;
-    return dual_writes_slabs(f, dt, rows, cols, rnd_r, rnd_c) && !(f->scale == NVFP4_SCALE_E8M0 && small_tensor(dt, t, f->block, use_hw_convert(), SMALL_DUAL));
+    return dual_writes_slabs(f, dt, rows, cols, rnd_r, rnd_c) && !(f->scale == NVFP4_SCALE_E8M0 && small_tensor(dt, t, f->block, f->scale, use_hw_convert(), SMALL_DUAL));
 }
 
 // An empty tensor (rows or cols 0) may come with a null data pointer.
@@ -234,7 +234,7 @@ void weight_slabs(const nvfp4_format *f, int64_t M, int64_t N, int64_t K, bool *
     QuantArgs w;
     w.rows = N;
     w.cols = K;
-    const bool any = !small_tensor(NVFP4_BF16, w, f->block, use_hw_convert(), SMALL_DUAL);
+    const bool any = !small_tensor(NVFP4_BF16, w, f->block, f->scale, use_hw_convert(), SMALL_DUAL);
     *w_slab = sw && (any ? gemm_reads_slabs(K, f->block, f->scale) : gemm_takes_slabs(M, N, K, f->block, f->scale));
     *wt_slab = sw && (any ? gemm_reads_slabs(N, f->block, f->scale) : gemm_takes_slabs(M, K, N, f->block, f->scale));
 }
@@ -880,7 +880,11 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
     GSource gw{known ? xw_scales + 1 : reinterpret_cast<const float *>(amax + 1), 0};
     GSource gx{known ? xw_scales + 0 : reinterpret_cast<const float *>(amax + 2), 0};
     // with both GEMMs wanted, dY is read once for its two orientations (streams seed, seed+1)
-    const bool dual = !dyq && dX && dW && quantize_dual_fused(in_dt, M, N, N, f->block, use_hw_convert());
+    QuantArgs dy_tensor;
+    dy_tensor.rows = M;
+    dy_tensor.cols = N;
+    const bool dual = !dyq && dX && dW && (quantize_dual_fused(in_dt, M, N, N, f->block, use_hw_convert()) ||
+                                           small_tensor(in_dt, dy_tensor, f->block, f->scale, use_hw_convert(), SMALL_DUAL));
     // layouts: dY's two sides as this call's dual pass writes them, W^T and X^T as the forward call wrote them
     const bool t_dx = gemm_takes_slabs(M, K, N, f->block, f->scale), t_dw = gemm_takes_slabs(N, K, M, f->block, f->scale);
     const bool sdy = dual && training_slabs(f, in_dt, M, N, NVFP4_SR, NVFP4_SR);
@@ -929,7 +933,7 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         return e;
     };
     const bool w_max = f->tensor_scale && !known && dX && !have_wt, x_max = f->tensor_scale && !known && dW && !have_xt;
-    auto small = [&](const QuantPlan &q) { return small_tensor(in_dt, quant_args(q), f->block, use_hw_convert(), SMALL_COLUMNS); };
+    auto small = [&](const QuantPlan &q) { return small_tensor(in_dt, quant_args(q), f->block, f->scale, use_hw_convert(), SMALL_COLUMNS); };
     bool together = dual && !dy_slab_r && !dy_slab_c && !(have_wt && have_xt) && (have_wt || small(qw)) && (have_xt || small(qx));
     if (dual) {
         DualArgs d;
@@ -951,7 +955,7 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         d.g_out2 = ts + 2;
         d.slab_r = dy_slab_r;
         d.slab_c = dy_slab_c;
-        together = together && small_tensor(in_dt, d.c, f->block, true, SMALL_DUAL);
+        together = together && small_tensor(in_dt, d.c, f->block, f->scale, true, SMALL_DUAL);
         if (together) {
             if ((w_max && maximum(qw, 1) != hipSuccess) || (x_max && maximum(qx, 2) != hipSuccess)) return NVFP4_EHIP;
             const QuantArgs aw = quant_args(qw), ax = quant_args(qx);

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(fs::NT) void small_backward_kernel(SmallBackward S)
         for (int blk = wave; blk < blocks; blk += NW) {
             if (blk != wave) load_column<DT, B>(S.dY, (int64_t)blk * B, m0, lane, m0 + row < P.M, v);
             uint32_t words[B / 8];
-            const uint32_t sbyte = column_block<DT, B, SF, NVFP4_SR>(v, g, 1.0f / (6.0f * g), draws + blk * (B * 64), lane, words);
+            const uint32_t sbyte = column_block<DT, B, SF, NVFP4_SR>(v, column_max(v), g, 1.0f / (6.0f * g), draws + blk * (B * 64), lane, words);
             const int c = blk * (B / 8);
             uint8_t *const stage = lds + (c >> 4) * G::STAGE;
 #pragma unroll

@@ -137,7 +137,7 @@ bool quantize_streams(const QuantArgs &P, int block, int sf, bool both, int rnd_
 // Tensors that quantize_small.hip serves (its kernels split them finer): rows of one tensor or of two (P1: both round to nearest), columns
 // of one, and both orientations of one tensor or of a forward call's X and W (W round to nearest).  Row-major outputs.
 enum SmallUse { SMALL_ROWS, SMALL_COLUMNS, SMALL_DUAL };
-bool small_tensor(int dt, const QuantArgs &P, int block, bool hw_convert, SmallUse use);
+bool small_tensor(int dt, const QuantArgs &P, int block, int sf, bool hw_convert, SmallUse use);
 hipError_t launch_quantize_small_rows(const QuantArgs &P, const QuantArgs *P1, int dt, int rounding, int block, int sf, hipStream_t st);
 hipError_t launch_quantize_small_columns(const QuantArgs &P, int dt, int rounding, int block, int sf, hipStream_t st);
 hipError_t launch_quantize_small_dual(const DualArgs &D, const DualArgs *W, int dt, int rnd_r, int rnd_c, int block, int sf, hipStream_t st);

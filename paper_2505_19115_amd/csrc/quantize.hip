@@ -1202,8 +1202,8 @@ static bool streams_dual(const QuantArgs &P, int block, int sf, int rnd_c, bool 
 bool quantize_streams(const QuantArgs &P, int block, int sf, bool both, int rnd_r, int rnd_c, bool slabs, bool cached, bool hw_convert)
 {
     if (!hw_convert || short_lane_tile(NVFP4_BF16, block, sf, rnd_r, rnd_c, COLUMNS, P.rows, P.cols)) return false;
-    if (!both) return !small_tensor(NVFP4_BF16, P, block, true, SMALL_COLUMNS) && streams_columns(P, block, sf, rnd_c, cached);
-    return (slabs || !small_tensor(NVFP4_BF16, P, block, true, SMALL_DUAL)) && quantize_dual_fused(NVFP4_BF16, P.rows, P.cols, P.ld, block, true) &&
+    if (!both) return !small_tensor(NVFP4_BF16, P, block, sf, true, SMALL_COLUMNS) && streams_columns(P, block, sf, rnd_c, cached);
+    return (slabs || !small_tensor(NVFP4_BF16, P, block, sf, true, SMALL_DUAL)) && quantize_dual_fused(NVFP4_BF16, P.rows, P.cols, P.ld, block, true) &&
            !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN) && streams_dual(P, block, sf, rnd_c, slabs, cached);
 }
 template <typename K, typename A>
@@ -1274,8 +1274,8 @@ static void launch_q_fmt(const QuantArgs &P, int axis, int rounding, int block, 
 hipError_t launch_quantize(const QuantArgs &P, int dt, int axis, int rounding, int block, int sf,
                            bool hw_convert, hipStream_t st)
 {
-    if (axis == 1 && small_tensor(dt, P, block, hw_convert, SMALL_ROWS)) return launch_quantize_small_rows(P, nullptr, dt, rounding, block, sf, st);
-    if (axis == 0 && small_tensor(dt, P, block, hw_convert, SMALL_COLUMNS)) return launch_quantize_small_columns(P, dt, rounding, block, sf, st);
+    if (axis == 1 && small_tensor(dt, P, block, sf, hw_convert, SMALL_ROWS)) return launch_quantize_small_rows(P, nullptr, dt, rounding, block, sf, st);
+    if (axis == 0 && small_tensor(dt, P, block, sf, hw_convert, SMALL_COLUMNS)) return launch_quantize_small_columns(P, dt, rounding, block, sf, st);
     if (dt == NVFP4_BF16)
         launch_q_fmt<NVFP4_BF16>(P, axis, rounding, block, sf, hw_convert, st);
     else
@@ -1414,7 +1414,7 @@ static hipError_t launch_column_side(const DualArgs &D, int dt, int rounding, in
 
 hipError_t launch_quantize_dual_pair(const DualArgs &x, const DualArgs &w, int dt, int block, int sf, bool hw_convert, hipStream_t st)
 {
-    if (!(x.slab_r || x.slab_c || w.slab_r || w.slab_c) && small_tensor(dt, x.c, block, hw_convert, SMALL_DUAL) && small_tensor(dt, w.c, block, hw_convert, SMALL_DUAL) &&
+    if (!(x.slab_r || x.slab_c || w.slab_r || w.slab_c) && small_tensor(dt, x.c, block, sf, hw_convert, SMALL_DUAL) && small_tensor(dt, w.c, block, sf, hw_convert, SMALL_DUAL) &&
         x.c.rows % block == 0 && w.c.rows % block == 0) {
         return launch_quantize_small_dual(x, &w, dt, NVFP4_RTN, NVFP4_SR, block, sf, st);
     }
@@ -1459,7 +1459,7 @@ static void launch_rows_pair_dt(const QuantArgs &a, const QuantArgs &b, int bloc
 
 hipError_t launch_quantize_rows_pair(const QuantArgs &a, const QuantArgs &b, int dt, int block, int sf, bool hw_convert, hipStream_t st)
 {
-    if (small_tensor(dt, a, block, hw_convert, SMALL_ROWS) && small_tensor(dt, b, block, hw_convert, SMALL_ROWS))
+    if (small_tensor(dt, a, block, sf, hw_convert, SMALL_ROWS) && small_tensor(dt, b, block, sf, hw_convert, SMALL_ROWS))
         return launch_quantize_small_rows(a, &b, dt, NVFP4_RTN, block, sf, st);
     auto wgs = [](const QuantArgs &P) { return (P.rows * (P.cols >> 3) + 256 * ROWS_UNROLL - 1) / (256 * ROWS_UNROLL); };
     if (hw_convert && wgs(a) + wgs(b) < ((int64_t)1 << 31) && (sf == NVFP4_SCALE_E4M3 || block == 32)) {
@@ -1482,7 +1482,7 @@ bool quantize_dual_fused(int dt, int64_t rows, int64_t cols, int64_t ld, int blo
 hipError_t launch_quantize_dual(const DualArgs &D, int dt, int rnd_r, int rnd_c, int block, int sf, bool hw_convert,
                                 hipStream_t st)
 {
-    if (!D.slab_r && !D.slab_c && small_tensor(dt, D.c, block, hw_convert, SMALL_DUAL)) return launch_quantize_small_dual(D, nullptr, dt, rnd_r, rnd_c, block, sf, st);
+    if (!D.slab_r && !D.slab_c && small_tensor(dt, D.c, block, sf, hw_convert, SMALL_DUAL)) return launch_quantize_small_dual(D, nullptr, dt, rnd_r, rnd_c, block, sf, st);
     // (SR rows with RtN columns is a combination no equation asks for: two kernels)
     if (quantize_dual_fused(dt, D.c.rows, D.c.cols, D.c.ld, block, hw_convert) && !(rnd_r == NVFP4_SR && rnd_c == NVFP4_RTN)) {
         if (dt == NVFP4_F32) launch_dual_fmt<NVFP4_F32>(D, rnd_r, rnd_c, block, sf, st);

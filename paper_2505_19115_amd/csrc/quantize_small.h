@@ -56,14 +56,20 @@ __device__ __forceinline__ void column_draws(const QuantArgs &P, int64_t row0, i
     }
     asm volatile("" ::: "memory");  // (other lanes of the wave read them below: the LDS keeps a wave's order, and so must the compiler)
 }
-// The lane's block of a column -> its scale byte and codes.
-template <int DT, int B, int SF, int RND>
-__device__ __forceinline__ uint32_t column_block(const float (&v)[B], float g, float k, const uint16_t *mine, int lane, uint32_t (&words)[B / 8])
+template <int B>
+__device__ __forceinline__ float column_max(const float (&v)[B])
 {
-    constexpr bool MXS = SF == NVFP4_SCALE_E8M0;
-    float a = 0.0f, q;
+    float a = 0.0f;
 #pragma unroll
     for (int r = 0; r < B; ++r) a = fmaxf(a, fabsf(v[r]));
+    return a;
+}
+// The lane's rows of a block of a column, whose maximum is a -> the block's scale byte and their codes.
+template <int DT, int B, int SF, int RND>
+__device__ __forceinline__ uint32_t column_block(const float (&v)[B], float a, float g, float k, const uint16_t *mine, int lane, uint32_t (&words)[B / 8])
+{
+    constexpr bool MXS = SF == NVFP4_SCALE_E8M0;
+    float q;
     const uint32_t sbyte = block_scale<SF, true, false>(a, g, k, &q);
     if (MXS) q = mx_scale_operand(sbyte);
 #pragma unroll
@@ -90,29 +96,40 @@ __device__ __forceinline__ uint32_t column_block(const float (&v)[B], float g, f
     return sbyte;
 }
 
-// One lane = one block of B rows of one column, a wave = 64 columns, the waves of a workgroup one below the other, so that the 8 or 16
-// code bytes that they store to an output row make up one line; row-major outputs, cols a multiple of 8.
+// One lane = one block of B rows of one column (of blocks of 64 and 128 rows: 32 rows, and two or four waves share a block and exchange
+// its maximum through LDS), a wave = 64 columns, the waves of a workgroup one below the other, so that the 8 or 16 code bytes that they
+// store to an output row make up one line; row-major outputs, cols a multiple of 8.
+constexpr int small_rows(int block) { return block < 32 ? block : 32; }
 template <int DT, int B, int SF, int RND>
 __device__ __forceinline__ float cols_small(const QuantArgs &P, const unsigned wg, uint32_t *draws)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned groups = (unsigned)((P.cols + 63) / 64), nblk = (unsigned)(P.rows / B);
+    constexpr int H = small_rows(B), WPB = B / H;  // rows of a lane, waves of a block
+    const unsigned groups = (unsigned)((P.cols + 63) / 64), nblk = (unsigned)(P.rows / H);
     const unsigned band = wg / groups, blk = band * (SMALL_NT / 64) + wave;
-    const int64_t row0 = (int64_t)blk * B, col0 = (int64_t)(wg - band * groups) * 64, col = col0 + lane_column<DT>(lane);
+    const int64_t row0 = (int64_t)blk * H, col0 = (int64_t)(wg - band * groups) * 64, col = col0 + lane_column<DT>(lane);
     const bool live = blk < nblk && col < P.cols;  // (of two lanes that share a dword both or neither: cols is even)
-    float v[B];
-    load_column<DT, B>(P, row0, col0, lane, live, v);
-    uint16_t *const mine = reinterpret_cast<uint16_t *>(draws) + wave * (B * 64);
-    if (RND == NVFP4_SR) column_draws<B>(P, row0, col0, lane, mine);
+    float v[H];
+    load_column<DT, H>(P, row0, col0, lane, live, v);
+    uint16_t *const mine = reinterpret_cast<uint16_t *>(draws) + wave * (H * 64);
+    if (RND == NVFP4_SR) column_draws<H>(P, row0, col0, lane, mine);
     const float g = resolve_g<DT, SMALL_NT, SF == NVFP4_SCALE_E4M3>(P);
     const float k = 1.0f / (6.0f * g);
-    uint32_t words[B / 8];
-    const uint32_t sbyte = column_block<DT, B, SF, RND>(v, g, k, mine, lane, words);
+    float a = column_max(v);
+    if constexpr (WPB > 1) {
+        __shared__ float part[SMALL_NT];
+        part[threadIdx.x] = a;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WPB; ++w) a = fmaxf(a, part[(wave / WPB * WPB + w) * 64 + lane]);
+    }
+    uint32_t words[H / 8];
+    const uint32_t sbyte = column_block<DT, H, SF, RND>(v, a, g, k, mine, lane, words);
     if (live) {
         uint8_t *const dst = P.codes + col * (P.rows >> 1) + (row0 >> 1);
 #pragma unroll
-        for (int w = 0; w < B / 8; w += 2) *reinterpret_cast<uint2 *>(dst + 4 * w) = make_uint2(words[w], words[w + 1]);
-        P.scales[col * (int64_t)nblk + blk] = (uint8_t)sbyte;
+        for (int w = 0; w < H / 8; w += 2) *reinterpret_cast<uint2 *>(dst + 4 * w) = make_uint2(words[w], words[w + 1]);
+        if (WPB == 1 || blk % WPB == 0) P.scales[col * (int64_t)(nblk / WPB) + blk / WPB] = (uint8_t)sbyte;
     }
     return g;
 }

@@ -6,7 +6,7 @@ namespace nvfp4 {
 template <int DT, int B, int SF>
 __global__ __launch_bounds__(SMALL_NT) void quantize_small_kernel(SmallJob j0, SmallJob j1, SmallJob j2, SmallJob j3)
 {
-    __shared__ __align__(16) uint32_t draws[SMALL_NT / 64 * B * 32];
+    __shared__ __align__(16) uint32_t draws[SMALL_NT / 64 * small_rows(B) * 32];
     unsigned wg = blockIdx.x;
     const unsigned e0 = j0.wgs, e1 = e0 + j1.wgs, e2 = e1 + j2.wgs;
     const SmallJob &J = wg < e0 ? j0 : wg < e1 ? j1 : wg < e2 ? j2 : j3;
@@ -62,17 +62,30 @@ __global__ __launch_bounds__(SMALL_NT) void quantize_small_rows_pair_kernel(Quan
 //   4096 x 4096     9.8 / 14.8  11.4 / 15.2  15.6 / 15.8  15.1 / 28.0  22.5 / 31.4     15.6 / 17.8  19.6 / 18.5  20.1 / 35.5  22.0 / 36.2
 // (MXFP4: the same lines, columns SR of 4096 x 4096 binary32 21.9 / 16.2.  The rows as jobs of the columns' kernel; by themselves, as they
 // are launched now, 0.4 us less.)
-bool small_tensor(int dt, const QuantArgs &P, int block, bool hw, SmallUse use)
+// E4M3 blocks of 64 (of 128 the same within 3 %), whose dual form is otherwise two launches; their rows by themselves stay where they are:
+//                  bf16 columns RtN  columns SR   RtN+RtN      SR+SR         binary32 columns RtN  columns SR   RtN+RtN      SR+SR
+//    256 x  256        5.8 / 3.8      7.8 / 5.0    8.5 / 3.7   10.9 / 5.0          7.3 / 3.4        8.6 / 4.6    9.2 / 3.4   11.6 / 4.6
+//   1024 x 1024        6.0 / 4.0      7.9 / 5.1    9.5 / 4.4   12.2 / 5.9          7.6 / 3.7        9.7 / 4.8   11.3 / 4.3   13.5 / 5.7
+//   2048 x 2048        8.5 / 5.3     10.6 / 6.4   12.5 / 9.6   15.5 / 11.0         8.5 / 6.4       10.6 / 7.3   13.7 / 11.8  16.4 / 12.1
+//   2048 x 4096        9.2 / 8.2     11.4 / 9.1   14.2 / 13.7  18.0 / 16.6        10.1 / 9.0       11.7 / 9.9   18.5 / 17.5  20.4 / 19.0
+//   4096 x 4096       11.7 / 11.7    16.3 / 16.4  20.0 / 20.2  26.0 / 26.0        17.5 / 18.2      19.9 / 19.1  32.4 / 32.1  35.3 / 34.4
+// (forward and backward of 1024 x 1024 x 1024 with saved operands, bf16, blocks of 64: 71.3 / 43.8)
+bool small_tensor(int dt, const QuantArgs &P, int block, int sf, bool hw, SmallUse use)
 {
     const bool bf16 = dt == NVFP4_BF16;
-    const int64_t M = 1 << 20, most = use == SMALL_ROWS ? (bf16 ? M : 4 * M) : use == SMALL_COLUMNS ? (bf16 ? 8 * M : 16 * M) : 4 * M;
-    return hw && (block == 16 || block == 32) && (P.cols & 7) == 0 && P.rows * P.cols <= most;
+    const int64_t M = 1 << 20;
+    // (narrow ones of more than 512 workgroup tiles of 128 x 256 are walked by the streaming kernels)
+    if (block > 32)
+        return hw && sf == NVFP4_SCALE_E4M3 && use != SMALL_ROWS && (P.cols & 7) == 0 && P.rows * P.cols <= 8 * M &&
+               ((P.rows + 127) / 128) * ((P.cols + 255) / 256) <= 512;
+    const int64_t most = use == SMALL_ROWS ? (bf16 ? M : 4 * M) : use == SMALL_COLUMNS ? (bf16 ? 8 * M : 16 * M) : 4 * M;
+    return hw && (P.cols & 7) == 0 && P.rows * P.cols <= most;
 }
 SmallJob small_job(const QuantArgs &q, int axis, int rounding, int block)
 {
     SmallJob j = {q, axis, rounding, 0, nullptr, {}};
     constexpr int WAVES = SMALL_NT / 64;
-    j.wgs = (unsigned)(axis == 1 ? (q.rows * (q.cols >> 3) + SMALL_NT - 1) / SMALL_NT : (q.rows / block + WAVES - 1) / WAVES * ((q.cols + 63) / 64));
+    j.wgs = (unsigned)(axis == 1 ? (q.rows * (q.cols >> 3) + SMALL_NT - 1) / SMALL_NT : (q.rows / small_rows(block) + WAVES - 1) / WAVES * ((q.cols + 63) / 64));
     return j;
 }
 // the jobs of a dual quantization (row-major outputs): rows, which also write the scale, and columns
@@ -93,7 +106,9 @@ template <int DT>
 static void launch_small_dt(const SmallJob (&j)[4], int block, int sf, hipStream_t st)
 {
     const dim3 grid(j[0].wgs + j[1].wgs + j[2].wgs + j[3].wgs), wg(SMALL_NT);
-    if (block == 16 && sf == NVFP4_SCALE_E4M3) hipLaunchKernelGGL((quantize_small_kernel<DT, 16, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    if (block == 64) hipLaunchKernelGGL((quantize_small_kernel<DT, 64, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    else if (block == 128) hipLaunchKernelGGL((quantize_small_kernel<DT, 128, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
+    else if (block == 16 && sf == NVFP4_SCALE_E4M3) hipLaunchKernelGGL((quantize_small_kernel<DT, 16, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
     else if (block == 16) hipLaunchKernelGGL((quantize_small_kernel<DT, 16, NVFP4_SCALE_E8M0>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
     else if (sf == NVFP4_SCALE_E4M3) hipLaunchKernelGGL((quantize_small_kernel<DT, 32, NVFP4_SCALE_E4M3>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);
     else hipLaunchKernelGGL((quantize_small_kernel<DT, 32, NVFP4_SCALE_E8M0>), grid, wg, 0, st, j[0], j[1], j[2], j[3]);

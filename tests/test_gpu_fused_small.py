@@ -74,7 +74,7 @@ def test_buffer_of_another_call_poisons_the_gradients():
     nv.linear_fwd(X, W, saved=saved, bwd_seed=seed)
     with pytest.raises(nv.Nvfp4Error):
         nv.linear_bwd(dY, None, None, seed + 1, saved=saved, K=K)
-    moved = saved.clone()  # an address that no forward call wrote to
+    moved = torch.empty(saved.numel() + 1280, dtype=torch.uint8, device="cuda")[1280:].copy_(saved)  # an address that no forward call wrote to
     good, bad = nv.linear_bwd(dY, None, None, seed, saved=moved, K=K), nv.linear_bwd(dY, None, None, seed + 1, saved=moved, K=K)
     assert all(torch.isfinite(t).all() for t in good) and all(torch.isnan(t).all() for t in bad)
 
