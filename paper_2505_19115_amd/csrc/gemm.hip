@@ -119,11 +119,12 @@ __device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float
 // 32 codes = two 16-element blocks; dword t (0..3) of the chunk feeds one MFMA step and
 // belongs to block t / 2.  A and B use the same assignment of contraction indices to (lane
 // half, step), which is all the instruction requires.
-template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL>
-__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmArgs P)
+// (wrow: the wave's first row in the tile)
+template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL, int BM>
+__device__ __forceinline__ void f16_tile(const GemmArgs &P, const int wrow)
 {
     constexpr int NT = 64 * WM * WN;  // threads of a group
-    constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN;
+    constexpr int BN = 32 * TB * WN;
     constexpr int SPT = KT / B;  // scale bytes per row per tile in global memory
     // A row-major row's scale bytes come 8 at a time: those of WINDOW K tiles.  A request per row costs the vector L1 the same for 1 byte
     // as for 8, and of a K tail the bytes past the row are shifted out below instead of left out one by one, which was a chain of 8
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     const int lane = threadIdx.x & 63;
     const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = KG == 1 ? 0 : wave_wg / NW, wave = wave_wg - group * NW, tid = wave * 64 + lane;  // (inside the group from here on)
-    const int wm = wave / WN, wn = wave % WN;
+    const int wn = wave % WN;
     const int r = lane & 31, h = lane >> 5;
     const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
     int ty, tx;
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
         const uint8_t *sA = stages + stage * STAGE + coff[p], *sB = sA + A_BYTES;
 #pragma unroll
         for (int a = 0; a < TA; ++a)
-            Q.ca[a] = *reinterpret_cast<const uint4 *>(sA + (wm * 32 * TA + 32 * a) * KTB);
+            Q.ca[a] = *reinterpret_cast<const uint4 *>(sA + (wrow + 32 * a) * KTB);
 #pragma unroll
         for (int b = 0; b < TB; ++b)
             Q.cb[b] = *reinterpret_cast<const uint4 *>(sB + (wn * 32 * TB + 32 * b) * KTB);
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
     auto load_scales = [&](int stage, int p, Scales &S) {
         const uint8_t *sS = stages + stage * STAGE + A_BYTES + B_BYTES + soff + 2 * p * (BM + BN) * 4;
 #pragma unroll
-        for (int a = 0; a < TA; ++a) S.sa[a] = *reinterpret_cast<const uint32_t *>(sS + (wm * 32 * TA + 32 * a) * 4);
+        for (int a = 0; a < TA; ++a) S.sa[a] = *reinterpret_cast<const uint32_t *>(sS + (wrow + 32 * a) * 4);
 #pragma unroll
         for (int b = 0; b < TB; ++b) S.sb[b] = *reinterpret_cast<const uint32_t *>(sS + (BM + wn * 32 * TB + 32 * b) * 4);
     };
@@ -433,7 +434,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
 
     // epilogue.  The MFMA's first operand is the B (N-side) fragment, so a lane holds four consecutive columns of one row.
     __syncthreads();  // every wave has read the last K tile: the stages may be overwritten
-    const int64_t row0 = m0 + wm * 32 * TA, col0 = n0 + wn * 32 * TB;
+    const int64_t row0 = m0 + wrow, col0 = n0 + wn * 32 * TB;
     uint8_t *const mine = lds + wave_wg * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2));
     if constexpr (KG == 1) {
         store_lines<OUT_DT, TA, TB>(P, acc, row0, col0, mine, lane);
@@ -447,6 +448,41 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
         // (of three tile rows the last group gets none)
         const int row = (group >> 1) * LO + (group & 1);
         if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, 1, TB>(P, last, row0 + row * 32, col0, mine, lane);
+    }
+}
+
+template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL>
+__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmArgs P)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % (WM * WN);
+    f16_tile<B, WM, WN, TA, TB, KG, OUT_DT, KTAIL, 32 * TA * WM>(P, wave / WN * 32 * TA);
+}
+
+// 160 x 256: the upper four waves have 96 rows, the lower four 64, one of each on every SIMD, whose matrix unit is thus as busy as with two
+// waves of 80.  Expansion of the operands bounds it as in the other tiles (2.06 us a K tile for 160 rows; 192 rows 2.33).  Which code a
+// wave runs is uniform over the wave; both halves issue the same number of barriers (one per K tile), loads and stores included.
+template <int B, int OUT_DT, bool KTAIL>
+__global__ __launch_bounds__(512, 2) void gemm_nt_f16_uneven_kernel(GemmArgs P)
+{
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4) f16_tile<B, 2, 4, 3, 2, 1, OUT_DT, KTAIL, 160>(P, 0);
+    else f16_tile<B, 2, 4, 2, 2, 1, OUT_DT, KTAIL, 160>(P, 96);
+}
+template <int B, bool KTAIL>
+static void launch_f16_uneven(const GemmArgs &P, int out_dt, hipStream_t st)
+{
+    constexpr int LDS_BYTES = 2 * (160 + 256) * (KTB + SROW);
+    static_assert(LDS_BYTES >= 8 * 32 * 64 * 4, "the epilogue's pieces");
+    const unsigned ntiles = (unsigned)(((P.N + 255) / 256) * ((P.M + 159) / 160));
+    if (out_dt == NVFP4_F32) {
+        auto k = gemm_nt_f16_uneven_kernel<B, NVFP4_F32, KTAIL>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(512), LDS_BYTES, st, P);
+    } else {
+        auto k = gemm_nt_f16_uneven_kernel<B, NVFP4_BF16, KTAIL>;
+        static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES), true);
+        (void)once;
+        hipLaunchKernelGGL(k, dim3(ntiles), dim3(512), LDS_BYTES, st, P);
     }
 }
 
@@ -496,6 +532,9 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
     } else if (tile == TILE_192x256) {
         if (ktail) launch_f16<B, 2, 4, 3, 2, 1, true>(P, out_dt, st);
         else launch_f16<B, 2, 4, 3, 2, 1, false>(P, out_dt, st);
+    } else if (tile == TILE_160x256) {
+        if (ktail) launch_f16_uneven<B, true>(P, out_dt, st);
+        else launch_f16_uneven<B, false>(P, out_dt, st);
     } else if (tile == TILE_128x256) {
         if (ktail) launch_f16<B, 2, 4, 2, 2, 1, true>(P, out_dt, st);
         else launch_f16<B, 2, 4, 2, 2, 1, false>(P, out_dt, st);
@@ -530,6 +569,7 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 //     4096 x  4096 x  4096           239.8     157.7     146.5     123.2     125.8     120.9     140.6     104.1
 //     8192 x  8192 x   256           287.3     130.6     138.0      46.6     125.8      52.3      49.9      47.6
 //     4096 x 11008 x   512           221.9      93.5      97.7      50.5      89.6      57.3      53.8      50.3
+// (160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.)
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
@@ -539,12 +579,12 @@ struct TileCost {
 static const TileCost E4M3_COST[TILES] = {
     {32, 32, 8, 512, 2900, 350, 860, 3},    {32, 64, 8, 512, 1300, 2400, 1430, 0},   {64, 32, 8, 512, 1400, 2300, 1410, 0},
     {64, 64, 4, 256, 3800, 770, 1115, 3},   {96, 128, 4, 512, 2000, 5600, 2600, 0},  {128, 128, 1, 256, 3700, 1200, 890, 8},
-    {128, 128, 4, 512, 2300, 5070, 3350, 0}, {128, 256, 1, 512, 500, 3800, 1740, 0}, {192, 256, 1, 512, 2500, 5200, 2330, 0},
+    {128, 128, 4, 512, 2300, 5070, 3350, 0}, {128, 256, 1, 512, 500, 3800, 1740, 0}, {160, 256, 1, 512, 1500, 4500, 2060, 0}, {192, 256, 1, 512, 2500, 5200, 2330, 0},
     {0, 0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 512, 0, 8500, 2650, 0}};
 static const TileCost E8M0_COST[TILES] = {
     {32, 32, 8, 512, 2700, 410, 585, 0},    {32, 64, 8, 512, 1400, 2140, 930, 0},    {64, 32, 8, 512, 1400, 2100, 935, 0},
     {64, 64, 4, 256, 3200, 910, 685, 0},    {0, 0, 0, 0, 0, 0, 0, 0},                {128, 128, 1, 256, 3200, 1390, 356, 28},
-    {0, 0, 0, 0, 0, 0, 0, 0},               {0, 0, 0, 0, 0, 0, 0, 0},                {0, 0, 0, 0, 0, 0, 0, 0},
+    {0, 0, 0, 0, 0, 0, 0, 0},               {0, 0, 0, 0, 0, 0, 0, 0},                {0, 0, 0, 0, 0, 0, 0, 0},                 {0, 0, 0, 0, 0, 0, 0, 0},
     {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
@@ -563,6 +603,11 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         // 6464 x 800 x 9856 139.1 / 127.2, 3072 x 1792 x 8256 102.2 / 121.7, 2377 x 1793 x 7552 with blocks of 64 92.9 / 109.2; three
         // 1280 x 6816 x 5760 103.3 / 118.8, 1381 x 5979 x 8800 167.4 / 202.9)
         if ((t == TILE_96x128_K4 || t == TILE_128x128_K4) && tiles > 256) continue;
+        // The 160-row tile is for one round of them in place of one of 192 rows, where it covers the rows with less padding.  us, 192 / 160
+        // rows: 777 x 12288 x 4096 79.1 / 69.4, 1600 x 6144 x 4096 75.7 / 72.1, 320 x 32768 x 1024 26.9 / 23.4, 2384 x 4096 x 512 16.2 / 14.3;
+        // with as many rows or more the shorter step is lost to the larger product: 960 x 10240 x 8192 142.6 / 143.3, 1281 x 7000 x 1024
+        // 25.1 / 25.6.  (Contractions up to 256, a few us of output more than of product, stay as they were: 777 x 12288 x 256 12.1 / 10.0 with the latter's output streamed.)
+        if (t == TILE_160x256 && (K <= 256 || tiles > 256 || (M + 159) / 160 * 160 >= (M + 191) / 192 * 192)) continue;
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
         if (rounds == 1) time *= 1.0 + 0.01 * c.alone;

@@ -369,3 +369,33 @@ def test_small_mxfp4_training_tensors(shape):
         got = nv.linear_bwd(dY, None, None, seed, fmt, saved=saved, K=K, **kw)
         for a, b in zip((Y, *got), (Yr, dX, dW)):
             assert torch.equal(a, b), list(kw)
+
+
+# 160 x 256, whose upper four waves have 96 rows and whose lower four 64: whole tiles, one row or column past a tile and past the upper
+# waves' rows, rows that reach into the next slab, whole contractions and K tails.
+UNEVEN = [(777, 12288, 1024), (961, 8193, 1056), (1537, 6144, 1088), (2399, 3841, 1184), (320, 32768, 1024), (1600, 6144, 1152)]
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "e4m3_32", "e4m3_128"])
+@pytest.mark.parametrize("shape", UNEVEN, ids=["x".join(map(str, s)) for s in UNEVEN])
+def test_uneven_waves_sampled(shape, fmt_name, out_dtype):
+    block, scale = FORMATS[fmt_name]
+    M, N, K = shape
+    K = -(-K // block) * block
+    assert nv.gemm_tile(M, N, K, nv.Format(block, scale, 1)) == (160, 256)
+    check_sampled((M, N, K), fmt_name, out_dtype)
+
+
+@pytest.mark.parametrize("shape", [(784, 12288, 1024), (2384, 3840, 1152)])
+def test_uneven_waves_across_slabs(shape):
+    M, N, K = shape
+    assert nv.gemm_tile(M, N, K) == (160, 256)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    X, W = (torch.randn((n, K), generator=g, device="cuda") for n in (M, N))
+    print(f"[case] gemm uneven tiles across slabs {M}x{N}x{K}", flush=True)
+    ops = [(nv.quantize_dual(t)[0], nv.quantize_dual(t, slab_rows=True)[0]) for t in (X, W)]
+    plain = nv.gemm(ops[0][0], ops[1][0], shape=shape)
+    for slabs in ((True, False), (False, True), (True, True)):
+        assert torch.equal(nv.gemm(ops[0][slabs[0]], ops[1][slabs[1]], slabs=slabs, shape=shape), plain), slabs
