@@ -438,6 +438,12 @@ __device__ __forceinline__ void f16_tile(const GemmArgs &P, const int wrow)
     uint8_t *const mine = lds + wave_wg * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2));
     if constexpr (KG == 1) {
         store_lines<OUT_DT, TA, TB>(P, acc, row0, col0, mine, lane);
+    } else if constexpr (KG == 2) {
+        // each group keeps one half of the tile rows
+        static_assert(TA % 2 == 0, "halves");
+        float16_t half[TA / 2][TB];
+        fold_groups<TA, TB, NW>(acc, half, lds, group, wave, lane);
+        store_lines<OUT_DT, TA / 2, TB>(P, half, row0 + group * (16 * TA), col0, mine, lane);
     } else {
         // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the tile rows
         constexpr int LO = (TA + 1) / 2, HI = TA - LO;
@@ -535,6 +541,9 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
     } else if (tile == TILE_160x256) {
         if (ktail) launch_f16_uneven<B, true>(P, out_dt, st);
         else launch_f16_uneven<B, false>(P, out_dt, st);
+    } else if (tile == TILE_128x256_K2) {
+        if (ktail) launch_f16<B, 1, 4, 4, 2, 2, true>(P, out_dt, st);
+        else launch_f16<B, 1, 4, 4, 2, 2, false>(P, out_dt, st);
     } else if (tile == TILE_128x256) {
         if (ktail) launch_f16<B, 2, 4, 2, 2, 1, true>(P, out_dt, st);
         else launch_f16<B, 2, 4, 2, 2, 1, false>(P, out_dt, st);
@@ -569,7 +578,8 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 //     4096 x  4096 x  4096           239.8     157.7     146.5     123.2     125.8     120.9     140.6     104.1
 //     8192 x  8192 x   256           287.3     130.6     138.0      46.6     125.8      52.3      49.9      47.6
 //     4096 x 11008 x   512           221.9      93.5      97.7      50.5      89.6      57.3      53.8      50.3
-// (160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.)
+// (128 x 256 with two groups, one round of it only: 2048 x 4096 x 4096 55.1, x 11008 138.4;
+// 160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.)
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
@@ -579,13 +589,14 @@ struct TileCost {
 static const TileCost E4M3_COST[TILES] = {
     {32, 32, 8, 512, 2900, 350, 860, 3},    {32, 64, 8, 512, 1300, 2400, 1430, 0},   {64, 32, 8, 512, 1400, 2300, 1410, 0},
     {64, 64, 4, 256, 3800, 770, 1115, 3},   {96, 128, 4, 512, 2000, 5600, 2600, 0},  {128, 128, 1, 256, 3700, 1200, 890, 8},
-    {128, 128, 4, 512, 2300, 5070, 3350, 0}, {128, 256, 1, 512, 500, 3800, 1740, 0}, {160, 256, 1, 512, 1500, 4500, 2060, 0}, {192, 256, 1, 512, 2500, 5200, 2330, 0},
+    {128, 128, 4, 512, 2300, 5070, 3350, 0}, {128, 256, 1, 512, 500, 3800, 1740, 0}, {128, 256, 2, 512, 2700, 3900, 3080, 0},
+    {160, 256, 1, 512, 1500, 4500, 2060, 0}, {192, 256, 1, 512, 2500, 5200, 2330, 0},
     {0, 0, 0, 0, 0, 0, 0, 0},               {256, 256, 1, 512, 0, 8500, 2650, 0}};
 static const TileCost E8M0_COST[TILES] = {
     {32, 32, 8, 512, 2700, 410, 585, 0},    {32, 64, 8, 512, 1400, 2140, 930, 0},    {64, 32, 8, 512, 1400, 2100, 935, 0},
     {64, 64, 4, 256, 3200, 910, 685, 0},    {0, 0, 0, 0, 0, 0, 0, 0},                {128, 128, 1, 256, 3200, 1390, 356, 28},
     {0, 0, 0, 0, 0, 0, 0, 0},               {0, 0, 0, 0, 0, 0, 0, 0},                {0, 0, 0, 0, 0, 0, 0, 0},                 {0, 0, 0, 0, 0, 0, 0, 0},
-    {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
+    {0, 0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
 
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {
@@ -608,6 +619,12 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         // with as many rows or more the shorter step is lost to the larger product: 960 x 10240 x 8192 142.6 / 143.3, 1281 x 7000 x 1024
         // 25.1 / 25.6.  (Contractions up to 256, a few us of output more than of product, stay as they were: 777 x 12288 x 256 12.1 / 10.0 with the latter's output streamed.)
         if (t == TILE_160x256 && (K <= 256 || tiles > 256 || (M + 159) / 160 * 160 >= (M + 191) / 192 * 192)) continue;
+        // 128 x 256 with two groups of waves: four waves of 128 x 64 on every other K tile need 6 vector instructions a MFMA where eight
+        // of 64 x 64 need 8, and a fold at the end, which 12 K tiles pay for.  One round of them, on most of the CUs (up to 160
+        // workgroups were not timed).  us, one group / two: 2048 x 4096 x 4096 59.5 / 55.1, f32 outputs 65.5 / 61.5, blocks of 64 64.6 / 58.0,
+        // 2048 x 4096 x 11008 155.5 / 138.4, 1700 x 4600 x 8192 121.8 / 112.6, 2688 x 2048 x 4096 51.1 / 47.7, 2048 x 4096 x 1536 27.8 / 27.6, x 1024 20.7 / 20.8
+        // (the first of each without streamed outputs, worth up to 1).
+        if (t == TILE_128x256_K2 && (tiles <= 160 || tiles > 256)) continue;
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
         if (rounds == 1) time *= 1.0 + 0.01 * c.alone;

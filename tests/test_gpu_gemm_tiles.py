@@ -399,3 +399,32 @@ def test_uneven_waves_across_slabs(shape):
     plain = nv.gemm(ops[0][0], ops[1][0], shape=shape)
     for slabs in ((True, False), (False, True), (True, True)):
         assert torch.equal(nv.gemm(ops[0][slabs[0]], ops[1][slabs[1]], slabs=slabs, shape=shape), plain), slabs
+
+
+# 128 x 256 with two groups of waves: an even and an odd number of K tiles (the second group's last one is zeros), K tails, edges.
+TWO_GROUPS = [(2048, 4096, 2048), (2000, 4001, 2944), (1921, 3841, 2912), (1793, 4096, 2272), (900, 8192, 3168)]
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("fmt_name", ["nvfp4", "e4m3_32", "e4m3_64"])
+@pytest.mark.parametrize("shape", TWO_GROUPS, ids=["x".join(map(str, s)) for s in TWO_GROUPS])
+def test_two_groups_sampled(shape, fmt_name, out_dtype):
+    block, scale = FORMATS[fmt_name]
+    M, N, K = shape
+    K = -(-K // block) * block
+    assert nv.gemm_tile(M, N, K) == (128, 256) and nv.gemm_split(M, N, K) == 2
+    check_sampled((M, N, K), fmt_name, out_dtype)
+
+
+@pytest.mark.parametrize("shape", [(2048, 4096, 2944), (2032, 4080, 2048)])
+def test_two_groups_on_slabs(shape):
+    M, N, K = shape
+    assert nv.gemm_split(M, N, K) == 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    X, W = (torch.randn((n, K), generator=g, device="cuda") for n in (M, N))
+    print(f"[case] gemm two groups on slabs {M}x{N}x{K}", flush=True)
+    ops = [(nv.quantize_dual(t)[0], nv.quantize_dual(t, slab_rows=True)[0]) for t in (X, W)]
+    plain = nv.gemm(ops[0][0], ops[1][0], shape=shape)
+    for slabs in ((True, False), (False, True), (True, True)):
+        assert torch.equal(nv.gemm(ops[0][slabs[0]], ops[1][slabs[1]], slabs=slabs, shape=shape), plain), slabs
