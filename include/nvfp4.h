@@ -449,7 +449,7 @@ uint32_t nvfp4_host_sr_bits(uint64_t seed, uint64_t element_index);
 uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent byte */
 /* The workgroup tile that the size rule of nvfp4_gemm gives an M x N x K product of this format (of f, the scale type
  * matters): rows * 65536 + columns of the output; 0 for sizes below 1 or a bad format.  Not a promise: the rule follows
- * measurements. */
+ * measurements (and products of up to 16 rows in NVFP4 and MXFP4 mostly run on a kernel without such tiles). */
 int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* Into how many parts the waves of that tile's workgroup divide the contraction (1: not at all); 0 as above. */
 int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);

@@ -228,7 +228,7 @@ void weight_slabs(const nvfp4_format *f, int64_t M, int64_t N, int64_t K, bool *
     const bool sw = dual_writes_slabs(f, NVFP4_BF16, N, K, NVFP4_RTN, NVFP4_RTN);  // (does not depend on the element type)
     // Written once and read by every micro-batch, so also for products that are too small to have their other operand in slabs: there a
     // K tile's scales are contiguous, where they take the vector L1 a request per row otherwise (256 x 11008 x 4096 32.0 -> 29.3 us,
-    // 512 x 4096 x 4096 23.3 -> 20.8, 16 x 11008 x 4096 9.9 -> 9.5).  A weight of the kernel for small tensors' sizes, which writes no
+    // 512 x 4096 x 4096 23.3 -> 20.8).  A weight of the kernel for small tensors' sizes, which writes no
     // slabs, follows its product: NVFP4 weights of that size keep their rows unless the product has 128 tiles of 256 x 256, MXFP4 ones are
     // slabs (and go through the tile kernels) where the contraction allows it.
     QuantArgs w;

@@ -187,7 +187,7 @@ __device__ __forceinline__ void f16_tile(const GemmArgs &P, const int wrow)
         const int row = isA ? trow : trow - BM;
         const int64_t base = isA ? m0 : n0, rows = isA ? P.M : P.N;
         const int64_t lr = base + row < rows ? row : rows - 1 - base;  // row inside the tile, clamped
-        // a slab holds all rows of a 256- or 128-row tile: nothing to clamp; one of 96 or 192 rows may reach into the next slab
+        // a slab holds all rows of a 256- or 128-row tile: nothing to clamp; one of 96, 160 or 192 rows may reach into the next slab
         const int srow = (int)(base & 255) + (int)(SPAN && isA ? lr : row);
         const uint32_t slab_off = (uint32_t)(slab_row(SPAN && isA ? srow & 255 : srow) * 64 + ch * 16) +
                                   (SPAN && isA && srow > 255 ? (uint32_t)nkt * (uint32_t)SLAB_CODE_BYTES : 0u);
@@ -562,7 +562,7 @@ static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStr
 // Which workgroup tile computes an M x N x K product: the one whose estimated time is least.  With R = the tiles of the
 // busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves or groups of waves),
 //     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
-// Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
+// (NVFP4 and MXFP4 products of up to 16 rows have a kernel of their own, gemm_is_thin().)  Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
 // expansion, LDS reads).  The constants (nanoseconds) are fitted to every tile timed on 245 shapes from 9 x 162 x 768 to 11008 x 4096 x
 // 4096, row-major and in slabs, both output types (profiles/gemm_tiles.txt); the choice is then 0.7 / 1.1 % (E4M3, bf16 / f32 outputs)
 // and 1.5 / 1.6 % (E8M0) slower than the best tile on average.  E4M3, bf16 outputs, us per tile choice:

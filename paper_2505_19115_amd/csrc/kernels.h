@@ -22,8 +22,8 @@ struct QuantArgs {
     int n_partials = 0;   // SELF_AMAX: every workgroup takes the maximum of x (dense) itself
 };
 // Tensors up to this size have few workgroups, and each reads all of it (from the L2) in less time than the maximum pass takes
-// as a launch of its own: a 16 x 4096 bf16 activation (on the line) quantized and multiplied with packed weights 18.0 -> 16.3 us,
-// the six launches of a 64 x 256 x 128 layer become four, 31.5 -> 28.3 us.
+// as a launch of its own: a 16 x 4096 bf16 activation (on the line) quantized and multiplied with packed weights 18.0 -> 16.3 us
+// (with the product's kernel of that time).
 constexpr int SELF_AMAX = -1;
 constexpr int64_t SELF_AMAX_BYTES = 128 * 1024;
 
