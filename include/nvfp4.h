@@ -243,7 +243,8 @@ nvfp4_status nvfp4_gemm_slab(int64_t M, int64_t N, int64_t K, const nvfp4_format
 
 /*
  * Forward GEMM, Eq. 4:  Y[M, N] = Q_RtN(X[M, K]) * Q_RtN(W[N, K])^T, blocks along K.
- * X, W dense row-major of in_dt; Y dense row-major of out_dt.
+ * X, W dense row-major of in_dt; Y dense row-major of out_dt, which may lie on X
+ * or W: both have been read before any of it is written.
  * xw_scales_out: NULL, or device fp32[2] that receives the per-tensor scales
  * {gX, gW} this call derived from max|X| and max|W| (1, 1 for a format without
  * tensor scale), to be handed to nvfp4_linear_bwd for the same X and W.
@@ -284,6 +285,8 @@ nvfp4_status nvfp4_linear_fwd(const void *X, const void *W, void *Y, int64_t M, 
  * the tag in the buffer itself is compared on the device and a mismatch turns
  * dX and dW into NaN.
  * With both dX and dW requested, dY is read once for its two quantizations.
+ * dX or dW may lie on dY, which has been read before either is written (on X or
+ * W only where those are not read).
  */
 nvfp4_status nvfp4_linear_bwd(const void *dY, const void *X, const void *W, void *dX, void *dW,
                               int64_t M, int64_t N, int64_t K, nvfp4_dtype in_dt,

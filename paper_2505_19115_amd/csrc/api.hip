@@ -111,6 +111,14 @@ nvfp4_status check_tensor(const void *x, int dt, int64_t rows, int64_t cols, int
     return NVFP4_OK;
 }
 
+// Whether an output of a linear call shares memory with one of its inputs.  The kernels that quantize and multiply in one launch store
+// outputs while other workgroups still read the input, so such calls go the separate way, which has read every input by then.
+bool shares_memory(const void *out, int64_t out_elements, int out_dt, const void *in, int64_t in_elements, int in_dt)
+{
+    const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
+    return out && in && o < i + (uintptr_t)(in_elements * (int64_t)elem_size(in_dt)) && i < o + (uintptr_t)(out_elements * (int64_t)elem_size(out_dt));
+}
+
 struct QuantPlan {
     const void *x;
     int dt;
@@ -736,10 +744,11 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
         // a small X of few rows: one launch quantizes it and multiplies
         const GemmArgs thin{M, N, K, nullptr, nullptr, wc, wsc, nullptr, g_w, Y, N, 0, b_slab};
         if (!saved && use_hw_convert() && (f->tensor_scale != 0) == (f->scale == NVFP4_SCALE_E4M3) && gemm_is_thin(thin, f->block, f->scale) &&
-            thin_takes_tensor(M, K, in_dt))
+            thin_takes_tensor(M, K, in_dt) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt))
             return launch_gemm_thin_tensor(thin, X, in_dt, ts, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }
-    if (!w_ops && use_hw_convert() && small_forward_takes(M, N, K, in_dt, f->block, f->scale)) {
+    if (!w_ops && use_hw_convert() && small_forward_takes(M, N, K, in_dt, f->block, f->scale) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt) &&
+        !shares_memory(Y, M * N, out_dt, W, N * K, in_dt)) {
         // a layer of a small network: everything in one launch, row-major (no product of this size takes slabs)
         SmallForward S{};
         S.P = GemmArgs{M, N, K, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, Y, N};
@@ -910,7 +919,8 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         tag.chk = reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(saved) + SAVED_TAG_OFFSET);
         if (!saved_matches(saved, tag)) return NVFP4_EINVAL;
     }
-    if (dual && have_wt && have_xt && !wt_slab && !xt_slab && use_hw_convert() && small_backward_takes(M, N, K, in_dt, f->block, f->scale)) {
+    if (dual && have_wt && have_xt && !wt_slab && !xt_slab && use_hw_convert() && small_backward_takes(M, N, K, in_dt, f->block, f->scale) &&
+        !shares_memory(dX, M * K, out_dt, dY, M * N, in_dt) && !shares_memory(dW, N * K, out_dt, dY, M * N, in_dt)) {
         SmallBackward S{};
         S.dx = GemmArgs{M, K, N, nullptr, nullptr, wtc, wts, nullptr, g_w, dX, K};
         S.dw = GemmArgs{N, K, M, nullptr, nullptr, xtc, xts, nullptr, g_x, dW, K};
