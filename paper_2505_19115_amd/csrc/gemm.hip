@@ -682,21 +682,10 @@ hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, i
     return e != hipSuccess ? e : launch_gemm_ksplit(P0, &P1, choose_gemm_tile(P0.M, P0.N, P0.K, sf), block, sf, out_dt, st);
 }
 
-// Outputs up to this size leave by nontemporal stores, which do not wait for a place in the L2 (us, kept / streamed: NVFP4 1024 x 4096 x 4096,
-// binary32 outputs, 38.1 / 36.6, bf16 35.5 / 34.4, 2048 x 4096 x 4096 66.7 / 65.8; MXFP4 2048 x 4096 x 4096 29.6 / 27.9), and still together
-// with a kernel that reads the output next (quantizer 39.2 / 38.3, 71.5 / 70.9, 34.4 / 33.4).  Of larger ones the next kernel finds more in the
-// last-level cache than the product gains: MXFP4 4096 x 11008 x 4096, 86 MB, 135.9 / 125.7, with a quantizer behind it 134.0 / 138.6; 40 MB 65.6 /
-// 67.8.  (Weight gradients, which are not read next, of 90 MB: the backward half of an MLP of 4096 / 11008 at 2048 tokens 697 / 706, the whole
-// one at 4096 tokens 2872 / 2848: not done.)  MXFP4 calls on packed weights, quantizer and product: 2048 x 4096 x 4096 36.8 / 36.0, 1024 x 4096 x
-// 4096 with binary32 outputs 31.8 / 30.5, but 628 x 5888 x 5504 with binary32 outputs 41.8 / 42.6, whose operands come from beyond the L2s too.
-constexpr int64_t STREAMED_OUTPUT = (int64_t)32 << 20;
-
-hipError_t launch_gemm(const GemmArgs &Q, int block, int sf, int out_dt, hipStream_t st)
+hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)
 {
-    GemmArgs P = Q;
     const hipError_t e = check_gemm(P, block, sf);
     if (e != hipSuccess) return e;
-    if (P.M * P.ldc * (out_dt == NVFP4_F32 ? 4 : 2) <= STREAMED_OUTPUT) P.stream = 1;
     if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
     if (gemm_is_thin(P, block, sf)) return launch_gemm_thin(P, sf, out_dt, st);
     const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);

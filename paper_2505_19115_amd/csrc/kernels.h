@@ -87,7 +87,6 @@ struct GemmArgs {
     void *out;
     int64_t ldc;
     int a_slab = 0, b_slab = 0;  // operand stored in the slab layout (only where gemm_reads_slabs() holds)
-    int stream = 0;              // the output leaves by nontemporal stores (larger tiles only; set by launch_gemm())
 };
 // True for the products whose operands the dual quantizer hands over as slabs (and nvfp4_gemm_slab() accepts): NVFP4 with at least
 // 128 output tiles of 256 x 256, MXFP4 with K >= 512, K a multiple of 128 in both.  Every tile of the GEMM kernels reads slabs.

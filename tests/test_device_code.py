@@ -176,3 +176,11 @@ def test_fused_layers_registers(tmp_path):
     assert len(fused) == 2 * 2 * 2 * 2  # (directions, element types, formats, output types)
     for args, v, s in fused:
         assert v <= 256 and s == 0, (args, v, s)
+
+
+def test_arguments_of_the_products(tmp_path):
+    # a launch's arguments are copied by the host: 16 bytes more cost calls that are bound by its work up to 0.2 us (store_lines.h)
+    for source, most in (("gemm", 96), ("gemm_mx", 96), ("gemm_ksplit", 196)):
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object(source, tmp_path)], capture_output=True, text=True, check=True).stdout
+        sizes = [int(n) for n in re.findall(r"\.kernarg_segment_size:\s+(\d+)", notes)]
+        assert sizes and max(sizes) <= most, source
