@@ -452,10 +452,12 @@ uint32_t nvfp4_host_sr_bits(uint64_t seed, uint64_t element_index);
 uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent byte */
 /* The workgroup tile that the size rule of nvfp4_gemm gives an M x N x K product of this format (of f, the scale type
  * matters): rows * 65536 + columns of the output; 0 for sizes below 1 or a bad format.  Not a promise: the rule follows
- * measurements (and products of up to 16 rows in NVFP4 and MXFP4 mostly run on a kernel without such tiles). */
+ * measurements (and where the next but one answers 1, the product has no such tile). */
 int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* Into how many parts the waves of that tile's workgroup divide the contraction (1: not at all); 0 as above. */
 int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
+/* 1 if the product runs on the kernel for up to 16 rows, 0 if on the tile that the first names.  Not a promise either. */
+int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* 1 if nvfp4_quantize down the columns (both = 0) or nvfp4_quantize_dual (both = 1) of a bf16 tensor walks its tiles with
  * resident workgroups, the next tile in flight (flags as in those calls; rounding_rows counts for both = 1).  Not a promise. */
 int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols,

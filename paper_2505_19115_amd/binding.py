@@ -138,6 +138,8 @@ def _load() -> C.CDLL:
     L.nvfp4_host_gemm_tile.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_gemm_split.restype = ci
     L.nvfp4_host_gemm_split.argtypes = [i64, i64, i64, fp]
+    L.nvfp4_host_gemm_few_rows.restype = ci
+    L.nvfp4_host_gemm_few_rows.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_quantize_streams.restype = ci
     L.nvfp4_host_quantize_streams.argtypes = [i64, i64, i64, ci, ci, ci, fp, u32]
     L.nvfp4_host_e4m3_encode_n.restype = None
@@ -165,7 +167,7 @@ EXPORTS = (
     "nvfp4_gemm_slab", "nvfp4_gemm_takes_slabs", "nvfp4_slab_codes_bytes", "nvfp4_slab_scales_bytes",
     "nvfp4_linear_fwd", "nvfp4_linear_bwd", "nvfp4_host_e4m3_encode", "nvfp4_host_e4m3_decode",
     "nvfp4_host_round_rtn", "nvfp4_host_round_sr", "nvfp4_host_philox4x32_10",
-    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
+    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_gemm_few_rows", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
     "nvfp4_host_round_rtn_n", "nvfp4_host_round_sr_n", "nvfp4_probe_mfma_rate",
     "nvfp4_quant_noise_workspace_bytes", "nvfp4_quant_noise", "nvfp4_quantize_static", "nvfp4_cross_check_switches",
     "nvfp4_weight_operands_bytes", "nvfp4_quantize_weight", "nvfp4_linear_fwd_wq", "nvfp4_linear_bwd_wq",
@@ -362,6 +364,12 @@ def gemm_split(M: int, N: int, K: int, fmt: Format = NVFP4) -> int:
     """nvfp4_host_gemm_split -> parts into which the waves of that tile's workgroup divide the contraction."""
     f = fmt.c()
     return lib.nvfp4_host_gemm_split(M, N, K, C.byref(f))
+
+
+def gemm_few_rows(M: int, N: int, K: int, fmt: Format = NVFP4) -> bool:
+    """nvfp4_host_gemm_few_rows -> whether the product runs on the kernel for up to 16 rows (then it has no such tile)."""
+    f = fmt.c()
+    return bool(lib.nvfp4_host_gemm_few_rows(M, N, K, C.byref(f)))
 
 
 def quantize_streams(rows: int, cols: int, ld: int, both: bool, rounding_rows: int, rounding_cols: int, fmt: Format = NVFP4, flags: int = 0) -> bool:

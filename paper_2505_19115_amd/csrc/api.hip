@@ -630,6 +630,11 @@ int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f
     return gemm_tile_split(choose_gemm_tile(M, N, K, f->scale));
 }
 
+int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
+{
+    return check_format(f) == NVFP4_OK && M > 0 && N > 0 && K > 0 && gemm_is_thin(M, N, K, f->block, f->scale) ? 1 : 0;
+}
+
 int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols, const nvfp4_format *f, uint32_t flags)
 {
     if (check_format(f) != NVFP4_OK || rows <= 0 || cols <= 0 || ld < cols) return 0;
@@ -743,7 +748,7 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
         if (xw_scales_out && hipMemcpyAsync(xw_scales_out + 1, WL.g, sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) return NVFP4_EHIP;
         // a small X of few rows: one launch quantizes it and multiplies
         const GemmArgs thin{M, N, K, nullptr, nullptr, wc, wsc, nullptr, g_w, Y, N, 0, b_slab};
-        if (!saved && use_hw_convert() && (f->tensor_scale != 0) == (f->scale == NVFP4_SCALE_E4M3) && gemm_is_thin(thin, f->block, f->scale) &&
+        if (!saved && use_hw_convert() && (f->tensor_scale != 0) == (f->scale == NVFP4_SCALE_E4M3) && gemm_is_thin(M, N, K, f->block, f->scale) &&
             thin_takes_tensor(M, K, in_dt) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt))
             return launch_gemm_thin_tensor(thin, X, in_dt, ts, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }

@@ -687,7 +687,7 @@ hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStre
     const hipError_t e = check_gemm(P, block, sf);
     if (e != hipSuccess) return e;
     if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
-    if (gemm_is_thin(P, block, sf)) return launch_gemm_thin(P, sf, out_dt, st);
+    if (gemm_is_thin(P.M, P.N, P.K, block, sf)) return launch_gemm_thin(P, sf, out_dt, st);
     const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);
     if (tile <= TILE_64x64) return launch_gemm_ksplit(P, nullptr, tile, block, sf, out_dt, st);
     if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(P, tile, out_dt, st);

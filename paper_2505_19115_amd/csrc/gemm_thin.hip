@@ -335,11 +335,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_nt_thin_kernel(GemmArgs P, const
 
 // ------------------------------------------------------------------ host side
 
-bool gemm_is_thin(const GemmArgs &P, int block, int sf)
+bool gemm_is_thin(int64_t M, int64_t N, int64_t K, int block, int sf)
 {
+    // (512 threads per 64 columns, and those of a launch are counted in 32 bits)
+    constexpr int64_t MOST_N = (int64_t)(0xFFFFFFFFu / 512) * 64;
     // one round of workgroups, or a contraction that is worth more (us, the tile kernels / this one: NVFP4 1 x 65536 x 128 5.2 / 8.5, 16 x 65536 x
     // 512 12.9 / 11.8, 16 x 131072 x 1024 36.0 / 29.2; MXFP4 16 x 65536 x 512 7.1 / 9.9, 4 x 131072 x 4096 58.4 / 59.5)
-    return P.M <= 16 && (P.N <= 64 * 256 || (sf == NVFP4_SCALE_E4M3 && P.K >= 512 && P.N <= 0x7FFFFF00)) && ((block == 16 && sf == NVFP4_SCALE_E4M3) || (block == 32 && sf == NVFP4_SCALE_E8M0));
+    return M <= 16 && (N <= 64 * 256 || (sf == NVFP4_SCALE_E4M3 && K >= 512 && N <= MOST_N)) && ((block == 16 && sf == NVFP4_SCALE_E4M3) || (block == 32 && sf == NVFP4_SCALE_E8M0));
 }
 bool thin_takes_tensor(int64_t M, int64_t K, int dt) { return M <= 16 && M * K * (dt == NVFP4_BF16 ? 2 : 4) <= THIN_TENSOR_BYTES; }
 

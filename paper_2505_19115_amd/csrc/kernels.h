@@ -212,7 +212,7 @@ int gemm_tile_split(GemmTile t);  // parts into which the waves of its workgroup
 hipError_t launch_gemm_ksplit(const GemmArgs &P, const GemmArgs *P1, GemmTile tile, int block, int sf, int out_dt, hipStream_t st);
 // Products of up to 16 rows in NVFP4 and MXFP4 (gemm_thin.hip), and the same with A as a dense tensor that the kernel quantizes itself
 // (rows, round to nearest; *g_out receives the tensor scale): P's A operand is not read.
-bool gemm_is_thin(const GemmArgs &P, int block, int sf);
+bool gemm_is_thin(int64_t M, int64_t N, int64_t K, int block, int sf);
 hipError_t launch_gemm_thin(const GemmArgs &P, int sf, int out_dt, hipStream_t st);
 bool thin_takes_tensor(int64_t M, int64_t K, int dt);
 hipError_t launch_gemm_thin_tensor(const GemmArgs &P, const void *X, int dt, float *g_out, int sf, int out_dt, hipStream_t st);

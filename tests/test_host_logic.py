@@ -380,6 +380,16 @@ def test_which_quantizers_stream():
     assert not nv.quantize_streams(5120, 5120, 5120, True, RTN, RTN, nv.MXFP4, nv.SLAB_ROWS | nv.SLAB_COLS)
 
 
+def test_few_rows_up_to_the_launch_limit():
+    # 512 threads for 64 columns, counted in 32 bits: a wider product stays on a tile that can be launched
+    last = 64 * ((1 << 32) // 512 - 1)
+    assert nv.gemm_few_rows(16, last, 512) and not nv.gemm_few_rows(16, last + 1, 512) and not nv.gemm_few_rows(1, 1 << 29, 512)
+    assert nv.gemm_tile(16, 1 << 29, 512) == (64, 64) and ((1 << 29) // 64) * 256 < 1 << 32
+    assert nv.gemm_few_rows(16, 16384, 32) and not nv.gemm_few_rows(16, 16385, 480) and nv.gemm_few_rows(16, 16385, 512)
+    assert nv.gemm_few_rows(16, 16384, 8192, nv.MXFP4) and not nv.gemm_few_rows(16, 16385, 8192, nv.MXFP4)
+    assert not nv.gemm_few_rows(17, 4096, 4096) and not nv.gemm_few_rows(16, 4096, 4096, nv.Format(64, 0, 1)) and not nv.gemm_few_rows(0, 64, 64)
+
+
 def test_no_tile_beyond_the_launch_limit():
     # a launch counts its threads in 32 bits, and no product that one of the tiles can serve may be given one that cannot
     # (rows, columns, parts of the contraction -> threads)
