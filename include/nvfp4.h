@@ -458,6 +458,9 @@ int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
 int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* 1 if the product runs on the kernel for up to 16 rows, 0 if on the tile that the first names.  Not a promise either. */
 int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
+/* Which calls of a layer on tensors of dt are one launch (a small network's): bit 0 a forward call, bit 1 one that leaves saved operands, bit 2 a
+ * backward call on these.  The answer of the size rules; not a promise. */
+int nvfp4_host_layer_fused(int64_t M, int64_t N, int64_t K, nvfp4_dtype dt, const nvfp4_format *f);
 /* 1 if nvfp4_quantize down the columns (both = 0) or nvfp4_quantize_dual (both = 1) of a bf16 tensor walks its tiles with
  * resident workgroups, the next tile in flight (flags as in those calls; rounding_rows counts for both = 1).  Not a promise. */
 int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols,

@@ -140,6 +140,8 @@ def _load() -> C.CDLL:
     L.nvfp4_host_gemm_split.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_gemm_few_rows.restype = ci
     L.nvfp4_host_gemm_few_rows.argtypes = [i64, i64, i64, fp]
+    L.nvfp4_host_layer_fused.restype = ci
+    L.nvfp4_host_layer_fused.argtypes = [i64, i64, i64, ci, fp]
     L.nvfp4_host_quantize_streams.restype = ci
     L.nvfp4_host_quantize_streams.argtypes = [i64, i64, i64, ci, ci, ci, fp, u32]
     L.nvfp4_host_e4m3_encode_n.restype = None
@@ -167,7 +169,7 @@ EXPORTS = (
     "nvfp4_gemm_slab", "nvfp4_gemm_takes_slabs", "nvfp4_slab_codes_bytes", "nvfp4_slab_scales_bytes",
     "nvfp4_linear_fwd", "nvfp4_linear_bwd", "nvfp4_host_e4m3_encode", "nvfp4_host_e4m3_decode",
     "nvfp4_host_round_rtn", "nvfp4_host_round_sr", "nvfp4_host_philox4x32_10",
-    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_gemm_few_rows", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
+    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_gemm_few_rows", "nvfp4_host_layer_fused", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
     "nvfp4_host_round_rtn_n", "nvfp4_host_round_sr_n", "nvfp4_probe_mfma_rate",
     "nvfp4_quant_noise_workspace_bytes", "nvfp4_quant_noise", "nvfp4_quantize_static", "nvfp4_cross_check_switches",
     "nvfp4_weight_operands_bytes", "nvfp4_quantize_weight", "nvfp4_linear_fwd_wq", "nvfp4_linear_bwd_wq",
@@ -370,6 +372,13 @@ def gemm_few_rows(M: int, N: int, K: int, fmt: Format = NVFP4) -> bool:
     """nvfp4_host_gemm_few_rows -> whether the product runs on the kernel for up to 16 rows (then it has no such tile)."""
     f = fmt.c()
     return bool(lib.nvfp4_host_gemm_few_rows(M, N, K, C.byref(f)))
+
+
+def layer_fused(M: int, N: int, K: int, dtype: torch.dtype = torch.float32, fmt: Format = NVFP4) -> tuple[bool, bool, bool]:
+    """nvfp4_host_layer_fused -> whether a forward call, one that leaves saved operands, and a backward call on these are one launch each."""
+    f = fmt.c()
+    bits = lib.nvfp4_host_layer_fused(M, N, K, F32 if dtype == torch.float32 else BF16, C.byref(f))
+    return bool(bits & 1), bool(bits & 2), bool(bits & 4)
 
 
 def quantize_streams(rows: int, cols: int, ld: int, both: bool, rounding_rows: int, rounding_cols: int, fmt: Format = NVFP4, flags: int = 0) -> bool:

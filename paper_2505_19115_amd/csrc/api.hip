@@ -635,6 +635,15 @@ int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format
     return check_format(f) == NVFP4_OK && M > 0 && N > 0 && K > 0 && gemm_is_thin(M, N, K, f->block, f->scale) ? 1 : 0;
 }
 
+int nvfp4_host_layer_fused(int64_t M, int64_t N, int64_t K, nvfp4_dtype dt_, const nvfp4_format *f)
+{
+    const int dt = raw(dt_);
+    if (check_format(f) != NVFP4_OK || !valid_dtype(dt) || M <= 0 || N <= 0 || K <= 0) return 0;
+    const bool g = f->tensor_scale != 0;
+    return (small_forward_takes(M, N, K, dt, f->block, f->scale, g, false) ? 1 : 0) | (small_forward_takes(M, N, K, dt, f->block, f->scale, g, true) ? 2 : 0) |
+           (small_backward_takes(M, N, K, dt, f->block, f->scale, g) ? 4 : 0);
+}
+
 int nvfp4_host_quantize_streams(int64_t rows, int64_t cols, int64_t ld, int both, int rounding_rows, int rounding_cols, const nvfp4_format *f, uint32_t flags)
 {
     if (check_format(f) != NVFP4_OK || rows <= 0 || cols <= 0 || ld < cols) return 0;
@@ -752,7 +761,7 @@ nvfp4_status linear_fwd_impl(const void *X, const void *W, const void *w_ops, vo
             thin_takes_tensor(M, K, in_dt) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt))
             return launch_gemm_thin_tensor(thin, X, in_dt, ts, f->scale, out_dt, st) == hipSuccess ? NVFP4_OK : NVFP4_EHIP;
     }
-    if (!w_ops && use_hw_convert() && small_forward_takes(M, N, K, in_dt, f->block, f->scale) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt) &&
+    if (!w_ops && use_hw_convert() && small_forward_takes(M, N, K, in_dt, f->block, f->scale, f->tensor_scale != 0, saved != nullptr) && !shares_memory(Y, M * N, out_dt, X, M * K, in_dt) &&
         !shares_memory(Y, M * N, out_dt, W, N * K, in_dt)) {
         // a layer of a small network: everything in one launch, row-major (no product of this size takes slabs)
         SmallForward S{};
@@ -924,7 +933,7 @@ nvfp4_status linear_bwd_impl(const void *dY, const nvfp4_dual_operands *dyq, con
         tag.chk = reinterpret_cast<const uint32_t *>(reinterpret_cast<const uint8_t *>(saved) + SAVED_TAG_OFFSET);
         if (!saved_matches(saved, tag)) return NVFP4_EINVAL;
     }
-    if (dual && have_wt && have_xt && !wt_slab && !xt_slab && use_hw_convert() && small_backward_takes(M, N, K, in_dt, f->block, f->scale) &&
+    if (dual && have_wt && have_xt && !wt_slab && !xt_slab && use_hw_convert() && small_backward_takes(M, N, K, in_dt, f->block, f->scale, f->tensor_scale != 0) &&
         !shares_memory(dX, M * K, out_dt, dY, M * N, in_dt) && !shares_memory(dW, N * K, out_dt, dY, M * N, in_dt)) {
         SmallBackward S{};
         S.dx = GemmArgs{M, K, N, nullptr, nullptr, wtc, wts, nullptr, g_w, dX, K};

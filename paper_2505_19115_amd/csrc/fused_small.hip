@@ -311,13 +311,39 @@ static bool small_product(int64_t M, int64_t N, int64_t K, int dt, int sf)
     const int64_t esz = dt == NVFP4_BF16 ? 2 : 4;
     return K <= fs::MOST_K && M * K * esz <= SELF_AMAX_BYTES && M > 16 && choose_gemm_tile(M, N, K, sf) <= TILE_64x64;
 }
-bool small_forward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf)
+static int64_t tiles(int64_t M, int64_t N, int rows) { return (M + rows - 1) / rows * ((N + 31) / 32); }
+// The workgroups of one launch repeat each other's work: every one quantizes its rows of X and W (or of dY) anew, and with a tensor scale reads
+// all of both tensors for their maxima.  So the rules count workgroups.  With a tensor scale it is those that the CUs hold at once (one per CU
+// in bf16, two in binary32), and without saved operands contractions up to 256, beyond which the quantizer's part of a tile is longer than the launch
+// it saves.  us, GPU time of a forward call in a graph, separate / one launch (NVFP4, bf16 unless said; + : with saved operands):
+//     480 x 512 x 64 (240 workgroups)  7.4 /  7.3   + (248) 8.9 /  7.2      512 x  512 x  64 (256)  7.4 /  7.3   + (264)  9.0 / 10.2
+//     576 x 512 x 64 (288)             7.8 / 11.1   + (297) 9.2 / 11.4     1024 x 1024 x  64 (1024) 10.0 / 28.3   +       11.8 / 31.6
+//     256 x 256 x 256 (64)             7.7 /  8.5   +       9.4 /  8.5      128 x  128 x 512 (16)   7.7 /  9.4   + (32)   9.3 /  9.4
+//     binary32: 512 x 512 x 64 (256)   7.8 /  7.4   + (264) 9.4 /  8.0     1024 x  512 x  32 (512)  8.7 /  9.0   + (518) 10.2 / 11.0
+// (as a program calls them the host's work for the second launch, 1 to 2 us, is saved besides: 128 x 128 x 256 8.9 / 8.0, x 512 10.1 / 9.6.)  Without a
+// tensor scale: MXFP4 1024 x 640 x 64 (640) 6.8 / 5.9, + 8.9 / 6.4, 1024 x 896 x 32 (896) 6.9 / 7.5, + (904) 9.2 / 7.9, 1024 x 1024 x 32 (1024) + 9.0 / 8.7; E4M3
+// 1024 x 512 x 32 bf16 1.05 times as fast, 768 x 768 x 32 0.84, binary32 960 x 768 x 32 1.16, 1024 x 1024 x 32 0.98.
+bool small_forward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf, bool tensor_scale, bool saved)
 {
-    return small_format(block, sf) && small_product(M, N, K, dt, sf) && N * K * (dt == NVFP4_BF16 ? 2 : 4) <= SELF_AMAX_BYTES;
+    if (!small_format(block, sf) || !small_product(M, N, K, dt, sf) || N * K * (dt == NVFP4_BF16 ? 2 : 4) > SELF_AMAX_BYTES) return false;
+    const int64_t product = tiles(M, N, 32), waves = SMALL_NT / 64;
+    if (sf == NVFP4_SCALE_E8M0) return product <= (saved ? 960 : 768);
+    if (!tensor_scale) return product <= (dt == NVFP4_BF16 ? 512 : 768);
+    const int64_t jobs = saved ? (K + 63) / 64 * ((M / block + waves - 1) / waves + (N / block + waves - 1) / waves) : 0;
+    return product + jobs <= (dt == NVFP4_BF16 ? 256 : 512) && (saved || K <= 256);
 }
-bool small_backward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf)
+// The backward kernel's LDS is one workgroup per CU's.  A second round is worth it for few rows of dY, whose quantization is the shorter part.  us,
+// GPU time in a graph, separate / one launch, NVFP4 bf16: 64 x 512 x 800 (250) 12.8 / 8.4, 64 x 512 x 832 (260) 12.9 / 12.6, 64 x 64 x 2880 (270) 12.4 / 13.1,
+// 128 x 128 x 1440 (270) 11.4 / 13.7, 256 x 256 x 640 (240) 12.8 / 9.4, x 704 (264) 12.5 / 15.6, x 4096 (1536) 16.0 / 44.7; binary32 64 x 512 x 1024 (320) 13.6 /
+// 12.2, 64 x 64 x 3456 (324) 0.99 times as fast; MXFP4 64 x 512 x 1024 11.6 / 10.2, 128 x 128 x 2048 (384) 10.4 / 10.3, 256 x 256 x 704 0.98 times as fast, x
+// 4096 13.9 / 30.3; E4M3 without a tensor scale 64 x 512 x 1024 1.20 times as fast, 128 x 128 x 1440 0.95.  (Slower within one round: 256 x 128 x 640
+// bf16 (200) 8.6 / 9.1, whose two products share a launch; the host's work again makes up for it.)
+bool small_backward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf, bool tensor_scale)
 {
-    return small_format(block, sf) && M <= fs::MOST_ROWS && small_product(M, K, N, dt, sf) && small_product(N, K, M, dt, sf);
+    if (!small_format(block, sf) || M > fs::MOST_ROWS || !small_product(M, K, N, dt, sf) || !small_product(N, K, M, dt, sf)) return false;
+    const int64_t wgs = tiles(M, K, 32) + tiles(N, K, 64);
+    const bool again = sf == NVFP4_SCALE_E8M0 ? M <= 128 : M <= 96 && (!tensor_scale || (dt == NVFP4_F32 && N >= 128));
+    return wgs <= (again ? 512 : 256);
 }
 
 static uint32_t reciprocal(int64_t d) { return (uint32_t)(((uint64_t)1 << 32) / (uint64_t)d) + 1u; }  // of chunk numbers below 2^13
@@ -330,7 +356,7 @@ static hipError_t launch_small_forward_fmt(SmallForward &S, int out_dt, hipStrea
     constexpr int LDS = MAIN + fs::FOLD + DRAWS;
     S.lds_aux = MAIN;
     S.row_mul = reciprocal(S.P.K >> 3);
-    S.tiles = (unsigned)((S.P.M + 31) / 32 * ((S.P.N + 31) / 32));
+    S.tiles = (unsigned)tiles(S.P.M, S.P.N, 32);
     const unsigned wgs = S.tiles + S.cx.wgs + S.cw.wgs;
     if (out_dt == NVFP4_F32) {
         auto k = small_forward_kernel<DT, B, SF, NVFP4_F32>;
@@ -363,8 +389,8 @@ static hipError_t launch_small_backward_fmt(SmallBackward &S, int out_dt, hipStr
     constexpr int LDS = MAIN + fs::FOLD + DRAWS;
     S.lds_aux = MAIN;
     S.row_mul = reciprocal(S.dx.K >> 3);
-    S.tiles = (unsigned)((S.dx.M + 31) / 32 * ((S.dx.N + 31) / 32));
-    const unsigned wgs = S.tiles + (unsigned)((S.dw.M + 63) / 64 * ((S.dw.N + 31) / 32));
+    S.tiles = (unsigned)tiles(S.dx.M, S.dx.N, 32);
+    const unsigned wgs = S.tiles + (unsigned)tiles(S.dw.M, S.dw.N, 64);
     if (out_dt == NVFP4_F32) {
         auto k = small_backward_kernel<DT, B, SF, NVFP4_F32>;
         static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS), true);

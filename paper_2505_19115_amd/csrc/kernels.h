@@ -195,8 +195,8 @@ struct SmallBackward {
     uint32_t row_mul;
     int lds_aux;
 };
-bool small_forward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf);
-bool small_backward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf);
+bool small_forward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf, bool tensor_scale, bool saved);
+bool small_backward_takes(int64_t M, int64_t N, int64_t K, int dt, int block, int sf, bool tensor_scale);
 hipError_t launch_small_forward(SmallForward S, const QuantArgs *cx, const QuantArgs *cw, int dt, int block, int sf, int out_dt, hipStream_t st);
 hipError_t launch_small_backward(SmallBackward S, int dt, int block, int sf, int out_dt, hipStream_t st);
 // Two independent products in one launch, where gemm_pairs() holds (both small, the same tile).

@@ -58,6 +58,15 @@ def test_layer_in_one_launch_per_call(shape, fmt_name, dtype):
         assert torch.equal(got[0], dX) and torch.equal(got[1], dW)
 
 
+# Both sides of the lines that the numbers of workgroups draw (test_host_logic.py): one round of them, the second round of few rows, separate calls.
+@pytest.mark.parametrize("shape,dtype,fmt_name", [((480, 512, 64), torch.bfloat16, "nvfp4"), ((512, 512, 64), torch.bfloat16, "nvfp4"), ((512, 544, 64), torch.bfloat16, "nvfp4"),
+                                                  ((1024, 512, 32), torch.float32, "nvfp4"), ((128, 128, 288), torch.bfloat16, "nvfp4"), ((1024, 800, 64), torch.bfloat16, "mxfp4"),
+                                                  ((1024, 992, 64), torch.bfloat16, "mxfp4"), ((128, 128, 1344), torch.bfloat16, "nvfp4"), ((128, 128, 1376), torch.bfloat16, "nvfp4"),
+                                                  ((256, 256, 704), torch.bfloat16, "mxfp4"), ((64, 512, 832), torch.float32, "nvfp4"), ((128, 128, 2720), torch.bfloat16, "mxfp4")])
+def test_layers_beside_the_lines(shape, dtype, fmt_name):
+    test_layer_in_one_launch_per_call(shape, fmt_name, dtype)
+
+
 @pytest.mark.parametrize("fmt_name", FORMATS)
 @pytest.mark.parametrize("M,N,K", [(17, 70, 96), (33, 33, 160), (63, 100, 512), (127, 31, 32), (200, 1, 64)])
 def test_ragged_forward(M, N, K, fmt_name):

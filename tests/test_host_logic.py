@@ -380,6 +380,28 @@ def test_which_quantizers_stream():
     assert not nv.quantize_streams(5120, 5120, 5120, True, RTN, RTN, nv.MXFP4, nv.SLAB_ROWS | nv.SLAB_COLS)
 
 
+def test_fused_layers_by_workgroups():
+    # the workgroups of a fused layer repeat each other's quantization, so what counts is their number, not the tensors' bytes alone (1024 x
+    # 1024 x 64, forward, 28 us in one launch of 1024, 10 in two): (forward, with saved operands, backward on these)
+    import torch
+    bf16, f32, U = torch.bfloat16, torch.float32, nv.Format(16, 0, 0)
+    for shape, dtype, fmt, want in (
+            ((64, 256, 128), f32, nv.NVFP4, (True, True, True)), ((32, 32, 32), bf16, nv.MXFP4, (True, True, True)),
+            ((480, 512, 64), bf16, nv.NVFP4, (True, True, False)), ((512, 512, 64), bf16, nv.NVFP4, (True, False, False)),
+            ((512, 544, 64), bf16, nv.NVFP4, (False, False, False)), ((512, 512, 64), f32, nv.NVFP4, (True, True, False)),
+            ((1024, 512, 32), f32, nv.NVFP4, (True, False, False)), ((1024, 544, 32), f32, nv.NVFP4, (False, False, False)),
+            ((128, 128, 256), bf16, nv.NVFP4, (True, True, True)), ((128, 128, 288), bf16, nv.NVFP4, (False, True, True)), ((128, 128, 512), bf16, U, (True, True, True)),
+            ((1024, 768, 64), bf16, nv.MXFP4, (True, True, False)), ((1024, 800, 64), bf16, nv.MXFP4, (False, True, False)),
+            ((1024, 992, 64), bf16, nv.MXFP4, (False, False, False)), ((1024, 512, 32), bf16, U, (True, True, False)), ((1024, 544, 32), bf16, U, (False, False, False)),
+            ((256, 256, 672), bf16, nv.NVFP4, (False, False, True)), ((256, 256, 704), bf16, nv.NVFP4, (False, False, False)), ((256, 256, 4096), bf16, nv.MXFP4, (False, False, False)),
+            ((128, 128, 1344), bf16, nv.NVFP4, (False, False, True)), ((128, 128, 1376), bf16, nv.NVFP4, (False, False, False)), ((128, 128, 8192), bf16, nv.NVFP4, (False, False, False)),
+            ((64, 512, 832), bf16, nv.NVFP4, (False, False, False)), ((64, 512, 832), f32, nv.NVFP4, (False, False, True)), ((64, 64, 2880), f32, nv.NVFP4, (False, False, False)),
+            ((64, 512, 832), bf16, U, (False, False, True)), ((128, 128, 2720), bf16, nv.MXFP4, (False, False, True)), ((128, 128, 2752), bf16, nv.MXFP4, (False, False, False))):
+        assert nv.layer_fused(*shape, dtype, fmt) == want, (shape, dtype, fmt)
+    # other blocks, a size of zero
+    assert nv.layer_fused(64, 256, 128, f32, nv.Format(32, 0, 1)) == (False, False, False) and nv.layer_fused(0, 32, 32) == (False, False, False)
+
+
 def test_few_rows_up_to_the_launch_limit():
     # 512 threads for 64 columns, counted in 32 bits: a wider product stays on a tile that can be launched
     last = 64 * ((1 << 32) // 512 - 1)
