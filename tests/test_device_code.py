@@ -147,8 +147,13 @@ def test_registers_of_small_tensors_and_four_groups(tmp_path):
     four = [(args, v, s) for args, v, s in kernels(registers("gemm", tmp_path), "gemm_nt_f16_kernel") if args[5] == 4]
     assert len(four) == 4 * 2 * 2 * 2  # (blocks, tiles, output types, K tail)
     for (block, wm, wn, ta, tb, groups, out, tail), v, s in four:
-        # (128 x 128 with blocks of 32 to 128 spills a few)
-        assert v <= 256 and s <= (7 if ta == 4 and block > 16 else 0), (block, ta, out, tail, v, s)
+        assert v <= 256 and s == 0, (block, ta, out, tail, v, s)
+    # two groups of four waves, and eight waves of 96 and 64 rows: two per SIMD as well
+    two = [(args, v, s) for args, v, s in kernels(registers("gemm", tmp_path), "gemm_nt_f16_kernel") if args[5] == 2]
+    uneven = list(kernels(registers("gemm", tmp_path), "gemm_nt_f16_uneven_kernel"))
+    assert len(two) == 4 * 2 * 2 and len(uneven) == 4 * 2 * 2  # (blocks, output types, K tail)
+    for args, v, s in two + uneven:
+        assert v <= 256 and s == 0, (args, v, s)
 
 
 def test_rows_of_small_tensors_bring_little_along(tmp_path):

@@ -203,8 +203,10 @@ def test_mxfp4_short_contractions(shape, tile, K):
     close(got, oracle.gemm_nt(A, B, of), oracle.gemm_nt(A, B, of, take_abs=True), f"K {K}", torch.float32)
 
 
-# Operands in slabs on tiles other than the 256 x 256 they were made for: the same bits as row-major operands.
-@pytest.mark.parametrize("fmt_name,shape,tile", [("nvfp4", (16, 32768, 1024), (32, 32)), ("nvfp4", (50, 32800, 1024), (64, 64)),
+# Operands in slabs on tiles other than the 256 x 256 they were made for: the same bits as row-major operands.  (16 rows: on the kernel for few
+# rows, whatever the rule of the tiles answers.)
+@pytest.mark.parametrize("fmt_name,shape,tile", [("nvfp4", (16, 32768, 1024), (32, 32)), ("nvfp4", (17, 32768, 1024), (32, 32)), ("nvfp4", (20, 32768, 4096), (32, 64)),
+                                                 ("nvfp4", (50, 32800, 1024), (64, 64)),
                                                  ("nvfp4", (96, 32700, 2048), (96, 128)), ("nvfp4", (128, 32768, 4096), (128, 128)),
                                                  ("mxfp4", (40, 2080, 1024), (32, 32)), ("mxfp4", (70, 4100, 1024), (32, 64)),
                                                  ("mxfp4", (100, 3000, 1024), (64, 32)), ("mxfp4", (33, 8200, 512), (64, 64)),
@@ -215,6 +217,7 @@ def test_slab_operands_on_every_tile(fmt_name, shape, tile):
     fmt = nv.Format(block, scale, 1 - scale)
     M, N, K = shape
     assert nv.gemm_tile(M, N, K, fmt) == tile and (fmt_name == "mxfp4" or nv.gemm_split(M, N, K, fmt) > 1)
+    assert nv.gemm_few_rows(M, N, K, fmt) == (M == 16)
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     # (rows padded to whole blocks for the quantizer; the product takes the first M and N of them)
@@ -226,14 +229,16 @@ def test_slab_operands_on_every_tile(fmt_name, shape, tile):
         assert torch.equal(nv.gemm(ops[0][slabs[0]], ops[1][slabs[1]], fmt, slabs=slabs, shape=shape), plain), slabs
 
 
-def test_packed_weights_of_a_wide_projection():
-    # 16 tokens against a vocabulary-sized weight: its packed operand is in slabs (128 output tiles of 256 x 256), the product runs on
-    # a tile whose waves divide the contraction
-    M, N, K = 16, 32768, 512
+@pytest.mark.parametrize("M", [16, 24])
+def test_packed_weights_of_a_wide_projection(M):
+    # few tokens against a vocabulary-sized weight: its packed operand is in slabs (128 output tiles of 256 x 256), the product runs on
+    # the kernel for few rows or on a tile whose waves divide the contraction
+    N, K = 32768, 512
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     X, W = (torch.randn((n, K), generator=g, device="cuda").to(torch.bfloat16) for n in (M, N))
     assert nv.gemm_tile(M, N, K)[0] <= 64 and nv.lib.nvfp4_gemm_takes_slabs(M, N, K, ctypes.byref(nv.NVFP4.c()))
+    assert nv.gemm_few_rows(M, N, K) == (M == 16)
     Y = nv.linear_fwd(X, None, w_operands=nv.quantize_weight(W, M), N=N)
     assert torch.equal(Y, nv.linear_fwd(X, W))
     assert torch.equal(Y, nv.gemm(nv.quantize(X), nv.quantize(W)))

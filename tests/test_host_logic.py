@@ -416,7 +416,7 @@ def test_no_tile_beyond_the_launch_limit():
     # a launch counts its threads in 32 bits, and no product that one of the tiles can serve may be given one that cannot
     # (rows, columns, parts of the contraction -> threads)
     threads = {(32, 32, 8): 512, (32, 64, 8): 512, (64, 32, 8): 512, (64, 64, 4): 256, (96, 128, 4): 512, (128, 128, 1): 256, (128, 128, 4): 512,
-               (128, 256, 1): 512, (192, 256, 1): 512, (256, 128, 1): 256, (256, 256, 1): 512}
+               (128, 256, 1): 512, (128, 256, 2): 512, (160, 256, 1): 512, (192, 256, 1): 512, (256, 128, 1): 256, (256, 256, 1): 512}
     seen = set()
     for fmt in (nv.NVFP4, nv.MXFP4):
         for M in (1, 64, 300, 2700, 2970, 4096, 1 << 18, 1 << 20, 1 << 24, 1 << 26, 1 << 28, (1 << 28) + 1, 1 << 30):
