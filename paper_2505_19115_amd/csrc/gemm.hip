@@ -617,13 +617,17 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         // The 160-row tile is for one round of them in place of one of 192 rows, where it covers the rows with less padding.  us, 192 / 160
         // rows: 777 x 12288 x 4096 79.1 / 69.4, 1600 x 6144 x 4096 75.7 / 72.1, 320 x 32768 x 1024 26.9 / 23.4, 2384 x 4096 x 512 16.2 / 14.3;
         // with as many rows or more the shorter step is lost to the larger product: 960 x 10240 x 8192 142.6 / 143.3, 1281 x 7000 x 1024
-        // 25.1 / 25.6.  (Contractions up to 256, a few us of output more than of product, stay as they were: 777 x 12288 x 256 12.1 / 10.0 with the latter's output streamed.)
+        // 25.1 / 25.6.  Contractions of one K tile are slower on it (bf16 / f32 outputs, 192 and 128 rows / 160: 777 x 12288 x 128 6.6 / 7.4 and 10.6 / 11.2,
+        // 3307 x 2944 x 128 6.9 / 9.0 and 10.3 / 12.0, 1352 x 7168 x 96 7.2 / 7.9 and 10.9 / 12.1); of two they would be faster (777 x 12288 x 256 10.5 / 9.4 and 14.6 /
+        // 12.9, 2505 x 3212 x 256 12.6 / 12.0 and 16.1 / 14.1, 1079 x 9184 x 160 11.9 / 11.3 and 14.4 / 13.9), and have not been moved to it so far.
         if (t == TILE_160x256 && (K <= 256 || tiles > 256 || (M + 159) / 160 * 160 >= (M + 191) / 192 * 192)) continue;
         // 128 x 256 with two groups of waves: four waves of 128 x 64 on every other K tile need 6 vector instructions a MFMA where eight
-        // of 64 x 64 need 8, and a fold at the end, which 12 K tiles pay for.  One round of them, on most of the CUs (up to 160
-        // workgroups were not timed).  us, one group / two: 2048 x 4096 x 4096 59.5 / 55.1, f32 outputs 65.5 / 61.5, blocks of 64 64.6 / 58.0,
-        // 2048 x 4096 x 11008 155.5 / 138.4, 1700 x 4600 x 8192 121.8 / 112.6, 2688 x 2048 x 4096 51.1 / 47.7, 2048 x 4096 x 1536 27.8 / 27.6, x 1024 20.7 / 20.8
-        // (the first of each without streamed outputs, worth up to 1).
+        // of 64 x 64 need 8, and a fold at the end, which 12 K tiles pay for.  One round of them, on most of the CUs.  us, one group / two:
+        // 2048 x 4096 x 4096 59.5 / 55.1, f32 outputs 65.5 / 61.5, blocks of 64 64.6 / 58.0, 2048 x 4096 x 11008 155.5 / 138.4, 1700 x 4600 x 8192 121.8 /
+        // 112.6, 2688 x 2048 x 4096 51.1 / 47.7, 2048 x 4096 x 1536 27.8 / 27.6, x 1024 20.7 / 20.8 (the first of each without streamed outputs, worth up to 1).
+        // Of up to 160 workgroups the estimate would give it some contractions of 1700 to 3300; most would be faster and some slower, and they have
+        // not been moved to it so far: 908 x 4996 x 3296 52.8 / 43.4, 1664 x 2512 x 2784 43.4 / 37.5, 1302 x 3388 x 2656 38.2 / 37.9, 1966 x 2337 x
+        // 2752 45.3 / 46.6.
         if (t == TILE_128x256_K2 && (tiles <= 160 || tiles > 256)) continue;
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);

@@ -7,7 +7,8 @@
 // 16 waves divide the K tiles (wave w takes w, w + NW, ...) and request as many of theirs at once as the LDS holds, by direct global -> LDS
 // loads, codes and scale bytes alike: with nothing staged in registers the loads in flight are counted, and a wave multiplies a K tile
 // when that one is there.  The MFMA tile is 16 x 16: no rows computed that a 16-token call does not have.  The sums of the waves are added
-// through the LDS in their order, so that the bits do not depend on the columns per workgroup or on how A came.
+// through the LDS in their order: the bits depend on the number of waves, which follows K and, past 12288 columns, N, and not on how A came
+// or on the columns per workgroup otherwise.
 // Two neighbouring lanes in a quad fetch two scale pieces of one row: with 16 rows across the lanes a scale load took the vector L1 64
 // requests instead of 16 (16 x 11008 x 4096 MXFP4, row-major: 7.8 instead of 6.5 us).
 // NVFP4 needs 8 vector instructions per 8 codes of B on top of that, 3 us of a CU's time at 16 x 11008 x 4096, of which 16 waves hide more
