@@ -121,7 +121,7 @@ __device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float
 // half, step), which is all the instruction requires.
 // (wrow: the wave's first row in the tile)
 template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL, int BM>
-__device__ __forceinline__ void f16_tile(const GemmArgs &P, const int wrow)
+__device__ __forceinline__ void f16_tile(const TileArgs &P, const int wrow)
 {
     constexpr int NT = 64 * WM * WN;  // threads of a group
     constexpr int BN = 32 * TB * WN;
@@ -458,7 +458,7 @@ __device__ __forceinline__ void f16_tile(const GemmArgs &P, const int wrow)
 }
 
 template <int B, int WM, int WN, int TA, int TB, int KG, int OUT_DT, bool KTAIL>
-__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmArgs P)
+__global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(TileArgs P)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % (WM * WN);
     f16_tile<B, WM, WN, TA, TB, KG, OUT_DT, KTAIL, 32 * TA * WM>(P, wave / WN * 32 * TA);
@@ -468,13 +468,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, 2) void gemm_nt_f16_kernel(GemmA
 // waves of 80.  Expansion of the operands bounds it as in the other tiles (2.06 us a K tile for 160 rows; 192 rows 2.33).  Which code a
 // wave runs is uniform over the wave; both halves issue the same number of barriers (one per K tile), loads and stores included.
 template <int B, int OUT_DT, bool KTAIL>
-__global__ __launch_bounds__(512, 2) void gemm_nt_f16_uneven_kernel(GemmArgs P)
+__global__ __launch_bounds__(512, 2) void gemm_nt_f16_uneven_kernel(TileArgs P)
 {
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4) f16_tile<B, 2, 4, 3, 2, 1, OUT_DT, KTAIL, 160>(P, 0);
     else f16_tile<B, 2, 4, 2, 2, 1, OUT_DT, KTAIL, 160>(P, 96);
 }
 template <int B, bool KTAIL>
-static void launch_f16_uneven(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_f16_uneven(const TileArgs &P, int out_dt, hipStream_t st)
 {
     constexpr int LDS_BYTES = 2 * (160 + 256) * (KTB + SROW);
     static_assert(LDS_BYTES >= 8 * 32 * 64 * 4, "the epilogue's pieces");
@@ -493,7 +493,7 @@ static void launch_f16_uneven(const GemmArgs &P, int out_dt, hipStream_t st)
 }
 
 template <int B, int WM, int WN, int TA, int TB, int KG, bool KTAIL>
-static void launch_f16(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_f16(const TileArgs &P, int out_dt, hipStream_t st)
 {
     constexpr int BM = 32 * TA * WM, BN = 32 * TB * WN, NT = 64 * WM * WN * KG;
     // two stages per group, what a fold of the groups exchanges, or the epilogue's pieces (one per wave, 32 rows of fp32)
@@ -529,7 +529,7 @@ bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf)
 }
 
 template <int B>
-static void launch_f16_tile(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st)
+static void launch_f16_tile(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st)
 {
     const bool ktail = (P.K % KT) != 0;
     if (tile == TILE_256x256) {
@@ -686,20 +686,42 @@ hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, i
     return e != hipSuccess ? e : launch_gemm_ksplit(P0, &P1, choose_gemm_tile(P0.M, P0.N, P0.K, sf), block, sf, out_dt, st);
 }
 
+// Outputs up to this size leave by nontemporal stores, which do not wait for a place in the L2 (us, kept / streamed: NVFP4 1024 x 4096 x 4096,
+// binary32 outputs, 38.1 / 36.6, bf16 35.5 / 34.4, 2048 x 4096 x 4096 66.7 / 65.8; MXFP4 2048 x 4096 x 4096 29.6 / 27.9), and still together
+// with a kernel that reads the output next (quantizer 39.2 / 38.3, 71.5 / 70.9, 34.4 / 33.4).  Of larger ones the next kernel finds more in the
+// last-level cache than the product gains: MXFP4 4096 x 11008 x 4096, 86 MB, 135.9 / 125.7, with a quantizer behind it 134.0 / 138.6; 40 MB 65.6 /
+// 67.8.  (Weight gradients, which are not read next, of 90 MB: the backward half of an MLP of 4096 / 11008 at 2048 tokens 697 / 706, the whole
+// one at 4096 tokens 2872 / 2848: not done.)
+// Calls on packed weights, quantizer and product, us, kept / streamed, one by one and from a graph, MXFP4: 2048 x 4096 x 4096 34.0 / 32.9 and 35.0 / 33.5,
+// 1024 x 4096 x 4096 with binary32 outputs 31.4 / 29.9 and 30.5 / 29.2, 4096 x 4096 x 2048 (32 MB) 32.3 / 31.3 and 31.8 / 30.6; of 70 random ones with 4 to
+// 32 MB 0.97 to 1.10 times as fast (less than 0.99: 3076 x 928 x 928 and 3857 x 928 x 960, NVFP4), 628 x 5888 x 5504 with binary32 outputs 40.8 / 41.0 and
+// 39.7 / 38.7.  Rows 32 KB apart are an exception near the line: MXFP4 1024 x 8192 x 1024 with binary32 outputs 17.2 / 18.2 and 17.1 / 18.3, x 2048 23.2 /
+// 24.0 and 24.8 / 25.9, 1000 x 8192 x 2048 23.1 / 23.5 and 23.6 / 24.2, NVFP4 1024 x 8192 x 1024 28.5 / 29.2 and 28.4 / 28.8; 896 x 8192 x 1024 15.8 / 14.9
+// and 1.02 times as fast (31 KB apart, 1024 x 7936 x 2048, 22.1 / 21.7 and 21.9 / 21.6; 64 KB apart, 512 x 16384 x 4096, 34.0 / 32.8).
+// The rule's answer is an argument of the larger tiles' kernels alone.  As a member of GemmArgs it lengthened the small products' arguments (two of these: 212
+// bytes instead of 196), and with them the host's work for a launch: a call of 64 x 4096 x 11008 MXFP4 on packed weights kept the host 8.80 us instead of
+// 8.50 (two libraries in turn in one process; on another box 5.45 and 5.41).  Asked in the kernels, from M and ldc, it had the 256 x 256 MXFP4 ones spill
+// registers: an MLP of 4096 / 11008 at 4096 tokens, three layers forward and backward, 1128 us instead of 1118.
+static bool streamed_output(int64_t rows, int64_t row_bytes)
+{
+    return rows * row_bytes <= (row_bytes == 32 << 10 ? (int64_t)28 << 20 : (int64_t)32 << 20);
+}
+
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)
 {
     const hipError_t e = check_gemm(P, block, sf);
     if (e != hipSuccess) return e;
-    if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(P, block, out_dt, st);
+    const TileArgs T{P, streamed_output(P.M, P.ldc * (out_dt == NVFP4_F32 ? 4 : 2))};
+    if (sf == NVFP4_SCALE_E4M3 && g_fp4_rescale_route && fp4_rescale_gemm_applies(P.K, block, P)) return launch_gemm_fp4_rescale(T, block, out_dt, st);
     if (gemm_is_thin(P.M, P.N, P.K, block, sf)) return launch_gemm_thin(P, sf, out_dt, st);
     const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);
     if (tile <= TILE_64x64) return launch_gemm_ksplit(P, nullptr, tile, block, sf, out_dt, st);
-    if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(P, tile, out_dt, st);
+    if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(T, tile, out_dt, st);
     switch (block) {
-    case 16: launch_f16_tile<16>(P, tile, out_dt, st); break;
-    case 32: launch_f16_tile<32>(P, tile, out_dt, st); break;
-    case 64: launch_f16_tile<64>(P, tile, out_dt, st); break;
-    case 128: launch_f16_tile<128>(P, tile, out_dt, st); break;
+    case 16: launch_f16_tile<16>(T, tile, out_dt, st); break;
+    case 32: launch_f16_tile<32>(T, tile, out_dt, st); break;
+    case 64: launch_f16_tile<64>(T, tile, out_dt, st); break;
+    case 128: launch_f16_tile<128>(T, tile, out_dt, st); break;
     default: return hipErrorNotSupported;
     }
     return hipGetLastError();

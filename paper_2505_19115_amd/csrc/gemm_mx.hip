@@ -47,7 +47,7 @@ constexpr int LDS_BYTES = 2 * STAGE;                         // 72 KB (>= the 64
 }  // namespace mxr
 
 template <int OUT_DT, int B>
-__global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(GemmArgs P)
+__global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(TileArgs P)
 {
     using namespace mx;
     using namespace mxr;
@@ -224,7 +224,7 @@ constexpr int PER_TILE = 10;  // direct-to-LDS instructions per wave per K tile:
 }  // namespace mxd
 
 template <int OUT_DT, bool A_SLAB, bool B_SLAB>
-__global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(GemmArgs P)
+__global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
 {
     using namespace mx;
     using namespace mxd;
@@ -514,7 +514,7 @@ struct Geom {
 }  // namespace mxt
 
 template <int OUT_DT, int WM, int WN, int TA, int TB>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(GemmArgs P)
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(TileArgs P)
 {
     using namespace mxt;
     using G = Geom<WM, WN, TA, TB>;
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(Gem
 }
 
 template <int WM, int WN, int TA, int TB>
-static void launch_mx_tile(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_mx_tile(const TileArgs &P, int out_dt, hipStream_t st)
 {
     using G = mxt::Geom<WM, WN, TA, TB>;
     const unsigned ntiles = (unsigned)(((P.N + G::BN - 1) / G::BN) * ((P.M + G::BM - 1) / G::BM));
@@ -768,7 +768,7 @@ static void launch_mx_tile(const GemmArgs &P, int out_dt, hipStream_t st)
 }
 
 template <int OUT_DT, bool A_SLAB, bool B_SLAB>
-static void launch_mx_dma_as(const GemmArgs &P, hipStream_t st)
+static void launch_mx_dma_as(const TileArgs &P, hipStream_t st)
 {
     const unsigned ntiles = (unsigned)(((P.N + mx::BN - 1) / mx::BN) * ((P.M + mx::BM - 1) / mx::BM));
     auto k = gemm_nt_mxfp4_dma_kernel<OUT_DT, A_SLAB, B_SLAB>;
@@ -778,7 +778,7 @@ static void launch_mx_dma_as(const GemmArgs &P, hipStream_t st)
 }
 
 template <int OUT_DT>
-static void launch_mx_dma_out(const GemmArgs &P, hipStream_t st)
+static void launch_mx_dma_out(const TileArgs &P, hipStream_t st)
 {
     if (P.a_slab && P.b_slab) launch_mx_dma_as<OUT_DT, true, true>(P, st);
     else if (P.a_slab) launch_mx_dma_as<OUT_DT, true, false>(P, st);
@@ -786,7 +786,7 @@ static void launch_mx_dma_out(const GemmArgs &P, hipStream_t st)
     else launch_mx_dma_as<OUT_DT, false, false>(P, st);
 }
 
-static void launch_mx_dma(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_mx_dma(const TileArgs &P, int out_dt, hipStream_t st)
 {
     if (out_dt == NVFP4_F32)
         launch_mx_dma_out<NVFP4_F32>(P, st);
@@ -795,7 +795,7 @@ static void launch_mx_dma(const GemmArgs &P, int out_dt, hipStream_t st)
 }
 
 template <int B>
-static void launch_rescale(const GemmArgs &P, int out_dt, hipStream_t st)
+static void launch_rescale(const TileArgs &P, int out_dt, hipStream_t st)
 {
     const unsigned ntiles = (unsigned)(((P.N + mx::BN - 1) / mx::BN) * ((P.M + mx::BM - 1) / mx::BM));
     if (out_dt == NVFP4_F32) {
@@ -818,7 +818,7 @@ bool fp4_rescale_gemm_applies(int64_t K, int block, const GemmArgs &P)
     return (block == 64 || block == 128) && K % 128 == 0 && (codes & 15) == 0 && !P.a_slab && !P.b_slab;
 }
 
-hipError_t launch_gemm_fp4_rescale(const GemmArgs &P, int block, int out_dt, hipStream_t st)
+hipError_t launch_gemm_fp4_rescale(const TileArgs &P, int block, int out_dt, hipStream_t st)
 {
     if (block == 64)
         launch_rescale<64>(P, out_dt, st);
@@ -836,7 +836,7 @@ bool mxfp4_gemm_takes_slabs(int64_t K)
     return K % 128 == 0 && K >= 512 && offsets_fit;
 }
 
-hipError_t launch_gemm_mxfp4(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st)
+hipError_t launch_gemm_mxfp4(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st)
 {
     const uintptr_t codes = reinterpret_cast<uintptr_t>(P.A_codes) | reinterpret_cast<uintptr_t>(P.B_codes);
     const uintptr_t scales = reinterpret_cast<uintptr_t>(P.A_scales) | reinterpret_cast<uintptr_t>(P.B_scales);

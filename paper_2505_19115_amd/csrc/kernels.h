@@ -88,6 +88,10 @@ struct GemmArgs {
     int64_t ldc;
     int a_slab = 0, b_slab = 0;  // operand stored in the slab layout (only where gemm_reads_slabs() holds)
 };
+// The arguments of the larger tiles' kernels
+struct TileArgs : GemmArgs {
+    int stream;  // the output leaves by nontemporal stores (set by launch_gemm())
+};
 // True for the products whose operands the dual quantizer hands over as slabs (and nvfp4_gemm_slab() accepts): NVFP4 with at least
 // 128 output tiles of 256 x 256, MXFP4 with K >= 512, K a multiple of 128 in both.  Every tile of the GEMM kernels reads slabs.
 bool gemm_takes_slabs(int64_t M, int64_t N, int64_t K, int block, int sf);
@@ -216,10 +220,10 @@ bool gemm_is_thin(int64_t M, int64_t N, int64_t K, int block, int sf);
 hipError_t launch_gemm_thin(const GemmArgs &P, int sf, int out_dt, hipStream_t st);
 bool thin_takes_tensor(int64_t M, int64_t K, int dt);
 hipError_t launch_gemm_thin_tensor(const GemmArgs &P, const void *X, int dt, float *g_out, int sf, int out_dt, hipStream_t st);
-hipError_t launch_gemm_mxfp4(const GemmArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
+hipError_t launch_gemm_mxfp4(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
 // E4M3 scales at blocks of 64 / 128 as unit-scale FP4 MFMAs per block + binary32 rescale (row-major operands, K % 128 == 0)
 bool fp4_rescale_gemm_applies(int64_t K, int block, const GemmArgs &P);
-hipError_t launch_gemm_fp4_rescale(const GemmArgs &P, int block, int out_dt, hipStream_t st);
+hipError_t launch_gemm_fp4_rescale(const TileArgs &P, int block, int out_dt, hipStream_t st);
 // Which of the two exact routes launch_gemm() takes for those formats: 0 = expanded to fp16 (the NVFP4 kernel), 1 = this one
 void set_fp4_rescale_route(int on);
 int fp4_rescale_route();
