@@ -22,6 +22,7 @@ namespace nvfp4 {
 
 typedef int int8v_t __attribute__((ext_vector_type(8)));
 typedef float float16v_t __attribute__((ext_vector_type(16)));
+typedef float float4v_t __attribute__((ext_vector_type(4)));
 
 namespace mx {
 constexpr int NT = 256, BM = 256, BN = 256, TA = 4, TB = 4;
@@ -220,8 +221,20 @@ constexpr int STAGE = (mx::BM + mx::BN) * ROWB;        // 32 KB of codes
 constexpr int SBUF = (mx::BM + mx::BN) * 16;           // 8 KB: the scales of four K tiles
 constexpr int SCALES0 = NS * STAGE, DUMP0 = SCALES0 + 2 * SBUF;
 constexpr int LDS_BYTES = DUMP0 + 4096;
+constexpr int FA = 8, FB = 8;  // fragments of 16 rows of a wave's part of A and of B
 constexpr int PER_TILE = 10;  // direct-to-LDS instructions per wave per K tile: 4 + 4 codes, 2 scale slots
 }  // namespace mxd
+
+// Written as assembly so that the 64 accumulators stay where they are: through the builtin the compiler moves them between the two halves of
+// the register file all the time and spills (some 700 moves per K tile).  What the compiler cannot know about it: an operand must not
+// have been written by the vector ALU in the two instructions before (here all come from LDS reads), and the result of the last one
+// must not be read for 11 wait states.
+__device__ __forceinline__ void mfma_16x16x128(float4v_t &acc, const uint4 &b, const uint4 &a, uint32_t sb, uint32_t sa)
+{
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    const u32x4_t vb = {b.x, b.y, b.z, b.w}, va = {a.x, a.y, a.z, a.w};
+    asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0] cbsz:4 blgp:4" : "+a"(acc) : "v"(vb), "v"(va), "v"(sb), "v"(sa));
+}
 
 template <int OUT_DT, bool A_SLAB, bool B_SLAB>
 __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
@@ -232,7 +245,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int r = lane & 31, g = lane >> 5;
+    const int r = lane & 15, g = lane >> 4;
     const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
     int ty, tx;
     tile_coords((int)blockIdx.x, ntx, nty, ty, tx);
@@ -240,13 +253,11 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     const int64_t Kb = P.K >> 1, Ks = P.K >> 5;
     const int nkt = (int)(P.K / KT);
 
-    float16v_t acc[TA][TB];
+    float4v_t acc[FA][FB];
 #pragma unroll
-    for (int a = 0; a < TA; ++a)
+    for (int a = 0; a < FA; ++a)
 #pragma unroll
-        for (int b = 0; b < TB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+        for (int b = 0; b < FB; ++b) acc[a][b] = float4v_t{0.0f, 0.0f, 0.0f, 0.0f};
 
     // ---- global -> LDS.  A code instruction fills 1 KB = 16 consecutive tile rows, lane i landing
     // at byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
@@ -331,161 +342,140 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
         dma16_chosen(go ? slab_scale_dst + (uint32_t)(kt & (NS - 1)) * 1024 : dump_dst, go ? (uint32_t)lane * 16 : 0u, uniform_ptr(base));
     };
 
-    // ---- LDS -> registers
+    // ---- LDS -> registers: fragment i of an operand is its rows 16 i + r, of which lane group g reads the 16-byte chunk g and the
+    // scale byte g
     struct Frags {
-        uint4 a[TA], b[TB];
+        uint4 a[FA], b[FB];
+        uint32_t sa[FA], sb[FB];
     };
-    struct Scales {
-        uint32_t a[TA], b[TB];
-    };
-    const int sw = (r >> 2) & 3;
-    const int rdA = (wm * 128 + r) * ROWB, rdB = (BM + wn * 128 + r) * ROWB;
-    // scale dword of fragment i (rows 32 i + r of the wave's part): row-major image [row][16 bytes], or the slab
-    // image [position][4 bytes] with the row at position slab_row(row) (for row 128 w + 32 i + r that is
-    // 128 w + 64 (i / 2) + 8 (r % 8) + 4 (i % 2) + r / 8: a lane part plus a constant per fragment)
-    const int rdS = SCALES0 + (A_SLAB ? slab_row(wm * 128 + r) * 4 : (wm * 128 + r) * 16);
-    const int rdT = SCALES0 + BM * 16 + (B_SLAB ? slab_row(wn * 128 + r) * 4 : (wn * 128 + r) * 16);
-    auto frag_off = [](bool slab, int i) -> int { return slab ? 256 * (i >> 1) + 16 * (i & 1) : 512 * i; };
+    const int rdA = (wm * 128 + r) * ROWB + ((g ^ ((r >> 2) & 3)) << 4), rdB = rdA + (BM + (wn - wm) * 128) * ROWB;
+    // scale bytes of fragment i (rows 16 i + r of the wave's part): row-major image [row][16 bytes], or the slab
+    // image [position][4 bytes] with the row at position slab_row(row) (for row 128 w + 16 i + r that is
+    // 128 w + 64 (i / 4) + 8 (r % 8) + 2 (i % 4) + r / 8: a lane part plus a constant per fragment)
+    const int rdS = SCALES0 + g + (A_SLAB ? slab_row(wm * 128 + r) * 4 : (wm * 128 + r) * 16);
+    const int rdT = SCALES0 + g + BM * 16 + (B_SLAB ? slab_row(wn * 128 + r) * 4 : (wn * 128 + r) * 16);
+    auto frag_off = [](bool slab, int i) -> int { return slab ? 256 * (i >> 2) + 8 * (i & 3) : 256 * i; };
     // where in the scale area the dwords of K tile kt start
     auto tile_off = [&](bool slab, int kt) -> int {
         const int G = kt >> 2;
         return slab ? (kt & (NS - 1)) * 1024 : (G & 1) * SBUF + (4 * kt - group_start(G));
     };
-    const int sh = 16 * g;
-    // fragment i of both operands (rows 32 i + r of the wave's A and B parts) for MFMA step s of tile kt
-    auto load_frag = [&](int kt, int s, Frags &F, int i) {
-        const uint8_t *p = lds + (kt & (NS - 1)) * STAGE + (((2 * g + s) ^ sw) << 4);
-        F.a[i] = *reinterpret_cast<const uint4 *>(p + rdA + 32 * i * ROWB);
-        F.b[i] = *reinterpret_cast<const uint4 *>(p + rdB + 32 * i * ROWB);
+    // half h (fragments 4 h .. 4 h + 3) of an operand, in eight reads, scales first; stage: the K tile's codes, scales: its scale bytes
+    auto read_a = [&](const uint8_t *stage, const uint8_t *scales, Frags &F, int h, int i) {
+        const int f = 4 * h + (i & 3);
+        if (i < 4) F.sa[f] = scales[frag_off(A_SLAB, f)];
+        else F.a[f] = *reinterpret_cast<const uint4 *>(stage + rdA + 16 * f * ROWB);
     };
-    // raw scale dwords of a tile (all four E8M0 bytes of the row); shifted into place when the tile starts
-    auto load_scale = [&](int kt, Scales &R, int i) {
-        R.a[i] = *reinterpret_cast<const uint32_t *>(lds + tile_off(A_SLAB, kt) + rdS + frag_off(A_SLAB, i));
-        R.b[i] = *reinterpret_cast<const uint32_t *>(lds + tile_off(B_SLAB, kt) + rdT + frag_off(B_SLAB, i));
-    };
-    auto shift_scales = [&](const Scales &R, Scales &S) {
-#pragma unroll
-        for (int a = 0; a < TA; ++a) S.a[a] = R.a[a] >> sh;
-#pragma unroll
-        for (int b = 0; b < TB; ++b) S.b[b] = R.b[b] >> sh;
+    auto read_b = [&](const uint8_t *stage, const uint8_t *scales, Frags &F, int h, int i) {
+        const int f = 4 * h + (i & 3);
+        if (i < 4) F.sb[f] = scales[frag_off(B_SLAB, f)];
+        else F.b[f] = *reinterpret_cast<const uint4 *>(stage + rdB + 16 * f * ROWB);
     };
     // one MFMA: output rows of A fragment ia against B fragment ib.  The first MFMA operand is the
     // B tile (its rows become accumulator rows), the second the A tile.
-#define NVFP4_MXD_MMA(F, S, s, ia, ib)                                                                    \
-    {                                                                                                     \
-        const int8v_t va = {(int)F.a[ia].x, (int)F.a[ia].y, (int)F.a[ia].z, (int)F.a[ia].w, 0, 0, 0, 0};  \
-        const int8v_t vb = {(int)F.b[ib].x, (int)F.b[ib].y, (int)F.b[ib].z, (int)F.b[ib].w, 0, 0, 0, 0};  \
-        acc[ia][ib] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vb, va, acc[ia][ib], 4, 4, s, (int)S.b[ib], s, \
-                                                                      (int)S.a[ia]);                      \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-    }
+    auto mma = [&](const Frags &F, int ia, int ib) { mfma_16x16x128(acc[ia][ib], F.b[ib], F.a[ia], F.sb[ib], F.sa[ia]); };
     // wait until at most n direct-to-LDS instructions of this wave are still in flight
 #define NVFP4_MXD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory");
-    // pins the software pipeline: the compiler's scheduler, left alone, sinks every LDS read down to
-    // its first use
-#define NVFP4_MXD_FENCE __builtin_amdgcn_sched_barrier(0);
 
-    Frags F0, F1;
-    Scales S, R;
-    // ten loads per batch, three batches: scale group 0 rides with tile 0 (eleven loads)
+    Frags F;
+    // K tiles 0 to 3, ten loads each; scale group 0 and the first half of group 1 ride with tile 0
     dma_scales(0, 0);
     dma_scales(0, 1);
+    if (4 < nkt) dma_scales(1, 0);
     dma_codes(0);
     dma_scale_slab(0, true);
-    dma_codes(1);
-    dma_filler();
-    dma_scale_slab(1, true);
-    dma_codes(2);
-    dma_filler();
-    dma_scale_slab(2, true);
-    NVFP4_MXD_WAIT(2 * PER_TILE)  // batch 0 has landed
+    for (int kt = 1; kt < NS; ++kt) {
+        dma_codes(kt);
+        dma_filler();
+        dma_scale_slab(kt, true);
+    }
+    NVFP4_MXD_WAIT(3 * PER_TILE)  // tile 0 has landed
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        load_frag(0, 0, F0, i);
-        load_scale(0, R, i);
+    for (int i = 0; i < 8; ++i) {
+        read_a(lds, lds + tile_off(A_SLAB, 0) + rdS, F, 0, i);
+        read_b(lds, lds + tile_off(B_SLAB, 0) + rdT, F, 0, i);
     }
 
-    // K tile kt (stage kt % 4).  With one wave per SIMD nothing hides an instruction that takes long
-    // to issue, so exactly one LDS read or one load follows each MFMA and issues in its shadow
-    // (scheduling fences pin that order).  Step 0 multiplies while step 1's fragments are read
-    // and the codes of tile kt + 3 are requested (into the stage tile kt - 1 occupied: every wave
-    // finished reading it before the barrier it passed during tile kt - 1), then one half of the
-    // next scale group (tiles 0 and 1 of a group) or a filler.  This wave's loads of tile kt + 1
-    // (issued two tiles ago; the two newest batches stay in flight) are waited for, ONE barrier,
-    // and step 1 multiplies while the first fragments and the scales of tile kt + 1 are read.
+    // K tile kt (stage kt % 4): a quarter of the wave's 64 MFMAs at a time, halves of A against halves of B, each half overwritten
+    // as soon as its last quarter is done.  Of B the half that the tile before ended without comes first (P, then Q):
+    //     A0 x P   while Q is read            A0 x Q   while A1 is read
+    //     wait for this wave's loads of tile kt + 1 (issued three tiles ago; the two newest batches stay in flight), ONE barrier,
+    //     which also says that every wave has read all of tile kt's stage
+    //     A1 x Q   while A0 of kt + 1 is read  A1 x P   while Q of kt + 1 is read, the next tile's P
+    // With one wave per SIMD nothing hides an instruction that takes long to issue, so at most one LDS read or one load follows each
+    // MFMA and issues in its shadow (scheduling fences pin that order): an LDS read every second MFMA (the LDS delivers four waves' 16
+    // bytes a lane in 32 cycles), and in the second half between them the loads of tile kt + 4 into the stage that is free now, one half
+    // of a row-major scale group (in the last tile of a group and the first of the next) and the scale slabs of tile kt + 4.
     // Every tile runs the same code: past the end the loads become one-request fillers (lane
     // offsets masked to zero, landing in the free stage) that keep the counted wait exact, and
     // the barrier / reads of the tile after the last one are harmless.
-    for (int kt = 0; kt < nkt; ++kt) {
-        const bool more = kt + 3 < nkt;
+    auto tile = [&](int kt, auto odd) {
+        constexpr int Pb = decltype(odd)::value, Qb = Pb ^ 1;
+        const bool more = kt + NS < nkt;
         const uint32_t lanes = more ? ~0u : 0u;
-        const uint32_t dst3 = code_dst + (uint32_t)((kt + 3) & (NS - 1)) * STAGE;
-        const uint8_t *pa = uniform_ptr(more ? tileA + (kt + 3) * stepA : tileA);
-        const uint8_t *pb = uniform_ptr(more ? tileB + (kt + 3) * stepB : tileA);
-        shift_scales(R, S);
-        NVFP4_MXD_FENCE
-        // step 0: MFMAs 0-7 each shadow one fragment read of step 1 (B fragments first: every row of
-        // MFMAs needs all four), MFMAs 8-15 each shadow one load of tile kt + 3; by the barrier the
-        // reads of this stage are long complete
-        {
-            const uint8_t *p = lds + (kt & (NS - 1)) * STAGE + (((2 * g + 1) ^ sw) << 4);
+        const uint32_t dst = code_dst + (uint32_t)(kt & (NS - 1)) * STAGE;
+        const uint8_t *pa = uniform_ptr(more ? tileA + (kt + NS) * stepA : tileA);
+        const uint8_t *pb = uniform_ptr(more ? tileB + (kt + NS) * stepB : tileA);
+        const int Gn = ((kt + 1) >> 2) + 1, part = (kt & 1) ^ 1;
+        const bool real = ((kt + 1) & 3) < 2 && 4 * Gn < nkt && !(part ? B_SLAB : A_SLAB);
+        const uint8_t *base = uniform_ptr(real ? (part ? tileSB : tileSA) + group_start(Gn) : tileA);
+        // (scale bytes stay as they were read: what an MFMA does not select may hold anything)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                NVFP4_MXD_MMA(F0, S, 0, j >> 2, j & 3)
-                if (j < 4)
-                    F1.b[j] = *reinterpret_cast<const uint4 *>(p + rdB + 32 * j * ROWB);
-                else if (j < 8)
-                    F1.a[j - 4] = *reinterpret_cast<const uint4 *>(p + rdA + 32 * (j - 4) * ROWB);
-                else if (j & 1)
-                    dma16(dst3 + BM * ROWB + ((j - 8) >> 1) * 1024, offB[(j - 8) >> 1] & lanes, pb);
-                else
-                    dma16(dst3 + ((j - 8) >> 1) * 1024, offA[(j - 8) >> 1] & lanes, pa);
-                NVFP4_MXD_FENCE
-            }
-        }
-        {
-            // slot of the row-major scale groups: halves of the next group ride with tiles 0 and 1 of this one
-            const int Gn = (kt >> 2) + 1, part = kt & 1;
-            const bool real = (kt & 3) < 2 && 4 * Gn < nkt && !(part ? B_SLAB : A_SLAB);
-            const uint8_t *base = real ? (part ? tileSB : tileSA) + group_start(Gn) : tileA;
-            dma16(real ? scale_dst + (Gn & 1) * SBUF + part * (BM * 16) : dump_dst, real ? (part ? offSB : offSA) : 0u, uniform_ptr(base));
-            // slot of the scale slabs: those of tile kt + 3, next to its codes
-            dma_scale_slab(kt + 3, more);
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(F.sa[i]), "+v"(F.sb[4 * Pb + i]));
+        const uint8_t *st = lds + (kt & (NS - 1)) * STAGE, *sa = lds + tile_off(A_SLAB, kt) + rdS, *sb = lds + tile_off(B_SLAB, kt) + rdT;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const int a = (j >> 2) & 3, b = 4 * (j < 16 ? Pb : Qb) + (j & 3);
+            mma(F, a, b);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j < 16 && j % 2 == 0) read_b(st, sb, F, Qb, j >> 1);
+            if (j >= 16 && j % 2 == 0) read_a(st, sa, F, 1, (j - 16) >> 1);
+            __builtin_amdgcn_sched_barrier(0);
         }
         NVFP4_MXD_WAIT(2 * PER_TILE)
         __syncthreads();
-        NVFP4_MXD_FENCE
-        // step 1: MFMAs 0-7 shadow the scale reads of tile kt + 1, MFMAs 8-15 its first fragments
-        {
-            const uint8_t *p = lds + ((kt + 1) & (NS - 1)) * STAGE + (((2 * g) ^ sw) << 4);
-            const uint8_t *qa = lds + tile_off(A_SLAB, kt + 1) + rdS, *qb = lds + tile_off(B_SLAB, kt + 1) + rdT;
+        __builtin_amdgcn_sched_barrier(0);
+        st = lds + ((kt + 1) & (NS - 1)) * STAGE;
+        sa = lds + tile_off(A_SLAB, kt + 1) + rdS;
+        sb = lds + tile_off(B_SLAB, kt + 1) + rdT;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                NVFP4_MXD_MMA(F1, S, 1, j >> 2, j & 3)
-                if (j < 4)
-                    R.a[j] = *reinterpret_cast<const uint32_t *>(qa + frag_off(A_SLAB, j));
-                else if (j < 8)
-                    R.b[j - 4] = *reinterpret_cast<const uint32_t *>(qb + frag_off(B_SLAB, j - 4));
-                else if (j < 12)
-                    F0.b[j - 8] = *reinterpret_cast<const uint4 *>(p + rdB + 32 * (j - 8) * ROWB);
-                else
-                    F0.a[j - 12] = *reinterpret_cast<const uint4 *>(p + rdA + 32 * (j - 12) * ROWB);
-                NVFP4_MXD_FENCE
+        for (int j = 0; j < 32; ++j) {
+            const int a = 4 + ((j >> 2) & 3), b = 4 * (j < 16 ? Qb : Pb) + (j & 3);
+            mma(F, a, b);
+            __builtin_amdgcn_sched_barrier(0);
+            if (j < 16 && j % 2 == 0) read_a(st, sa, F, 0, j >> 1);
+            if (j >= 16 && j % 2 == 0) read_b(st, sb, F, Qb, (j - 16) >> 1);
+            if (j % 2 && j < 16) {
+                const int u = j >> 2;
+                if (j & 2) dma16(dst + BM * ROWB + u * 1024, offB[u] & lanes, pb);
+                else dma16(dst + u * 1024, offA[u] & lanes, pa);
             }
+            if (j == 17) dma16(real ? scale_dst + (Gn & 1) * SBUF + part * (BM * 16) : dump_dst, real ? (part ? offSB : offSA) : 0u, base);
+            if (j == 21) dma_scale_slab(kt + NS, more);
+            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    int kt = 0;
+    for (; kt + 1 < nkt; kt += 2) {
+        tile(kt, std::integral_constant<int, 0>{});
+        tile(kt + 1, std::integral_constant<int, 1>{});
     }
-#undef NVFP4_MXD_FENCE
+    if (kt < nkt) tile(kt, std::integral_constant<int, 0>{});
 #undef NVFP4_MXD_WAIT
-#undef NVFP4_MXD_MMA
 
     // every load of every wave has landed and every fragment has been read: stage 0 is free for
     // the epilogue's line buffers
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int b = 0; b < FB; ++b) asm volatile("" : "+a"(acc[a][b]));
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
     const int w = __builtin_amdgcn_readfirstlane(wave);
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
+    store_lines<OUT_DT, FA, FB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------

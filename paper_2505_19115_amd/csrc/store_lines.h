@@ -1,12 +1,13 @@
-// GEMM epilogue shared by the tile kernels: a wave's TA x TB accumulator tiles of 32 x 32 -> output rows in complete pieces.
+// GEMM epilogue shared by the tile kernels: a wave's TA x TB accumulator tiles of 32 x 32 or 16 x 16 -> output rows in complete pieces.
 #pragma once
 #include "kernels.h"
 
 namespace nvfp4 {
 
-// Accumulator register 4 q + e of lane (r = lane % 32, h = lane / 32) of tile (a, b) is output row 32 a + r, column
-// 32 b + 8 q + 4 h + e of the wave's part, which starts at (row0, col0).  32 rows at a time are transposed through a private
-// piece of LDS (`mine`, 32 rows x 32 TB elements; 16-byte pieces XOR-swizzled by row) so that a store instruction writes
+// Tiles of 32 x 32 (16 accumulators a lane) or of 16 x 16 (4 a lane, TA even).  32 x 32: register 4 q + e of lane (r = lane % 32,
+// h = lane / 32) of tile (a, b) is output row 32 a + r, column 32 b + 8 q + 4 h + e of the wave's part, which starts at (row0, col0);
+// 16 x 16: register e of lane (r = lane % 16, g = lane / 16) is row 16 a + r, column 16 b + 4 g + e.  32 rows at a time are transposed
+// through a private piece of LDS (`mine`, 32 rows of the wave's columns; 16-byte pieces XOR-swizzled by row) so that a store instruction writes
 // whole rows of 64 or 128 bytes instead of 32 pieces of 8: measured 2.5-5 % of a GEMM.  Pieces past the edge are cut
 // element by element, so a tile at the edge of a ragged output keeps wide stores everywhere else.
 // No wave may still read `mine`, no load may still write it.  The lane coordinates are re-derived from an opaque copy so
@@ -23,34 +24,38 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
     typedef float f2_t __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    constexpr int MT = sizeof(ACC) == 16 ? 16 : 32;                    // rows and columns of an MFMA tile
+    constexpr int IN = 32 / MT;                                        // tile rows per 32 rows
+    static_assert(TA % IN == 0, "32 rows at a time");
     constexpr int ESZ = OUT_DT == NVFP4_F32 ? 4 : 2, EPC = 16 / ESZ;   // element size, elements per piece
-    constexpr int ROWB = 32 * TB * ESZ, CPR = ROWB / 16, SWZ = CPR - 1;  // bytes and pieces per row (CPR a power of two)
+    constexpr int ROWB = MT * TB * ESZ, CPR = ROWB / 16, SWZ = CPR - 1;  // bytes and pieces per row (CPR a power of two)
     constexpr int RPS = 64 / CPR;                                        // rows per store instruction
     static_assert((CPR & SWZ) == 0, "the swizzle needs a power of two");
-    const unsigned r = lane & 31, h = lane >> 5;
+    const unsigned r = lane & (MT - 1), g = lane / MT;
     const unsigned rowl0 = lane / CPR, c = lane % CPR;
     const int64_t grow0 = row0 + rowl0, gcol = col0 + EPC * c;
     uint8_t *const dst0 = reinterpret_cast<uint8_t *>(P.out) + (grow0 * P.ldc + gcol) * ESZ;
 #pragma unroll
-    for (int a = 0; a < TA; ++a) {
+    for (int a = 0; a < TA / IN; ++a) {
 #pragma unroll
-        for (int b = 0; b < TB; ++b)
+        for (int i = 0; i < IN; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float y0 = acc[a][b][4 * q] * gg, y1 = acc[a][b][4 * q + 1] * gg;
-                const float y2 = acc[a][b][4 * q + 2] * gg, y3 = acc[a][b][4 * q + 3] * gg;
-                if (OUT_DT == NVFP4_F32) {
-                    const unsigned p = 8 * b + 2 * q + h;
-                    *reinterpret_cast<float4 *>(mine + r * ROWB + ((p ^ (r & SWZ)) << 4)) = make_float4(y0, y1, y2, y3);
-                } else {
-                    const f2_t lo = {y0, y1}, hi = {y2, y3};
-                    uint2 w;
-                    w.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2_t));
-                    w.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2_t));
-                    const unsigned p = 4 * b + q;
-                    *reinterpret_cast<uint2 *>(mine + r * ROWB + ((p ^ (r & SWZ)) << 4) + 8 * h) = w;
+            for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int q = 0; q < MT * MT / 256; ++q) {
+                    const ACC &t = acc[IN * a + i][b];
+                    const float y0 = t[4 * q] * gg, y1 = t[4 * q + 1] * gg, y2 = t[4 * q + 2] * gg, y3 = t[4 * q + 3] * gg;
+                    const unsigned row = MT * i + r, col4 = MT / 4 * b + 64 / MT * q + g;  // (column / 4)
+                    if (OUT_DT == NVFP4_F32) {
+                        *reinterpret_cast<float4 *>(mine + row * ROWB + ((col4 ^ (row & SWZ)) << 4)) = make_float4(y0, y1, y2, y3);
+                    } else {
+                        const f2_t lo = {y0, y1}, hi = {y2, y3};
+                        uint2 w;
+                        w.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, b2_t));
+                        w.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, b2_t));
+                        *reinterpret_cast<uint2 *>(mine + row * ROWB + (((col4 >> 1) ^ (row & SWZ)) << 4) + 8 * (col4 & 1)) = w;
+                    }
                 }
-            }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
         for (int i = 0; i < CPR / 2; ++i) {
@@ -92,7 +97,8 @@ __device__ __forceinline__ void store_lines(const TileArgs &P, const ACC (&acc)[
     const bool wide = P.ldc % (OUT_DT == NVFP4_F32 ? 4 : 8) == 0;
     const bool half = P.ldc % 4 == 0;  // (bf16 rows start at multiples of 8 bytes: 303 x 6548 x 128 8.5 us in single elements)
     // (row0 and col0 are the same in the whole wave)
-    if (wide && row0 + 32 * TA <= P.M && col0 + 32 * TB <= P.N) {
+    constexpr int MT = sizeof(ACC) == 16 ? 16 : 32;
+    if (wide && row0 + MT * TA <= P.M && col0 + MT * TB <= P.N) {
         if (P.stream) store_lines_form<OUT_DT, TA, TB, true, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
         else store_lines_form<OUT_DT, TA, TB, true, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
     } else
