@@ -196,8 +196,8 @@ __global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(TileArgs P)
 // scale area, instead of one dword per row per tile.
 //
 // LDS: four code stages [512 rows][64 bytes] with the 16-byte chunk c of row r at slot
-// c ^ ((r >> 2) & 3) (sixteen consecutive rows reading one logical chunk cover all sixteen 16-byte
-// slots of the 256-byte bank period); two scale buffers [512 rows][16 bytes] (a group of four K
+// c ^ quad_xor(r / 4): the sixteen lanes that the LDS serves at a time cover all sixteen 16-byte
+// slots of the 256-byte bank period; two scale buffers [512 rows][16 bytes] (a group of four K
 // tiles each); 4 KB that absorbs the filler loads.  MFMA step s (0, 1) of lane half g multiplies
 // chunk 2 g + s of the tile: the lane shifts the tile's scale dword right by 16 g once and the
 // instruction's byte select is the compile-time s.
@@ -221,8 +221,11 @@ constexpr int STAGE = (mx::BM + mx::BN) * ROWB;        // 32 KB of codes
 constexpr int SBUF = (mx::BM + mx::BN) * 16;           // 8 KB: the scales of four K tiles
 constexpr int SCALES0 = NS * STAGE, DUMP0 = SCALES0 + 2 * SBUF;
 constexpr int LDS_BYTES = DUMP0 + 4096;
+// 0, 2, 3, 1 for q mod 4.  An instruction's lanes read 16 rows, chunk g in lane group g, and are served 0-3 with 12-15, 20-27 (and the rest of the
+// 32, and the same of the other 32): rows 4-11 of the next chunk beside rows 0-3 and 12-15 of one, which q itself would put into the same
+// slots (4096 x 4096 x 16384: 393 conflict cycles per K tile and CU).
+__device__ __forceinline__ int quad_xor(int q) { return ((q << 1) & 2) ^ ((q >> 1 & 1) * 3); }
 constexpr int FA = 8, FB = 8;  // fragments of 16 rows of a wave's part of A and of B
-constexpr int PER_TILE = 10;  // direct-to-LDS instructions per wave per K tile: 4 + 4 codes, 2 scale slots
 }  // namespace mxd
 
 // Written as assembly so that the 64 accumulators stay where they are: through the builtin the compiler moves them between the two halves of
@@ -263,16 +266,16 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // at byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
     // the lane fetches.  Rows past the edge are clamped to the last row (their products land in
     // outputs that are never stored).  Lane offsets are relative to the tile's first row, the
-    // 64-bit part of the address is wave-uniform.
+    // 64-bit part of the address is wave-uniform.  A wave's four instructions fetch 64 rows; of a slab, which holds all 256 rows, they
+    // lie 128 bytes apart (slab_row(16 u + j) = 2 u + slab_row(j), 64 bytes a position), a constant of the instruction.
     const int64_t mrows = P.M - m0 < BM ? P.M - m0 : BM, nrows = P.N - n0 < BN ? P.N - n0 : BN;
-    uint32_t offA[4], offB[4];
+    uint32_t offA[A_SLAB ? 1 : 4], offB[B_SLAB ? 1 : 4];
+    const int c = (lane & 3) ^ quad_xor(lane >> 4);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int row = (wave * 4 + u) * 16 + (lane >> 2);
-        const int c = (lane & 3) ^ ((lane >> 4) & 3);
-        // (an operand in the slab layout has all 256 rows of the tile, 64 bytes apart, in slab order)
-        offA[u] = A_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < mrows ? row : mrows - 1) * Kb + c * 16);
-        offB[u] = B_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < nrows ? row : nrows - 1) * Kb + c * 16);
+        if (!A_SLAB || u == 0) offA[A_SLAB ? 0 : u] = A_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < mrows ? row : mrows - 1) * Kb + c * 16);
+        if (!B_SLAB || u == 0) offB[B_SLAB ? 0 : u] = B_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < nrows ? row : nrows - 1) * Kb + c * 16);
     }
     const int srow = wave * 64 + lane;
     const uint32_t offSA = (uint32_t)((srow < mrows ? srow : mrows - 1) * Ks);
@@ -286,60 +289,48 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // Issued through inline assembly on purpose: the compiler's wait-count pass treats a
     // direct-to-LDS load as a possible writer of every LDS location and would wait for ALL of them
     // before the next LDS read.  Here a stage is never read before the explicit counted wait and
-    // the barrier that follow its loads.
+    // the barrier that follow its loads.  In two parts: the destination goes into m0 (nothing else here uses it), and the load follows
+    // at least one instruction later.
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
+#define NVFP4_MXD_DST(base, more) asm volatile("s_add_u32 m0, %0, %1" : : "s"(base), "n"(more) : "scc", "m0");
+#define NVFP4_MXD_LOAD(voff, base, more) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(voff), "s"(base), "n"(more) : "memory");
+    // part u of four of an operand's codes (codes of K tile kt: tile + kt * step; row-major: 64 bytes further along every row; slabs: the
+    // next 16 KB slab) into stage st.  The constant of a slab's load counts for both of its addresses.
+#define NVFP4_MXD_DST_A(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + (u) * (A_SLAB ? 1024 - 128 : 1024))
+#define NVFP4_MXD_DST_B(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + BM * ROWB + (u) * (B_SLAB ? 1024 - 128 : 1024))
+#define NVFP4_MXD_LOAD_A(u, p) NVFP4_MXD_LOAD(offA[A_SLAB ? 0 : (u)], p, A_SLAB ? 128 * (u) : 0)
+#define NVFP4_MXD_LOAD_B(u, p) NVFP4_MXD_LOAD(offB[B_SLAB ? 0 : (u)], p, B_SLAB ? 128 * (u) : 0)
     const uint32_t code_dst = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
-    const uint32_t scale_dst = __builtin_amdgcn_readfirstlane(lds0 + SCALES0 + wave * 1024);
-    const uint32_t dump_dst = __builtin_amdgcn_readfirstlane(lds0 + DUMP0 + wave * 1024);
-    auto dma16 = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
-    };
-    // dma16_chosen: for an address that was selected right before.  The compiler selects 64-bit values in vector registers and reads the
-    // lane back, and the load has to come five wait states after that read, which the compiler does not put into inline assembly.
-    // (tests/test_device_code.py has every such load's distance; waiting at all of them costs the small MXFP4 products 3 %.)
-    auto dma16_chosen = [&](uint32_t lds_addr, uint32_t voff, const uint8_t *base) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
-    };
-    // codes of K tile kt: tile + kt * step (row-major: 64 bytes further along every row; slabs: the next 16 KB slab)
-    const uint8_t *tileA = A_SLAB ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb;
-    const uint8_t *tileB = B_SLAB ? P.B_codes + (int64_t)tx * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb;
-    constexpr int64_t stepA = A_SLAB ? SLAB_CODE_BYTES : ROWB, stepB = B_SLAB ? SLAB_CODE_BYTES : ROWB;
-    // scales: the tile's rows in the row-major matrix, or the tile row's scale slabs (one per K tile)
-    const uint8_t *tileSA = A_SLAB ? P.A_scales + (int64_t)ty * nkt * SLAB_MX_SCALE_BYTES : P.A_scales + m0 * Ks;
-    const uint8_t *tileSB = B_SLAB ? P.B_scales + (int64_t)tx * nkt * SLAB_MX_SCALE_BYTES : P.B_scales + n0 * Ks;
-    auto dma_codes = [&](int kt) {
-        const uint32_t st = (uint32_t)(kt & (NS - 1)) * STAGE;
-        const uint8_t *pa = uniform_ptr(tileA + kt * stepA), *pb = uniform_ptr(tileB + kt * stepB);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            dma16(code_dst + st + u * 1024, offA[u], pa);
-            dma16(code_dst + st + BM * ROWB + u * 1024, offB[u], pb);
-        }
-    };
-    // Scale group G = the 16 scale bytes of a row that cover K tiles 4 G .. 4 G + 3; the window of the
-    // last group is moved back to end with the row (Ks >= 16), so no load passes the end of a row.
+    const uint8_t *tileA = uniform_ptr(A_SLAB ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb);
+    const uint8_t *tileB = uniform_ptr(B_SLAB ? P.B_codes + (int64_t)tx * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb);
+    uint32_t stepA = A_SLAB ? SLAB_CODE_BYTES : ROWB, stepB = B_SLAB ? SLAB_CODE_BYTES : ROWB;
+    // Scale slabs (one per K tile): wave 0 fetches A's, wave 1 B's, 16 bytes per lane, into stage kt % 4 of that operand's part of the first
+    // scale buffer; the other waves (and a wave whose operand is row-major) issue a one-request filler (the first bytes of A's codes: a
+    // valid address in both layouts), so that every wave has the same number of loads per tile, which the counted waits rely on.
+    constexpr bool SLABS = A_SLAB || B_SLAB, GROUPS = !A_SLAB || !B_SLAB;
+    const int w01 = __builtin_amdgcn_readfirstlane(wave);
+    const bool slab_loader = (w01 == 0 && A_SLAB) || (w01 == 1 && B_SLAB);
+    const uint8_t *slab_ptr = uniform_ptr(!slab_loader ? tileA
+                                          : w01 == 0   ? P.A_scales + (int64_t)ty * nkt * SLAB_MX_SCALE_BYTES
+                                                       : P.B_scales + (int64_t)tx * nkt * SLAB_MX_SCALE_BYTES);
+    uint32_t slab_step = __builtin_amdgcn_readfirstlane(slab_loader ? (uint32_t)SLAB_MX_SCALE_BYTES : 0u);
+    uint32_t slab_voff = slab_loader ? (uint32_t)lane * 16 : 0u;
+    const uint32_t slab_dst = __builtin_amdgcn_readfirstlane(lds0 + (slab_loader ? SCALES0 + w01 * BM * 16 : DUMP0));
+    // Row-major scales.  Group G = the 16 scale bytes of a row that cover K tiles 4 G .. 4 G + 3; the window of the
+    // last group is moved back to end with the row (Ks >= 16), so no load passes the end of a row.  Part 0: this wave's 64 A rows, part 1:
+    // its 64 B rows.
+    const uint8_t *const rowsSA = P.A_scales + m0 * Ks, *const rowsSB = P.B_scales + n0 * Ks;
+    const uint32_t scale_dst = __builtin_amdgcn_readfirstlane(lds0 + SCALES0 + wave * 1024), dump_dst = __builtin_amdgcn_readfirstlane(lds0 + DUMP0);
     auto group_start = [&](int G) -> int { return 16 * G + 16 <= Ks ? 16 * G : (int)Ks - 16; };
-    // keeps the number of loads per tile constant (the counted waits rely on it): one request, lands in the dump
-    // (the first bytes of A's codes: a valid address in both layouts)
-    auto dma_filler = [&]() { dma16_chosen(dump_dst, 0u, uniform_ptr(tileA)); };
-    // row-major scales, group G.  part 0: this wave's 64 A rows, part 1: its 64 B rows
-    auto dma_scales = [&](int G, int part) {
-        if ((part == 0 && A_SLAB) || (part == 1 && B_SLAB)) {
-            dma_filler();
-            return;
-        }
-        const uint8_t *base = (part ? tileSB : tileSA) + group_start(G);
-        dma16_chosen(scale_dst + (G & 1) * SBUF + part * (BM * 16), part ? offSB : offSA, uniform_ptr(base));
+    auto group_dst = [&](int G, int part, bool real) {
+        const uint32_t d = __builtin_amdgcn_readfirstlane(real ? scale_dst + (G & 1) * SBUF + part * (BM * 16) : dump_dst);
+        NVFP4_MXD_DST(d, 0)
     };
-    // scale slabs of K tile kt (real: kt < nkt): wave 0 fetches A's, wave 1 B's, 16 bytes per lane, into stage
-    // kt % 4 of that operand's part of the first scale buffer; the other waves (and a wave whose operand is
-    // row-major) fill in
-    const uint32_t slab_scale_dst = __builtin_amdgcn_readfirstlane(lds0 + SCALES0 + (wave == 1 ? BM * 16 : 0));
-    const bool slab_loader = __builtin_amdgcn_readfirstlane((wave == 0 && A_SLAB) || (wave == 1 && B_SLAB));
-    auto dma_scale_slab = [&](int kt, bool real) {
-        const bool go = slab_loader && real;
-        const uint8_t *base = go ? (wave == 0 ? tileSA : tileSB) + (int64_t)kt * SLAB_MX_SCALE_BYTES : tileA;
-        dma16_chosen(go ? slab_scale_dst + (uint32_t)(kt & (NS - 1)) * 1024 : dump_dst, go ? (uint32_t)lane * 16 : 0u, uniform_ptr(base));
+    // (the compiler selects the address in vector registers and reads the lane back; the load has to come five wait states after that)
+    auto group_load = [&](int G, int part, bool real) {
+        const uint8_t *const base = uniform_ptr(real ? (part ? rowsSB : rowsSA) + group_start(G) : tileA);
+        const uint32_t off = real ? (part ? offSB : offSA) : 0u;
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base) : "memory");
     };
 
     // ---- LDS -> registers: fragment i of an operand is its rows 16 i + r, of which lane group g reads the 16-byte chunk g and the
@@ -348,121 +339,209 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
         uint4 a[FA], b[FB];
         uint32_t sa[FA], sb[FB];
     };
-    const int rdA = (wm * 128 + r) * ROWB + ((g ^ ((r >> 2) & 3)) << 4), rdB = rdA + (BM + (wn - wm) * 128) * ROWB;
+    // (an LDS instruction's constant reaches 64 KB, two stages: a base for each two, hidden from the compiler, which would add them up for
+    // each tile)
+    const uint8_t *baseA[2], *baseB[2], *baseSA, *baseSB;
+    baseA[0] = lds + (wm * 128 + r) * ROWB + ((g ^ quad_xor(r >> 2)) << 4);
+    baseB[0] = baseA[0] + (BM + (wn - wm) * 128) * ROWB;
+    baseA[1] = baseA[0] + 2 * STAGE;
+    baseB[1] = baseB[0] + 2 * STAGE;
     // scale bytes of fragment i (rows 16 i + r of the wave's part): row-major image [row][16 bytes], or the slab
     // image [position][4 bytes] with the row at position slab_row(row) (for row 128 w + 16 i + r that is
     // 128 w + 64 (i / 4) + 8 (r % 8) + 2 (i % 4) + r / 8: a lane part plus a constant per fragment)
-    const int rdS = SCALES0 + g + (A_SLAB ? slab_row(wm * 128 + r) * 4 : (wm * 128 + r) * 16);
-    const int rdT = SCALES0 + g + BM * 16 + (B_SLAB ? slab_row(wn * 128 + r) * 4 : (wn * 128 + r) * 16);
+    baseSA = lds + SCALES0 + g + (A_SLAB ? slab_row(wm * 128 + r) * 4 : (wm * 128 + r) * 16);
+    baseSB = lds + SCALES0 + g + BM * 16 + (B_SLAB ? slab_row(wn * 128 + r) * 4 : (wn * 128 + r) * 16);
+#define NVFP4_MXD_HIDE(p) { uint32_t v = (uint32_t)(uintptr_t)(lds_ptr_t)(p); asm volatile("" : "+v"(v)); (p) = (const uint8_t *)(lds_ptr_t)(uintptr_t)v; }
+    NVFP4_MXD_HIDE(baseA[0]) NVFP4_MXD_HIDE(baseA[1]) NVFP4_MXD_HIDE(baseB[0]) NVFP4_MXD_HIDE(baseB[1]) NVFP4_MXD_HIDE(baseSA) NVFP4_MXD_HIDE(baseSB)
     auto frag_off = [](bool slab, int i) -> int { return slab ? 256 * (i >> 2) + 8 * (i & 3) : 256 * i; };
-    // where in the scale area the dwords of K tile kt start
-    auto tile_off = [&](bool slab, int kt) -> int {
+    // where in the scale area the dwords of K tile kt, in stage st, start
+    auto tile_off = [&](bool slab, int kt, int st) -> int {
         const int G = kt >> 2;
-        return slab ? (kt & (NS - 1)) * 1024 : (G & 1) * SBUF + (4 * kt - group_start(G));
+        return slab ? st * 1024 : (G & 1) * SBUF + (4 * kt - group_start(G));
     };
-    // half h (fragments 4 h .. 4 h + 3) of an operand, in eight reads, scales first; stage: the K tile's codes, scales: its scale bytes
-    auto read_a = [&](const uint8_t *stage, const uint8_t *scales, Frags &F, int h, int i) {
+    // half h (fragments 4 h .. 4 h + 3) of an operand of the K tile in stage st, in eight reads, scales (at `scales`) first
+    auto read_a = [&](int st, const uint8_t *scales, Frags &F, int h, int i) {
         const int f = 4 * h + (i & 3);
         if (i < 4) F.sa[f] = scales[frag_off(A_SLAB, f)];
-        else F.a[f] = *reinterpret_cast<const uint4 *>(stage + rdA + 16 * f * ROWB);
+        else F.a[f] = *reinterpret_cast<const uint4 *>(baseA[st >> 1] + (st & 1) * STAGE + 16 * f * ROWB);
     };
-    auto read_b = [&](const uint8_t *stage, const uint8_t *scales, Frags &F, int h, int i) {
+    auto read_b = [&](int st, const uint8_t *scales, Frags &F, int h, int i) {
         const int f = 4 * h + (i & 3);
         if (i < 4) F.sb[f] = scales[frag_off(B_SLAB, f)];
-        else F.b[f] = *reinterpret_cast<const uint4 *>(stage + rdB + 16 * f * ROWB);
+        else F.b[f] = *reinterpret_cast<const uint4 *>(baseB[st >> 1] + (st & 1) * STAGE + 16 * f * ROWB);
     };
     // one MFMA: output rows of A fragment ia against B fragment ib.  The first MFMA operand is the
     // B tile (its rows become accumulator rows), the second the A tile.
     auto mma = [&](const Frags &F, int ia, int ib) { mfma_16x16x128(acc[ia][ib], F.b[ib], F.a[ia], F.sb[ib], F.sa[ia]); };
     // wait until at most n direct-to-LDS instructions of this wave are still in flight
 #define NVFP4_MXD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory");
+    constexpr int PER_TILE = 8 + SLABS + GROUPS;  // direct-to-LDS instructions per wave and K tile
 
     Frags F;
-    // K tiles 0 to 3, ten loads each; scale group 0 and the first half of group 1 ride with tile 0
-    dma_scales(0, 0);
-    dma_scales(0, 1);
-    if (4 < nkt) dma_scales(1, 0);
-    dma_codes(0);
-    dma_scale_slab(0, true);
-    for (int kt = 1; kt < NS; ++kt) {
-        dma_codes(kt);
-        dma_filler();
-        dma_scale_slab(kt, true);
+    // (at the end of a tile, the next one's first scales: else the compiler carries them as bytes and masks them again)
+    auto keep_scales = [](Frags &F, auto half) {
+        __builtin_amdgcn_s_waitcnt(0xC37F);  // lgkmcnt(3): three of the fragments are still under way
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(F.sa[i]), "+v"(F.sb[4 * decltype(half)::value + i]));
+    };
+    const uint8_t *pa = tileA, *pb = tileB;  // of A's K tile kt + 4 and B's kt + 3, from here on
+    // K tiles 0 to 2 and A's part of tile 3; scale group 0 rides with tile 0
+    if (GROUPS) {
+        group_dst(0, 0, !A_SLAB);
+        group_load(0, 0, !A_SLAB);
+        group_dst(0, 1, !B_SLAB);
+        group_load(0, 1, !B_SLAB);
     }
-    NVFP4_MXD_WAIT(3 * PER_TILE)  // tile 0 has landed
+    auto prologue = [&](auto st) {
+        constexpr int S = decltype(st)::value;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            NVFP4_MXD_DST_A(S, u)
+            asm volatile("s_nop 4");
+            NVFP4_MXD_LOAD_A(u, pa)
+            if (S < 3) {
+                NVFP4_MXD_DST_B(S, u)
+                asm volatile("s_nop 4");
+                NVFP4_MXD_LOAD_B(u, pb)
+            }
+        }
+        pa += stepA;
+        if (S < 3) {
+            pb += stepB;
+            if (SLABS) {
+                NVFP4_MXD_DST(slab_dst, S * 1024)
+                asm volatile("s_nop 4");
+                NVFP4_MXD_LOAD(slab_voff, slab_ptr, 0)
+                slab_ptr += slab_step;
+            }
+            if (GROUPS && S > 0) {
+                group_dst(0, 0, false);
+                group_load(0, 0, false);
+            }
+        }
+    };
+    prologue(std::integral_constant<int, 0>{});
+    prologue(std::integral_constant<int, 1>{});
+    prologue(std::integral_constant<int, 2>{});
+    prologue(std::integral_constant<int, 3>{});
+    NVFP4_MXD_WAIT(2 * PER_TILE + 4)  // tile 0 has landed
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        read_a(lds, lds + tile_off(A_SLAB, 0) + rdS, F, 0, i);
-        read_b(lds, lds + tile_off(B_SLAB, 0) + rdT, F, 0, i);
+        read_a(0, baseSA + tile_off(A_SLAB, 0, 0), F, 0, i);
+        read_b(0, baseSB + tile_off(B_SLAB, 0, 0), F, 0, i);
     }
+    keep_scales(F, std::integral_constant<int, 0>{});
 
     // K tile kt (stage kt % 4): a quarter of the wave's 64 MFMAs at a time, halves of A against halves of B, each half overwritten
     // as soon as its last quarter is done.  Of B the half that the tile before ended without comes first (P, then Q):
-    //     A0 x P   while Q is read            A0 x Q   while A1 is read
-    //     wait for this wave's loads of tile kt + 1 (issued three tiles ago; the two newest batches stay in flight), ONE barrier,
-    //     which also says that every wave has read all of tile kt's stage
+    //     A0 x P   while Q is read             A0 x Q   while A1 is read
+    //     wait for this wave's loads of tile kt + 1 (two and a half tiles old; those of the two tiles behind it stay in flight), ONE
+    //     barrier, which also says that every wave has read all of tile kt's stage
     //     A1 x Q   while A0 of kt + 1 is read  A1 x P   while Q of kt + 1 is read, the next tile's P
-    // With one wave per SIMD nothing hides an instruction that takes long to issue, so at most one LDS read or one load follows each
-    // MFMA and issues in its shadow (scheduling fences pin that order): an LDS read every second MFMA (the LDS delivers four waves' 16
-    // bytes a lane in 32 cycles), and in the second half between them the loads of tile kt + 4 into the stage that is free now, one half
-    // of a row-major scale group (in the last tile of a group and the first of the next) and the scale slabs of tile kt + 4.
+    // In the first half B's codes and the scales of tile kt + 3 are requested (into the stage that tile kt - 1 left at its barrier), in the
+    // second A's codes of tile kt + 4.
+    // A wave has its SIMD to itself and issues an instruction every 8 cycles or so; a MFMA takes 16.  So what bounds a K tile, beside
+    // power, is the number of instructions beyond one per MFMA: stages and with them all LDS addresses are constants (four tiles a trip),
+    // pointers advance in scalar registers, the load's destination is one addition, and one LDS read, load or destination follows each MFMA
+    // (scheduling fences pin that order).  4096 x 4096 x 16384: 195 instructions a K tile 125.2 us, 135 111.3;
+    // 4096 x 11008 x 4096 100.0 and 88.0.
     // Every tile runs the same code: past the end the loads become one-request fillers (lane
-    // offsets masked to zero, landing in the free stage) that keep the counted wait exact, and
+    // offsets zero, landing in the free stage) that keep the counted wait exact, and
     // the barrier / reads of the tile after the last one are harmless.
-    auto tile = [&](int kt, auto odd) {
-        constexpr int Pb = decltype(odd)::value, Qb = Pb ^ 1;
-        const bool more = kt + NS < nkt;
-        const uint32_t lanes = more ? ~0u : 0u;
-        const uint32_t dst = code_dst + (uint32_t)(kt & (NS - 1)) * STAGE;
-        const uint8_t *pa = uniform_ptr(more ? tileA + (kt + NS) * stepA : tileA);
-        const uint8_t *pb = uniform_ptr(more ? tileB + (kt + NS) * stepB : tileA);
-        const int Gn = ((kt + 1) >> 2) + 1, part = (kt & 1) ^ 1;
-        const bool real = ((kt + 1) & 3) < 2 && 4 * Gn < nkt && !(part ? B_SLAB : A_SLAB);
-        const uint8_t *base = uniform_ptr(real ? (part ? tileSB : tileSA) + group_start(Gn) : tileA);
-        // (scale bytes stay as they were read: what an MFMA does not select may hold anything)
+    int kt = 0;
+    auto tile = [&](auto stage) {
+        constexpr int ST = decltype(stage)::value, BEFORE = (ST + 3) & 3, NEXT = (ST + 1) & 3, Pb = ST & 1, Qb = Pb ^ 1;
+        if (kt + 4 >= nkt) {
+            asm volatile("");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(F.sa[i]), "+v"(F.sb[4 * Pb + i]));
-        const uint8_t *st = lds + (kt & (NS - 1)) * STAGE, *sa = lds + tile_off(A_SLAB, kt) + rdS, *sb = lds + tile_off(B_SLAB, kt) + rdT;
+            for (int u = 0; u < (A_SLAB ? 1 : 4); ++u) offA[u] = 0;
+            pa = tileA;
+            stepA = 0;
+            if (kt + 3 >= nkt) {
+                asm volatile("");
+#pragma unroll
+                for (int u = 0; u < (B_SLAB ? 1 : 4); ++u) offB[u] = 0;
+                slab_voff = 0;
+                pb = slab_ptr = tileA;
+                stepB = slab_step = 0;
+            }
+        }
+        const uint8_t *sa = baseSA + tile_off(A_SLAB, kt, ST), *sb = baseSB + tile_off(B_SLAB, kt, ST);
+        const int Gn = (kt >> 2) + 1, part = kt & 1;
+        const bool real = GROUPS && (kt & 3) < 2 && 4 * Gn < nkt && !(part ? B_SLAB : A_SLAB);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
-            const int a = (j >> 2) & 3, b = 4 * (j < 16 ? Pb : Qb) + (j & 3);
-            mma(F, a, b);
+            mma(F, (j >> 2) & 3, 4 * (j < 16 ? Pb : Qb) + (j & 3));
             __builtin_amdgcn_sched_barrier(0);
-            if (j < 16 && j % 2 == 0) read_b(st, sb, F, Qb, j >> 1);
-            if (j >= 16 && j % 2 == 0) read_a(st, sa, F, 1, (j - 16) >> 1);
+            const int q = j & 15, i = q % 3 != 2 && q < 12 ? q / 3 * 2 + q % 3 : -1;  // reads behind MFMAs 0, 1, 3, 4, 6, 7, 9, 10 of a quarter
+            if (i >= 0 && j < 16) read_b(ST, sb, F, Qb, i);
+            if (i >= 0 && j >= 16) read_a(ST, sa, F, 1, i);
+            // the loads' two parts behind the others: B's codes, a scale slab, a scale group
+            if (j == 2) NVFP4_MXD_DST_B(BEFORE, 0)
+            if (j == 5) NVFP4_MXD_LOAD_B(0, pb)
+            if (j == 8) NVFP4_MXD_DST_B(BEFORE, 1)
+            if (j == 11) NVFP4_MXD_LOAD_B(1, pb)
+            if (j == 12) NVFP4_MXD_DST_B(BEFORE, 2)
+            if (j == 13) NVFP4_MXD_LOAD_B(2, pb)
+            if (j == 14) NVFP4_MXD_DST_B(BEFORE, 3)
+            if (j == 15) NVFP4_MXD_LOAD_B(3, pb)
+            if (SLABS && j == 18) NVFP4_MXD_DST(slab_dst, BEFORE * 1024)
+            if (SLABS && j == 21) NVFP4_MXD_LOAD(slab_voff, slab_ptr, 0)
+            if (GROUPS && j == 24) group_dst(Gn, part, real);
+            if (GROUPS && j == 27) group_load(Gn, part, real);
+            if (j == 28) pb += stepB;
+            if (SLABS && j == 29) slab_ptr += slab_step;
             __builtin_amdgcn_sched_barrier(0);
         }
         NVFP4_MXD_WAIT(2 * PER_TILE)
         __syncthreads();
+        sa = baseSA + tile_off(A_SLAB, kt + 1, NEXT);
+        sb = baseSB + tile_off(B_SLAB, kt + 1, NEXT);
         __builtin_amdgcn_sched_barrier(0);
-        st = lds + ((kt + 1) & (NS - 1)) * STAGE;
-        sa = lds + tile_off(A_SLAB, kt + 1) + rdS;
-        sb = lds + tile_off(B_SLAB, kt + 1) + rdT;
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
-            const int a = 4 + ((j >> 2) & 3), b = 4 * (j < 16 ? Qb : Pb) + (j & 3);
-            mma(F, a, b);
+            mma(F, 4 + ((j >> 2) & 3), 4 * (j < 16 ? Qb : Pb) + (j & 3));
             __builtin_amdgcn_sched_barrier(0);
-            if (j < 16 && j % 2 == 0) read_a(st, sa, F, 0, j >> 1);
-            if (j >= 16 && j % 2 == 0) read_b(st, sb, F, Qb, (j - 16) >> 1);
-            if (j % 2 && j < 16) {
-                const int u = j >> 2;
-                if (j & 2) dma16(dst + BM * ROWB + u * 1024, offB[u] & lanes, pb);
-                else dma16(dst + u * 1024, offA[u] & lanes, pa);
-            }
-            if (j == 17) dma16(real ? scale_dst + (Gn & 1) * SBUF + part * (BM * 16) : dump_dst, real ? (part ? offSB : offSA) : 0u, base);
-            if (j == 21) dma_scale_slab(kt + NS, more);
+            const int q = j & 15, i = q % 3 != 2 && q < 12 ? q / 3 * 2 + q % 3 : -1;
+            if (i >= 0 && j < 16) read_a(NEXT, sa, F, 0, i);
+            if (i >= 0 && j >= 16) read_b(NEXT, sb, F, Qb, i);
+            if (j == 2) NVFP4_MXD_DST_A(ST, 0)
+            if (j == 5) NVFP4_MXD_LOAD_A(0, pa)
+            if (j == 8) NVFP4_MXD_DST_A(ST, 1)
+            if (j == 11) NVFP4_MXD_LOAD_A(1, pa)
+            if (j == 18) NVFP4_MXD_DST_A(ST, 2)
+            if (j == 21) NVFP4_MXD_LOAD_A(2, pa)
+            if (j == 24) NVFP4_MXD_DST_A(ST, 3)
+            if (j == 27) NVFP4_MXD_LOAD_A(3, pa)
+            if (j == 28) pa += stepA;
             __builtin_amdgcn_sched_barrier(0);
         }
+        keep_scales(F, std::integral_constant<int, Qb>{});
+        ++kt;
     };
-    int kt = 0;
-    for (; kt + 1 < nkt; kt += 2) {
-        tile(kt, std::integral_constant<int, 0>{});
-        tile(kt + 1, std::integral_constant<int, 1>{});
+    while (kt + 4 <= nkt) {
+        tile(std::integral_constant<int, 0>{});
+        tile(std::integral_constant<int, 1>{});
+        tile(std::integral_constant<int, 2>{});
+        tile(std::integral_constant<int, 3>{});
     }
-    if (kt < nkt) tile(kt, std::integral_constant<int, 0>{});
+    if (kt < nkt) {
+        tile(std::integral_constant<int, 0>{});
+        if (kt < nkt) {
+            tile(std::integral_constant<int, 1>{});
+            if (kt < nkt) tile(std::integral_constant<int, 2>{});
+        }
+    }
 #undef NVFP4_MXD_WAIT
+#undef NVFP4_MXD_HIDE
+#undef NVFP4_MXD_DST
+#undef NVFP4_MXD_LOAD
+#undef NVFP4_MXD_DST_A
+#undef NVFP4_MXD_DST_B
+#undef NVFP4_MXD_LOAD_A
+#undef NVFP4_MXD_LOAD_B
 
     // every load of every wave has landed and every fragment has been read: stage 0 is free for
     // the epilogue's line buffers
