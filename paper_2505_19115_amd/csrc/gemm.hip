@@ -16,6 +16,7 @@
 // Operand storage: row-major ([rows, K/2] codes, [rows, K/B] scale bytes), or, for blocks of 16, the slab layout of
 // kernels.h, in which the 256 rows x 64 code bytes (and 256 x 8 scale bytes) of a K tile are one contiguous piece.  Only
 // addresses differ: per-lane offsets, two base pointers and their step per K tile.
+#include "gemm_fold.h"
 #include "kernels.h"
 #include "nvfp4_math.h"
 #include "store_lines.h"
@@ -50,52 +51,6 @@ __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
     r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
     r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
     return r;
-}
-
-// Sums of two halves of a workgroup (SIDE waves each, wave `w` of one facing wave `w` of the other) over the same N x TB tiles:
-// the lower half keeps the first (N + 1) / 2 tile rows, the upper half the rest, each sends the other what it does not keep
-// through the LDS (64 lanes x float4 per accumulator quarter: 1 KB, no bank conflicts).
-template <int N, int TB, int SIDE>
-__device__ __forceinline__ void fold_groups(const float16_t (&acc)[N][TB], float16_t (&kept)[(N + 1) / 2][TB], uint8_t *lds, bool upper, int w,
-                                            int lane)
-{
-    constexpr int LO = (N + 1) / 2, HI = N - LO, ROW = TB * 4096;
-    uint8_t *const from_lower = lds + w * (HI * ROW) + lane * 16, *const from_upper = lds + SIDE * (HI * ROW) + w * (LO * ROW) + lane * 16;
-    const uint8_t *const theirs = upper ? from_lower : from_upper;
-    uint8_t *const ours = upper ? from_upper : from_lower;
-    // (what goes and what stays is chosen by value: a choice between array elements would put the accumulators into memory)
-#pragma unroll
-    for (int a = 0; a < LO; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b)
-            if (a < HI || upper) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float y[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float lo = acc[a][b][4 * q + e], hi = a < HI ? acc[LO + a < N ? LO + a : 0][b][4 * q + e] : 0.0f;
-                        y[e] = upper ? lo : hi;
-                        kept[a][b][4 * q + e] = upper ? hi : lo;
-                    }
-                    *reinterpret_cast<float4 *>(ours + (a * TB + b) * 4096 + 1024 * q) = make_float4(y[0], y[1], y[2], y[3]);
-                }
-            } else {
-                kept[a][b] = acc[a][b];
-            }
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < LO; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b)
-            if (a < HI || !upper) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 o = *reinterpret_cast<const float4 *>(theirs + (a * TB + b) * 4096 + 1024 * q);
-                    kept[a][b][4 * q] += o.x; kept[a][b][4 * q + 1] += o.y; kept[a][b][4 * q + 2] += o.z; kept[a][b][4 * q + 3] += o.w;
-                }
-            }
-    __syncthreads();
 }
 
 // Tile geometry.  A workgroup is KG groups of WM x WN waves; a wave owns (32 TA) x (32 TB) outputs as
@@ -437,13 +392,13 @@ __device__ __forceinline__ void f16_tile(const TileArgs &P, const int wrow)
     const int64_t row0 = m0 + wrow, col0 = n0 + wn * 32 * TB;
     uint8_t *const mine = lds + wave_wg * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2));
     if constexpr (KG == 1) {
-        store_lines<OUT_DT, TA, TB>(P, acc, row0, col0, mine, lane);
+        store_lines<OUT_DT, TB>(P, acc, row0, col0, mine, lane);
     } else if constexpr (KG == 2) {
         // each group keeps one half of the tile rows
         static_assert(TA % 2 == 0, "halves");
         float16_t half[TA / 2][TB];
         fold_groups<TA, TB, NW>(acc, half, lds, group, wave, lane);
-        store_lines<OUT_DT, TA / 2, TB>(P, half, row0 + group * (16 * TA), col0, mine, lane);
+        store_lines<OUT_DT, TB>(P, half, row0 + group * (16 * TA), col0, mine, lane);
     } else {
         // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the tile rows
         constexpr int LO = (TA + 1) / 2, HI = TA - LO;
@@ -453,7 +408,7 @@ __device__ __forceinline__ void f16_tile(const TileArgs &P, const int wrow)
         fold_groups<LO, TB, 2 * NW>(half, last, lds, group & 1, (group >> 1) * NW + wave, lane);
         // (of three tile rows the last group gets none)
         const int row = (group >> 1) * LO + (group & 1);
-        if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, 1, TB>(P, last, row0 + row * 32, col0, mine, lane);
+        if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, TB>(P, last, row0 + row * 32, col0, mine, lane);
     }
 }
 
@@ -717,6 +672,7 @@ hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStre
     const GemmTile tile = choose_gemm_tile(P.M, P.N, P.K, sf);
     if (tile <= TILE_64x64) return launch_gemm_ksplit(P, nullptr, tile, block, sf, out_dt, st);
     if (sf == NVFP4_SCALE_E8M0) return launch_gemm_mxfp4(T, tile, out_dt, st);
+    if (launch_gemm_wide(T, tile, block, out_dt, st)) return hipGetLastError();
     switch (block) {
     case 16: launch_f16_tile<16>(T, tile, out_dt, st); break;
     case 32: launch_f16_tile<32>(T, tile, out_dt, st); break;

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(TileArgs P)
     }
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
     const int w = __builtin_amdgcn_readfirstlane(wave);
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
+    store_lines<OUT_DT, TB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -256,11 +256,11 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     const int64_t Kb = P.K >> 1, Ks = P.K >> 5;
     const int nkt = (int)(P.K / KT);
 
-    float4v_t acc[FA][FB];
+    float4v_t acc[FA / 2][2 * FB];  // (tile rows in pairs, as the epilogue takes them)
 #pragma unroll
-    for (int a = 0; a < FA; ++a)
+    for (int a = 0; a < FA / 2; ++a)
 #pragma unroll
-        for (int b = 0; b < FB; ++b) acc[a][b] = float4v_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = 0; b < 2 * FB; ++b) acc[a][b] = float4v_t{0.0f, 0.0f, 0.0f, 0.0f};
 
     // ---- global -> LDS.  A code instruction fills 1 KB = 16 consecutive tile rows, lane i landing
     // at byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     };
     // one MFMA: output rows of A fragment ia against B fragment ib.  The first MFMA operand is the
     // B tile (its rows become accumulator rows), the second the A tile.
-    auto mma = [&](const Frags &F, int ia, int ib) { mfma_16x16x128(acc[ia][ib], F.b[ib], F.a[ia], F.sb[ib], F.sa[ia]); };
+    auto mma = [&](const Frags &F, int ia, int ib) { mfma_16x16x128(acc[ia >> 1][FB * (ia & 1) + ib], F.b[ib], F.a[ia], F.sb[ib], F.sa[ia]); };
     // wait until at most n direct-to-LDS instructions of this wave are still in flight
 #define NVFP4_MXD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory");
     constexpr int PER_TILE = 8 + SLABS + GROUPS;  // direct-to-LDS instructions per wave and K tile
@@ -549,12 +549,12 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     __syncthreads();
     asm volatile("s_nop 15" ::: "memory");
 #pragma unroll
-    for (int a = 0; a < FA; ++a)
+    for (int a = 0; a < FA / 2; ++a)
 #pragma unroll
-        for (int b = 0; b < FB; ++b) asm volatile("" : "+a"(acc[a][b]));
+        for (int b = 0; b < 2 * FB; ++b) asm volatile("" : "+a"(acc[a][b]));
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
     const int w = __builtin_amdgcn_readfirstlane(wave);
-    store_lines<OUT_DT, FA, FB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
+    store_lines<OUT_DT, FB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -815,7 +815,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_nt_mxfp4_tile_kernel(Til
 
     __syncthreads();
     static_assert(NW * 32 * 32 * TB * 4 <= G::LDS, "the epilogue's pieces");
-    store_lines<OUT_DT, TA, TB>(P, acc, m0 + wm * 32 * TA, n0 + wn * 32 * TB, lds + wave * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2)), lane);
+    store_lines<OUT_DT, TB>(P, acc, m0 + wm * 32 * TA, n0 + wn * 32 * TB, lds + wave * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2)), lane);
 }
 
 template <int WM, int WN, int TA, int TB>

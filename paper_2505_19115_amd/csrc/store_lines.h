@@ -4,10 +4,11 @@
 
 namespace nvfp4 {
 
-// Tiles of 32 x 32 (16 accumulators a lane) or of 16 x 16 (4 a lane, TA even).  32 x 32: register 4 q + e of lane (r = lane % 32,
+// Tiles of 32 x 32 (16 accumulators a lane) or of 16 x 16 (4 a lane).  32 x 32: register 4 q + e of lane (r = lane % 32,
 // h = lane / 32) of tile (a, b) is output row 32 a + r, column 32 b + 8 q + 4 h + e of the wave's part, which starts at (row0, col0);
-// 16 x 16: register e of lane (r = lane % 16, g = lane / 16) is row 16 a + r, column 16 b + 4 g + e.  32 rows at a time are transposed
-// through a private piece of LDS (`mine`, 32 rows of the wave's columns; 16-byte pieces XOR-swizzled by row) so that a store instruction writes
+// 16 x 16: register e of lane (r = lane % 16, g = lane / 16) is row 16 a + r, column 16 b + 4 g + e.  acc holds TB tiles a row, one row of
+// them or two in each of its S strips.  A strip at a time (32 rows, or 16) is transposed
+// through a private piece of LDS (`mine`, the strip's rows of the wave's columns; 16-byte pieces XOR-swizzled by row) so that a store instruction writes
 // whole rows of 64 or 128 bytes instead of 32 pieces of 8: measured 2.5-5 % of a GEMM.  Pieces past the edge are cut
 // element by element, so a tile at the edge of a ragged output keeps wide stores everywhere else.
 // No wave may still read `mine`, no load may still write it.  The lane coordinates are re-derived from an opaque copy so
@@ -16,8 +17,8 @@ namespace nvfp4 {
 // for one at its edge, and pieces as vector values: in one form, with pieces as structs of four words, the compiler stored the last
 // word of a piece apart, sharing that store with the cut pieces, and binary32 rows left in 12 + 4 bytes: 8192 x 8192 x 1024 (E4M3,
 // 256 x 256 tiles) 151 us against 137.
-template <int OUT_DT, int TA, int TB, bool FULL, bool STREAM, class ACC>
-__device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&acc)[TA][TB], int64_t row0, int64_t col0, uint8_t *mine,
+template <int OUT_DT, int TB, bool FULL, bool STREAM, int S, int C, class ACC>
+__device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&acc)[S][C], int64_t row0, int64_t col0, uint8_t *mine,
                                                  unsigned lane, float gg, bool wide, bool half)
 {
     typedef __bf16 b2_t __attribute__((ext_vector_type(2)));
@@ -25,8 +26,8 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     constexpr int MT = sizeof(ACC) == 16 ? 16 : 32;                    // rows and columns of an MFMA tile
-    constexpr int IN = 32 / MT;                                        // tile rows per 32 rows
-    static_assert(TA % IN == 0, "32 rows at a time");
+    constexpr int IN = C / TB, ROWS = MT * IN;                         // tile rows and rows of a strip
+    static_assert(C == IN * TB && ROWS <= 32, "whole tile rows");
     constexpr int ESZ = OUT_DT == NVFP4_F32 ? 4 : 2, EPC = 16 / ESZ;   // element size, elements per piece
     constexpr int ROWB = MT * TB * ESZ, CPR = ROWB / 16, SWZ = CPR - 1;  // bytes and pieces per row (CPR a power of two)
     constexpr int RPS = 64 / CPR;                                        // rows per store instruction
@@ -36,14 +37,14 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
     const int64_t grow0 = row0 + rowl0, gcol = col0 + EPC * c;
     uint8_t *const dst0 = reinterpret_cast<uint8_t *>(P.out) + (grow0 * P.ldc + gcol) * ESZ;
 #pragma unroll
-    for (int a = 0; a < TA / IN; ++a) {
+    for (int a = 0; a < S; ++a) {
 #pragma unroll
         for (int i = 0; i < IN; ++i)
 #pragma unroll
             for (int b = 0; b < TB; ++b)
 #pragma unroll
                 for (int q = 0; q < MT * MT / 256; ++q) {
-                    const ACC &t = acc[IN * a + i][b];
+                    const ACC &t = acc[a][TB * i + b];
                     const float y0 = t[4 * q] * gg, y1 = t[4 * q + 1] * gg, y2 = t[4 * q + 2] * gg, y3 = t[4 * q + 3] * gg;
                     const unsigned row = MT * i + r, col4 = MT / 4 * b + 64 / MT * q + g;  // (column / 4)
                     if (OUT_DT == NVFP4_F32) {
@@ -58,15 +59,15 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
                 }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < CPR / 2; ++i) {
+        for (int i = 0; i < ROWS / RPS; ++i) {
             const unsigned rowl = rowl0 + RPS * i;
             const u32x4_t v = *reinterpret_cast<const u32x4_t *>(mine + rowl * ROWB + ((c ^ (rowl & SWZ)) << 4));
-            uint8_t *const dst = dst0 + (int64_t)(32 * a + RPS * i) * P.ldc * ESZ;
+            uint8_t *const dst = dst0 + (int64_t)(ROWS * a + RPS * i) * P.ldc * ESZ;
             if (FULL && STREAM) {
                 __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(dst));
             } else if (FULL) {
                 *reinterpret_cast<u32x4_t *>(dst) = v;
-            } else if (grow0 + 32 * a + RPS * i < P.M) {
+            } else if (grow0 + ROWS * a + RPS * i < P.M) {
                 if (wide && gcol + EPC <= P.N) {
                     *reinterpret_cast<u32x4_t *>(dst) = v;
                 } else if (OUT_DT == NVFP4_BF16 && half && gcol + EPC <= P.N) {
@@ -88,8 +89,8 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
     }
 }
 
-template <int OUT_DT, int TA, int TB, class ACC>
-__device__ __forceinline__ void store_lines(const TileArgs &P, const ACC (&acc)[TA][TB], int64_t row0, int64_t col0, uint8_t *mine,
+template <int OUT_DT, int TB, int S, int C, class ACC>
+__device__ __forceinline__ void store_lines(const TileArgs &P, const ACC (&acc)[S][C], int64_t row0, int64_t col0, uint8_t *mine,
                                             int lane)
 {
     asm volatile("" : "+v"(lane));
@@ -98,11 +99,11 @@ __device__ __forceinline__ void store_lines(const TileArgs &P, const ACC (&acc)[
     const bool half = P.ldc % 4 == 0;  // (bf16 rows start at multiples of 8 bytes: 303 x 6548 x 128 8.5 us in single elements)
     // (row0 and col0 are the same in the whole wave)
     constexpr int MT = sizeof(ACC) == 16 ? 16 : 32;
-    if (wide && row0 + MT * TA <= P.M && col0 + MT * TB <= P.N) {
-        if (P.stream) store_lines_form<OUT_DT, TA, TB, true, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
-        else store_lines_form<OUT_DT, TA, TB, true, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+    if (wide && row0 + MT * (C / TB) * S <= P.M && col0 + MT * TB <= P.N) {
+        if (P.stream) store_lines_form<OUT_DT, TB, true, true>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+        else store_lines_form<OUT_DT, TB, true, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
     } else
-        store_lines_form<OUT_DT, TA, TB, false, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
+        store_lines_form<OUT_DT, TB, false, false>(P, acc, row0, col0, mine, (unsigned)lane, gg, wide, half);
 }
 
 }  // namespace nvfp4
