@@ -9,7 +9,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libnvfp4.so")
-SOURCES = ("quantize.hip", "quantize_small.hip", "gemm.hip", "gemm_wide.hip", "gemm_mx.hip", "gemm_ksplit.hip", "gemm_thin.hip", "fused_small.hip", "probe.hip", "noise.hip", "api.hip")
+SOURCES = ("quantize.hip", "quantize_small.hip", "gemm.hip", "gemm_wide16.hip", "gemm_wide32.hip", "gemm_wide64.hip", "gemm_wide128.hip", "gemm_mx.hip", "gemm_ksplit.hip", "gemm_thin.hip", "fused_small.hip", "probe.hip", "noise.hip", "api.hip")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -662,6 +662,22 @@ static bool streamed_output(int64_t rows, int64_t row_bytes)
     return rows * row_bytes <= (row_bytes == 32 << 10 ? (int64_t)28 << 20 : (int64_t)32 << 20);
 }
 
+// Four waves of 128 columns where gemm_wide.h has the tile, but not for short contractions: with one wave per SIMD nothing covers the latencies of a start and an
+// end (bf16 outputs, us, the kernels above / those: 2384 x 4096 x 288 11.6 / 12.7, x 512 13.2 / 14.0, x 768 17.0 / 17.4, 777 x 12288 x 512 13.2 / 14.0,
+// x 1024 21.3 / 21.2, 320 x 32768 x 512 13.7 / 14.3, x 1024 22.4 / 21.7, 2505 x 3212 x 256 12.7 / 17.7, 3072 x 8192 x 512 29.8 / 31.0, x 1024 50.3 / 48.3,
+// 4096 x 11008 x 512 54.3 / 54.5, x 1024 85.7 / 81.4).
+static bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st)
+{
+    if (P.K <= 7 * KT) return false;
+    switch (block) {
+    case 16: return launch_gemm_wide16(P, tile, out_dt, st);
+    case 32: return launch_gemm_wide32(P, tile, out_dt, st);
+    case 64: return launch_gemm_wide64(P, tile, out_dt, st);
+    case 128: return launch_gemm_wide128(P, tile, out_dt, st);
+    default: return false;
+    }
+}
+
 hipError_t launch_gemm(const GemmArgs &P, int block, int sf, int out_dt, hipStream_t st)
 {
     const hipError_t e = check_gemm(P, block, sf);

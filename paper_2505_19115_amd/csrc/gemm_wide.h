@@ -1,6 +1,6 @@
 // Block-scaled FP4 products with E4M3 scales on four waves of 16 TA x 128 outputs, one wave per SIMD: the products of gemm.hip on
-// v_mfma_f32_16x16x32_f16, for workgroup tiles of 256 x 256, 192 x 256, 160 x 256 (2 x 2 waves), 128 x 256 (two groups of 1 x 2 waves on every
-// other K tile) and 128 or 96 x 128 (four waves on every fourth K tile).  Operands, layouts and arithmetic are those described there.
+// v_mfma_f32_16x16x32_f16, for workgroup tiles of 256 x 256, 192 x 256, 160 x 256 (2 x 2 waves) and 128 x 256 (two groups of 1 x 2 waves on every
+// other K tile).  Operands, layouts and arithmetic are those described there.
 //
 // What bounds them: the matrix unit's power, then the instructions of the one wave a SIMD has, which issues one every 5 cycles or so.
 // Expanding the operands takes 8 (TA + 8) / (8 TA) vector instructions per MFMA of 16 cycles, 2 for TA = 8 (eight waves of 128 x 64 need 3, shared by
@@ -11,6 +11,8 @@
 //     16 x 16 x 32, four waves of 128 x 128                                         1.76                                          1.98
 // The 16 x 16 instruction does the same work with less power (the accumulators are read and written once per 32 products, not 16), and
 // converts and multiplies in fours leave no instruction waiting for the one before.
+// (A header, so that each block size is compiled by itself: gemm_wide16.hip to gemm_wide128.hip.)
+#pragma once
 #include <type_traits>
 #include <utility>
 
@@ -26,7 +28,7 @@ typedef float float4v_t __attribute__((ext_vector_type(4)));
 
 namespace wide {
 
-constexpr int KT = 128, KTB = 64, SROW = 16, TB = 8;  // K tile, bytes of codes and of scales per row and K tile (in the LDS), fragments of B per wave
+constexpr int KT = 128, KTB = 64, TB = 8;  // K tile, bytes of codes per row and K tile, fragments of B per wave
 
 // 0, 2, 3, 1 for q mod 4: see the direct-to-LDS kernel of gemm_mx.hip, whose code stages and fragment reads are the same
 __device__ __forceinline__ int quad_xor(int q) { return ((q << 1) & 2) ^ ((q >> 1 & 1) * 3); }
@@ -55,7 +57,8 @@ template <int WM, int WN, int KG, int TA>
 struct Geom {
     static constexpr int NW = WM * WN, NT = 64 * NW, BM = 16 * TA * WM, BN = 16 * TB * WN, ROWS = BM + BN;
     static constexpr int NSR = (ROWS + NT - 1) / NT;                   // scale rows per thread (the last ones may repeat the last row)
-    static constexpr int STAGE = ROWS * KTB + NSR * NT * SROW;         // codes, then scales
+    static constexpr int SBLOCKS = WM * ((TA + 3) / 4) + WN * (TB / 4);  // scales in the LDS: 1 KB for each four fragments of a wave
+    static constexpr int STAGE = ROWS * KTB + SBLOCKS * 1024;          // codes, then scales
     static constexpr int IN = TA % 2 == 0 ? 2 : 1, S = TA / IN;        // tile rows per strip of the epilogue, strips
     static constexpr int STAGES = KG * 2 * STAGE, PIECES = 4 * 16 * IN * 16 * TB * 4, FOLD = KG == 1 ? 0 : KG / 2 * BM * BN * 4;
     static constexpr int LDS = STAGES > PIECES ? (STAGES > FOLD ? STAGES : FOLD) : (PIECES > FOLD ? PIECES : FOLD);
@@ -198,37 +201,49 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
             for (int t = 0; t < (int)Ks; ++t) gs[u] = gs[u] >> 8 | (uint64_t)srow_ptr[u][t] << 56;
         }
     };
-    // LDS: [16 rows][4 chunks][16 rows] dwords, a fragment's 64 lanes read 256 contiguous bytes.  Chunk c of row tid + NT u, for step j.
-    const uint32_t srow_dst = (uint32_t)(tid >> 4) * 256 + (tid & 15) * 4;
-    auto stash = [&](int stage, int j, int u, int c) {
+    // LDS: 1 KB for four fragments of a wave, [4 chunks][16 rows][4 fragments] dwords, so that a lane reads the scales of all four (of its chunk and
+    // row) at once.  Chunks 2 p and 2 p + 1 of row tid + NT u, for step j.
+    uint32_t srow_dst[NSR];
+#pragma unroll
+    for (int u = 0; u < NSR; ++u) {
+        const int srow = tid + NT * u < ROWS ? tid + NT * u : ROWS - 1;
+        const bool isA = srow < BM;
+        const int frag = (isA ? srow : srow - BM) >> 4, per = isA ? TA : TB, blocks = (per + 3) / 4;
+        const int w = frag / per, i = frag - w * per;
+        srow_dst[u] = (uint32_t)((isA ? 0 : WM * ((TA + 3) / 4) * 1024) + (w * blocks + (i >> 2)) * 1024 + (srow & 15) * 16 + (i & 3) * 4);
+    }
+    auto stash = [&](int stage, int j, int u, int p) {
         const int kj = j * KG + group;
         // bits of the window in front of the K tile's scales; what follows the row is shifted in as zeros, and all of a K tile past the
         // last one is
         const int at = WINDOWS ? 8 * (kj * SPT - window(kj)) : (KG == 1 || kj < nkt) ? 0 : 64;
         uint64_t w = gs[u];
         if (WINDOWS || KG > 1) w = at < 64 ? w >> at : 0;
-        const int i0 = (32 * c) / B, i1 = (32 * c + 16) / B;  // (constants after unrolling)
-        const uint32_t sel = 0x0C000C00u | (uint32_t)i0 | ((uint32_t)i1 << 16);
-        *reinterpret_cast<uint32_t *>(stages + stage * STAGE + ROWS * KTB + srow_dst + NT * u * 16 + c * 64) =
-            __builtin_amdgcn_perm((uint32_t)(w >> 32), (uint32_t)w, sel) << 7;
+        uint32_t *const dst = reinterpret_cast<uint32_t *>(stages + stage * STAGE + ROWS * KTB + srow_dst[u]);
+#pragma unroll
+        for (int c = 2 * p; c < 2 * p + 2; ++c) {
+            const int i0 = (32 * c) / B, i1 = (32 * c + 16) / B;  // (constants after unrolling)
+            const uint32_t sel = 0x0C000C00u | (uint32_t)i0 | ((uint32_t)i1 << 16);
+            dst[64 * c] = __builtin_amdgcn_perm((uint32_t)(w >> 32), (uint32_t)w, sel) << 7;
+        }
     };
 
     // ---- LDS -> registers: fragment i of an operand is its rows 16 i + r, of which lane group g has chunk g: 32 codes (dword t for MFMA step
     // t of four) and the scales of their two blocks
     u32x4_t ca[TA], cb[TB];
-    uint32_t sa[TA], sb[TB];
+    u32x4_t sa[(TA + 3) / 4], sb[TB / 4];  // of four fragments each
     const uint8_t *const fragA = stages + (wm * 16 * TA + r) * KTB + ((g ^ quad_xor(r >> 2)) << 4);
     const uint8_t *const fragB = stages + (BM + wn * 16 * TB + r) * KTB + ((g ^ quad_xor(r >> 2)) << 4);
-    const uint8_t *const scalA = stages + ROWS * KTB + wm * (256 * TA) + lane * 4;
-    const uint8_t *const scalB = stages + ROWS * KTB + BM * SROW + wn * (256 * TB) + lane * 4;
+    const uint8_t *const scalA = stages + ROWS * KTB + wm * ((TA + 3) / 4 * 1024) + lane * 16;
+    const uint8_t *const scalB = stages + ROWS * KTB + (WM * ((TA + 3) / 4) + wn * (TB / 4)) * 1024 + lane * 16;
     auto read_a = [&](int stage, int i) {
         ca[i] = *reinterpret_cast<const u32x4_t *>(fragA + stage * STAGE + i * (16 * KTB));
-        sa[i] = *reinterpret_cast<const uint32_t *>(scalA + stage * STAGE + i * 256);
     };
     auto read_b = [&](int stage, int i) {
         cb[i] = *reinterpret_cast<const u32x4_t *>(fragB + stage * STAGE + i * (16 * KTB));
-        sb[i] = *reinterpret_cast<const uint32_t *>(scalB + stage * STAGE + i * 256);
     };
+    auto read_sa = [&](int stage, int q) { sa[q] = *reinterpret_cast<const u32x4_t *>(scalA + stage * STAGE + q * 1024); };
+    auto read_sb = [&](int stage, int q) { sb[q] = *reinterpret_cast<const u32x4_t *>(scalB + stage * STAGE + q * 1024); };
     // ---- expansion: 8 instructions per fragment and step, four converts and four multiplies by the scale
     u32x4_t fa[2], fb[2][TB];
     uint32_t ta[4], tb[4];
@@ -248,11 +263,11 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
     // instruction k of A's fragment i for step t into fa[to], of B's into fb[t & 1]
     auto expand_a = [&](int i, int t, int to, int k) {
         if (k < 4) ta[k] = convert(ca[i][t], k);
-        else fa[to][k - 4] = scaled(ta[k - 4], sa[i], t >> 1);
+        else fa[to][k - 4] = scaled(ta[k - 4], sa[i >> 2][i & 3], t >> 1);
     };
     auto expand_b = [&](int i, int t, int k) {
         if (k < 4) tb[k] = convert(cb[i][t], k);
-        else fb[t & 1][i][k - 4] = scaled(tb[k - 4], sb[i], t >> 1);
+        else fb[t & 1][i][k - 4] = scaled(tb[k - 4], sb[i >> 2][i & 3], t >> 1);
     };
 
     // ---- start: K tile 0 of the group into stage 0, 1 into stage 1
@@ -270,7 +285,7 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
 #pragma unroll
     for (int u = 0; u < NSR; ++u)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) stash(0, 0, u, c);
+        for (int p = 0; p < 2; ++p) stash(0, 0, u, p);
     aim(1);
 #pragma unroll
     for (int u = 0; u < NSR; ++u) load_scales(1, u);
@@ -285,7 +300,11 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(CI) : "memory");  // K tile 0 has landed
     __syncthreads();
 #pragma unroll
+    for (int q = 0; q < TB / 4; ++q) read_sb(0, q);
+#pragma unroll
     for (int i = 0; i < TB; ++i) read_b(0, i);
+#pragma unroll
+    for (int q = 0; q < (TA + 3) / 4; ++q) read_sa(0, q);
 #pragma unroll
     for (int i = 0; i < TA; ++i) read_a(0, i);
 #pragma unroll
@@ -298,7 +317,7 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
     // The group's step j, its K tile in registers (stage ST is free at the barrier): four MFMA steps of TA rows of 8 MFMAs.  Under a row's MFMAs the
     // next row's fragment of A is expanded and a share of B's fragments for the next step.  In step 1 the scales of step j + 1 go into the
     // other stage, where its codes are by then, ONE barrier; in step 2 a fragment of B is read again as soon as its last dword has been
-    // expanded, in step 3 those of A; in steps 2 and 3 the loads of step j + 2 are requested.  Scheduling fences pin the order.
+    // expanded, in step 3 those of A; in step 2 the loads of step j + 2 are requested.  Scheduling fences pin the order.
     int j = 0;
     auto tile = [&](auto stc) __attribute__((always_inline)) {
         constexpr int NEXT = decltype(stc)::value ^ 1, N = 8 * TA;
@@ -319,19 +338,24 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
                 else expand_b((lo + k - 8) >> 3, (t + 1) & 3, (lo + k - 8) & 7);
             }
             // scales of the next K tile: behind the wait for this wave's loads
-            constexpr int FIRST = N - 8 - 4 * NSR;
+            constexpr int FIRST = N - 8 - 2 * NSR;
             if constexpr (t == 1 && x == FIRST) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if constexpr (t == 1 && x >= FIRST && x < FIRST + 4 * NSR) stash(NEXT, j + 1, (x - FIRST) >> 2, (x - FIRST) & 3);
-            // reads: fragment i of B behind the row that expands its last dword, the second such fragment of a row after the first
+            if constexpr (t == 1 && x >= FIRST && x < FIRST + 2 * NSR) stash(NEXT, j + 1, (x - FIRST) >> 1, (x - FIRST) & 1);
+            // reads: fragment i of B behind the row that expands its last dword, the second such fragment of a row after the first; the scales
+            // of four behind the last of them
 #pragma unroll
             for (int i = 0; i < TB; ++i) {
                 const int done = (8 * i + 7) * TA / 64;  // the row of instruction 8 i + 7
                 const int slot = i == 0 || (8 * i - 1) * TA / 64 != done ? 0 : 2;
-                if (b == slot && ((t == 2 && a == done + 1) || (t == 3 && a == 0 && done == TA - 1))) read_b(NEXT, i);
+                const bool here = (t == 2 && a == done + 1) || (t == 3 && a == 0 && done == TA - 1);
+                if (b == slot && here) read_b(NEXT, i);
+                if (b == 4 && here && i % 4 == 3) read_sb(NEXT, i / 4);
             }
+            // A's row a has been expanded under row a - 1
             if constexpr (t == 3 && b == 6) read_a(NEXT, a);
+            if constexpr (t == 3 && b == 5 && (a % 4 == 3 || a == TA - 1)) read_sa(NEXT, a / 4);
             if constexpr (t == 2 && b == 7 && a < NSR) load_scales(j + 2, a);
-            constexpr int GAP = (2 * N - 8) / CI, y = (t - 2) * N + x - 4;
+            constexpr int GAP = (N - 4) / CI, y = (t - 2) * N + x - 1;
             if constexpr (t >= 2 && y >= 0 && y / GAP < CI) {
                 if constexpr (y % GAP == 0) load_dst(stc, y / GAP);
                 if constexpr (y % GAP == 2) load_codes(y / GAP);
@@ -362,22 +386,12 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
     uint8_t *const mine = lds + wave_wg * (G::PIECES / 4 / (OUT_DT == NVFP4_F32 ? 1 : 2));
     if constexpr (KG == 1) {
         store_lines<OUT_DT, TB>(P, acc, row0, col0, mine, lane);
-    } else if constexpr (KG == 2) {
+    } else {
         // each group keeps one half of the strips
-        static_assert(S % 2 == 0, "halves");
+        static_assert(KG == 2 && S % 2 == 0, "halves");
         float4v_t half[S / 2][IN * TB];
         fold_groups<S, IN * TB, NW>(acc, half, lds, group, wave, lane);
         store_lines<OUT_DT, TB>(P, half, row0 + group * (8 * TA), col0, mine, lane);
-    } else {
-        // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the strips
-        constexpr int LO = (S + 1) / 2, HI = S - LO;
-        static_assert(KG == 4 && IN == 2 && LO == 2, "four groups, three or four strips");
-        float4v_t half[LO][IN * TB], last[1][IN * TB];
-        fold_groups<S, IN * TB, 2 * NW>(acc, half, lds, group >= 2, (group & 1) * NW + wave, lane);
-        fold_groups<LO, IN * TB, 2 * NW>(half, last, lds, group & 1, (group >> 1) * NW + wave, lane);
-        // (of three strips the last group gets none)
-        const int strip = (group >> 1) * LO + (group & 1);
-        if ((group & 1) < (group >= 2 ? HI : LO)) store_lines<OUT_DT, TB>(P, last, row0 + strip * 32, col0, mine, lane);
     }
 }
 
@@ -399,6 +413,7 @@ static void launch_wide(const TileArgs &P, int out_dt, hipStream_t st)
     }
 }
 
+// False for a tile that is not one of these
 template <int B, bool KTAIL>
 static bool launch_wide_tile(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st)
 {
@@ -407,18 +422,6 @@ static bool launch_wide_tile(const TileArgs &P, GemmTile tile, int out_dt, hipSt
     case TILE_192x256: launch_wide<B, 2, 2, 1, 6, KTAIL>(P, out_dt, st); return true;
     case TILE_160x256: launch_wide<B, 2, 2, 1, 5, KTAIL>(P, out_dt, st); return true;
     case TILE_128x256_K2: launch_wide<B, 1, 2, 2, 8, KTAIL>(P, out_dt, st); return true;
-    case TILE_128x128_K4: launch_wide<B, 1, 1, 4, 8, KTAIL>(P, out_dt, st); return true;
-    case TILE_96x128_K4: launch_wide<B, 1, 1, 4, 6, KTAIL>(P, out_dt, st); return true;
-    default: return false;
-    }
-}
-
-// False for a tile that this file does not have
-bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st)
-{
-    const bool ktail = P.K % wide::KT != 0;
-    switch (block) {
-    case 16: return ktail ? launch_wide_tile<16, true>(P, tile, out_dt, st) : launch_wide_tile<16, false>(P, tile, out_dt, st);
     default: return false;
     }
 }

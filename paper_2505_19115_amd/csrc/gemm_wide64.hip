@@ -1,0 +1,10 @@
+#include "gemm_wide.h"
+
+namespace nvfp4 {
+
+bool launch_gemm_wide64(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st)
+{
+    return P.K % wide::KT ? launch_wide_tile<64, true>(P, tile, out_dt, st) : launch_wide_tile<64, false>(P, tile, out_dt, st);
+}
+
+}  // namespace nvfp4

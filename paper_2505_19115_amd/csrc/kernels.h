@@ -220,7 +220,11 @@ bool gemm_is_thin(int64_t M, int64_t N, int64_t K, int block, int sf);
 hipError_t launch_gemm_thin(const GemmArgs &P, int sf, int out_dt, hipStream_t st);
 bool thin_takes_tensor(int64_t M, int64_t K, int dt);
 hipError_t launch_gemm_thin_tensor(const GemmArgs &P, const void *X, int dt, float *g_out, int sf, int out_dt, hipStream_t st);
-bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st);  // E4M3 scales; false: not one of its tiles
+// E4M3 scales, four waves of 128 columns (gemm_wide.h), by block size; false: not one of its tiles
+bool launch_gemm_wide16(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
+bool launch_gemm_wide32(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
+bool launch_gemm_wide64(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
+bool launch_gemm_wide128(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
 hipError_t launch_gemm_mxfp4(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
 // E4M3 scales at blocks of 64 / 128 as unit-scale FP4 MFMAs per block + binary32 rescale (row-major operands, K % 128 == 0)
 bool fp4_rescale_gemm_applies(int64_t K, int block, const GemmArgs &P);
