@@ -43,7 +43,21 @@ class Format:
     tensor_scale: int = 1
 
     def c(self) -> _Format:
-        return _Format(self.block, self.scale, self.tensor_scale)
+        c = self.__dict__.get("_c")  # (made once: entries only read it)
+        if c is None:
+            c = self.__dict__["_c"] = _Format(self.block, self.scale, self.tensor_scale)
+        return c
+
+    def _sizes(self, entry, *sizes: int) -> int:
+        """The answer of one of the library's size functions for this format, of those asked lately."""
+        known = self.__dict__.get("_known")
+        if known is None or len(known) > 1000:
+            known = self.__dict__["_known"] = {}
+        key = (entry, *sizes)
+        n = known.get(key)
+        if n is None:
+            n = known[key] = getattr(lib, entry)(*sizes, C.byref(self.c()))
+        return n
 
 
 NVFP4 = Format(16, SCALE_E4M3, 1)
@@ -203,6 +217,31 @@ def _stream() -> int:
     return _raw_stream(_raw_device())
 
 
+# A call's own workspace, which no tensor has to stand for: a block of torch's caching allocator on the call's stream, given back behind the
+# launches, as the workspace tensor was (0.4 us of the host's work instead of 1.3, of the 13 for a decode call of two launches; outputs with
+# their sizes as arguments instead of a tuple 1.3 instead of 1.6, sizes asked once 0.3).  Without torch's raw entry, or for tensors of another
+# device than the current one, a tensor.
+_raw_alloc = getattr(torch._C, "_cuda_cudaCachingAllocator_raw_alloc", None)
+_raw_delete = getattr(torch._C, "_cuda_cudaCachingAllocator_raw_delete", None)
+
+
+class _Block:
+    """nbytes of device memory for launches on `stream` until the block is deleted."""
+    __slots__ = ("ptr", "tensor")
+
+    def __init__(self, nbytes: int, like: torch.Tensor, stream: int):
+        if _raw_delete is None or _raw_alloc is None or _raw_device is None or nbytes <= 0 or like.get_device() != _raw_device():
+            self.tensor = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
+            self.ptr = self.tensor.data_ptr()
+        else:
+            self.tensor, self.ptr = None, 0
+            self.ptr = _raw_alloc(nbytes, stream)
+
+    def __del__(self):
+        if self.tensor is None and self.ptr:
+            _raw_delete(self.ptr)
+
+
 def _check(code: int, where: str) -> None:
     if code != OK:
         raise Nvfp4Error(code, where)
@@ -239,18 +278,19 @@ def quantize(x: torch.Tensor, axis: int = 1, rounding: int = RTN, seed: int = 0,
     outer, inner = (rows, cols) if axis == 1 else (cols, rows)
     f = fmt.c()
     if out is None:
-        codes = torch.empty((outer, inner // 2), dtype=torch.uint8, device=x.device)
-        scales = torch.empty((outer, inner // fmt.block), dtype=torch.uint8, device=x.device)
+        codes = torch.empty(outer, inner // 2, dtype=torch.uint8, device=x.device)
+        scales = torch.empty(outer, inner // fmt.block, dtype=torch.uint8, device=x.device)
         g = torch.empty(1, dtype=torch.float32, device=x.device) if tensor_scale is None else tensor_scale
     else:
         codes, scales, g = out
         if tensor_scale is not None:
             g = tensor_scale
     flags = PRESET_TSCALE if tensor_scale is not None else 0
-    ws = torch.empty(lib.nvfp4_quantize_workspace_bytes(rows, cols), dtype=torch.uint8, device=x.device)
+    stream, ws_bytes = _stream(), lib.nvfp4_quantize_workspace_bytes(rows, cols)
+    block = _Block(ws_bytes, x, stream)
     _check(lib.nvfp4_quantize(x.data_ptr(), _dtype_tag(x), rows, cols, ld, axis, rounding, seed,
                               C.byref(f), codes.data_ptr(), scales.data_ptr(), g.data_ptr(), flags,
-                              ws.data_ptr(), ws.numel(), _stream()), "nvfp4_quantize")
+                              block.ptr, ws_bytes, stream), "nvfp4_quantize")
     return codes, scales, g
 
 
@@ -402,15 +442,17 @@ def linear_fwd(X: torch.Tensor, W: torch.Tensor, fmt: Format = NVFP4,
     assert (W is None) != (w_operands is None), "give W or w_operands"
     M, K = X.shape
     N = W.shape[0] if W is not None else N
-    f = fmt.c()
+    stream = _stream()
     if workspace is None:
-        workspace = torch.empty(lib.nvfp4_linear_fwd_workspace_bytes(M, N, K, C.byref(f)),
-                                dtype=torch.uint8, device=X.device)
-    Y = torch.empty((M, N), dtype=out_dtype, device=X.device) if out is None else out
+        ws_bytes = fmt._sizes("nvfp4_linear_fwd_workspace_bytes", M, N, K)
+        block = _Block(ws_bytes, X, stream)
+        ws = block.ptr
+    else:
+        ws, ws_bytes = workspace.data_ptr(), workspace.numel()
+    Y = torch.empty(M, N, dtype=out_dtype, device=X.device) if out is None else out
     entry = lib.nvfp4_linear_fwd if w_operands is None else lib.nvfp4_linear_fwd_wq
     _check(entry(X.data_ptr(), (W if w_operands is None else w_operands).data_ptr(), Y.data_ptr(), M, N, K, _dtype_tag(X),
-                 _dtype_tag(Y), C.byref(f), workspace.data_ptr(), workspace.numel(),
-                 _stream(), None if scales_out is None else scales_out.data_ptr(),
+                 _dtype_tag(Y), C.byref(fmt.c()), ws, ws_bytes, stream, None if scales_out is None else scales_out.data_ptr(),
                  None if saved is None else saved.data_ptr(), bwd_seed),
            "nvfp4_linear_fwd")
     return Y
@@ -429,21 +471,24 @@ def linear_bwd(dY: torch.Tensor, X: torch.Tensor, W: torch.Tensor, seed: int, fm
     assert saved is not None or (X is not None and (W is not None or w_operands is not None))
     M, N = dY.shape
     K = K if K is not None else (X.shape[1] if X is not None else W.shape[1])
-    f = fmt.c()
+    stream = _stream()
     if workspace is None:
-        workspace = torch.empty(lib.nvfp4_linear_bwd_workspace_bytes(M, N, K, C.byref(f)),
-                                dtype=torch.uint8, device=dY.device)
+        ws_bytes = fmt._sizes("nvfp4_linear_bwd_workspace_bytes", M, N, K)
+        block = _Block(ws_bytes, dY, stream)
+        ws = block.ptr
+    else:
+        ws, ws_bytes = workspace.data_ptr(), workspace.numel()
     if out is None:
-        dX = torch.empty((M, K), dtype=out_dtype, device=dY.device)
-        dW = torch.empty((N, K), dtype=out_dtype, device=dY.device)
+        dX = torch.empty(M, K, dtype=out_dtype, device=dY.device)
+        dW = torch.empty(N, K, dtype=out_dtype, device=dY.device)
     else:
         dX, dW = out
     entry = lib.nvfp4_linear_bwd if w_operands is None else lib.nvfp4_linear_bwd_wq
     third = w_operands if w_operands is not None else W
     _check(entry(dY.data_ptr(), None if X is None else X.data_ptr(),
                                 None if third is None else third.data_ptr(), dX.data_ptr(),
-                                dW.data_ptr(), M, N, K, _dtype_tag(dY), _dtype_tag(dX), C.byref(f),
-                                seed, workspace.data_ptr(), workspace.numel(), _stream(),
+                                dW.data_ptr(), M, N, K, _dtype_tag(dY), _dtype_tag(dX), C.byref(fmt.c()),
+                                seed, ws, ws_bytes, stream,
                                 None if xw_scales is None else xw_scales.data_ptr(),
                                 None if saved is None else saved.data_ptr()),
            "nvfp4_linear_bwd")
@@ -583,12 +628,16 @@ def quant_noise(x: torch.Tensor, q, axis: int = 1, fmt: Format = NVFP4, out: tor
     rows, cols = x.shape
     codes, scales, g = q
     f = fmt.c()
-    ws = workspace
-    if ws is None:
-        ws = torch.empty(max(lib.nvfp4_quant_noise_workspace_bytes(rows, cols, axis), 16), dtype=torch.uint8, device=x.device)
+    stream = _stream()
+    if workspace is None:
+        ws_bytes = max(lib.nvfp4_quant_noise_workspace_bytes(rows, cols, axis), 16)
+        block = _Block(ws_bytes, x, stream)
+        ws = block.ptr
+    else:
+        ws, ws_bytes = workspace.data_ptr(), workspace.numel()
     if out is None:
         out = torch.empty(2, dtype=torch.float64, device=x.device)
     _check(lib.nvfp4_quant_noise(x.data_ptr(), _dtype_tag(x), rows, cols, x.stride(0) if rows > 1 else cols, axis,
                                  C.byref(f), codes.data_ptr(), scales.data_ptr(), g.data_ptr(), out.data_ptr(),
-                                 ws.data_ptr(), ws.numel(), _stream()), "nvfp4_quant_noise")
+                                 ws, ws_bytes, stream), "nvfp4_quant_noise")
     return out
