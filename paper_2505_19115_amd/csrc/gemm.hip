@@ -514,6 +514,12 @@ static void launch_f16_tile(const TileArgs &P, GemmTile tile, int out_dt, hipStr
     }
 }
 
+// Four waves of 128 columns where gemm_wide.h has the tile, but not for short contractions: with one wave per SIMD nothing covers the latencies of a start and an
+// end (bf16 outputs, us, the kernels above / those: 2384 x 4096 x 288 11.6 / 12.7, x 512 13.2 / 14.0, x 768 17.0 / 17.4, 777 x 12288 x 512 13.2 / 14.0,
+// x 1024 21.3 / 21.2, 320 x 32768 x 512 13.7 / 14.3, x 1024 22.4 / 21.7, 2505 x 3212 x 256 12.7 / 17.7, 3072 x 8192 x 512 29.8 / 31.0, x 1024 50.3 / 48.3,
+// 4096 x 11008 x 512 54.3 / 54.5, x 1024 85.7 / 81.4).
+static bool wide_contraction(int64_t K) { return K > 7 * KT; }
+
 // Which workgroup tile computes an M x N x K product: the one whose estimated time is least.  With R = the tiles of the
 // busiest of the 256 CUs and S = the serial steps of a workgroup (K tiles of 128, divided among its waves or groups of waves),
 //     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
@@ -553,6 +559,24 @@ static const TileCost E8M0_COST[TILES] = {
     {0, 0, 0, 0, 0, 0, 0, 0},               {0, 0, 0, 0, 0, 0, 0, 0},                {0, 0, 0, 0, 0, 0, 0, 0},                 {0, 0, 0, 0, 0, 0, 0, 0},
     {0, 0, 0, 0, 0, 0, 0, 0},               {256, 128, 1, 256, 2900, 3150, 556, 30}, {256, 256, 1, 512, 0, 8500, 1000, 0}};
 
+// The same where four waves of 128 columns serve the tile (launch_gemm_wide()), us, estimate / measured: 4096 x 4096 x 1408 35.7 / 35.4, x 11008 226.9 / 226.9;
+// 6720 x 1536 x 1408 29.4 / 27.2, 3072 x 4096 x 4096 73.9 / 73.9; 777 x 12288 x 1024 21.2 / 21.2, x 4096 65.8 / 65.9; 2048 x 4096 x 1536 25.0 / 24.4, x 4096 51.6 / 50.2,
+// x 11008 123.4 / 123.5; and for the direct-to-LDS kernel in MXFP4: 4096 x 4096 x 4096 33.3 / 33.2, x 16384 111.5 / 111.3.
+// From 16 K tiles on (12 in MXFP4); with the fewer of short contractions these estimates favour the large tiles too much (us, the choice without them / with:
+// 3953 x 4992 x 960 43.1 / 45.7, 1906 x 9312 x 1056 45.7 / 48.5, 5847 x 3008 x 1472 58.6 / 60.3, 2429 x 7840 x 2016 80.6 / 81.3, 2599 x 1952 x 3008 44.0 / 38.5,
+// 1591 x 7328 x 4736 105.9 / 96.9, 5803 x 6368 x 11776 767 / 710; MXFP4 4737 x 2208 x 512 8.6 / 10.1, 3098 x 2592 x 1024 10.7 / 11.8, 4998 x 1664 x 1664 15.6 / 14.5,
+// 702 x 11872 x 2048 18.1 / 16.5, 4644 x 11648 x 7552 274 / 229).
+static const TileCost *wide_cost(int tile, int64_t K, int sf)
+{
+    // (a round of several 4 to 7 % above one alone)
+    static const TileCost k2 = {128, 256, 2, 512, 2700, 6550, 2765, -4}, r160 = {160, 256, 1, 512, 1500, 5000, 1935, -4},
+                          r192 = {192, 256, 1, 512, 1000, 5300, 2205, -4}, r256 = {256, 256, 1, 512, 0, 8000, 2650, -4},
+                          direct = {256, 256, 1, 512, 0, 7710, 873, -7};
+    if (sf == NVFP4_SCALE_E8M0) return tile == TILE_256x256 && K > 11 * KT && mxfp4_gemm_takes_slabs(K) ? &direct : nullptr;
+    if (K <= 15 * KT) return nullptr;
+    return tile == TILE_128x256_K2 ? &k2 : tile == TILE_160x256 ? &r160 : tile == TILE_192x256 ? &r192 : tile == TILE_256x256 ? &r256 : nullptr;
+}
+
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {
     const TileCost *const cost = sf == NVFP4_SCALE_E8M0 ? E8M0_COST : E4M3_COST;
@@ -560,7 +584,8 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
     int best = TILE_256x256;
     double best_time = 0;
     for (int t = 0; t < TILES; ++t) {
-        const TileCost &c = cost[t];
+        const TileCost *const wide = wide_cost(t, K, sf);
+        const TileCost &c = wide ? *wide : cost[t];
         if (c.bm == 0) continue;  // (not built)
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
         if (tiles * c.threads > 0xFFFFFFFF) continue;  // (the threads of a launch are counted in 32 bits)
@@ -662,13 +687,10 @@ static bool streamed_output(int64_t rows, int64_t row_bytes)
     return rows * row_bytes <= (row_bytes == 32 << 10 ? (int64_t)28 << 20 : (int64_t)32 << 20);
 }
 
-// Four waves of 128 columns where gemm_wide.h has the tile, but not for short contractions: with one wave per SIMD nothing covers the latencies of a start and an
-// end (bf16 outputs, us, the kernels above / those: 2384 x 4096 x 288 11.6 / 12.7, x 512 13.2 / 14.0, x 768 17.0 / 17.4, 777 x 12288 x 512 13.2 / 14.0,
-// x 1024 21.3 / 21.2, 320 x 32768 x 512 13.7 / 14.3, x 1024 22.4 / 21.7, 2505 x 3212 x 256 12.7 / 17.7, 3072 x 8192 x 512 29.8 / 31.0, x 1024 50.3 / 48.3,
-// 4096 x 11008 x 512 54.3 / 54.5, x 1024 85.7 / 81.4).
+// (false: not one of the tiles of gemm_wide.h, or a short contraction)
 static bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st)
 {
-    if (P.K <= 7 * KT) return false;
+    if (!wide_contraction(P.K)) return false;
     switch (block) {
     case 16: return launch_gemm_wide16(P, tile, out_dt, st);
     case 32: return launch_gemm_wide32(P, tile, out_dt, st);

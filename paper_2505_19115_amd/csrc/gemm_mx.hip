@@ -308,14 +308,14 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // scale buffer; the other waves (and a wave whose operand is row-major) issue a one-request filler (the first bytes of A's codes: a
     // valid address in both layouts), so that every wave has the same number of loads per tile, which the counted waits rely on.
     constexpr bool SLABS = A_SLAB || B_SLAB, GROUPS = !A_SLAB || !B_SLAB;
-    const int w01 = __builtin_amdgcn_readfirstlane(wave);
-    const bool slab_loader = (w01 == 0 && A_SLAB) || (w01 == 1 && B_SLAB);
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const bool slab_loader = (wave_s == 0 && A_SLAB) || (wave_s == 1 && B_SLAB);
     const uint8_t *slab_ptr = uniform_ptr(!slab_loader ? tileA
-                                          : w01 == 0   ? P.A_scales + (int64_t)ty * nkt * SLAB_MX_SCALE_BYTES
+                                          : wave_s == 0   ? P.A_scales + (int64_t)ty * nkt * SLAB_MX_SCALE_BYTES
                                                        : P.B_scales + (int64_t)tx * nkt * SLAB_MX_SCALE_BYTES);
     uint32_t slab_step = __builtin_amdgcn_readfirstlane(slab_loader ? (uint32_t)SLAB_MX_SCALE_BYTES : 0u);
     uint32_t slab_voff = slab_loader ? (uint32_t)lane * 16 : 0u;
-    const uint32_t slab_dst = __builtin_amdgcn_readfirstlane(lds0 + (slab_loader ? SCALES0 + w01 * BM * 16 : DUMP0));
+    const uint32_t slab_dst = __builtin_amdgcn_readfirstlane(lds0 + (slab_loader ? SCALES0 + wave_s * BM * 16 : DUMP0));
     // Row-major scales.  Group G = the 16 scale bytes of a row that cover K tiles 4 G .. 4 G + 3; the window of the
     // last group is moved back to end with the row (Ks >= 16), so no load passes the end of a row.  Part 0: this wave's 64 A rows, part 1:
     // its 64 B rows.
@@ -553,8 +553,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
 #pragma unroll
         for (int b = 0; b < 2 * FB; ++b) asm volatile("" : "+a"(acc[a][b]));
     constexpr int PIECE = 32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2);  // of the epilogue, per wave
-    const int w = __builtin_amdgcn_readfirstlane(wave);
-    store_lines<OUT_DT, FB>(P, acc, m0 + (w >> 1) * 128, n0 + (w & 1) * 128, lds + w * PIECE, lane);
+    store_lines<OUT_DT, FB>(P, acc, m0 + (wave_s >> 1) * 128, n0 + (wave_s & 1) * 128, lds + wave_s * PIECE, lane);
 }
 
 // ---------------------------------------------------------------------------------------------

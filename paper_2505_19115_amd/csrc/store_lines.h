@@ -70,6 +70,7 @@ __device__ __forceinline__ void store_lines_form(const TileArgs &P, const ACC (&
 #pragma unroll
         for (int i = 0; i < ROWS / RPS; ++i) {
             unsigned rowl = rowl0 + RPS * i;
+            if (FORM == STORE_WHOLE_PIECES) asm volatile("" : "+v"(rowl));  // (addresses of one store at a time: registers)
             if (FORM == STORE_WHOLE_PIECES) {
                 const unsigned last = P.M - (row0 + ROWS * a) < ROWS ? (unsigned)(P.M - (row0 + ROWS * a)) - 1 : ROWS - 1;
                 rowl = rowl < last ? rowl : last;
