@@ -34,10 +34,10 @@ struct Geom {
 __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
 {
     const half2_t s2 = {s, s};
-    half2_t h0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 0) * s2;
-    half2_t h1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 1) * s2;
-    half2_t h2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 2) * s2;
-    half2_t h3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 3) * s2;
+    half2_t h0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 0), h1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 1);
+    half2_t h2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 2), h3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 256.0f, 3);
+    asm("" : "+v"(h0), "+v"(h1), "+v"(h2), "+v"(h3));  // (in fours, see gemm.hip: 1024 x 1024 x 2048 8.5 / 8.4 us, x 2048 in blocks of 64 9.3 / 8.9)
+    h0 *= s2; h1 *= s2; h2 *= s2; h3 *= s2;
     half8_t r;
     r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
     r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
