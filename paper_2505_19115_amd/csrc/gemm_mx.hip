@@ -373,6 +373,12 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // one MFMA: output rows of A fragment ia against B fragment ib.  The first MFMA operand is the
     // B tile (its rows become accumulator rows), the second the A tile.
     auto mma = [&](const Frags &F, int ia, int ib) { mfma_16x16x128(acc[ia >> 1][FB * (ia & 1) + ib], F.b[ib], F.a[ia], F.sb[ib], F.sa[ia]); };
+    // MFMA j of two quarters -> fragments of A and B inside their halves: there and back, so that one operand of two changes from one MFMA to
+    // the next, also from quarter to quarter
+    auto there_and_back = [](int j) -> int2 {
+        const int row = j >> 2 & 3, i = j & 3;
+        return make_int2(j < 16 ? row : 3 - row, row & 1 ? 3 - i : i);
+    };
     // wait until at most n direct-to-LDS instructions of this wave are still in flight
 #define NVFP4_MXD_WAIT(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory");
     constexpr int PER_TILE = 8 + SLABS + GROUPS;  // direct-to-LDS instructions per wave and K tile
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
-            mma(F, (j >> 2) & 3, 4 * (j < 16 ? Pb : Qb) + (j & 3));
+            mma(F, there_and_back(j).x, 4 * (j < 16 ? Pb : Qb) + there_and_back(j).y);
             __builtin_amdgcn_sched_barrier(0);
             const int q = j & 15, i = q % 3 != 2 && q < 12 ? q / 3 * 2 + q % 3 : -1;  // reads behind MFMAs 0, 1, 3, 4, 6, 7, 9, 10 of a quarter
             if (i >= 0 && j < 16) read_b(ST, sb, F, Qb, i);
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
-            mma(F, 4 + ((j >> 2) & 3), 4 * (j < 16 ? Qb : Pb) + (j & 3));
+            mma(F, 4 + there_and_back(j).x, 4 * (j < 16 ? Qb : Pb) + there_and_back(j).y);
             __builtin_amdgcn_sched_barrier(0);
             const int q = j & 15, i = q % 3 != 2 && q < 12 ? q / 3 * 2 + q % 3 : -1;
             if (i >= 0 && j < 16) read_a(NEXT, sa, F, 0, i);

@@ -327,7 +327,9 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
         __builtin_amdgcn_sched_barrier(0);
         static_for<4 * N>([&](auto xc) __attribute__((always_inline)) {
             constexpr int t = decltype(xc)::value / N, x = decltype(xc)::value % N, a = x >> 3, b = x & 7;
-            mfma_16x16x32(acc[a / IN][a % IN * TB + b], fb[t & 1][b], fa[(t * TA + a) & 1]);
+            // (there and back: from one MFMA to the next one operand of two changes; 8192 x 8192 x 8192 657 -> 651 us, 4096 x 4096 x 11008 220 -> 219)
+            constexpr int col = a & 1 ? 7 - b : b;
+            mfma_16x16x32(acc[a / IN][a % IN * TB + col], fb[t & 1][col], fa[(t * TA + a) & 1]);
             __builtin_amdgcn_sched_barrier(0);
             // the row's vector instructions: 8 for A's next fragment, then its share of B's 64
             constexpr int lo = 64 * a / TA, hi = 64 * (a + 1) / TA, len = 8 + hi - lo;
