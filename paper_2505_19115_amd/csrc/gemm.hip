@@ -580,6 +580,37 @@ static const TileCost *wide_cost(int tile, int64_t K, int sf)
     return tile == TILE_128x256_K2 ? &k2 : tile == TILE_160x256 ? &r160 : tile == TILE_192x256 ? &r192 : tile == TILE_256x256 ? &r256 : nullptr;
 }
 
+// Whole rounds of 256 x 256 tiles and one of smaller ones in the place of the last, where the tiles do not fill that: as many tile columns (or rows) of
+// 256 as the rounds before it hold, and a smaller tile for the rest, of which the CUs take one round (and the places that the first part leaves
+// in its own last one).  Returns the estimated time in nanoseconds, 0 where there is no such division.
+// The chip is bound by power, and idle CUs leave theirs to the others: of the 17 % that a round of 192 rows is shorter, a third comes back in a step (six such
+// products and all else 2573 / 2553 us), and nothing with 16 K tiles (a backward call of two 607 / 611).  From 18 K tiles on.
+// For whole K tiles, and where the rule below would choose 256 x 256, or three rounds or more of 192 x 256 at 4 % more by the estimates (us, without / with:
+// 4096 x 11008 x 4096 272.7 / 261.9, 5000 x 5000 x 4096 168.9 / 161.1, 10587 x 3564 x 4224 275.0 / 254.9, 5004 x 7556 x 3584 236.0 / 220.9, 12020 x 3328 x 5504 in
+// blocks of 64 335.8 / 302.5, 5714 x 6852 x 7296 with f32 outputs 446.4 / 401.4, 2793 x 10068 x 2560 124.2 / 126.0; in place of 192 x 256
+// 9510 x 7272 x 3072 341.4 / 320.8, 7291 x 9712 x 2304 249.9 / 237.5).  Of two rounds of 192 x 256 some are faster and some slower: 2947 x 7552 x 9472 320.8 / 302.2,
+// 2731 x 7460 x 5248 183.6 / 189.0, 5407 x 3836 x 2432 98.9 / 102.2; products that the rule gives 128 x 128 are faster there: 5276 x 3676 x 3328 117.2 / 128.8.
+static double wide_mix(int64_t M, int64_t N, int64_t K, int sf, WideMix *X)
+{
+    if (sf != NVFP4_SCALE_E4M3 || K % KT || K <= 17 * KT) return 0;
+    const int64_t ny = (M + 255) / 256, nx = (N + 255) / 256, steps = K / KT, full = (ny * nx - 1) / 256 * 256;
+    if (full == 0 || ny * nx % 256 == 0 || full > (int64_t)1 << 20) return 0;
+    const TileCost &big = *wide_cost(TILE_256x256, K, sf);
+    double best = 0;
+    for (int tile : {(int)TILE_192x256, (int)TILE_128x256_K2}) {
+        const TileCost &c = *wide_cost(tile, K, sf);
+        const double time = (double)(full / 256) * (big.tile + (double)big.step * (double)steps) + c.fixed + c.tile + (double)c.step * (double)((steps + c.kwaves - 1) / c.kwaves);
+        for (int rows = 0; rows < 2; ++rows) {
+            const int64_t across = rows ? nx : ny, split = full / across;
+            const int64_t second = rows ? (M - split * 256 + c.bm - 1) / c.bm * nx : (M + c.bm - 1) / c.bm * (nx - split);
+            if (split == 0 || second > 256 + full - split * across || (best != 0 && (time > best || (time == best && second >= X->second)))) continue;
+            best = time;
+            *X = {(unsigned)(split * across), (unsigned)second, (int)split, rows, tile};
+        }
+    }
+    return best;
+}
+
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
 {
     const TileCost *const cost = sf == NVFP4_SCALE_E8M0 ? E8M0_COST : E4M3_COST;
@@ -620,6 +651,11 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
             best_time = time;
             best = t;
         }
+    }
+    WideMix X;
+    if (best == TILE_192x256 && ((M + 191) / 192) * ((N + 255) / 256) > 512) {
+        const double mixed = wide_mix(M, N, K, sf, &X);
+        if (mixed != 0 && mixed < 0.96 * best_time) best = TILE_256x256;
     }
     return (GemmTile)best;
 }
@@ -694,6 +730,15 @@ static bool streamed_output(int64_t rows, int64_t row_bytes)
 static bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st)
 {
     if (!wide_contraction(P.K)) return false;
+    WideMix X;
+    if (tile == TILE_256x256 && wide_mix(P.M, P.N, P.K, NVFP4_SCALE_E4M3, &X) != 0) {
+        switch (block) {
+        case 16: launch_gemm_wide_mixed16(P, X, out_dt, st); return true;
+        case 32: launch_gemm_wide_mixed32(P, X, out_dt, st); return true;
+        case 64: launch_gemm_wide_mixed64(P, X, out_dt, st); return true;
+        case 128: launch_gemm_wide_mixed128(P, X, out_dt, st); return true;
+        }
+    }
     switch (block) {
     case 16: return launch_gemm_wide16(P, tile, out_dt, st);
     case 32: return launch_gemm_wide32(P, tile, out_dt, st);

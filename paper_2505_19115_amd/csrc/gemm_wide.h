@@ -67,29 +67,25 @@ struct Geom {
 
 }  // namespace wide
 
+// The tile whose first output is (m0, n0)
 template <int B, int WM, int WN, int KG, int TA, int OUT_DT, bool KTAIL>
-__global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
+__device__ __forceinline__ void wide_tile(const TileArgs &P, uint8_t *const lds, const int64_t m0, const int64_t n0)
 {
     using namespace wide;
     using G = Geom<WM, WN, KG, TA>;
-    constexpr int NW = G::NW, NT = G::NT, BM = G::BM, BN = G::BN, ROWS = G::ROWS, NSR = G::NSR, STAGE = G::STAGE, IN = G::IN, S = G::S;
+    constexpr int NW = G::NW, NT = G::NT, BM = G::BM, ROWS = G::ROWS, NSR = G::NSR, STAGE = G::STAGE, IN = G::IN, S = G::S;
     constexpr int SPT = KT / B;       // scale bytes per row and K tile in global memory
     constexpr int WINDOW = 8 / SPT;   // row-major scales come 8 bytes at a time: those of so many K tiles
     constexpr bool WINDOWS = KTAIL || WINDOW > 1;
     constexpr int NI = ROWS / 16, CI = (NI + NW - 1) / NW;  // direct loads of a K tile, 16 rows each: A's, then B's; per wave
     constexpr bool EVEN = TA * WM % NW == 0 && TB * WN % NW == 0;  // each wave loads as many of A as the others, and of B
     constexpr int CA = TA * WM / NW, CB = TB * WN / NW;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int lane = threadIdx.x & 63;
     const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = KG == 1 ? 0 : wave_wg / NW, wave = wave_wg - group * NW, tid = wave * 64 + lane;  // (inside the group from here on)
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 15, g = lane >> 4;
-    const int ntx = (int)((P.N + BN - 1) / BN), nty = (int)((P.M + BM - 1) / BM);
-    int ty, tx;
-    tile_coords(blockIdx.x, ntx, nty, ty, tx);
-    const int64_t m0 = (int64_t)ty * BM, n0 = (int64_t)tx * BN;
     const int64_t Kb = P.K >> 1, Ks = P.K / B;
     const int nkt = (int)((P.K + KT - 1) / KT);
     const int steps = (nkt + KG - 1) / KG;            // K tiles that every group walks: j KG + group
@@ -397,6 +393,34 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
     }
 }
 
+template <int B, int WM, int WN, int KG, int TA, int OUT_DT, bool KTAIL>
+__global__ __launch_bounds__(256) void gemm_nt_f16_wide_kernel(TileArgs P)
+{
+    using G = wide::Geom<WM, WN, KG, TA>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    int ty, tx;
+    tile_coords(blockIdx.x, (int)((P.N + G::BN - 1) / G::BN), (int)((P.M + G::BM - 1) / G::BM), ty, tx);
+    wide_tile<B, WM, WN, KG, TA, OUT_DT, KTAIL>(P, lds, (int64_t)ty * G::BM, (int64_t)tx * G::BN);
+}
+
+// Whole rounds of 256 x 256 tiles and, in the place of a partly filled last round of them, one of smaller tiles (192 x 256, or 128 x 256 in two groups):
+// X.first workgroups take the first X.split tile rows or columns of the output, those that follow the rest.
+template <int B, int WM, int WN, int KG, int TA, int OUT_DT>
+__global__ __launch_bounds__(256) void gemm_nt_f16_wide_mixed_kernel(TileArgs P, WideMix X)
+{
+    using G = wide::Geom<WM, WN, KG, TA>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    int ty, tx;
+    if (blockIdx.x < X.first) {
+        tile_coords(blockIdx.x, X.rows ? (int)((P.N + 255) / 256) : X.split, X.rows ? X.split : (int)((P.M + 255) / 256), ty, tx);
+        wide_tile<B, 2, 2, 1, 8, OUT_DT, false>(P, lds, (int64_t)ty * 256, (int64_t)tx * 256);
+    } else {
+        const int64_t m1 = X.rows ? (int64_t)X.split * 256 : 0, n1 = X.rows ? 0 : (int64_t)X.split * 256;
+        tile_coords(blockIdx.x - X.first, (int)((P.N - n1 + G::BN - 1) / G::BN), (int)((P.M - m1 + G::BM - 1) / G::BM), ty, tx);
+        wide_tile<B, WM, WN, KG, TA, OUT_DT, false>(P, lds, m1 + (int64_t)ty * G::BM, n1 + (int64_t)tx * G::BN);
+    }
+}
+
 template <int B, int WM, int WN, int KG, int TA, bool KTAIL>
 static void launch_wide(const TileArgs &P, int out_dt, hipStream_t st)
 {
@@ -412,6 +436,30 @@ static void launch_wide(const TileArgs &P, int out_dt, hipStream_t st)
         static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS), true);
         (void)once;
         hipLaunchKernelGGL(k, dim3(ntiles), dim3(256), G::LDS, st, P);
+    }
+}
+
+template <int B, int WM, int WN, int KG, int TA, int OUT_DT>
+static void launch_wide_mixed_as(const TileArgs &P, const WideMix &X, hipStream_t st)
+{
+    using G = wide::Geom<WM, WN, KG, TA>;
+    using G256 = wide::Geom<2, 2, 1, 8>;
+    constexpr int LDS = G::LDS > G256::LDS ? G::LDS : G256::LDS;
+    auto k = gemm_nt_f16_wide_mixed_kernel<B, WM, WN, KG, TA, OUT_DT>;
+    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS), true);
+    (void)once;
+    hipLaunchKernelGGL(k, dim3(X.first + X.second), dim3(256), LDS, st, P, X);
+}
+
+template <int B>
+static void launch_wide_mixed(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st)
+{
+    if (X.tile == TILE_192x256) {
+        if (out_dt == NVFP4_F32) launch_wide_mixed_as<B, 2, 2, 1, 6, NVFP4_F32>(P, X, st);
+        else launch_wide_mixed_as<B, 2, 2, 1, 6, NVFP4_BF16>(P, X, st);
+    } else {
+        if (out_dt == NVFP4_F32) launch_wide_mixed_as<B, 1, 2, 2, 8, NVFP4_F32>(P, X, st);
+        else launch_wide_mixed_as<B, 1, 2, 2, 8, NVFP4_BF16>(P, X, st);
     }
 }
 

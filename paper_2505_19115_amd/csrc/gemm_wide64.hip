@@ -7,4 +7,6 @@ bool launch_gemm_wide64(const TileArgs &P, GemmTile tile, int out_dt, hipStream_
     return P.K % wide::KT ? launch_wide_tile<64, true>(P, tile, out_dt, st) : launch_wide_tile<64, false>(P, tile, out_dt, st);
 }
 
+void launch_gemm_wide_mixed64(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st) { launch_wide_mixed<64>(P, X, out_dt, st); }
+
 }  // namespace nvfp4

@@ -225,6 +225,16 @@ bool launch_gemm_wide16(const TileArgs &P, GemmTile tile, int out_dt, hipStream_
 bool launch_gemm_wide32(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
 bool launch_gemm_wide64(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
 bool launch_gemm_wide128(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);
+// The same with two kinds of tiles in one launch (wide_mix() of gemm.hip): `first` of 256 x 256 over the first `split` tile rows (`rows`) or columns of
+// 256, then `second` of TILE_192x256 or TILE_128x256_K2 over the rest
+struct WideMix {
+    unsigned first, second;
+    int split, rows, tile;
+};
+void launch_gemm_wide_mixed16(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
+void launch_gemm_wide_mixed32(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
+void launch_gemm_wide_mixed64(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
+void launch_gemm_wide_mixed128(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
 hipError_t launch_gemm_mxfp4(const TileArgs &P, GemmTile tile, int out_dt, hipStream_t st);  // block 32, E8M0
 // E4M3 scales at blocks of 64 / 128 as unit-scale FP4 MFMAs per block + binary32 rescale (row-major operands, K % 128 == 0)
 bool fp4_rescale_gemm_applies(int64_t K, int block, const GemmArgs &P);
