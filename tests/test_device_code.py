@@ -198,3 +198,48 @@ def test_arguments_of_the_products(tmp_path):
         notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", code_object(source, tmp_path)], capture_output=True, text=True, check=True).stdout
         sizes = [int(n) for n in re.findall(r"\.kernarg_segment_size:\s+(\d+)", notes)]
         assert sizes and max(sizes) <= most, source
+
+
+def late_operands(asm):
+    """(number of matrix instructions on accumulators of the AGPRs, the kernels of those of which a vector instruction wrote an operand less than
+    two wait states before)."""
+    kernel, before, found, late = "", [], 0, []
+    span = lambda t: (lambda m: set(range(int(m.group(1)), int(m.group(2) or m.group(1)) + 1)) if m else set())(re.fullmatch(r"v\[?(\d+)(?::(\d+)\])?", t.strip()))
+    for line in asm.splitlines():
+        head = re.match(r"^[0-9a-f]+ <(.*)>:", line)
+        if head:
+            kernel, before = head.group(1), []
+            continue
+        ins = line.split("//")[0].strip()
+        if not ins:
+            continue
+        if ins.startswith("v_mfma") and " a[" in ins:
+            found += 1
+            operands = set().union(*(span(t) for t in re.findall(r"v\[\d+:\d+\]|\bv\d+\b", ins.split(" ", 1)[1])))
+            states = 0
+            for prev in reversed(before):
+                if states >= 2:
+                    break
+                if prev.startswith("v_") and not prev.startswith("v_mfma") and span(prev.split(" ", 1)[1].split(",")[0]) & operands:
+                    late.append(kernel)
+                    break
+                states += int(prev.split()[1]) + 1 if prev.startswith("s_nop") else 1
+        before = before[-3:] + [ins]
+    return found, late
+
+
+def test_late_operands_are_found():
+    text = "0000 <k>:\n v_pk_mul_f16 v7, v3, v2\n{} v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], a[0:3]\n"
+    assert late_operands(text.format(" s_add_u32 s0, s0, s1\n")) == (1, ["k"]) and late_operands(text.format(" s_nop 1\n")) == (1, [])
+
+
+# The matrix instructions of the kernels with one wave per SIMD are inline assembly, so the compiler does not keep their operands' wait states, nor those of
+# the direct loads' addresses.  512 registers, none spilled; outputs in whole pieces, as above.
+@pytest.mark.parametrize("source", ["gemm_wide16", "gemm_wide32", "gemm_wide64", "gemm_wide128", "gemm_mx"])
+def test_products_of_one_wave_per_simd(source, tmp_path):
+    asm = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", code_object(source, tmp_path)], capture_output=True, text=True, check=True).stdout
+    loads, unwaited = unwaited_loads(asm)
+    found, late = late_operands(asm)
+    assert loads > 0 and not unwaited and found > 0 and not late and asm.count("global_store_dwordx3") == 0
+    for args, v, s in kernels(registers(source, tmp_path), "wide" if source != "gemm_mx" else "gemm_nt_mxfp4_dma_kernel"):
+        assert v <= 512 and s == 0, (args, v, s)
