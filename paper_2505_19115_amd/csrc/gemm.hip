@@ -10,8 +10,8 @@
 //     v_cvt_scalef32_pk_f16_fp4 (code pair -> fp16 pair, times 2^8)  and
 //     v_pk_mul_f16 by the block scale written as fp16(scale * 2^-8),
 // which is exact for every E4M3 byte, including its subnormals; the MFMA operands themselves
-// are always normal fp16 numbers or zero.  The contraction runs on v_mfma_f32_32x32x16_f16 with
-// fp32 accumulation; the tensor scales multiply once in the epilogue.
+// are always normal fp16 numbers or zero.  The contraction runs on v_mfma_f32_32x32x16_f16 (contractions of more than seven K tiles
+// on large tiles: v_mfma_f32_16x16x32_f16, gemm_wide.h) with fp32 accumulation; the tensor scales multiply once in the epilogue.
 //
 // Operand storage: row-major ([rows, K/2] codes, [rows, K/B] scale bytes), or, for blocks of 16, the slab layout of
 // kernels.h, in which the 256 rows x 64 code bytes (and 256 x 8 scale bytes) of a K tile are one contiguous piece.  Only
@@ -57,7 +57,7 @@ __device__ __forceinline__ half8_t dequant8(uint32_t w, _Float16 s)
 }
 
 // Tile geometry.  A workgroup is KG groups of WM x WN waves; a wave owns (32 TA) x (32 TB) outputs as
-// TA x TB MFMA tiles.  The production shape is 2 x 4 waves of 4 x 2 tiles: 256 x 256 per
+// TA x TB MFMA tiles.  The largest shape is 2 x 4 waves of 4 x 2 tiles: 256 x 256 per
 // workgroup, 128 accumulator registers per wave, so TWO waves fit on every SIMD.  That is
 // the point of the shape: measured on gfx950, one wave alone issues a VALU instruction only
 // every ~8 cycles, two waves per SIMD reach the full rate of one per 4 cycles, and the
@@ -543,7 +543,8 @@ static bool wide_contraction(int64_t K) { return K > 7 * KT; }
 //     8192 x  8192 x   256           287.3     130.6     138.0      46.6     125.8      52.3      49.9      47.6
 //     4096 x 11008 x   512           221.9      93.5      97.7      50.5      89.6      57.3      53.8      50.3
 // (128 x 256 with two groups, one round of it only: 2048 x 4096 x 4096 55.1, x 11008 138.4;
-// 160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.)
+// 160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.  All with eight waves; what four waves of 128 columns take
+// stands at wide_cost().)
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
