@@ -322,7 +322,7 @@ def main() -> int:
     # the step (in_step_gemms); achieved = the step's GEMM FLOPs / their summed durations, i.e. the average launch.
     step_gemm_ms = in_step["gemm_ms_per_step"]
     step_gemm_tflops = flop_per_step / (step_gemm_ms * 1e-3) / 1e12
-    roofline = {"kernel": "gemm_nt_f16_kernel: the 9 GEMM launches of the step (4 x 4096x11008x4096, 3 x 4096x4096x11008, 2 x 11008x4096x4096)",
+    roofline = {"kernel": "gemm_nt_f16_wide_kernel, gemm_nt_f16_wide_mixed_kernel: the 9 GEMM launches of the step (4 x 4096x11008x4096, 3 x 4096x4096x11008, 2 x 11008x4096x4096)",
                 "bound": "mfma", "achieved": round(step_gemm_tflops, 2), "peak": PEAK_F16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(step_gemm_tflops / PEAK_F16_TFLOPS, 4),
                 "frac_of_fp4_peak": round(step_gemm_tflops / PEAK_FP4_TFLOPS, 4),
