@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "mx_codes.h"
 #include "nvfp4_math.h"
 #include "store_lines.h"
 
@@ -265,17 +266,13 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // at byte 16 i (row i / 4, slot i % 4), so the swizzle is applied by choosing WHICH global chunk
     // the lane fetches.  Rows past the edge are clamped to the last row (their products land in
     // outputs that are never stored).  Lane offsets are relative to the tile's first row, the
-    // 64-bit part of the address is wave-uniform.  A wave's four instructions fetch 64 rows; of a slab, which holds all 256 rows, they
-    // lie 128 bytes apart (slab_row(16 u + j) = 2 u + slab_row(j), 64 bytes a position), a constant of the instruction.
+    // 64-bit part of the address is wave-uniform (mx_codes.h).
     const int64_t mrows = P.M - m0 < BM ? P.M - m0 : BM, nrows = P.N - n0 < BN ? P.N - n0 : BN;
-    uint32_t offA[A_SLAB ? 1 : 4], offB[B_SLAB ? 1 : 4];
+    MxCodes<A_SLAB> A;
+    MxCodes<B_SLAB> B;
     const int c = (lane & 3) ^ quad_xor(lane >> 4);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int row = (wave * 4 + u) * 16 + (lane >> 2);
-        if (!A_SLAB || u == 0) offA[A_SLAB ? 0 : u] = A_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < mrows ? row : mrows - 1) * Kb + c * 16);
-        if (!B_SLAB || u == 0) offB[B_SLAB ? 0 : u] = B_SLAB ? (uint32_t)(slab_row(row) * 64 + c * 16) : (uint32_t)((row < nrows ? row : nrows - 1) * Kb + c * 16);
-    }
+    A.lane_offsets(wave, lane, c, mrows, Kb);
+    B.lane_offsets(wave, lane, c, nrows, Kb);
     const int srow = wave * 64 + lane;
     const uint32_t offSA = (uint32_t)((srow < mrows ? srow : mrows - 1) * Ks);
     const uint32_t offSB = (uint32_t)((srow < nrows ? srow : nrows - 1) * Ks);
@@ -293,23 +290,21 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)lds;
 #define NVFP4_MXD_DST(base, more) asm volatile("s_add_u32 m0, %0, %1" : : "s"(base), "n"(more) : "scc", "m0");
 #define NVFP4_MXD_LOAD(voff, base, more) asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(voff), "s"(base), "n"(more) : "memory");
-    // part u of four of an operand's codes (codes of K tile kt: tile + kt * step; row-major: 64 bytes further along every row; slabs: the
-    // next 16 KB slab) into stage st.  The constant of a slab's load counts for both of its addresses.
-#define NVFP4_MXD_DST_A(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + (u) * (A_SLAB ? 1024 - 128 : 1024))
-#define NVFP4_MXD_DST_B(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + BM * ROWB + (u) * (B_SLAB ? 1024 - 128 : 1024))
-#define NVFP4_MXD_LOAD_A(u, p) NVFP4_MXD_LOAD(offA[A_SLAB ? 0 : (u)], p, A_SLAB ? 128 * (u) : 0)
-#define NVFP4_MXD_LOAD_B(u, p) NVFP4_MXD_LOAD(offB[B_SLAB ? 0 : (u)], p, B_SLAB ? 128 * (u) : 0)
+    // part u of four of an operand's codes into stage st.  The constant of a slab's load counts for both of its addresses.
+#define NVFP4_MXD_DST_A(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + (u) * (1024 - A.more(1)))
+#define NVFP4_MXD_DST_B(st, u) NVFP4_MXD_DST(code_dst, (st) * STAGE + BM * ROWB + (u) * (1024 - B.more(1)))
+#define NVFP4_MXD_LOAD_A(u) NVFP4_MXD_LOAD(A.off[A_SLAB ? 0 : (u)], A.p, A.more(u))
+#define NVFP4_MXD_LOAD_B(u) NVFP4_MXD_LOAD(B.off[B_SLAB ? 0 : (u)], B.p, B.more(u))
     const uint32_t code_dst = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
-    const uint8_t *tileA = uniform_ptr(A_SLAB ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb);
-    const uint8_t *tileB = uniform_ptr(B_SLAB ? P.B_codes + (int64_t)tx * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb);
-    uint32_t stepA = A_SLAB ? SLAB_CODE_BYTES : ROWB, stepB = B_SLAB ? SLAB_CODE_BYTES : ROWB;
+    A.start(uniform_ptr(A_SLAB ? P.A_codes + (int64_t)ty * nkt * SLAB_CODE_BYTES : P.A_codes + m0 * Kb));  // (A.p: K tile kt + 4 in the loop)
+    B.start(uniform_ptr(B_SLAB ? P.B_codes + (int64_t)tx * nkt * SLAB_CODE_BYTES : P.B_codes + n0 * Kb));  // (B.p: kt + 3)
     // Scale slabs (one per K tile): wave 0 fetches A's, wave 1 B's, 16 bytes per lane, into stage kt % 4 of that operand's part of the first
     // scale buffer; the other waves (and a wave whose operand is row-major) issue a one-request filler (the first bytes of A's codes: a
     // valid address in both layouts), so that every wave has the same number of loads per tile, which the counted waits rely on.
     constexpr bool SLABS = A_SLAB || B_SLAB, GROUPS = !A_SLAB || !B_SLAB;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const bool slab_loader = (wave_s == 0 && A_SLAB) || (wave_s == 1 && B_SLAB);
-    const uint8_t *slab_ptr = uniform_ptr(!slab_loader ? tileA
+    const uint8_t *slab_ptr = uniform_ptr(!slab_loader ? A.tile
                                           : wave_s == 0   ? P.A_scales + (int64_t)ty * nkt * SLAB_MX_SCALE_BYTES
                                                        : P.B_scales + (int64_t)tx * nkt * SLAB_MX_SCALE_BYTES);
     uint32_t slab_step = __builtin_amdgcn_readfirstlane(slab_loader ? (uint32_t)SLAB_MX_SCALE_BYTES : 0u);
@@ -327,7 +322,7 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     };
     // (the compiler selects the address in vector registers and reads the lane back; the load has to come five wait states after that)
     auto group_load = [&](int G, int part, bool real) {
-        const uint8_t *const base = uniform_ptr(real ? (part ? rowsSB : rowsSA) + group_start(G) : tileA);
+        const uint8_t *const base = uniform_ptr(real ? (part ? rowsSB : rowsSA) + group_start(G) : A.tile);
         const uint32_t off = real ? (part ? offSB : offSA) : 0u;
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base) : "memory");
     };
@@ -389,7 +384,6 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
 #pragma unroll
         for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(F.sa[i]), "+v"(F.sb[4 * decltype(half)::value + i]));
     };
-    const uint8_t *pa = tileA, *pb = tileB;  // of A's K tile kt + 4 and B's kt + 3, from here on
     // K tiles 0 to 2 and A's part of tile 3; scale group 0 rides with tile 0
     if (GROUPS) {
         group_dst(0, 0, !A_SLAB);
@@ -403,16 +397,16 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
         for (int u = 0; u < 4; ++u) {
             NVFP4_MXD_DST_A(S, u)
             asm volatile("s_nop 4");
-            NVFP4_MXD_LOAD_A(u, pa)
+            NVFP4_MXD_LOAD_A(u)
             if (S < 3) {
                 NVFP4_MXD_DST_B(S, u)
                 asm volatile("s_nop 4");
-                NVFP4_MXD_LOAD_B(u, pb)
+                NVFP4_MXD_LOAD_B(u)
             }
         }
-        pa += stepA;
+        A.advance();
         if (S < 3) {
-            pb += stepB;
+            B.advance();
             if (SLABS) {
                 NVFP4_MXD_DST(slab_dst, S * 1024)
                 asm volatile("s_nop 4");
@@ -452,24 +446,20 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     // (scheduling fences pin that order).  4096 x 4096 x 16384: 195 instructions a K tile 125.2 us, 135 111.3;
     // 4096 x 11008 x 4096 100.0 and 88.0.
     // Every tile runs the same code: past the end the loads become one-request fillers (lane
-    // offsets zero, landing in the free stage) that keep the counted wait exact, and
+    // offsets zero, the codes' from their own operand's first tile, landing in the free stage) that keep the counted wait exact, and
     // the barrier / reads of the tile after the last one are harmless.
     int kt = 0;
     auto tile = [&](auto stage) {
         constexpr int ST = decltype(stage)::value, BEFORE = (ST + 3) & 3, NEXT = (ST + 1) & 3, Pb = ST & 1, Qb = Pb ^ 1;
         if (kt + 4 >= nkt) {
             asm volatile("");
-#pragma unroll
-            for (int u = 0; u < (A_SLAB ? 1 : 4); ++u) offA[u] = 0;
-            pa = tileA;
-            stepA = 0;
+            A.past_end();
             if (kt + 3 >= nkt) {
                 asm volatile("");
-#pragma unroll
-                for (int u = 0; u < (B_SLAB ? 1 : 4); ++u) offB[u] = 0;
+                B.past_end();
                 slab_voff = 0;
-                pb = slab_ptr = tileA;
-                stepB = slab_step = 0;
+                slab_ptr = A.tile;
+                slab_step = 0;
             }
         }
         const uint8_t *sa = baseSA + tile_off(A_SLAB, kt, ST), *sb = baseSB + tile_off(B_SLAB, kt, ST);
@@ -485,18 +475,18 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
             if (i >= 0 && j >= 16) read_a(ST, sa, F, 1, i);
             // the loads' two parts behind the others: B's codes, a scale slab, a scale group
             if (j == 2) NVFP4_MXD_DST_B(BEFORE, 0)
-            if (j == 5) NVFP4_MXD_LOAD_B(0, pb)
+            if (j == 5) NVFP4_MXD_LOAD_B(0)
             if (j == 8) NVFP4_MXD_DST_B(BEFORE, 1)
-            if (j == 11) NVFP4_MXD_LOAD_B(1, pb)
+            if (j == 11) NVFP4_MXD_LOAD_B(1)
             if (j == 12) NVFP4_MXD_DST_B(BEFORE, 2)
-            if (j == 13) NVFP4_MXD_LOAD_B(2, pb)
+            if (j == 13) NVFP4_MXD_LOAD_B(2)
             if (j == 14) NVFP4_MXD_DST_B(BEFORE, 3)
-            if (j == 15) NVFP4_MXD_LOAD_B(3, pb)
+            if (j == 15) NVFP4_MXD_LOAD_B(3)
             if (SLABS && j == 18) NVFP4_MXD_DST(slab_dst, BEFORE * 1024)
             if (SLABS && j == 21) NVFP4_MXD_LOAD(slab_voff, slab_ptr, 0)
             if (GROUPS && j == 24) group_dst(Gn, part, real);
             if (GROUPS && j == 27) group_load(Gn, part, real);
-            if (j == 28) pb += stepB;
+            if (j == 28) B.advance();
             if (SLABS && j == 29) slab_ptr += slab_step;
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -513,14 +503,14 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
             if (i >= 0 && j < 16) read_a(NEXT, sa, F, 0, i);
             if (i >= 0 && j >= 16) read_b(NEXT, sb, F, Qb, i);
             if (j == 2) NVFP4_MXD_DST_A(ST, 0)
-            if (j == 5) NVFP4_MXD_LOAD_A(0, pa)
+            if (j == 5) NVFP4_MXD_LOAD_A(0)
             if (j == 8) NVFP4_MXD_DST_A(ST, 1)
-            if (j == 11) NVFP4_MXD_LOAD_A(1, pa)
+            if (j == 11) NVFP4_MXD_LOAD_A(1)
             if (j == 18) NVFP4_MXD_DST_A(ST, 2)
-            if (j == 21) NVFP4_MXD_LOAD_A(2, pa)
+            if (j == 21) NVFP4_MXD_LOAD_A(2)
             if (j == 24) NVFP4_MXD_DST_A(ST, 3)
-            if (j == 27) NVFP4_MXD_LOAD_A(3, pa)
-            if (j == 28) pa += stepA;
+            if (j == 27) NVFP4_MXD_LOAD_A(3)
+            if (j == 28) A.advance();
             __builtin_amdgcn_sched_barrier(0);
         }
         keep_scales(F, std::integral_constant<int, Qb>{});
