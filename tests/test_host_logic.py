@@ -428,3 +428,28 @@ def test_no_tile_beyond_the_launch_limit():
                     seen.add(t)
                     assert -(-M // t[0]) * -(-N // t[1]) * threads[t] < 1 << 32, (M, N, K, t)
     assert {(96, 128, 4), (128, 128, 4), (128, 128, 1), (256, 256, 1)} <= seen
+
+
+def test_formats_keep_nothing_of_a_call():
+    # what c() returns is the caller's to change; a format's own fields are all that it holds, copied, pickled and unpacked as such
+    import copy
+    import pickle
+    for fmt in (nv.NVFP4, nv.MXFP4, nv.Format(64, nv.SCALE_E4M3, 1)):
+        fields = dict(block=fmt.block, scale=fmt.scale, tensor_scale=fmt.tensor_scale)
+        c = fmt.c()
+        c.block, c.scale, c.tensor_scale = 7, 8, 9
+        again = fmt.c()
+        assert (again.block, again.scale, again.tensor_scale) == tuple(fields.values())
+        assert vars(fmt) == fields and nv.Format(**vars(fmt)) == fmt and copy.deepcopy(fmt) == pickle.loads(pickle.dumps(fmt)) == fmt
+    with pytest.raises(TypeError):
+        nv.Format(16.0, nv.SCALE_E4M3, 1).c()
+
+
+def test_known_sizes():
+    # by value, of both calls and all formats, and not without bound
+    for M in range(32, 32 * 1200, 32):
+        for name in ("nvfp4_linear_fwd_workspace_bytes", "nvfp4_linear_bwd_workspace_bytes"):
+            f = (nv.NVFP4 if M % 64 else nv.MXFP4).c()
+            assert nv._workspace_bytes(name, M, 64, 96, f) == getattr(nv.lib, name)(M, 64, 96, C.byref(f))
+    assert len(nv._known_sizes) <= 1000
+    assert nv._workspace_bytes("nvfp4_linear_fwd_workspace_bytes", 64, 96, 128, nv.Format(7, 8, 9).c()) == 0  # (a format that the library refuses)
