@@ -232,11 +232,11 @@ class _Block:
     __slots__ = ("ptr", "tensor")
 
     def __init__(self, nbytes: int, like: torch.Tensor, stream: int):
+        self.tensor, self.ptr = None, 0  # (either of the two ways may raise, and __del__ then finds a block that holds nothing)
         if _raw_delete is None or _raw_alloc is None or _raw_device is None or nbytes <= 0 or like.get_device() != _raw_device():
             self.tensor = torch.empty(nbytes, dtype=torch.uint8, device=like.device)
             self.ptr = self.tensor.data_ptr()
         else:
-            self.tensor, self.ptr = None, 0
             self.ptr = _raw_alloc(nbytes, stream)
 
     def __del__(self):

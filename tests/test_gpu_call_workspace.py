@@ -67,3 +67,14 @@ def test_blocks_in_a_graph():
         want = calls(X, W, dY, nv.NVFP4)
         torch.cuda.synchronize()
         assert torch.equal(Y, want[0]) and torch.equal(dX, want[1]) and torch.equal(dW, want[2]), i
+
+
+@pytest.mark.parametrize("lacking", ["_raw_alloc", "_raw_delete", "_raw_device"])
+def test_tensors_where_torch_has_no_raw_entry(lacking, monkeypatch):
+    X, W, dY = tensors(64, 96, 128)
+    print(f"[case] tensors for a call, without {lacking}", flush=True)
+    want = calls(X, W, dY, nv.NVFP4, torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+    monkeypatch.setattr(nv, lacking, None)
+    got = calls(X, W, dY, nv.NVFP4)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))

@@ -453,3 +453,27 @@ def test_known_sizes():
             assert nv._workspace_bytes(name, M, 64, 96, f) == getattr(nv.lib, name)(M, 64, 96, C.byref(f))
     assert len(nv._known_sizes) <= 1000
     assert nv._workspace_bytes("nvfp4_linear_fwd_workspace_bytes", 64, 96, 128, nv.Format(7, 8, 9).c()) == 0  # (a format that the library refuses)
+
+
+@pytest.mark.parametrize("lacking", [None, "_raw_alloc", "_raw_delete", "_raw_device"])
+def test_a_block_that_could_not_be_had(lacking, monkeypatch):
+    # out of memory, with and without torch's raw entries: the caller gets that error, and nothing else is reported about the half-made block
+    import gc
+    import sys
+
+    def no_memory(*a, **k):
+        raise MemoryError("no memory")
+
+    like = type("Tensor", (), {"get_device": lambda self: 0, "device": "cpu"})()
+    unraisable, freed = [], []
+    monkeypatch.setattr(sys, "unraisablehook", lambda u: unraisable.append(u.exc_value))
+    monkeypatch.setattr(nv, "_raw_device", lambda: 0)
+    monkeypatch.setattr(nv, "_raw_alloc", no_memory)
+    monkeypatch.setattr(nv, "_raw_delete", freed.append)
+    monkeypatch.setattr(nv.torch, "empty", no_memory)
+    if lacking:
+        monkeypatch.setattr(nv, lacking, None)
+    with pytest.raises(MemoryError):
+        nv._Block(64, like, 0)
+    gc.collect()
+    assert not unraisable and not freed
