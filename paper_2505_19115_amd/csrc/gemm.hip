@@ -396,12 +396,6 @@ __device__ __forceinline__ void f16_tile(const TileArgs &P, const int wrow)
     uint8_t *const mine = lds + wave_wg * (32 * 32 * TB * (OUT_DT == NVFP4_F32 ? 4 : 2));
     if constexpr (KG == 1) {
         store_lines<OUT_DT, TB>(P, acc, row0, col0, mine, lane);
-    } else if constexpr (KG == 2) {
-        // each group keeps one half of the tile rows
-        static_assert(TA % 2 == 0, "halves");
-        float16_t half[TA / 2][TB];
-        fold_groups<TA, TB, NW>(acc, half, lds, group, wave, lane);
-        store_lines<OUT_DT, TB>(P, half, row0 + group * (16 * TA), col0, mine, lane);
     } else {
         // the groups' sums over their own K tiles: two groups at a time, each keeping one half of the tile rows
         constexpr int LO = (TA + 1) / 2, HI = TA - LO;
@@ -499,9 +493,6 @@ static void launch_f16_tile(const TileArgs &P, GemmTile tile, int out_dt, hipStr
     } else if (tile == TILE_160x256) {
         if (ktail) launch_f16_uneven<B, true>(P, out_dt, st);
         else launch_f16_uneven<B, false>(P, out_dt, st);
-    } else if (tile == TILE_128x256_K2) {
-        if (ktail) launch_f16<B, 1, 4, 4, 2, 2, true>(P, out_dt, st);
-        else launch_f16<B, 1, 4, 4, 2, 2, false>(P, out_dt, st);
     } else if (tile == TILE_128x256) {
         if (ktail) launch_f16<B, 2, 4, 2, 2, 1, true>(P, out_dt, st);
         else launch_f16<B, 2, 4, 2, 2, 1, false>(P, out_dt, st);
@@ -636,14 +627,15 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         // 3307 x 2944 x 128 6.9 / 9.0 and 10.3 / 12.0, 1352 x 7168 x 96 7.2 / 7.9 and 10.9 / 12.1); of two they would be faster (777 x 12288 x 256 10.5 / 9.4 and 14.6 /
         // 12.9, 2505 x 3212 x 256 12.6 / 12.0 and 16.1 / 14.1, 1079 x 9184 x 160 11.9 / 11.3 and 14.4 / 13.9), and have not been moved to it so far.
         if (t == TILE_160x256 && (K <= 256 || tiles > 256 || (M + 159) / 160 * 160 >= (M + 191) / 192 * 192)) continue;
-        // 128 x 256 with two groups of waves: four waves of 128 x 64 on every other K tile need 6 vector instructions a MFMA where eight
-        // of 64 x 64 need 8, and a fold at the end, which 12 K tiles pay for.  One round of them, on most of the CUs.  us, one group / two:
-        // 2048 x 4096 x 4096 59.5 / 55.1, f32 outputs 65.5 / 61.5, blocks of 64 64.6 / 58.0, 2048 x 4096 x 11008 155.5 / 138.4, 1700 x 4600 x 8192 121.8 /
-        // 112.6, 2688 x 2048 x 4096 51.1 / 47.7, 2048 x 4096 x 1536 27.8 / 27.6, x 1024 20.7 / 20.8 (the first of each without streamed outputs, worth up to 1).
+        // 128 x 256 with two groups of two waves of 128 x 128 each, every other K tile (gemm_wide.h, which has it for contractions of more than seven
+        // K tiles): 2 vector instructions a MFMA of 16 cycles, where eight waves of 64 x 64 need 8 a MFMA of 32, but one wave per SIMD and a fold at the
+        // end, which 12 K tiles pay for.  One round of them, on most of the CUs.  us, one group / two: 2048 x 4096 x 4096 66.6 / 59.1, f32 outputs 65.3 /
+        // 57.3, blocks of 64 60.7 / 54.6, 2048 x 4096 x 11008 162.0 / 131.5, 1700 x 4600 x 8192 120.6 / 101.3, 2688 x 2048 x 4096 52.1 / 48.9, 2048 x
+        // 4096 x 1536 24.8 / 24.3, x 1280 21.3 / 21.4, x 1024 17.6 / 18.8.
         // Of up to 160 workgroups the estimate would give it some contractions of 1700 to 3300; most would be faster and some slower, and they have
-        // not been moved to it so far: 908 x 4996 x 3296 52.8 / 43.4, 1664 x 2512 x 2784 43.4 / 37.5, 1302 x 3388 x 2656 38.2 / 37.9, 1966 x 2337 x
-        // 2752 45.3 / 46.6.
-        if (t == TILE_128x256_K2 && (tiles <= 160 || tiles > 256)) continue;
+        // not been moved to it so far (the choice / two groups): 908 x 4996 x 3296 55.1 / 47.9, 1664 x 2512 x 2784 43.5 / 39.6, 1302 x 3388 x 2656 36.3 / 38.7,
+        // 1966 x 2337 x 2752 43.6 / 42.4.
+        if (t == TILE_128x256_K2 && (!wide_contraction(K) || tiles <= 160 || tiles > 256)) continue;
         const int64_t rounds = (tiles + 255) / 256, steps = (nkt + c.kwaves - 1) / c.kwaves;
         double time = (double)rounds * ((double)c.tile + (double)c.step * (double)steps);
         if (rounds == 1) time *= 1.0 + 0.01 * c.alone;

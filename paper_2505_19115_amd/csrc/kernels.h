@@ -207,7 +207,7 @@ hipError_t launch_small_backward(SmallBackward S, int dt, int block, int sf, int
 bool gemm_pairs(const GemmArgs &P0, const GemmArgs &P1, int sf);
 hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, int sf, int out_dt, hipStream_t st);
 // Workgroup tiles (rows x columns of the output) of the GEMM kernels: up to 64 x 64 in gemm_ksplit.hip (the waves of a
-// workgroup divide the contraction), the larger ones in gemm.hip (E4M3 scales; K2, K4: two or four groups of waves divide the contraction) and
+// workgroup divide the contraction), the larger ones in gemm.hip and gemm_wide.h (E4M3 scales; K2, K4: two or four groups of waves divide the contraction) and
 // gemm_mx.hip (E8M0).
 enum GemmTile { TILE_32x32, TILE_32x64, TILE_64x32, TILE_64x64, TILE_96x128_K4, TILE_128x128, TILE_128x128_K4, TILE_128x256, TILE_128x256_K2, TILE_160x256, TILE_192x256, TILE_256x128, TILE_256x256, TILES };
 GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf);

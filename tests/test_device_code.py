@@ -148,12 +148,14 @@ def test_registers_of_small_tensors_and_four_groups(tmp_path):
     assert len(four) == 4 * 2 * 2 * 2  # (blocks, tiles, output types, K tail)
     for (block, wm, wn, ta, tb, groups, out, tail), v, s in four:
         assert v <= 256 and s == 0, (block, ta, out, tail, v, s)
-    # two groups of four waves, and eight waves of 96 and 64 rows: two per SIMD as well
-    two = [(args, v, s) for args, v, s in kernels(registers("gemm", tmp_path), "gemm_nt_f16_kernel") if args[5] == 2]
+    # eight waves of 96 and 64 rows: two per SIMD as well
     uneven = list(kernels(registers("gemm", tmp_path), "gemm_nt_f16_uneven_kernel"))
-    assert len(two) == 4 * 2 * 2 and len(uneven) == 4 * 2 * 2  # (blocks, output types, K tail)
-    for args, v, s in two + uneven:
+    assert len(uneven) == 4 * 2 * 2  # (blocks, output types, K tail)
+    for args, v, s in uneven:
         assert v <= 256 and s == 0, (args, v, s)
+    # (128 x 256 in two groups is a tile of the kernels of four waves alone: test_products_of_one_wave_per_simd)
+    assert not [args for args, v, s in kernels(registers("gemm", tmp_path), "gemm_nt_f16_kernel") if args[5] == 2]
+    assert [args for args, v, s in kernels(registers("gemm_wide16", tmp_path), "gemm_nt_f16_wide_kernel") if args[3] == 2]
 
 
 def test_rows_of_small_tensors_bring_little_along(tmp_path):

@@ -477,3 +477,13 @@ def test_a_block_that_could_not_be_had(lacking, monkeypatch):
         nv._Block(64, like, 0)
     gc.collect()
     assert not unraisable and not freed
+
+
+def test_two_group_tiles_are_of_long_contractions():
+    # 128 x 256 in two groups has a kernel for contractions of more than seven K tiles only, and the rule names it for those only
+    for K in range(32, 7 * 128 + 1, 32):
+        for M in list(range(128, 8193, 384)) + [2048]:
+            for N in list(range(256, 12289, 768)) + [4096]:
+                assert nv.gemm_split(M, N, K) == 1 or nv.gemm_tile(M, N, K) != (128, 256), (M, N, K)
+    for M, N, K in ((2048, 4096, 1536), (2048, 4096, 4096), (8204, 580, 1472)):
+        assert nv.gemm_tile(M, N, K) == (128, 256) and nv.gemm_split(M, N, K) == 2
