@@ -512,6 +512,8 @@ static void launch_f16_tile(const TileArgs &P, GemmTile tile, int out_dt, hipStr
 // end (bf16 outputs, us, the kernels above / those: 2384 x 4096 x 288 11.6 / 12.7, x 512 13.2 / 14.0, x 768 17.0 / 17.4, 777 x 12288 x 512 13.2 / 14.0,
 // x 1024 21.3 / 21.2, 320 x 32768 x 512 13.7 / 14.3, x 1024 22.4 / 21.7, 2505 x 3212 x 256 12.7 / 17.7, 3072 x 8192 x 512 29.8 / 31.0, x 1024 50.3 / 48.3,
 // 4096 x 11008 x 512 54.3 / 54.5, x 1024 85.7 / 81.4).
+// They fetch the scales of a row eight bytes at a time, so a row has to have as many; of more than seven K tiles it has (blocks of 128: K is a multiple
+// of 128 too).
 static bool wide_contraction(int64_t K) { return K > 7 * KT; }
 
 // Which workgroup tile computes an M x N x K product: the one whose estimated time is least.  With R = the tiles of the
@@ -722,7 +724,7 @@ static bool streamed_output(int64_t rows, int64_t row_bytes)
 // (false: not one of the tiles of gemm_wide.h, or a short contraction)
 static bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int out_dt, hipStream_t st)
 {
-    if (!wide_contraction(P.K)) return false;
+    if (!wide_contraction(P.K) || P.K / block < 8) return false;
     WideMix X;
     if (tile == TILE_256x256 && wide_mix(P.M, P.N, P.K, NVFP4_SCALE_E4M3, &X) != 0) {
         switch (block) {

@@ -183,18 +183,14 @@ __device__ __forceinline__ void wide_tile(const TileArgs &P, uint8_t *const lds,
             srow_step[u] = (int)SLAB_SCALE_BYTES;
         }
     }
-    // first byte of the window that K tile kt lies in: the last one ends with the row, also if that is shorter
+    // first byte of the window that K tile kt lies in: the last one ends with the row, which has eight bytes or more (launch_gemm_wide())
     auto window = [&](int kt) { return kt / WINDOW * 8 + 8 < (int)Ks ? kt / WINDOW * 8 : (int)Ks - 8; };
     auto load_scales = [&](int j, int u) {
         const int kt = j * KG + group < nkt ? j * KG + group : nkt - 1;
         if constexpr (!WINDOWS) {
             gs[u] = *reinterpret_cast<const uint64_t *>(srow_ptr[u] + (int64_t)kt * srow_step[u]);
-        } else if (Ks >= 8) {
-            // (the groups' K tiles lie KG apart: a window each)
-            if (WINDOW == 1 || KG > 1 || j == 0 || kt % WINDOW == 0) __builtin_memcpy(&gs[u], srow_ptr[u] + window(kt), 8);
-        } else if (j == 0) {
-            gs[u] = 0;
-            for (int t = 0; t < (int)Ks; ++t) gs[u] = gs[u] >> 8 | (uint64_t)srow_ptr[u][t] << 56;
+        } else if (WINDOW == 1 || KG > 1 || j == 0 || kt % WINDOW == 0) {  // (the groups' K tiles lie KG apart: a window each)
+            __builtin_memcpy(&gs[u], srow_ptr[u] + window(kt), 8);
         }
     };
     // LDS: 1 KB for four fragments of a wave, [4 chunks][16 rows][4 fragments] dwords, so that a lane reads the scales of all four (of its chunk and
