@@ -452,10 +452,14 @@ uint32_t nvfp4_host_sr_bits(uint64_t seed, uint64_t element_index);
 uint8_t nvfp4_host_e8m0_encode(float a);            /* a > 0 -> shared-exponent byte */
 /* The workgroup tile that the size rule of nvfp4_gemm gives an M x N x K product of this format (of f, the scale type
  * matters): rows * 65536 + columns of the output; 0 for sizes below 1 or a bad format.  Not a promise: the rule follows
- * measurements (and where the next but one answers 1, the product has no such tile). */
+ * measurements (and where nvfp4_host_gemm_few_rows answers 1, the product has no such tile). */
 int nvfp4_host_gemm_tile(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* Into how many parts the waves of that tile's workgroup divide the contraction (1: not at all); 0 as above. */
 int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
+/* 1 if the output is shared by two kinds of tiles, 0 if not (or for sizes and formats as above): parts = {1 if the first kind, 256 x 256, takes the
+ * first 256 * split rows, 0 if columns; split; its tiles; those of the second kind, which takes the rest; rows and columns of one of these; the parts into
+ * which its workgroup divides the contraction}.  Not a promise either. */
+int nvfp4_host_gemm_mixed(int64_t M, int64_t N, int64_t K, const nvfp4_format *f, int32_t parts[7]);
 /* 1 if the product runs on the kernel for up to 16 rows, 0 if on the tile that the first names.  Not a promise either. */
 int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format *f);
 /* Which calls of a layer on tensors of dt are one launch (a small network's): bit 0 a forward call, bit 1 one that leaves saved operands, bit 2 a

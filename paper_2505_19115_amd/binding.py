@@ -138,6 +138,8 @@ def _load() -> C.CDLL:
     L.nvfp4_host_gemm_tile.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_gemm_split.restype = ci
     L.nvfp4_host_gemm_split.argtypes = [i64, i64, i64, fp]
+    L.nvfp4_host_gemm_mixed.restype = ci
+    L.nvfp4_host_gemm_mixed.argtypes = [i64, i64, i64, fp, vp]
     L.nvfp4_host_gemm_few_rows.restype = ci
     L.nvfp4_host_gemm_few_rows.argtypes = [i64, i64, i64, fp]
     L.nvfp4_host_layer_fused.restype = ci
@@ -185,7 +187,7 @@ EXPORTS = (
     "nvfp4_gemm_slab", "nvfp4_gemm_takes_slabs", "nvfp4_slab_codes_bytes", "nvfp4_slab_scales_bytes",
     "nvfp4_linear_fwd", "nvfp4_linear_bwd", "nvfp4_host_e4m3_encode", "nvfp4_host_e4m3_decode",
     "nvfp4_host_round_rtn", "nvfp4_host_round_sr", "nvfp4_host_philox4x32_10",
-    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_gemm_few_rows", "nvfp4_host_layer_fused", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
+    "nvfp4_host_sr_bits", "nvfp4_host_e8m0_encode", "nvfp4_host_gemm_tile", "nvfp4_host_gemm_split", "nvfp4_host_gemm_mixed", "nvfp4_host_gemm_few_rows", "nvfp4_host_layer_fused", "nvfp4_host_quantize_streams", "nvfp4_host_e4m3_encode_n",
     "nvfp4_host_round_rtn_n", "nvfp4_host_round_sr_n", "nvfp4_probe_mfma_rate",
     "nvfp4_quant_noise_workspace_bytes", "nvfp4_quant_noise", "nvfp4_quantize_static", "nvfp4_cross_check_switches",
     "nvfp4_weight_operands_bytes", "nvfp4_quantize_weight", "nvfp4_linear_fwd_wq", "nvfp4_linear_bwd_wq",
@@ -408,6 +410,16 @@ def gemm_split(M: int, N: int, K: int, fmt: Format = NVFP4) -> int:
     """nvfp4_host_gemm_split -> parts into which the waves of that tile's workgroup divide the contraction."""
     f = fmt.c()
     return lib.nvfp4_host_gemm_split(M, N, K, C.byref(f))
+
+
+def gemm_mixed(M: int, N: int, K: int, fmt: Format = NVFP4) -> dict | None:
+    """nvfp4_host_gemm_mixed -> how two kinds of tiles share the output, or None: the first (256 x 256) takes the first `split` 256 rows
+    (`rows`) or columns with `first` tiles, the second, of `tile` in `groups` parts of the contraction, the rest with `second`."""
+    f = fmt.c()
+    p = (C.c_int32 * 7)()
+    if not lib.nvfp4_host_gemm_mixed(M, N, K, C.byref(f), p):
+        return None
+    return dict(rows=bool(p[0]), split=p[1], first=p[2], second=p[3], tile=(p[4], p[5]), groups=p[6])
 
 
 def gemm_few_rows(M: int, N: int, K: int, fmt: Format = NVFP4) -> bool:

@@ -630,6 +630,17 @@ int nvfp4_host_gemm_split(int64_t M, int64_t N, int64_t K, const nvfp4_format *f
     return gemm_tile_split(choose_gemm_tile(M, N, K, f->scale));
 }
 
+int nvfp4_host_gemm_mixed(int64_t M, int64_t N, int64_t K, const nvfp4_format *f, int32_t parts[7])
+{
+    WideMix X;
+    if (check_format(f) != NVFP4_OK || !parts || M <= 0 || N <= 0 || K <= 0 || !gemm_mixes_tiles(M, N, K, f->scale, &X)) return 0;
+    int rows, cols;
+    gemm_tile_size((GemmTile)X.tile, &rows, &cols);
+    const int32_t values[7] = {X.rows, X.split, (int32_t)X.first, (int32_t)X.second, rows, cols, gemm_tile_split((GemmTile)X.tile)};
+    memcpy(parts, values, sizeof(values));
+    return 1;
+}
+
 int nvfp4_host_gemm_few_rows(int64_t M, int64_t N, int64_t K, const nvfp4_format *f)
 {
     return check_format(f) == NVFP4_OK && M > 0 && N > 0 && K > 0 && gemm_is_thin(M, N, K, f->block, f->scale) ? 1 : 0;

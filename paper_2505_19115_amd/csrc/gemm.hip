@@ -655,6 +655,11 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
     return (GemmTile)best;
 }
 
+bool gemm_mixes_tiles(int64_t M, int64_t N, int64_t K, int sf, WideMix *X)
+{
+    return choose_gemm_tile(M, N, K, sf) == TILE_256x256 && wide_mix(M, N, K, sf, X) != 0;
+}
+
 void gemm_tile_size(GemmTile t, int *rows, int *cols)
 {
     const TileCost &c = E4M3_COST[t].bm ? E4M3_COST[t] : E8M0_COST[t];
@@ -726,7 +731,7 @@ static bool launch_gemm_wide(const TileArgs &P, GemmTile tile, int block, int ou
 {
     if (!wide_contraction(P.K) || P.K / block < 8) return false;
     WideMix X;
-    if (tile == TILE_256x256 && wide_mix(P.M, P.N, P.K, NVFP4_SCALE_E4M3, &X) != 0) {
+    if (tile == TILE_256x256 && wide_mix(P.M, P.N, P.K, NVFP4_SCALE_E4M3, &X) != 0) {  // (gemm_mixes_tiles() says the same)
         switch (block) {
         case 16: launch_gemm_wide_mixed16(P, X, out_dt, st); return true;
         case 32: launch_gemm_wide_mixed32(P, X, out_dt, st); return true;

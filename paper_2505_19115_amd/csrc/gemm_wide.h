@@ -406,14 +406,14 @@ __global__ __launch_bounds__(256) void gemm_nt_f16_wide_mixed_kernel(TileArgs P,
 {
     using G = wide::Geom<WM, WN, KG, TA>;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    int ty, tx;
+    static_assert(G::BN == 256, "columns of the second part's tiles");
+    int64_t m0, n0;
     if (blockIdx.x < X.first) {
-        tile_coords(blockIdx.x, X.rows ? (int)((P.N + 255) / 256) : X.split, X.rows ? X.split : (int)((P.M + 255) / 256), ty, tx);
-        wide_tile<B, 2, 2, 1, 8, OUT_DT, false>(P, lds, (int64_t)ty * 256, (int64_t)tx * 256);
+        mixed_first(X, blockIdx.x, P.M, P.N, m0, n0);
+        wide_tile<B, 2, 2, 1, 8, OUT_DT, false>(P, lds, m0, n0);
     } else {
-        const int64_t m1 = X.rows ? (int64_t)X.split * 256 : 0, n1 = X.rows ? 0 : (int64_t)X.split * 256;
-        tile_coords(blockIdx.x - X.first, (int)((P.N - n1 + G::BN - 1) / G::BN), (int)((P.M - m1 + G::BM - 1) / G::BM), ty, tx);
-        wide_tile<B, WM, WN, KG, TA, OUT_DT, false>(P, lds, m1 + (int64_t)ty * G::BM, n1 + (int64_t)tx * G::BN);
+        mixed_second(X, blockIdx.x, P.M, P.N, G::BM, m0, n0);
+        wide_tile<B, WM, WN, KG, TA, OUT_DT, false>(P, lds, m0, n0);
     }
 }
 

@@ -106,7 +106,7 @@ int64_t tensor_amax_partials(int64_t rows, int64_t cols, int64_t ld);
 // XCD x = id % 8 is given a contiguous band of a walk over the grid, and the walk itself goes
 // down panels of 4 tile rows column by column: the ~32 workgroups an XCD runs at a time then
 // cover about 4 x 8 tiles and share 12 operand strips in its L2 instead of 33.
-__device__ __forceinline__ void tile_coords(int wg, int ntx, int nty, int &ty, int &tx)
+__host__ __device__ __forceinline__ void tile_coords(int wg, int ntx, int nty, int &ty, int &tx)
 {
     const int ntiles = ntx * nty;
     const int per = (ntiles + 7) / 8, xcd = wg & 7, slot = wg >> 3;
@@ -231,6 +231,25 @@ struct WideMix {
     unsigned first, second;
     int split, rows, tile;
 };
+// The first output (m0, n0) of the tile of workgroup wg < X.first of such a launch for an output of M x N; of one behind these, of the second part with its tiles of
+// bm x 256.  (Also for the host, which counts how often each output is covered.)
+__host__ __device__ __forceinline__ void mixed_first(const WideMix &X, unsigned wg, int64_t M, int64_t N, int64_t &m0, int64_t &n0)
+{
+    int ty, tx;
+    tile_coords((int)wg, X.rows ? (int)((N + 255) / 256) : X.split, X.rows ? X.split : (int)((M + 255) / 256), ty, tx);
+    m0 = (int64_t)ty * 256;
+    n0 = (int64_t)tx * 256;
+}
+__host__ __device__ __forceinline__ void mixed_second(const WideMix &X, unsigned wg, int64_t M, int64_t N, int bm, int64_t &m0, int64_t &n0)
+{
+    int ty, tx;
+    const int64_t m1 = X.rows ? (int64_t)X.split * 256 : 0, n1 = X.rows ? 0 : (int64_t)X.split * 256;
+    tile_coords((int)(wg - X.first), (int)((N - n1 + 255) / 256), (int)((M - m1 + bm - 1) / bm), ty, tx);
+    m0 = m1 + (int64_t)ty * bm;
+    n0 = n1 + (int64_t)tx * 256;
+}
+// The division that launch_gemm() takes for a product with E4M3 scales; false: one kind of tiles
+bool gemm_mixes_tiles(int64_t M, int64_t N, int64_t K, int sf, WideMix *X);
 void launch_gemm_wide_mixed16(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
 void launch_gemm_wide_mixed32(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);
 void launch_gemm_wide_mixed64(const TileArgs &P, const WideMix &X, int out_dt, hipStream_t st);

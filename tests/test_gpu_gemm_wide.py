@@ -31,6 +31,12 @@ TILES = [((5975, 1281, 928), (160, 256), 1), ((8280, 903, 1024), (160, 256), 1),
 MIXED = [((1796, 13201, 2304), "columns, 192"), ((2313, 10244, 2432), "rows, 192"), ((2696, 13396, 2304), "columns, two groups"), ((11795, 3084, 2432), "rows, two groups")]
 
 
+def assert_mixed(M, N, K, which):
+    """The library takes this division (and the tests of two kinds of tiles reach the kernel that they name)."""
+    mix = nv.gemm_mixed(M, N, K)
+    assert mix is not None and mix["rows"] == which.startswith("rows") and (mix["tile"], mix["groups"]) == (((192, 256), 1) if "192" in which else ((128, 256), 2)), (mix, which)
+
+
 def operand(rng, rows, K, block):
     return (rng.integers(0, 256, (rows, K // 2)).astype(np.uint8), rng.integers(0x01, 0x7F, (rows, K // block)).astype(np.uint8), 0.75)
 
@@ -67,9 +73,10 @@ def test_tiles(shape, tile, groups, block, out_dtype):
 
 
 @pytest.mark.parametrize("block,out_dtype", [(16, torch.bfloat16), (16, torch.float32), (32, torch.float32), (64, torch.bfloat16), (128, torch.float32)])
-@pytest.mark.parametrize("shape", [s for s, _ in MIXED], ids=[f"{'x'.join(map(str, s))}: {n}" for s, n in MIXED])
-def test_two_kinds_of_tiles(shape, block, out_dtype):
+@pytest.mark.parametrize("shape,which", MIXED, ids=[f"{'x'.join(map(str, s))}: {n}" for s, n in MIXED])
+def test_two_kinds_of_tiles(shape, which, block, out_dtype):
     M, N, K = shape
+    assert_mixed(M, N, K, which)
     assert nv.gemm_tile(M, N, K) == (256, 256) and -(-M // 256) * -(-N // 256) % 256 and -(-M // 256) * -(-N // 256) > 256
     (A, B, fmt, whole) = (lambda d, f, o: (*d, f, o))(*check(shape, block, out_dtype))
     if out_dtype == torch.float32:
@@ -82,9 +89,10 @@ def test_two_kinds_of_tiles(shape, block, out_dtype):
             assert bool(((part - whole[i:i + 592]).abs() <= 2 * K * 2.0 ** -24 * nA[i:i + 592, None] * nB[None]).all())
 
 
-@pytest.mark.parametrize("shape", [s for s, _ in MIXED], ids=[n for _, n in MIXED])
-def test_two_kinds_of_tiles_on_slabs(shape):
+@pytest.mark.parametrize("shape,which", MIXED, ids=[n for _, n in MIXED])
+def test_two_kinds_of_tiles_on_slabs(shape, which):
     M, N, K = (-(-n // 16) * 16 for n in shape)
+    assert_mixed(M, N, K, which)
     assert nv.gemm_tile(M, N, K) == (256, 256)
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
