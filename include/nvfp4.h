@@ -193,6 +193,11 @@ nvfp4_status nvfp4_quantize_dual(const void *x, nvfp4_dtype dt, int64_t rows, in
  * tensor_scales: device fp32[2] = {gA, gB}.
  * out: [M, N] of out_dt with leading dimension ldc.  Products are exact;
  * accumulation is fp32.
+ * The order of summation follows from M, N, K and the format and is the same from
+ * call to call, whatever the operands' layout.  It need not be the same for all of
+ * an output: where two kinds of tiles share one (nvfp4_host_gemm_mixed), those of
+ * one kind may add the contraction in two halves, so that equal rows of an operand
+ * may give rows of the output that differ by the rounding of fp32 sums.
  * K must be a multiple of the block and of 32, at most 2^23; M, N >= 1.
  * Formats: E4M3 scales with blocks 16/32/64/128 (operands expanded exactly to
  * fp16 for the matrix instruction; blocks 64/128 have a second, slower route on
