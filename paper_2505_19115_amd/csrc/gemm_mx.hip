@@ -221,10 +221,6 @@ constexpr int STAGE = (mx::BM + mx::BN) * ROWB;        // 32 KB of codes
 constexpr int SBUF = (mx::BM + mx::BN) * 16;           // 8 KB: the scales of four K tiles
 constexpr int SCALES0 = NS * STAGE, DUMP0 = SCALES0 + 2 * SBUF;
 constexpr int LDS_BYTES = DUMP0 + 4096;
-// 0, 2, 3, 1 for q mod 4.  An instruction's lanes read 16 rows, chunk g in lane group g, and are served 0-3 with 12-15, 20-27 (and the rest of the
-// 32, and the same of the other 32): rows 4-11 of the next chunk beside rows 0-3 and 12-15 of one, which q itself would put into the same
-// slots (4096 x 4096 x 16384: 393 conflict cycles per K tile and CU).
-__device__ __forceinline__ int quad_xor(int q) { return ((q << 1) & 2) ^ ((q >> 1 & 1) * 3); }
 constexpr int FA = 8, FB = 8;  // fragments of 16 rows of a wave's part of A and of B
 }  // namespace mxd
 

@@ -30,9 +30,6 @@ namespace wide {
 
 constexpr int KT = 128, KTB = 64, TB = 8;  // K tile, bytes of codes per row and K tile, fragments of B per wave
 
-// 0, 2, 3, 1 for q mod 4: see the direct-to-LDS kernel of gemm_mx.hip, whose code stages and fragment reads are the same
-__device__ __forceinline__ int quad_xor(int q) { return ((q << 1) & 2) ^ ((q >> 1 & 1) * 3); }
-
 // Written as assembly so that the accumulators stay where they are: with 64 of them the compiler moves the builtin's between the two halves of
 // the register file.  What it cannot know about it: an operand must not have been written by the vector ALU in the two instructions before, and
 // the result of the last one must not be read for 11 wait states.

@@ -119,6 +119,12 @@ __host__ __device__ __forceinline__ void tile_coords(int wg, int ntx, int nty, i
     ty = panel * GH + in_panel - tx * rows;
 }
 
+// 0, 2, 3, 1 for q mod 4: with chunk c (16 bytes of four) of row r of a code stage at slot c ^ quad_xor(r / 4), the fragment reads of 16x16 MFMAs
+// spread over the banks.  An instruction's lanes read 16 rows, chunk g in lane group g, and are served 0-3 with 12-15, 20-27 (and the rest of the
+// 32, and the same of the other 32): rows 4-11 of the next chunk beside rows 0-3 and 12-15 of one, which r / 4 itself would put into the same
+// slots (MXFP4: 393 conflict cycles per K tile and CU, and 128 with this, which are its reads of scale bytes).
+__device__ __forceinline__ int quad_xor(int q) { return ((q << 1) & 2) ^ ((q >> 1 & 1) * 3); }
+
 hipError_t launch_tensor_amax(const void *x, int dt, int64_t rows, int64_t cols, int64_t ld,
                               uint32_t *amax_bits, uint32_t *partials, float *g_out, hipStream_t st);
 // Dense tensors only: at most AMAX_DENSE_PARTIALS partial maxima into `partials`, no fold kernel
