@@ -521,23 +521,22 @@ static bool wide_contraction(int64_t K) { return K > 7 * KT; }
 //     time = fixed + R (tile + step S),      a little more where a CU has only one workgroup (R = 1, `alone` in percent).
 // (NVFP4 and MXFP4 products of up to 16 rows have a kernel of their own, gemm_is_thin().)  Small tiles put more workgroups on the chip and walk K in parallel; large ones do less work per product (operand
 // expansion, LDS reads).  The constants (nanoseconds) are fitted to every tile timed on 245 shapes from 9 x 162 x 768 to 11008 x 4096 x
-// 4096, row-major and in slabs, both output types (profiles/gemm_tiles.txt); the choice is then 0.7 / 1.1 % (E4M3, bf16 / f32 outputs)
-// and 1.5 / 1.6 % (E8M0) slower than the best tile on average.  E4M3, bf16 outputs, us per tile choice:
-//                                 32x32     64x64  96x128K4   128x128 128x128K4   128x256   192x256   256x256
-//       64 x  4096 x 11008            11.7      27.0      51.6      76.5      60.9     120.1     158.0     193.7
-//      256 x 11008 x  4096            43.5      30.7      46.9      31.8      28.8      47.7      63.0      76.3
-//      512 x 11008 x  4096            82.0      57.4      72.3      55.1      58.2      50.1      63.4      77.6
-//      777 x 12288 x  4096           144.1     100.1      96.0      85.3      88.5     104.1      79.2      83.2
-//     1056 x  2080 x  2784            29.7      26.6      21.7      26.1      25.3      36.4      49.7      58.4
-//     2048 x  4096 x  4096           120.3      80.0      74.2      63.6      62.8      61.7      67.3      77.0
-//     2048 x  4096 x 11008           315.8     207.3     182.3     167.1     155.1     156.3     172.0     199.7
-//     3072 x  8192 x  4096           358.1     234.2     199.7     183.2     185.3     181.7     163.6     175.6
-//     4096 x  4096 x  4096           239.8     157.7     146.5     123.2     125.8     120.9     140.6     104.1
-//     8192 x  8192 x   256           287.3     130.6     138.0      46.6     125.8      52.3      49.9      47.6
-//     4096 x 11008 x   512           221.9      93.5      97.7      50.5      89.6      57.3      53.8      50.3
-// (128 x 256 with two groups, one round of it only: 2048 x 4096 x 4096 55.1, x 11008 138.4;
-// 160 x 256, one round of it only: 777 x 12288 x 4096 69.4; see choose_gemm_tile.  All with eight waves; what four waves of 128 columns take
-// stands at wide_cost().)
+// 4096, row-major and in slabs, both output types; those of the tiles that four waves of 128 columns serve from 16 K tiles on stand at wide_cost().  The present
+// kernels' times on these shapes are in profiles/gemm_tiles.txt; the choice is 0.9 / 1.3 % (E4M3, bf16 / f32 outputs) and 1.3 / 1.4 % (E8M0) slower than the
+// best tile on average.  E4M3, bf16 outputs, us per tile choice:
+//                               32x32     64x64  96x128K4   128x128 128x128K4   128x256 128x256K2   160x256   192x256   256x256
+//        64 x  4096 x 11008      11.7      26.5      47.3      78.7      58.6     117.9     103.6     143.2     153.3     182.0
+//       256 x 11008 x  4096      41.4      30.2      43.7      32.3      27.2      46.2      45.8      57.7      63.6      75.1
+//       512 x 11008 x  4096      81.9      57.8      68.2      54.3      56.3      49.0      47.8      59.4      64.5      76.3
+//       777 x 12288 x  4096     150.6      96.7      92.9      85.6      86.1     103.2      95.4      65.6      72.6      78.4
+//      1056 x  2080 x  2784      29.1      26.5      19.1      23.8      22.6      34.3      33.8      43.9      47.0      54.3
+//      2048 x  4096 x  4096     137.9      80.8      73.9      64.6      64.9      61.6      55.4      64.9      67.1      77.5
+//      2048 x  4096 x 11008     308.3     205.2     171.2     165.4     154.6     156.7     130.6     160.3     166.8     194.4
+//      3072 x  8192 x  4096     378.5     229.3     200.9     182.9     186.7     179.1     159.5     188.9     152.0     144.9
+//      4096 x  4096 x  4096     251.5     154.8     141.7     122.6     122.9     119.2     107.8     124.9     137.4      92.5
+//      8192 x  8192 x   256     290.8     133.2     140.0      43.4     127.5      51.7         -      53.4      48.6      46.6
+//      4096 x 11008 x   512     223.4      97.4      99.0      49.8      90.9      57.0         -      56.6      51.9      48.2
+// (128 x 256 in two groups and 160 x 256 are for one round of them: see choose_gemm_tile().)
 // (a short contraction wants small tiles: the waves of several workgroups per CU cover each other's epilogues; products that leave
 // a 256 x 256 grid short of the 256 CUs, or just past a round of them, take 192 or 128 rows of the same eight waves.)
 struct TileCost {
@@ -562,7 +561,8 @@ static const TileCost E8M0_COST[TILES] = {
 // From 16 K tiles on (12 in MXFP4); with the fewer of short contractions these estimates favour the large tiles too much (us, the choice without them / with:
 // 3953 x 4992 x 960 43.1 / 45.7, 1906 x 9312 x 1056 45.7 / 48.5, 5847 x 3008 x 1472 58.6 / 60.3, 2429 x 7840 x 2016 80.6 / 81.3, 2599 x 1952 x 3008 44.0 / 38.5,
 // 1591 x 7328 x 4736 105.9 / 96.9, 5803 x 6368 x 11776 767 / 710; MXFP4 4737 x 2208 x 512 8.6 / 10.1, 3098 x 2592 x 1024 10.7 / 11.8, 4998 x 1664 x 1664 15.6 / 14.5,
-// 702 x 11872 x 2048 18.1 / 16.5, 4644 x 11648 x 7552 274 / 229).
+// 702 x 11872 x 2048 18.1 / 16.5, 4644 x 11648 x 7552 274 / 229).  Of 8 to 15 K tiles, which are chosen by the costs above and run on four waves, the
+// choice is 0.5 / 0.2 % (bf16 / f32 outputs) slower than the best tile on average of 40 products.
 static const TileCost *wide_cost(int tile, int64_t K, int sf)
 {
     // (a round of several 4 to 7 % above one alone)
@@ -623,9 +623,9 @@ GemmTile choose_gemm_tile(int64_t M, int64_t N, int64_t K, int sf)
         // 1280 x 6816 x 5760 103.3 / 118.8, 1381 x 5979 x 8800 167.4 / 202.9)
         if ((t == TILE_96x128_K4 || t == TILE_128x128_K4) && tiles > 256) continue;
         // The 160-row tile is for one round of them in place of one of 192 rows, where it covers the rows with less padding.  us, 192 / 160
-        // rows: 777 x 12288 x 4096 79.1 / 69.4, 1600 x 6144 x 4096 75.7 / 72.1, 320 x 32768 x 1024 26.9 / 23.4, 2384 x 4096 x 512 16.2 / 14.3;
-        // with as many rows or more the shorter step is lost to the larger product: 960 x 10240 x 8192 142.6 / 143.3, 1281 x 7000 x 1024
-        // 25.1 / 25.6.  Contractions of one K tile are slower on it (bf16 / f32 outputs, 192 and 128 rows / 160: 777 x 12288 x 128 6.6 / 7.4 and 10.6 / 11.2,
+        // rows: 777 x 12288 x 4096 74.6 / 65.4, 1600 x 6144 x 4096 69.2 / 64.9, 320 x 32768 x 1024 23.3 / 21.7, 2384 x 4096 x 512 13.3 / 12.5;
+        // with as many rows or more there is little in it, and such products have not been moved to it: 960 x 10240 x 8192 126.7 / 123.2, 1281 x 7000 x
+        // 1024 22.8 / 22.7.  Contractions of one K tile are slower on it (bf16 / f32 outputs, 192 and 128 rows / 160: 777 x 12288 x 128 6.6 / 7.4 and 10.6 / 11.2,
         // 3307 x 2944 x 128 6.9 / 9.0 and 10.3 / 12.0, 1352 x 7168 x 96 7.2 / 7.9 and 10.9 / 12.1); of two they would be faster (777 x 12288 x 256 10.5 / 9.4 and 14.6 /
         // 12.9, 2505 x 3212 x 256 12.6 / 12.0 and 16.1 / 14.1, 1079 x 9184 x 160 11.9 / 11.3 and 14.4 / 13.9), and have not been moved to it so far.
         if (t == TILE_160x256 && (K <= 256 || tiles > 256 || (M + 159) / 160 * 160 >= (M + 191) / 192 * 192)) continue;
@@ -706,17 +706,17 @@ hipError_t launch_gemm_pair(const GemmArgs &P0, const GemmArgs &P1, int block, i
 }
 
 // Outputs up to this size leave by nontemporal stores, which do not wait for a place in the L2 (us, kept / streamed: NVFP4 1024 x 4096 x 4096,
-// binary32 outputs, 38.1 / 36.6, bf16 35.5 / 34.4, 2048 x 4096 x 4096 66.7 / 65.8; MXFP4 2048 x 4096 x 4096 29.6 / 27.9), and still together
-// with a kernel that reads the output next (quantizer 39.2 / 38.3, 71.5 / 70.9, 34.4 / 33.4).  Of larger ones the next kernel finds more in the
-// last-level cache than the product gains: MXFP4 4096 x 11008 x 4096, 86 MB, 135.9 / 125.7, with a quantizer behind it 134.0 / 138.6; 40 MB 65.6 /
-// 67.8.  (Weight gradients, which are not read next, of 90 MB: the backward half of an MLP of 4096 / 11008 at 2048 tokens 697 / 706, the whole
-// one at 4096 tokens 2872 / 2848: not done.)
+// binary32 outputs, 37.1 / 36.1, bf16 34.4 / 33.7, 2048 x 4096 x 4096 52.7 / 51.1, 4096 x 4096 x 4096 87.0 / 85.2; MXFP4 2048 x 4096 x 4096 28.2 / 26.8,
+// 4096 x 4096 x 4096 32.7 / 31.5), and still together with a kernel that reads the output next, but for the first (quantizer 44.2 / 44.5, 41.2 / 40.6, 60.1 / 59.4,
+// 101.1 / 100.3; 31.6 / 30.8, 40.4 / 40.1).  Of larger ones the next kernel finds more in the last-level cache: MXFP4 5120 x 4096 x 4096, 40 MB, 62.7 / 62.3, with a
+// quantizer behind it 72.6 / 73.2; 4096 x 11008 x 4096, 86 MB, 88.5 / 91.8 and 106.4 / 110.8.  (Weight gradients, which are not read next, of 90 MB, with the
+// products of eight waves: the backward half of an MLP of 4096 / 11008 at 2048 tokens 697 / 706, the whole one at 4096 tokens 2872 / 2848: not done.)
 // Calls on packed weights, quantizer and product, us, kept / streamed, one by one and from a graph, MXFP4: 2048 x 4096 x 4096 34.0 / 32.9 and 35.0 / 33.5,
 // 1024 x 4096 x 4096 with binary32 outputs 31.4 / 29.9 and 30.5 / 29.2, 4096 x 4096 x 2048 (32 MB) 32.3 / 31.3 and 31.8 / 30.6; of 70 random ones with 4 to
 // 32 MB 0.97 to 1.10 times as fast (less than 0.99: 3076 x 928 x 928 and 3857 x 928 x 960, NVFP4), 628 x 5888 x 5504 with binary32 outputs 40.8 / 41.0 and
-// 39.7 / 38.7.  Rows 32 KB apart are an exception near the line: MXFP4 1024 x 8192 x 1024 with binary32 outputs 17.2 / 18.2 and 17.1 / 18.3, x 2048 23.2 /
-// 24.0 and 24.8 / 25.9, 1000 x 8192 x 2048 23.1 / 23.5 and 23.6 / 24.2, NVFP4 1024 x 8192 x 1024 28.5 / 29.2 and 28.4 / 28.8; 896 x 8192 x 1024 15.8 / 14.9
-// and 1.02 times as fast (31 KB apart, 1024 x 7936 x 2048, 22.1 / 21.7 and 21.9 / 21.6; 64 KB apart, 512 x 16384 x 4096, 34.0 / 32.8).
+// 39.7 / 38.7 (all with the kernels on 32 x 32 MFMAs).  Rows 32 KB apart are an exception near the line (the product, and with a quantizer of its output): MXFP4
+// 1024 x 8192 x 1024 with binary32 outputs 14.3 / 14.7 and 28.4 / 28.9, NVFP4 22.7 / 22.5 and 41.3 / 41.6; MXFP4 896 x 8192 x 1024 12.9 / 11.7 and 25.1 / 24.8,
+// 31 KB apart, 1024 x 7936 x 2048, 18.0 / 16.7 and 27.0 / 25.8.
 // The rule's answer is an argument of the larger tiles' kernels alone.  As a member of GemmArgs it lengthened the small products' arguments (two of these: 212
 // bytes instead of 196), and with them the host's work for a launch: a call of 64 x 4096 x 11008 MXFP4 on packed weights kept the host 8.80 us instead of
 // 8.50 (two libraries in turn in one process; on another box 5.45 and 5.41).  Asked in the kernels, from M and ldc, it had the 256 x 256 MXFP4 ones spill

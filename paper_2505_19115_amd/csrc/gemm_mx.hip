@@ -205,8 +205,8 @@ __global__ __launch_bounds__(256) void gemm_nt_fp4_rescale_kernel(TileArgs P)
 // An operand in the slab layout (A_SLAB / B_SLAB) brings its scales as slabs too: 256 positions x 4 bytes per K
 // tile, contiguous, so ONE instruction of one wave fetches the scales of a whole K tile (wave 0: A, wave 1: B), they
 // travel with the codes of their tile through four 1 KB stages (which take the place of that operand's part of the
-// first scale buffer), and a lane reads its row's dword at position slab_row(row): 32 consecutive rows are 32
-// different banks.  (Row-major scales lie 16 bytes apart in LDS, so 32 rows share 16 banks and those reads conflict.)
+// first scale buffer), and lane group g reads byte g of its row's dword at position slab_row(row): 16 rows are 16 different banks, and yet each such read
+// takes two cycles more (128 per K tile and CU, all that is left of conflicts in the loop).  Row-major scales lie 16 bytes apart in LDS.
 //
 // Every wave issues the same direct-to-LDS instructions per K tile, which the counted waits rely on: 4 + 4 codes, one slot for a
 // row-major scale group where an operand is row-major and one for a scale slab where one comes in slabs; a slot with nothing to fetch
@@ -436,8 +436,8 @@ __global__ __launch_bounds__(256) void gemm_nt_mxfp4_dma_kernel(TileArgs P)
     //     A1 x Q   while A0 of kt + 1 is read  A1 x P   while Q of kt + 1 is read, the next tile's P
     // In the first half B's codes and the scales of tile kt + 3 are requested (into the stage that tile kt - 1 left at its barrier), in the
     // second A's codes of tile kt + 4.
-    // A wave has its SIMD to itself and issues an instruction every 8 cycles or so; a MFMA takes 16.  So what bounds a K tile, beside
-    // power, is the number of instructions beyond one per MFMA: stages and with them all LDS addresses are constants (four tiles a trip),
+    // A wave has its SIMD to itself and issues an instruction every 8 cycles or so; a MFMA takes 16.  So what bounds a K tile (1160 cycles, 1024 of them its
+    // MFMAs, at 1.9 to 2.1 GHz by their power), is the number of instructions beyond one per MFMA: stages and with them all LDS addresses are constants (four tiles a trip),
     // pointers advance in scalar registers, the load's destination is one addition, and one LDS read, load or destination follows each MFMA
     // (scheduling fences pin that order).  4096 x 4096 x 16384: 195 instructions a K tile 125.2 us, 135 111.3;
     // 4096 x 11008 x 4096 100.0 and 88.0.

@@ -2,7 +2,12 @@
 // v_mfma_f32_16x16x32_f16, for workgroup tiles of 256 x 256, 192 x 256, 160 x 256 (2 x 2 waves) and 128 x 256 (two groups of 1 x 2 waves on every
 // other K tile).  Operands, layouts and arithmetic are those described there.
 //
-// What bounds them: the matrix unit's power, then the instructions of the one wave a SIMD has, which issues one every 5 cycles or so.
+// What bounds them: the instructions of the one wave a SIMD has, which issues one every 5.8 to 6 cycles, at a clock that the matrix unit's power sets (2.05 to
+// 2.3 GHz), and a start and an end of 22000 cycles a tile that nothing covers.  Counted (two lengths of K where there is a K tile's share; instructions
+// of all kinds and cycles of a wave for each K tile of its own, of these MFMAs, 16 cycles each):
+//     256 x 256                                                       838 instructions  4850 cycles  4096 in MFMAs (pipe busy 53 % of a launch with 16 K tiles, 73 % with 86)
+//     128 x 256 in two groups                                         866               5170         4096 (51 % with 32 K tiles, 64 % with 86)
+//     160 x 256 (from 32 K tiles, start and end as in the others)     630               3700         2560 (47 % with 32)
 // Expanding the operands takes 8 (TA + 8) / (8 TA) vector instructions per MFMA of 16 cycles, 2 for TA = 8 (eight waves of 128 x 64 need 3, shared by
 // two waves).  Measured with registers only, operands of quantized normal numbers, all 256 CUs, PFLOP/s:
 //     32 x 32 x 16, eight waves of 128 x 64, each convert right before its multiply 1.57, four converts and then four multiplies 1.63
