@@ -1,4 +1,5 @@
 """CPU-only checks of outputs that two kinds of tiles share: which products take one, and that the tiles cover every output once."""
+import ctypes as C
 import os
 import random
 import shutil
@@ -36,6 +37,8 @@ def test_which_products_mix_tiles():
         assert nv.gemm_mixed(M, N, K) is None
     assert nv.gemm_mixed(4096, 11008, 4096) == dict(rows=False, split=32, first=512, second=242, tile=(192, 256), groups=1)
     assert nv.gemm_mixed(4096, 11008, 4096, nv.Format(8, nv.SCALE_E4M3, 1)) is None
+    f = nv.NVFP4.c()
+    assert nv.lib.nvfp4_host_gemm_mixed(4096, 11008, 4096, C.byref(f), None) == 0 and nv.lib.nvfp4_host_gemm_mixed(4096, 11008, 4096, None, (C.c_int32 * 7)()) == 0
 
 
 @pytest.mark.skipif(not shutil.which(CLANG), reason="needs the ROCm compilers")
